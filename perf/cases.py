@@ -259,13 +259,18 @@ def _plan(case, cfg):
     return B.Plan(desc, _regions(case), budget)
 
 
-def prepare(case, seed):
-    """Input, weights, the plan with its weights bound and its workspace: what such a program keeps."""
-    cfg = _config(case)
+def _inputs(case, cfg, seed):
+    """The input and the weights in bind order."""
     dtype = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
     gen = torch.Generator(device="cuda").manual_seed(seed)
     x = torch.randn(_input_shape(cfg), generator=gen, device="cuda").to(dtype)
-    weights = [_values(n, s, case, dtype, gen) for n, s in _tensors(cfg)]
+    return x, [_values(n, s, case, dtype, gen) for n, s in _tensors(cfg)]
+
+
+def prepare(case, seed):
+    """Input, weights, the plan with its weights bound and its workspace: what such a program keeps."""
+    cfg = _config(case)
+    x, weights = _inputs(case, cfg, seed)
     plan = _plan(case, cfg)
     plan.ac_plan_bind_weights(weights)
     workspace = B.empty_workspace(plan.ac_plan_query().workspace_bytes)
@@ -285,3 +290,128 @@ def tolerance(case):
         return {"rel": 4e-6, "max": 4e-5}
     rel = max(1e-2, 5e-3 * math.sqrt(case.get("layers", 1)))
     return {"rel": rel, "max": 15 * rel}
+
+
+# ---- the same in 64 bits, plain torch -----------------------------------------------------------
+
+def _norm(x, gain, shift):
+    return torch.nn.functional.layer_norm(x, x.shape[-1:], gain, shift, 1e-5)
+
+
+def _act(x, name):
+    if name == "relu":
+        return torch.relu(x)
+    return torch.nn.functional.gelu(x, approximate="tanh" if name == "gelu_tanh" else "none")
+
+
+def _attend(q, k, v, heads, causal, rows=2048):
+    """q [s, heads * dh] against k, v [t, heads * dh] of one sequence, some query rows of one head at a time."""
+    out, dh, at = torch.empty_like(q), q.shape[1] // heads, torch.arange(k.shape[0], device=q.device)
+    for h in range(heads):
+        c = slice(h * dh, (h + 1) * dh)
+        for a in range(0, q.shape[0], rows):
+            b = min(q.shape[0], a + rows)
+            seen = b if causal else k.shape[0]
+            p = q[a:b, c] @ k[:seen, c].T.contiguous()
+            p *= 1.0 / math.sqrt(dh)
+            if causal:
+                p.masked_fill_(at[None, :seen] > at[a:b, None], -math.inf)
+            out[a:b, c] = torch.softmax(p, -1) @ v[:seen, c]
+    return out
+
+
+def _layer(x, w, heads, causal, activation, sequences, context=None, gated=False):
+    """One pre-LN layer on [tokens, d]; attention inside each of `sequences` equal runs of tokens."""
+    d, s = x.shape[1], x.shape[0] // sequences
+    qkv = _norm(x, w["ln1_g"], w["ln1_b"]) @ w["w_qkv"].T + w["b_qkv"]
+    ctx = torch.cat([_attend(*t.split(d, -1), heads, causal) for t in qkv.split(s)])
+    x = x + ctx @ w["w_o"].T + w["b_o"]
+    if context is not None:
+        q = _norm(x, w["lnc_g"], w["lnc_b"]) @ w["w_qc"].T
+        kv = [(t @ w["w_kvc"].T).split(d, -1) for t in context]
+        ctx = torch.cat([_attend(t, *kv[i], heads, False) for i, t in enumerate(q.split(s))])
+        x = x + ctx @ w["w_oc"].T + w["b_oc"]
+    hid = _norm(x, w["ln2_g"], w["ln2_b"]) @ w["w_1"].T + w["b_1"]
+    if gated:
+        value, gate = hid.chunk(2, -1)
+        hid = value * _act(gate, activation)
+    else:
+        hid = _act(hid, activation)
+    return x + hid @ w["w_2"].T + w["b_2"]
+
+
+def _tri_mul(z, w, outgoing):
+    t = _norm(z, w["ln_in_g"], w["ln_in_b"])
+    a, b = (torch.sigmoid(t @ w[f"w_{n}g"].T + w[f"b_{n}g"]) * (t @ w[f"w_{n}p"].T + w[f"b_{n}p"]) for n in "ab")
+    o = torch.empty_like(a)
+    for c in range(a.shape[2]):     # o[i, j] = sum_k a[i, k] b[j, k], or a[k, i] b[k, j]
+        ac, bc = a[:, :, c].contiguous(), b[:, :, c].contiguous()
+        o[:, :, c] = ac @ bc.T.contiguous() if outgoing else ac.T.contiguous() @ bc
+    g = torch.sigmoid(t @ w["w_g"].T + w["b_g"])
+    return z + g * (_norm(o, w["ln_out_g"], w["ln_out_b"]) @ w["w_o"].T + w["b_o"])
+
+
+def _tri_att(z, w, heads, starting):
+    if not starting:                # the starting node's form on the transposed pair tensor
+        return _tri_att(z.transpose(0, 1), w, heads, True).transpose(0, 1)
+    t = _norm(z, w["ln_g"], w["ln_b"])
+    bias = (t @ w["w_bias"].T).permute(2, 0, 1)
+    out = torch.empty_like(t @ w["w_q"].T)
+    dh = out.shape[2] // heads
+    for a in range(0, z.shape[0], 64):
+        q, k, v = ((t[a:a + 64] @ w[n].T).unflatten(-1, (heads, dh)).transpose(1, 2).contiguous() for n in ("w_q", "w_k", "w_v"))
+        p = torch.softmax(torch.matmul(q, k.transpose(2, 3).contiguous()) / math.sqrt(dh) + bias, -1)
+        out[a:a + 64] = torch.matmul(p, v).transpose(1, 2).flatten(2)
+    return z + (torch.sigmoid(t @ w["w_g"].T + w["b_g"]) * out) @ w["w_o"].T + w["b_o"]
+
+
+def _pair_block(z, w, heads, activation):
+    def of(p):
+        return {n[len(p):]: t for n, t in w.items() if n.startswith(p)}
+    z = _tri_mul(_tri_mul(z, of("tmo."), True), of("tmi."), False)
+    z = _tri_att(_tri_att(z, of("tas."), heads, True), of("tae."), heads, False)
+    w = of("pt.")
+    return z + _act(_norm(z, w["ln_g"], w["ln_b"]) @ w["w_1"].T + w["b_1"], activation) @ w["w_2"].T + w["b_2"]
+
+
+def _group_norm(x, groups, gain, shift):
+    return torch.nn.functional.group_norm(x.permute(0, 3, 1, 2), groups, gain, shift, 1e-5).permute(0, 2, 3, 1)
+
+
+def _conv(x, w):
+    b, h, wd, c = x.shape
+    xp, w = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1)), w.view(-1, 3, 3, c)
+    return sum(xp[:, i:i + h, j:j + wd] @ w[:, i, j].T.contiguous() for i in range(3) for j in range(3))
+
+
+def _res_block(x, w, groups):
+    silu = torch.nn.functional.silu
+    h = _conv(silu(_group_norm(x, groups, w["gn1_g"], w["gn1_b"])), w["w1"]) + (w["b1"] + w["temb"])[:, None, None, :]
+    return x + _conv(silu(_group_norm(h, groups, w["gn2_g"], w["gn2_b"])), w["w2"]) + w["b2"]
+
+
+def _attn_block(x, w, cfg):
+    t = _group_norm(x, cfg.groups, w["gn_g"], w["gn_b"]).reshape(-1, cfg.channels) @ w["w_in"].T + w["b_in"]
+    context = w["context"].split(cfg.context_tokens) if cfg.context_tokens else None
+    t = _layer(t, w, cfg.heads, False, "gelu_erf", cfg.batch, context, cfg.gated)
+    return x + (t @ w["w_out"].T + w["b_out"]).view_as(x)
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits."""
+    cfg = _config(case)
+    x, weights = _inputs(case, cfg, seed)
+    x, names = x.double(), [n for n, _ in _tensors(cfg)]
+    layers = 1 if case["family"] == "pair" else cfg.layers
+    per = len(names) // layers
+    for i in range(layers):
+        w = {n: t.double() for n, t in zip(names[:per], weights[i * per:(i + 1) * per])}
+        if case["family"] == "transformer":
+            x = _layer(x, w, cfg.heads, cfg.causal, cfg.activation, cfg.batch)
+        elif case["family"] == "pair":
+            x = _pair_block(x, w, cfg.heads, cfg.activation)
+        else:
+            x = _res_block(x, w, cfg.groups)
+            if cfg.heads:
+                x = _attn_block(x, w, cfg)
+    return x.contiguous()
