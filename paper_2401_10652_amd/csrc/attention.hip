@@ -118,6 +118,163 @@ __global__ void __launch_bounds__(128) attention_rows(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
+// fp32 MFMA kernel: v_mfma_f32_16x16x4_f32, row-major values.
+//
+// fp32 problems are short (a thousand keys or so) and few, so what bounds them is how many waves there
+// are and how long each one's chain over the keys is.  A block owns 16 query rows of one head and its four
+// waves take the 32-key tiles in turn (tile t goes to wave t mod 4: a rule on the key's position alone,
+// so a row's result does not depend on the segment it lies in); their running maxima, sums and
+// outputs meet in LDS at the end, in wave order.  No operand is staged: a lane loads 16 bytes of its key
+// row, element e of which feeds matrix instruction e, the scores come out transposed (lane = query,
+// registers = 4 consecutive keys) which is the operand layout of the second product, and value rows are
+// read whole, lane l16 holding d = NV l16 .. NV l16 + NV - 1.
+// Measured (1024 x 1024 causal, 8 heads of 64 / 256 x 256, 4 heads of 16): 916 / 71 us with one thread per
+// row (the kernel above), 35 / 5.7 us here.
+// ------------------------------------------------------------------------------------
+template <int DH>
+__global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
+  constexpr int NW = 4, KS = DH / 16, NV = DH / 16, VL = NV < 4 ? NV : 4;   // VL: floats per value load
+  constexpr int OROW = DH + 4;
+  typedef float vload __attribute__((ext_vector_type(VL == 1 ? 2 : VL)));
+  __shared__ float s_o[NW][16][OROW];
+  __shared__ float s_ml[NW][16][2];
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, l16 = lane % 16, grp = lane / 16;
+  const int sq = (int)a.sq, sk = (int)a.sk;
+  const int nqb = (sq + 15) / 16;
+  const int64_t bh = blockIdx.x / nqb;
+  int qb = (int)(blockIdx.x % nqb);
+  if (a.causal) qb = nqb - 1 - qb;                         // longest rows first
+  const int64_t b = bh / a.heads;
+  const int h = (int)(bh % a.heads), q0 = qb * 16;
+  const int row = q0 + l16, rowc = row < sq ? row : sq - 1;   // rows past the end shadow the last one; never stored
+  const int qpos = (int)a.q_offset + rowc;
+  const float* kb = (const float*)a.k + b * a.sk_b + h * DH + 4 * grp;
+  const float* vb = (const float*)a.v + b * a.sv_b + h * DH + NV * l16;
+  const float* bias = a.bias ? (const float*)a.bias + h * a.s_bias_h + (int64_t)rowc * a.ld_bias : nullptr;
+  f32x4 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    qf[ks] = *reinterpret_cast<const f32x4*>((const float*)a.q + b * a.sq_b + (int64_t)rowc * a.ldq + h * DH + 16 * ks + 4 * grp);
+
+  int kv_end = sk;
+  if (a.causal) {
+    const int last = q0 + 15 < sq - 1 ? q0 + 15 : sq - 1;
+    if ((int)a.q_offset + last + 1 < kv_end) kv_end = (int)a.q_offset + last + 1;
+  }
+  const int n_tiles = (kv_end + 31) / 32;
+
+  f32x4 kf[2][KS], acc_o[NV];
+  float vf[2][4][NV];
+  auto load_k = [&](int t) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      int key = 32 * t + 16 * u + l16; if (key > sk - 1) key = sk - 1;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[u][ks] = *reinterpret_cast<const f32x4*>(kb + (int64_t)key * a.ldk + 16 * ks);
+    }
+  };
+  auto load_v = [&](int t) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int key = 32 * t + 16 * u + 4 * grp + r; if (key > sk - 1) key = sk - 1;
+        const float* p = vb + (int64_t)key * a.ldv;
+        if constexpr (VL == 1) vf[u][r][0] = *p;
+        else {
+#pragma unroll
+          for (int c = 0; c < NV / VL; ++c) {
+            const vload v = *reinterpret_cast<const vload*>(p + c * VL);
+#pragma unroll
+            for (int e = 0; e < VL; ++e) vf[u][r][c * VL + e] = v[e];
+          }
+        }
+      }
+  };
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc_o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // running maximum (of the scaled scores in the log2 domain) and this lane's share of the sum
+  float m_run = -INFINITY, l_run = 0.f;
+  const float scale2 = rsqrtf((float)DH) * kLog2e;
+
+  if (wave < n_tiles) { load_k(wave); load_v(wave); }
+  for (int t = wave; t < n_tiles; t += NW) {
+    f32x4 s[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) s[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][ks][e], qf[ks][e], s[u], 0, 0, 0);
+    if (t + NW < n_tiles) load_k(t + NW);
+    // lane holds keys 32 t + 16 u + 4 grp + r of query row l16
+    float mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int key = 32 * t + 16 * u + 4 * grp + r;
+        float v = s[u][r] * scale2;
+        if (key >= sk || (a.causal && key > qpos)) v = -INFINITY;
+        else if (bias) v = fmaf(bias[key], kLog2e, v);
+        s[u][r] = v;
+        mx = fmaxf(mx, v);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const float m_exp = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp2(-inf) = 0, not NaN
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_exp);
+    m_run = m_new;
+    l_run *= alpha;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc_o[i][r] *= alpha;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float p = __builtin_amdgcn_exp2f(s[u][r] - m_exp);
+        l_run += p;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) acc_o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[u][r][i], p, acc_o[i], 0, 0, 0);
+      }
+    if (t + NW < n_tiles) load_v(t + NW);
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  // acc_o[i][r]: query row l16, d = NV (4 grp + r) + i
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s_o[wave][l16][NV * (4 * grp + r) + i] = acc_o[i][r];
+  if (grp == 0) { s_ml[wave][l16][0] = m_run; s_ml[wave][l16][1] = l_run; }
+  __syncthreads();
+  for (int c = tid; c < 16 * DH; c += 256) {
+    const int rl = c / DH, d = c % DH;
+    const int64_t orow = q0 + rl;
+    if (orow >= sq) continue;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_ml[w][rl][0]);
+    float L = 0.f, o = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (s_ml[w][rl][0] == -INFINITY) continue;   // this wave saw no key of the row
+      const float f = __builtin_amdgcn_exp2f(s_ml[w][rl][0] - M);
+      L += s_ml[w][rl][1] * f;
+      o += s_o[w][rl][d] * f;
+    }
+    o *= 1.0f / L;
+    if (a.gate) o *= ((const float*)a.gate)[b * a.sg_b + orow * a.ldg + h * DH + d];
+    ((float*)a.ctx)[b * a.sc_b + orow * a.ldc + h * DH + d] = o;
+  }
+}
+
+// ------------------------------------------------------------------------------------
 // bf16 MFMA kernel.
 // ------------------------------------------------------------------------------------
 constexpr int kQB = 128;   // query rows per block of the 4-wave kernel (32 per wave)
@@ -821,6 +978,25 @@ static bool mfma_attn_eligible(const AttnArgs& a) {
   return true;
 }
 
+// fp32 problems whose q, k and v rows can be read 16 bytes at a time
+static bool mfma_f32_attn_eligible(const AttnArgs& a) {
+  if (a.dtype != AC_F32 || a.v_transposed) return false;
+  if (a.head_dim != 16 && a.head_dim != 32 && a.head_dim != 64 && a.head_dim != 128) return false;
+  if (a.ldq % 4 || a.ldk % 4 || a.ldv % 4 || a.sq_b % 4 || a.sk_b % 4 || a.sv_b % 4) return false;
+  return al(a.q, 16) && al(a.k, 16) && al(a.v, 16);
+}
+
+static hipError_t mfma_f32_attn_dispatch(const AttnArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)(((a.sq + 15) / 16) * a.heads * a.batch));
+  switch (a.head_dim) {
+    case 16: hipLaunchKernelGGL((attention_mfma_f32<16>), grid, dim3(256), 0, s, a); break;
+    case 32: hipLaunchKernelGGL((attention_mfma_f32<32>), grid, dim3(256), 0, s, a); break;
+    case 64: hipLaunchKernelGGL((attention_mfma_f32<64>), grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((attention_mfma_f32<128>), grid, dim3(256), 0, s, a); break;
+  }
+  return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t generic_attn_dispatch(const AttnArgs& a, hipStream_t s) {
   dim3 grid((unsigned)((a.sq + 127) / 128), (unsigned)a.heads, (unsigned)a.batch);
@@ -874,6 +1050,7 @@ hipError_t launch_attention(const AttnArgs& a_in, hipStream_t s) {
     }
   }
   if (a.dtype == AC_BF16) return generic_attn_dispatch<bf16_t>(a, s);
+  if (mfma_f32_attn_eligible(a)) return mfma_f32_attn_dispatch(a, s);
   return generic_attn_dispatch<float>(a, s);
 }
 

@@ -14,6 +14,8 @@
 // fp32 path and odd shapes: an LDS-tiled FMA kernel with full bounds checks.
 #include "common.h"
 
+#include <type_traits>
+
 namespace ac {
 
 // ------------------------------------------------------------------------------------
@@ -122,6 +124,156 @@ __device__ __forceinline__ void tile_of_block(int64_t tiles_m, int64_t tiles_n, 
   const int64_t gsz = tiles_m - first < GM ? tiles_m - first : GM;
   tm = first + (t % width) % gsz;
   tn = (t % width) / gsz;
+}
+
+// ------------------------------------------------------------------------------------
+// fp32 MFMA kernel: v_mfma_f32_16x16x4_f32, full fp32 operands and sums.
+//
+// What bounds it: fp32 launches here are small (a few hundred rows), so the time is the serial chain
+// over k and the share of the chip's 1024 SIMDs that has a wave at all, not the 157 TFLOP/s.  Hence
+// no LDS staging and no barrier in the k loop: a lane loads 16 bytes of its operand row straight
+// into registers (4 consecutive k; the four lane groups of the instruction cover 16), element e of
+// which is its operand of matrix instruction e, and loads run D steps ahead.  The four waves of a block
+// share its output tile and take a quarter of k each (a quarter of the chain, four times the waves);
+// the partial sums meet in LDS and are added in order.  Where k is cut depends on k alone, so a row's bits
+// do not depend on the launch it falls in nor on the tile.
+// Measured against the FMA kernel above: 64 x 64 x 256 40 -> 5.8 us, 256 x 512 x 2048 284 -> 15 us,
+// 256 x 2048 x 512 78 -> 11.5 us, 1024 x 1536 x 512 86 -> 31 us.
+// ------------------------------------------------------------------------------------
+constexpr int kF32Runs = 4;
+// Length of a run of k.
+__device__ __forceinline__ int f32_run_len(int64_t k) { return (int)((k + 16 * kF32Runs - 1) / (16 * kF32Runs)) * 16; }
+
+// bias, activation, multiplier, residual and the store for 4 consecutive columns of one row
+__device__ __forceinline__ void epilogue_store_f32x4(const LinearArgs& g, bool vec, int64_t product, int64_t m, int64_t n, f32x4 v) {
+  if (m >= g.m) return;
+  if (vec && n + 4 <= g.n && n + 4 <= g.n_split) {
+    if (g.bias) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>((const float*)g.bias + n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] += t[j];
+    }
+    if (g.act != AC_ACT_NONE) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = apply_act_rt(v[j], g.act);
+    }
+    if (g.mul) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>((const float*)g.mul + m * g.ldmul + n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] *= t[j];
+    }
+    if (g.resid) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>((const float*)g.resid + m * g.ldr + n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] += t[j];
+    }
+    *reinterpret_cast<f32x4*>((float*)g.out + product * g.so_b + out_row(g, m) + n) = v;
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (n + j >= g.n) continue;
+    if (g.batch > 1) ((float*)g.out)[product * g.so_b + m * g.ldo + n + j] = v[j];
+    else epilogue_store_one<float>(g, m, n + j, v[j]);
+  }
+}
+
+template <int TM, int TN>
+__global__ void __launch_bounds__(256) linear_mfma_f32(LinearArgs g, int vec) {
+  constexpr int BM = 16 * TM, BN = 16 * TN;   // block tile
+  constexpr int D = 4;                        // k steps of 16 in flight
+  __shared__ float part[kF32Runs * BM * (BN + 4)];
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, l16 = lane % 16, grp = lane / 16;
+  int64_t tm_, tn_;
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_);
+  const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
+  const float* a = (const float*)g.a + product * g.sa_b;
+  const float* w = (const float*)g.w + product * g.sw_b;
+  const float* ap[TM];
+  const float* wp[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {   // rows past the end shadow the last one; never stored
+    int64_t r = m0 + 16 * i + l16; if (r > g.m - 1) r = g.m - 1;
+    ap[i] = a + r * g.lda;
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    int64_t r = n0 + 16 * j + l16; if (r > g.n - 1) r = g.n - 1;
+    wp[j] = w + r * g.ldw;
+  }
+  const int k = (int)g.k, run = f32_run_len(g.k);
+  f32x4 acc[TM][TN];
+  // operands of the 16 k from k0 on; past the end of k any valid address (nothing uses what comes)
+  auto load = [&](f32x4 (&fa)[TM], f32x4 (&fw)[TN], int k0) {
+    const int kk = k0 + 4 * grp, kc = kk < k ? kk : 0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const f32x4*>(ap[i] + kc);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fw[j] = *reinterpret_cast<const f32x4*>(wp[j] + kc);
+  };
+  auto multiply = [&](const f32x4 (&fa)[TM], const f32x4 (&fw)[TN]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int lo = wave * run, hi = lo + run < k ? lo + run : k;
+  if (lo < hi) {
+    const int steps = (hi - lo) / 16;
+    f32x4 fa[D][TM], fw[D][TN];
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(fa[d], fw[d], lo + 16 * d);
+    int s = 0;
+    for (; s + D <= steps; s += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        multiply(fa[d], fw[d]);
+        load(fa[d], fw[d], lo + 16 * (s + d + D));
+      }
+    }
+#pragma unroll
+    for (int d = 0; d + 1 < D; ++d)
+      if (s + d < steps) multiply(fa[d], fw[d]);
+    if (lo + 16 * steps < hi) {        // k ends inside a step: lane groups past the end multiply zeros
+      load(fa[0], fw[0], lo + 16 * steps);
+      const bool in = lo + 16 * steps + 4 * grp < hi;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) fa[0][i][e] = in ? fa[0][i][e] : 0.f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) fw[0][j][e] = in ? fw[0][j][e] : 0.f;
+      multiply(fa[0], fw[0]);
+    }
+  }
+  // acc[i][j][r]: row m = m0 + 16 i + l16, column n = n0 + 16 j + 4 grp + r
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      *reinterpret_cast<f32x4*>(part + (wave * BM + 16 * i + l16) * (BN + 4) + 16 * j + 4 * grp) = acc[i][j];
+  __syncthreads();
+  for (int c = tid; c < BM * BN / 4; c += 256) {
+    const int rl = c / (BN / 4), cl = (c % (BN / 4)) * 4;
+    f32x4 v = *reinterpret_cast<const f32x4*>(part + rl * (BN + 4) + cl);
+#pragma unroll
+    for (int r = 1; r < kF32Runs; ++r) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>(part + (r * BM + rl) * (BN + 4) + cl);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += t[e];
+    }
+    epilogue_store_f32x4(g, vec, product, m0 + rl, n0 + cl, v);
+  }
 }
 
 // Block id -> position in a 1-D list of work items such that each XCD gets a contiguous run.
@@ -847,6 +999,29 @@ static bool mfma_eligible(const LinearArgs& g) {
   return true;
 }
 
+// fp32 products whose rows can be read 16 bytes at a time
+static bool mfma_f32_eligible(const LinearArgs& g) {
+  if (g.k % 4 != 0 || g.k > (1 << 30) || g.lda % 4 != 0 || g.ldw % 4 != 0 || g.bias_period > 0) return false;
+  if (g.batch > 1 && (g.sa_b % 4 != 0 || g.sw_b % 4 != 0)) return false;
+  return aligned_to(g.a, 16) && aligned_to(g.w, 16);
+}
+// ... and whose epilogue operands and output can be moved 16 bytes at a time
+static bool f32_rows_vectorisable(const LinearArgs& g) {
+  if (g.n_split % 4 != 0 || g.ldo % 4 != 0 || !aligned_to(g.out, 16)) return false;
+  if (g.batch > 1 && g.so_b % 4 != 0) return false;
+  if (g.o_period != INT64_MAX && (g.o_s1 % 4 != 0 || g.o_s2 % 4 != 0)) return false;
+  if (g.mul && (g.ldmul % 4 != 0 || !aligned_to(g.mul, 16))) return false;
+  if (g.resid && (g.ldr % 4 != 0 || !aligned_to(g.resid, 16))) return false;
+  return aligned_to(g.bias, 16);
+}
+
+template <int TM, int TN>
+static hipError_t mfma_f32_launch(const LinearArgs& g, hipStream_t s) {
+  const int64_t tiles = ((g.m + 16 * TM - 1) / (16 * TM)) * ((g.n + 16 * TN - 1) / (16 * TN));
+  hipLaunchKernelGGL((linear_mfma_f32<TM, TN>), dim3((unsigned)tiles, (unsigned)g.batch), dim3(256), 0, s, g, f32_rows_vectorisable(g) ? 1 : 0);
+  return hipGetLastError();
+}
+
 hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
   LinearArgs g = g_in;
   if (g.m <= 0 || g.n <= 0) return hipSuccess;
@@ -897,6 +1072,26 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
       case 3: return mfma_launch<64, 256, 1, 4>(g, s);
       case 4: return mfma_launch<64, 64, 2, 2>(g, s);
       default: return mfma_launch<32, 64, 1, 2>(g, s);
+    }
+  }
+  if (g.dtype == AC_F32 && mfma_f32_eligible(g)) {
+    // Rounds of 256 tiles (one per CU) x area of the tile; on a tie the larger tile, which reads less per output.
+    // 256 x 512 x 2048: 27 / 19 / 15 / 18 us with tiles of 32x64 / 32x32 / 32x16 / 16x16 (64, 128, 256 and 512 of them),
+    // 256 x 2048 x 512: 11.5 / 12.9 / 17.5 / 22 us (256 of 32x64).
+    static const int shapes[4][2] = {{2, 4}, {2, 2}, {2, 1}, {1, 1}};
+    int best = 0;
+    int64_t best_t = INT64_MAX;
+    for (int c = 0; c < 4; ++c) {
+      const int64_t bm = 16 * shapes[c][0], bn = 16 * shapes[c][1];
+      const int64_t tiles = ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn) * g.batch;
+      const int64_t t = (tiles + 255) / 256 * bm * bn;
+      if (t < best_t) { best = c; best_t = t; }
+    }
+    switch (best) {
+      case 0: return mfma_f32_launch<2, 4>(g, s);
+      case 1: return mfma_f32_launch<2, 2>(g, s);
+      case 2: return mfma_f32_launch<2, 1>(g, s);
+      default: return mfma_f32_launch<1, 1>(g, s);
     }
   }
   dim3 grid((unsigned)((g.n + 63) / 64), (unsigned)((g.m + 63) / 64), (unsigned)g.batch);

@@ -1,0 +1,68 @@
+"""GPU parity of the fp32 matrix-core kernels at the edges of their tiles, against the fp64 oracle, through the C-ABI."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import transformer as O
+from util import check, draw, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2401_10652_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("m,n,k", [
+    (1, 4, 4),                       # one row, less than one step of k: three of the four runs of k empty
+    (15, 20, 12), (17, 16, 68),      # 16x16 tiles; a run that ends inside a step
+    (64, 33, 64),                    # columns that end inside a 16-byte store
+    (250, 520, 2052),                # 32x16 tiles, ragged last run
+    (700, 1020, 260),                # 32x32 tiles, ragged both ways
+    (1100, 2100, 100),               # 32x64 tiles, ragged both ways
+])
+def test_linear_f32(B, m, n, k):
+    import torch
+    a, w = draw((m, k), 110, "f32"), draw((n, k), 111, "f32", 1 / math.sqrt(k))
+    bias, res = draw((n,), 112, "f32", 0.5), draw((m, n), 113, "f32")
+    da, dw, db, dr = (B.to_device(t, "f32") for t in (a, w, bias, res))
+    out = torch.full((m, n), float("nan"), device="cuda")
+    B.ac_op_linear(da, dw, out, bias=db, residual=dr)
+    torch.cuda.synchronize()
+    check(host(out), O.linear(a, w, bias) + res, "f32")
+    # a row's bits do not depend on the launch it falls in (nor on the tile shape that takes)
+    part = torch.full((m, n), float("nan"), device="cuda")
+    for r0 in range(0, m, 33):
+        r1 = min(m, r0 + 33)
+        B.ac_op_linear(da[r0:r1], dw, part[r0:r1], bias=db, residual=dr[r0:r1])
+    torch.cuda.synchronize()
+    assert torch.equal(part, out)
+
+
+@pytest.mark.parametrize("dh", [16, 32, 64, 128])
+@pytest.mark.parametrize("sq,sk,causal,off", [
+    (1, 1, False, 0), (16, 32, False, 0), (17, 33, True, 16), (70, 129, False, 0), (200, 200, True, 0), (40, 300, True, 260)])
+def test_attention_f32(B, dh, sq, sk, causal, off):
+    """Row counts around 16 and key counts around 32 (a wave without a tile, a ragged last tile), segments inside a
+    causal sequence; q, k and v are column blocks of one packed tensor."""
+    import torch
+    heads = 2
+    d = heads * dh
+    q, k, v = draw((sq, d), 120, "f32"), draw((sk, d), 121, "f32"), draw((sk, d), 122, "f32")
+    packed = torch.zeros((max(sq, sk), 3 * d), device="cuda")
+    packed[:sq, :d], packed[:sk, d:2 * d], packed[:sk, 2 * d:] = (B.to_device(t, "f32") for t in (q, k, v))
+    ctx = torch.full((sq, d), float("nan"), device="cuda")
+    views = packed[:sq, :d], packed[:sk, d:2 * d], packed[:sk, 2 * d:]
+    B.ac_op_attention(*views, ctx, heads, dh, causal=causal, q_offset=off)
+    torch.cuda.synchronize()
+    check(host(ctx), O.attention(q, k, v, heads, causal, q_offset=off), "f32")
+    part = torch.full((sq, d), float("nan"), device="cuda")
+    for r0 in range(0, sq, 7):
+        r1 = min(sq, r0 + 7)
+        B.ac_op_attention(views[0][r0:r1], views[1], views[2], part[r0:r1], heads, dh, causal=causal, q_offset=off + r0)
+    torch.cuda.synchronize()
+    assert torch.equal(part, ctx)
