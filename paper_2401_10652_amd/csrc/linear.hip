@@ -2,10 +2,8 @@
 // (AutoChunk section 2.2: the QKV / output / feed-forward projections applied to one
 // segment of rows; these are dense contractions and run on the bf16 matrix cores.)
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16, 256 threads = 4 waves in a 2x2 arrangement, block
-// tile BM x BN x 64 double-buffered in LDS (rows padded by 16 bytes so that the 128-bit
-// fragment reads of 32 consecutive rows hit distinct banks).  The weight rows feed the
-// MFMA "A" operand and the activation rows the "B" operand, so that every lane ends up
+// bf16 path: v_mfma_f32_32x32x16_bf16, block tiles of 32x64 to 256x256 by 64 k.  The weight rows
+// feed the MFMA "A" operand and the activation rows the "B" operand, so that every lane ends up
 // with one output row m and groups of 4 consecutive output columns n: the bias, multiplier
 // and residual are then 8-byte vector accesses and the result is stored 8 bytes at a time.
 // The K loop order does not depend on the tile's position in m, so a row's result is
@@ -13,6 +11,8 @@
 //
 // fp32 path and odd shapes: an LDS-tiled FMA kernel with full bounds checks.
 #include "common.h"
+
+#include <type_traits>
 
 #include <type_traits>
 
@@ -103,7 +103,8 @@ __global__ void __launch_bounds__(256) linear_fma(LinearArgs g) {
 }
 
 // ------------------------------------------------------------------------------------
-// bf16 MFMA kernel.
+// bf16 MFMA kernel, tiles staged through registers (128x128 on four waves, two blocks per CU, whose prologues and epilogues
+// overlap; 32x64 on two, for launches that would leave CUs without a tile).
 // ------------------------------------------------------------------------------------
 constexpr int kBK = 64;            // k extent of one LDS stage
 constexpr int kLdsRow = kBK + 8;   // padded row, in elements (144 bytes)
@@ -446,11 +447,7 @@ __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)
   }
 }
 
-// CONV: the A operand is gathered from channels-last images as the 3x3 convolution needs it (implicit GEMM):
-// a k tile of 64 lies inside one window position (conv_c is a multiple of 64), so it is the same 64 input
-// channels of the pixel shifted by that position for every row of the tile, or zeros where the shifted pixel
-// falls outside its image.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool CONV = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(LinearArgs g) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;           // threads
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
@@ -480,21 +477,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(Linea
   const bf16_t* a_src[A_CHUNKS];
   const bf16_t* w_src[W_CHUNKS];
   int a_dst[A_CHUNKS], w_dst[W_CHUNKS];
-  int a_taps[A_CHUNKS];   // CONV: bit t set = window position t of this row's pixel lies inside the image
 #pragma unroll
   for (int i = 0; i < A_CHUNKS; ++i) {
     const int c = tid + NT * i, row = c >> 3, ch = c & 7;
     int64_t gr = m0 + row; if (gr > g.m - 1) gr = g.m - 1;
-    a_src[i] = a + gr * (CONV ? (int64_t)g.conv_c : g.lda) + ch * 8;
+    a_src[i] = a + gr * g.lda + ch * 8;
     a_dst[i] = row * kLdsRow + ch * 8;
-    a_taps[i] = 0;
-    if (CONV) {
-      const int pix = (int)(gr % ((int64_t)g.conv_h * g.conv_w)), ph = pix / g.conv_w, pw = pix % g.conv_w;
-      for (int t = 0; t < 9; ++t) {
-        const int hh = ph + t / 3 - 1, ww = pw + t % 3 - 1;
-        if (hh >= 0 && hh < g.conv_h && ww >= 0 && ww < g.conv_w) a_taps[i] |= 1 << t;
-      }
-    }
   }
 #pragma unroll
   for (int i = 0; i < W_CHUNKS; ++i) {
@@ -530,20 +518,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(Linea
   constexpr int S = TM * TN < 4 ? 4 : 2;
   auto load_regs = [&](bf16x8 (&ar)[A_CHUNKS], bf16x8 (&wr)[W_CHUNKS], int64_t kt) {
     const int64_t koff = kt * kBK;
-    if (CONV) {
-      const int tap = (int)(koff / g.conv_c), c0 = (int)(koff % g.conv_c);
-      const int64_t shift = ((int64_t)(tap / 3 - 1) * g.conv_w + (tap % 3 - 1)) * g.conv_c + c0;
 #pragma unroll
-      for (int i = 0; i < A_CHUNKS; ++i) {
-        const bool inside = (a_taps[i] >> tap) & 1;
-        const bf16x8 v = *reinterpret_cast<const bf16x8*>(a_src[i] + (inside ? shift : (int64_t)c0));   // always a valid address
-        const bf16x8 zero = {};
-        ar[i] = inside ? v : zero;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < A_CHUNKS; ++i) ar[i] = *reinterpret_cast<const bf16x8*>(a_src[i] + koff);
-    }
+    for (int i = 0; i < A_CHUNKS; ++i) ar[i] = *reinterpret_cast<const bf16x8*>(a_src[i] + koff);
 #pragma unroll
     for (int i = 0; i < W_CHUNKS; ++i) wr[i] = *reinterpret_cast<const bf16x8*>(w_src[i] + koff);
   };
@@ -589,7 +565,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(Linea
   // (kt+1) & 1, multiplies tile kt from registers and writes tile kt+2 into buffer kt & 1 (whose reads were
   // issued a step ago and have completed before the barrier).  Same instructions on the same operands in the
   // same order per output element as the loop above, so results do not depend on which loop ran.
-  constexpr bool FRAGS_AHEAD = TM == 1 && TN == 1 && !CONV;
+  constexpr bool FRAGS_AHEAD = TM == 1 && TN == 1;
   if constexpr (FRAGS_AHEAD) {
     bf16x8 ra[S][A_CHUNKS], rw[S][W_CHUNKS];
     bf16x8 fa[2][KSTEPS], fw[2][KSTEPS];
@@ -674,9 +650,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(Linea
 template <int BM, int BN>
 constexpr size_t mfma_lds_bytes() { return (size_t)2 * (BM + BN) * kLdsRow * sizeof(bf16_t) + kGeluTableBytes; }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool CONV = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N>
 static hipError_t mfma_launch(const LinearArgs& g, hipStream_t s) {
-  auto kern = linear_mfma_bf16<BM, BN, WAVES_M, WAVES_N, CONV>;
+  auto kern = linear_mfma_bf16<BM, BN, WAVES_M, WAVES_N>;
   constexpr size_t lds = mfma_lds_bytes<BM, BN>();
   // the attribute is per function; set once per process (the initialiser runs once, thread-safe)
   static const hipError_t attr_status = hipFuncSetAttribute(
@@ -684,6 +660,375 @@ static hipError_t mfma_launch(const LinearArgs& g, hipStream_t s) {
   if (attr_status != hipSuccess) return attr_status;
   const int64_t tiles = ((g.m + BM - 1) / BM) * ((g.n + BN - 1) / BN);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)g.batch), dim3(64 * WAVES_M * WAVES_N), lds, s, g);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------
+// bf16 MFMA kernel, tiles by direct global-to-LDS loads through a ring of STAGES buffers.
+//
+// What bounds it: a k loop that stages through registers pays for every byte twice, once as a load and once as an
+// LDS store (LDS takes stores at about a third of its read rate), and with two buffers all waves wait at
+// every barrier for the youngest loads.  Here one wave instruction moves 1 KB from memory into LDS with no register
+// and no store instruction, a tile has STAGES - 2 whole steps to arrive (the wait before a barrier counts the younger
+// tiles' loads as still in flight), and the fragments of tile kt + 1 are read from LDS between the matrix instructions of
+// tile kt, so that the matrix pipe waits neither for LDS nor for memory.  Addresses are a scalar base, a scalar tile offset and
+// 32 bits per lane (buffer loads: 1204 against 1157 TFLOP/s with 64-bit lane addresses, 65536 x 2048 x 8192).
+// Measured against register staging with the same tiles (65536 x 2048 x 8192 / 6400 x 1024 x 1024 / 4096 x 768 x 768):
+// 256x128 2152 -> 1840 us / 22.1 -> 20.0 / 16.8 -> 15.2, 64x64 3570 -> 3376 / 31.0 -> 27.1 / 14.4 -> 11.7.
+//
+// LDS rows are BK elements without padding (a direct load writes 1 KB of consecutive LDS); the 16-byte chunks
+// of a row are permuted instead: chunk c of row r lies at position c ^ swz(r).  A 128-bit read serves 16 lanes at a time over
+// 256 bytes of banks, lanes 0-3, 12-15, 20-23, 24-27 together and the other sixteen of a half-wave together; swz gives
+// either set sixteen different slots (SQ_LDS_BANK_CONFLICT 1 % of SQ_LDS_IDX_ACTIVE; a rule for runs of 16 or 32 consecutive lanes
+// left 50 % on 64-byte rows).  The permutation is applied to the lane's global address, inside one cache line.
+// Same matrix instructions on the same operands in the same k order as the kernel above: equal bits.
+// ------------------------------------------------------------------------------------
+template <int BK> __device__ __forceinline__ int ring_swizzle(int r) {
+  return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3;
+}
+constexpr int ring_lds_bytes(int bm, int bn, int bk, int stages) {
+  const int ring = stages * (bm + bn) * bk * 2;
+  const int out = bm * (bn + 8) * 2, out_t = bn * (bm + 8) * 2;       // the epilogue's staging tile, plain or transposed
+  const int most = out > out_t ? out : out_t;
+  return ring > most ? ring : most;
+}
+__device__ const bf16_t kZeroRow[64] __attribute__((aligned(128))) = {};   // source of the chunks of pixels outside their image
+
+// After the k loop (every load landed, every wave past its last LDS read): one branch per launch, so the activation is
+// inlined without a per-element switch.
+template <int BM, int BN, int WAVES_M, int WAVES_N>
+__device__ __forceinline__ void finish_tile(const LinearArgs& g, f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32],
+                                            unsigned char* smem, float* gelu_tab, int64_t m0, int64_t n0, int wave_m, int wave_n,
+                                            int l32, int half, int tid) {
+  bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
+  if (g.act == AC_ACT_GELU_ERF) { gelu_table_fill(gelu_tab, tid, 64 * WAVES_M * WAVES_N); __syncthreads(); }
+  switch (g.act) {
+    case AC_ACT_GELU_ERF: epilogue_tile<AC_ACT_GELU_ERF, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_GELU_TANH: epilogue_tile<AC_ACT_GELU_TANH, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_RELU: epilogue_tile<AC_ACT_RELU, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_SIGMOID: epilogue_tile<AC_ACT_SIGMOID, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    default: epilogue_tile<AC_ACT_NONE, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+  }
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(LinearArgs g) {
+  constexpr int NW = WAVES_M * WAVES_N;
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+  constexpr int ROWB = BK * 2, CPR = ROWB / 16, RPI = 1024 / ROWB;      // bytes and chunks per LDS row, rows per load instruction
+  constexpr int A_I = BM / RPI / NW, W_I = BN / RPI / NW, PER = A_I + W_I;   // load instructions of a wave per tile
+  constexpr int KSTEPS = BK / 16, READS = KSTEPS * (TM + TN), MMAS = KSTEPS * TM * TN;
+  constexpr int STAGE = (BM + BN) * ROWB;
+  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && STAGES >= 3 && (NW * RPI) % 32 == 0 && MMAS >= PER, "tile / wave layout mismatch");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  float* gelu_tab = reinterpret_cast<float*>(smem_raw + ring_lds_bytes(BM, BN, BK, STAGES));
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
+  const int l32 = lane % 32, half = lane / 32;
+  int64_t tm_, tn_;
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_);
+  const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
+  g.out = (bf16_t*)g.out + product * g.so_b;
+
+  // Sources: a wave-uniform base that advances with k plus a 32-bit byte offset per lane and instruction (rows past the end
+  // shadow the last one; their results are never stored).
+  const int64_t lda = CONV ? (int64_t)g.conv_c : g.lda;
+  const unsigned char* a_base = (const unsigned char*)((const bf16_t*)g.a + product * g.sa_b + m0 * lda);
+  const unsigned char* w_base = (const unsigned char*)((const bf16_t*)g.w + product * g.sw_b + n0 * g.ldw);
+  const int row_in = lane / CPR;                                        // row of the instruction this lane moves
+  const int src_chunk = (lane % CPR) ^ ring_swizzle<BK>(wave * RPI + row_in);   // (NW instructions apart is a multiple of 32 rows)
+  uint32_t a_off[A_I], w_off[W_I];
+  int a_taps[A_I];   // CONV: bit t set = window position t of this row's pixel lies inside the image
+#pragma unroll
+  for (int i = 0; i < A_I; ++i) {
+    const int64_t last = g.m - 1 - m0;
+    const int row = (wave + NW * i) * RPI + row_in;
+    const int64_t rc = row < last ? row : last;
+    a_off[i] = (uint32_t)(rc * lda * 2) + src_chunk * 16;
+    a_taps[i] = 0;
+    if (CONV) {
+      const int pix = (int)((m0 + rc) % ((int64_t)g.conv_h * g.conv_w)), ph = pix / g.conv_w, pw = pix % g.conv_w;
+      for (int t = 0; t < 9; ++t) {
+        const int hh = ph + t / 3 - 1, ww = pw + t % 3 - 1;
+        if (hh >= 0 && hh < g.conv_h && ww >= 0 && ww < g.conv_w) a_taps[i] |= 1 << t;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < W_I; ++i) {
+    const int64_t last = g.n - 1 - n0;
+    const int row = (wave + NW * i) * RPI + row_in;
+    w_off[i] = (uint32_t)((row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
+  }
+  // (addresses: base and tile offset in scalar registers, 32 bits per lane; every lane's address is valid, so the range is open)
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, -1, 0x00027000);
+  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(w_base), 0, -1, 0x00027000);
+  auto to_lds = [](const unsigned char* src, unsigned char* dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+  };
+  // load instruction x of the PER that bring in this wave's share of tile kt
+  auto load_part = [&](int kt, int stage, int x) {
+    unsigned char* dst = smem_raw + stage * STAGE + (x < A_I ? x * NW * 1024 : BM * ROWB + (x - A_I) * NW * 1024) + wave * 1024;
+    auto buffer_to_lds = [](__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, uint32_t tile_off, unsigned char* lds) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, lane_off, tile_off, 0, 0);
+    };
+    if (x >= A_I) {
+      buffer_to_lds(w_rsrc, w_off[x - A_I], kt * ROWB, dst);
+    } else if (CONV) {
+      const int koff = kt * BK, tap = koff / g.conv_c, c0 = koff % g.conv_c;   // a tile lies inside one window position
+      const int64_t shift = (((int64_t)(tap / 3 - 1) * g.conv_w + (tap % 3 - 1)) * g.conv_c + c0) * 2;
+      to_lds((a_taps[x] >> tap) & 1 ? a_base + shift + a_off[x] : (const unsigned char*)kZeroRow, dst);
+    } else {
+      buffer_to_lds(a_rsrc, a_off[x], kt * ROWB, dst);
+    }
+  };
+  // this wave's loads of all but the youngest `tiles` tiles have landed and its LDS reads are done, then every wave's
+  auto arrived = [&](int tiles) {
+    constexpr int kNoExp = 7 << 4;   // (the wait counters' encoding; expcnt is not waited for, lgkmcnt is waited to 0)
+    auto wait = [](auto n) {
+      constexpr int N = decltype(n)::value;
+      static_assert(N < 64, "vmcnt has 6 bits");
+      __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | kNoExp);
+    };
+    asm volatile("" ::: "memory");
+    if (STAGES >= 5 && tiles >= 3) wait(std::integral_constant<int, STAGES >= 5 ? 3 * PER : 0>{});
+    else if (STAGES >= 4 && tiles >= 2) wait(std::integral_constant<int, STAGES >= 4 ? 2 * PER : 0>{});
+    else if (tiles >= 1) wait(std::integral_constant<int, PER>{});
+    else wait(std::integral_constant<int, 0>{});
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  bf16x8 fa[2][KSTEPS][TM], fw[2][KSTEPS][TN];
+  int frag_off[KSTEPS];
+#pragma unroll
+  for (int ks = 0; ks < KSTEPS; ++ks) frag_off[ks] = l32 * ROWB + (((ks * 2 + half) ^ ring_swizzle<BK>(l32)) * 16);
+  const unsigned char* const sA = smem_raw + wave_m * WM * ROWB;
+  const unsigned char* const sW = smem_raw + BM * ROWB + wave_n * WN * ROWB;
+  // read r of a tile's READS fragments, in the order the matrix instructions want them
+  auto read_frag = [&](bf16x8 (&fa_)[KSTEPS][TM], bf16x8 (&fw_)[KSTEPS][TN], int base, int r) {
+    const int ks = r / (TM + TN), x = r % (TM + TN);
+    if (x < TN) fw_[ks][x] = *reinterpret_cast<const bf16x8*>(sW + base + frag_off[ks] + x * 32 * ROWB);
+    else fa_[ks][x - TN] = *reinterpret_cast<const bf16x8*>(sA + base + frag_off[ks] + (x - TN) * 32 * ROWB);
+  };
+  const int kt_count = (int)(g.k / BK);
+  // Step kt: multiply tile kt (its fragments are in registers), read tile kt + 1's, and load tile kt + STAGES into the
+  // buffer tile kt lay in.  `stage` = kt % STAGES.
+  int kt = 0, stage = 0;
+  auto step = [&](const bf16x8 (&ca)[KSTEPS][TM], const bf16x8 (&cw)[KSTEPS][TN], bf16x8 (&na)[KSTEPS][TM], bf16x8 (&nw)[KSTEPS][TN]) {
+    const bool more = kt + STAGES < kt_count;
+    const int free_stage = stage;
+    stage = stage + 1 == STAGES ? 0 : stage + 1;
+    const int base = stage * STAGE;
+    __builtin_amdgcn_sched_barrier(0);
+    int done = 0;
+#pragma unroll
+    for (int x = 0; x < MMAS; ++x) {
+      const int ks = x / (TM * TN), i = (x / TN) % TM, j = x % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cw[ks][j], ca[ks][i], acc[i][j], 0, 0, 0);
+      // the reads are spread over the first three quarters of the matrix instructions (past the last tile they
+      // fetch what an older tile left in the ring; nothing uses it)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (done < READS && done * (3 * MMAS) < (x + 1) * 4 * READS) read_frag(na, nw, base, done++);
+      // the loads are spread too: issued together after a barrier, those of all waves queue up at the one address
+      // unit and hold back the matrix instructions behind them
+      if (x % (MMAS / PER) == 0 && x / (MMAS / PER) < PER) {
+        if (more) load_part(kt + STAGES, free_stage, x / (MMAS / PER));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int newest = kt + STAGES < kt_count ? kt + STAGES : kt_count - 1;
+    arrived(newest - (kt + 2));
+    ++kt;
+  };
+  const int ahead = kt_count < STAGES ? kt_count : STAGES;
+  for (int t = 0; t < ahead; ++t) {
+#pragma unroll
+    for (int x = 0; x < PER; ++x) load_part(t, t, x);
+  }
+  arrived(ahead - 1 < STAGES - 2 ? ahead - 1 : STAGES - 2);             // tile 0 (and, with a full ring, tile 1)
+#pragma unroll
+  for (int r = 0; r < READS; ++r) read_frag(fa[0], fw[0], 0, r);
+  arrived(ahead - 2);                                                   // tile 1
+  while (true) {
+    step(fa[0], fw[0], fa[1], fw[1]);
+    if (kt >= kt_count) break;
+    step(fa[1], fw[1], fa[0], fw[0]);
+    if (kt >= kt_count) break;
+  }
+  finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
+}
+
+// ------------------------------------------------------------------------------------
+// bf16 MFMA kernel, 256x256 tiles on eight waves, 64 k per tile.
+//
+// What bounds it: the operand stream.  A CU keeps about a hundred requests to L2 in flight at some 400 clocks each, one per
+// cache line touched, so loads must ask for whole 128-byte lines (rows of 64 k: 32-k rows doubled the requests and
+// ran the L1 at its limit with the matrix pipe 66 % busy) and must not pause.  Two whole 64-k tiles fill the LDS, so
+// the ring of the kernel above would have one tile in flight at best; here the unit that is freed and loaded is half a tile,
+// split along the ROWS: a wave's 128x64 outputs are four quadrants, half 0 of the rows of A and W (a0, w0) and
+// half 1 (a1, w1), visited as a0w0, a0w1 | a1w1, a1w0, and while two quadrants are multiplied the fragments of the
+// next two are read:
+//   step X(t): multiply a0w0, a0w1 of tile t;  read w1, a1 of tile t;      load half 0 of tile t + 2
+//   step Y(t): multiply a1w1, a1w0 of tile t;  read a0, w0 of tile t + 1;  load half 1 of tile t + 2
+// Every load has two whole steps and what is left of its own to arrive.  Fragment registers: a0, a1 and two sets for w that
+// swap roles every tile.  Against the ring on 32-k rows and against register staging: 65536 x 2048 x 8192 in 1645 us
+// (1337 TFLOP/s; 1811 and 1873), 65536 x 8192 x 2048 in 1836 (2041 and 2011), 4000 x 4096 x 1024 in 35.8 (38.3 and 38.1).
+// Same matrix instructions in the same k order per output as the kernels above: equal bits.
+// ------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
+  constexpr int BM = 256, BN = 256, WAVES_M = 2, WAVES_N = 4, NW = 8, TM = 4, TN = 2, BK = 64, ROWB = 128;
+  constexpr int BUF = (BM + BN) * ROWB;                                 // bytes of one tile
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  float* gelu_tab = reinterpret_cast<float*>(smem_raw + ring_lds_bytes(BM, BN, BK, 2));
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
+  const int l32 = lane % 32, half = lane / 32;
+  int64_t tm_, tn_;
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_);
+  const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
+  g.out = (bf16_t*)g.out + product * g.so_b;
+
+  const bf16_t* a_base = (const bf16_t*)g.a + product * g.sa_b + m0 * g.lda;
+  const bf16_t* w_base = (const bf16_t*)g.w + product * g.sw_b + n0 * g.ldw;
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a_base), 0, -1, 0x00027000);
+  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(w_base), 0, -1, 0x00027000);
+  // A load instruction moves 8 rows of 128 bytes.  Instruction j (0, 1) of this wave in half h: first row of its eight.
+  auto a_row = [&](int h, int j) { return j * 128 + h * 64 + wave * 8; };
+  auto w_row = [&](int h, int j) { return (wave / 4 + 2 * j) * 64 + h * 32 + (wave % 4) * 8; };
+  const int row_in = lane / 8;
+  const int src_chunk = (lane % 8) ^ ring_swizzle<BK>(wave * 8 + row_in);
+  uint32_t a_off[2][2], w_off[2][2];                                    // rows past the end shadow the last one
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int64_t la = g.m - 1 - m0, lw = g.n - 1 - n0;
+      const int ra = a_row(h, j) + row_in, rw = w_row(h, j) + row_in;
+      a_off[h][j] = (uint32_t)((ra < la ? ra : la) * g.lda * 2) + src_chunk * 16;
+      w_off[h][j] = (uint32_t)((rw < lw ? rw : lw) * g.ldw * 2) + src_chunk * 16;
+    }
+  auto load_half = [&](int kt, int h, int x) {                          // instruction x of the four of half h of tile kt
+    unsigned char* dst = smem_raw + (kt & 1) * BUF + (x < 2 ? a_row(h, x) : BM + w_row(h, x - 2)) * ROWB;
+    if (x < 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (__attribute__((address_space(3))) void*)dst, 16, a_off[h][x], kt * ROWB, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (__attribute__((address_space(3))) void*)dst, 16, w_off[h][x - 2], kt * ROWB, 0, 0);
+  };
+  // this wave's loads of all but the youngest `halves` half tiles have landed and its LDS reads are done, then every wave's
+  auto arrived = [&](int halves) {
+    asm volatile("" ::: "memory");
+    if (halves >= 2) __builtin_amdgcn_s_waitcnt(0x78);                  // vmcnt(8) lgkmcnt(0)
+    else if (halves == 1) __builtin_amdgcn_s_waitcnt(0x74);             // vmcnt(4) lgkmcnt(0)
+    else __builtin_amdgcn_s_waitcnt(0x70);                              // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  bf16x8 a0[2][4], a1[2][4], wa[4], wb[4];                              // [32-row tile][k step of 16]
+  int frag_off[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) frag_off[ks] = l32 * ROWB + (((ks * 2 + half) ^ ring_swizzle<BK>(l32)) * 16);
+  const unsigned char* const sA = smem_raw + wave_m * 128 * ROWB;
+  const unsigned char* const sW = smem_raw + (BM + wave_n * 64) * ROWB;
+  auto read_a = [&](bf16x8 (&f)[2][4], int kt, int h, int x) {          // fragment x of 8
+    f[x & 1][x >> 1] = *reinterpret_cast<const bf16x8*>(sA + (kt & 1) * BUF + (h * 64 + (x & 1) * 32) * ROWB + frag_off[x >> 1]);
+  };
+  auto read_w = [&](bf16x8 (&f)[4], int kt, int h, int x) {             // fragment x of 4
+    f[x] = *reinterpret_cast<const bf16x8*>(sW + (kt & 1) * BUF + h * 32 * ROWB + frag_off[x]);
+  };
+  const int kt_count = (int)(g.k / BK);
+  // Both steps: 16 matrix instructions, 12 fragment reads among the first 12 of them, 4 loads spread evenly.  (Past the last
+  // tile the reads fetch what an older one left; nothing uses it.)
+  auto step_x = [&](int kt, bf16x8 (&w0)[4], bf16x8 (&w1)[4]) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const int q = x / 8, ks = (x % 8) / 2, i = x % 2;
+      if (q == 0) acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0[ks], a0[i][ks], acc[i][0], 0, 0, 0);
+      else acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[ks], a0[i][ks], acc[i][1], 0, 0, 0);
+      if (x < 4) read_w(w1, kt, 1, x);
+      else if (x < 12) read_a(a1, kt, 1, x - 4);
+      if (x % 4 == 0) { if (kt + 2 < kt_count) load_half(kt + 2, 0, x / 4); }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // read next: half 0 of tile kt + 1.  Younger: its half 1, half 0 of kt + 2
+    arrived(kt + 2 < kt_count ? 2 : kt + 1 < kt_count ? 1 : 0);
+  };
+  auto step_y = [&](int kt, bf16x8 (&w0)[4], bf16x8 (&w1)[4]) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const int q = x / 8, ks = (x % 8) / 2, i = x % 2;
+      if (q == 0) acc[2 + i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[ks], a1[i][ks], acc[2 + i][1], 0, 0, 0);
+      else acc[2 + i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0[ks], a1[i][ks], acc[2 + i][0], 0, 0, 0);
+      if (x < 8) read_a(a0, kt + 1, 0, x);
+      else if (x < 12) read_w(w1, kt + 1, 0, x - 8);
+      if (x % 4 == 0) { if (kt + 2 < kt_count) load_half(kt + 2, 1, x / 4); }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // read next: half 1 of tile kt + 1.  Younger: both halves of kt + 2
+    arrived(kt + 2 < kt_count ? 2 : 0);
+  };
+#pragma unroll
+  for (int x = 0; x < 8; ++x) load_half(0, x / 4, x % 4);
+  if (kt_count > 1) {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) load_half(1, x / 4, x % 4);
+  }
+  arrived(kt_count > 1 ? 2 : 0);                                        // tile 0
+#pragma unroll
+  for (int x = 0; x < 8; ++x) read_a(a0, 0, 0, x);
+#pragma unroll
+  for (int x = 0; x < 4; ++x) read_w(wa, 0, 0, x);
+  arrived(kt_count > 1 ? 2 : 0);                                        // (every wave has read half 0 of tile 0)
+  for (int kt = 0; ; kt += 2) {
+    step_x(kt, wa, wb);
+    step_y(kt, wa, wb);
+    if (kt + 1 >= kt_count) break;
+    step_x(kt + 1, wb, wa);
+    step_y(kt + 1, wb, wa);
+    if (kt + 2 >= kt_count) break;
+  }
+  finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false>
+static hipError_t ring_launch(const LinearArgs& g, hipStream_t s) {
+  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV>;
+  constexpr size_t ring = ring_lds_bytes(BM, BN, BK, STAGES);
+  static const hipError_t attr_status = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(ring + kGeluTableBytes));
+  if (attr_status != hipSuccess) return attr_status;
+  const int64_t tiles = ((g.m + BM - 1) / BM) * ((g.n + BN - 1) / BN);
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)g.batch), dim3(64 * WAVES_M * WAVES_N),
+                     ring + (g.act == AC_ACT_GELU_ERF ? kGeluTableBytes : 0), s, g);
+  return hipGetLastError();
+}
+
+static hipError_t quad_launch(const LinearArgs& g, hipStream_t s) {
+  constexpr size_t lds = ring_lds_bytes(256, 256, 64, 2);
+  static const hipError_t attr_status = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(linear_quad_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds + kGeluTableBytes));
+  if (attr_status != hipSuccess) return attr_status;
+  const int64_t tiles = ((g.m + 255) / 256) * ((g.n + 255) / 256);
+  hipLaunchKernelGGL(linear_quad_bf16, dim3((unsigned)tiles, (unsigned)g.batch), dim3(512),
+                     lds + (g.act == AC_ACT_GELU_ERF ? kGeluTableBytes : 0), s, g);
   return hipGetLastError();
 }
 
@@ -988,7 +1333,7 @@ static bool mfma_eligible(const LinearArgs& g) {
   if (g.dtype != AC_BF16) return false;
   if (g.k < kBK || g.k % kBK != 0) return false;
   if (g.n % 4 != 0 || g.n_split % 4 != 0) return false;
-  if (g.lda % 8 != 0 || g.ldw % 8 != 0) return false;
+  if (g.lda % 8 != 0 || g.ldw % 8 != 0 || g.lda >= (1 << 22) || g.ldw >= (1 << 22)) return false;   // (32-bit byte offsets inside a tile)
   if (!aligned_to(g.a, 16) || !aligned_to(g.w, 16)) return false;
   if (g.n_split > 0 && (g.ldo % 4 != 0 || !aligned_to(g.out, 8))) return false;
   if (g.o_period != INT64_MAX && (g.o_s1 % 4 != 0 || g.o_s2 % 4 != 0)) return false;
@@ -997,6 +1342,34 @@ static bool mfma_eligible(const LinearArgs& g) {
   if (g.mul && (g.ldmul % 4 != 0 || !aligned_to(g.mul, 8))) return false;
   if (g.resid && (g.ldr % 4 != 0 || !aligned_to(g.resid, 8))) return false;
   return true;
+}
+
+// Tile shapes of the bf16 GEMM, and the one with the least estimated time.  A launch is tiles / 256 rounds of the CUs (a last
+// round that is partly empty runs faster: half of it is counted) of k / 64 steps plus a prologue and an epilogue per tile, plus
+// what is paid once; the three times of a shape, in us, are fitted to 67 launches of 512 to 65536 rows x 64 to 4096
+// columns x 64 to 4096 deep, batched ones among them, on which the choice is within 5 % of the best shape but for three (7 %).  Shapes whose blocks
+// share a CU pay little per tile and more per step.  Examples (us; 256x256 / 256x128 / 128x128 ring / 128x128 / 128x64 /
+// 64x64 / 32x64):  65536x1024x1024  144 / 181 / 230 / 182 / 236 / 251 / 359;  6400x1024x1024  27 / 20 / 23 / 23 / 26 / 27 / 35;
+// 4000x1024x4096  78 / 56 / 42 / 46 / 52 / 64 / 83;  512x1024x4096  72 / 43 / 27 / 40 / 29 / 21 / 14.5.
+// The k order is the same for all of them, and so are the bits.
+enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x64, kTileShapes };
+static TileShape best_tile(const LinearArgs& g, bool conv) {
+  struct Cost { int bm, bn; double step, tile, once; bool conv; };
+  static const Cost costs[kTileShapes] = {{256, 256, 1.09, 11.7, 0.0, false}, {256, 128, 0.68, 8.1, 0.0, false},
+                                          {128, 128, 0.45, 5.1, 0.3, true},   {128, 128, 0.54, 2.6, 4.3, false},
+                                          {128, 64, 0.36, 1.4, 4.3, true},    {64, 64, 0.17, 0.8, 4.8, true},
+                                          {32, 64, 0.13, 0.65, 5.3, false}};
+  int best = -1;
+  double best_t = 0;
+  for (int c = 0; c < kTileShapes; ++c) {
+    if (conv && !costs[c].conv) continue;
+    const int64_t tiles = ((g.m + costs[c].bm - 1) / costs[c].bm) * ((g.n + costs[c].bn - 1) / costs[c].bn) * g.batch;
+    const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
+    const double rounds = whole <= 1 ? 1 : 0.5 * (exact + whole);
+    const double t = rounds * ((double)(g.k / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
+    if (best < 0 || t < best_t) { best = c; best_t = t; }
+  }
+  return (TileShape)best;
 }
 
 // fp32 products whose rows can be read 16 bytes at a time
@@ -1035,42 +1408,30 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
   if (g.batch > 1 && (g.bias || g.mul || g.resid || g.out_t || g.act != AC_ACT_NONE)) return hipErrorInvalidValue;
   if (g.batch > 65535 || g.m > 0x7fffffffLL) return hipErrorInvalidValue;
   if (g.conv_c > 0) {
-    // 3x3 convolution as an implicit GEMM on 128x128 tiles; bf16 images with channels in multiples of 64 only
+    // 3x3 convolution as an implicit GEMM; bf16 images with channels in multiples of 64 only
     if (g.dtype != AC_BF16 || g.conv_c % kBK != 0 || g.conv_h < 1 || g.conv_w < 1 || g.k != 9 * (int64_t)g.conv_c ||
         g.m % ((int64_t)g.conv_h * g.conv_w) != 0 || g.batch != 1)
       return hipErrorInvalidValue;
     g.lda = g.conv_c;
     if (!mfma_eligible(g)) return hipErrorInvalidValue;
-    return mfma_launch<128, 128, 2, 2, true>(g, s);
+    switch (best_tile(g, true)) {
+      case k128x128Ring: return ring_launch<128, 128, 2, 4, 64, 3, true>(g, s);
+      case k128x64: return ring_launch<128, 64, 2, 2, 64, 3, true>(g, s);
+      default: return ring_launch<64, 64, 2, 2, 64, 3, true>(g, s);
+    }
   }
   if (mfma_eligible(g)) {
-    // A CU takes in at most 64 bytes per clock from L2 while its matrix cores retire 4096
-    // flops per clock, so a tile needs >= 64 flops per loaded byte just to break even: 128x128
-    // tiles sit exactly there, 256x256 tiles have twice that.  Pick the tile with the least
-    // estimated time: tiles per CU (rounded up) x padded tile area / measured efficiency of
-    // that tile shape.  The k order is the same for all of them.
-    // The small tiles are for launches of a few hundred rows.  Their k loop runs at the rate one CU
-    // stages operands (measured: ~80 GB/s per CU, i.e. (BM + BN) x 128 bytes per k step), so with at
-    // most one tile per CU the time goes with BM + BN, and a launch that needs a second tile on some
-    // CUs takes twice as long: 512 x 768 is faster as 192 tiles of 32x64 than as 96 of 64x64 (and no
-    // faster as 384 of 32x32).  64x128 tiles were measured too: 512 x 3072 x 768 takes 12.7 us as 192
-    // of those against 11.0 us as 384 tiles of 64x64.
-    struct Cand { int bm, bn; double eff; };
-    static const Cand cands[6] = {{256, 256, 0.41}, {256, 128, 0.376}, {128, 128, 0.36}, {64, 256, 0.26},
-                                  {64, 64, 0.253}, {32, 64, 0.169}};
-    int best = 0;
-    double best_t = 0;
-    for (int c = 0; c < 6; ++c) {
-      const int64_t tiles = ((g.m + cands[c].bm - 1) / cands[c].bm) * ((g.n + cands[c].bn - 1) / cands[c].bn) * g.batch;
-      const double t = (double)((tiles + 255) / 256) * cands[c].bm * cands[c].bn / cands[c].eff;
-      if (c == 0 || t < best_t) { best = c; best_t = t; }
-    }
-    switch (best) {
-      case 0: return mfma_launch<256, 256, 2, 4>(g, s);
-      case 1: return mfma_launch<256, 128, 4, 2>(g, s);
-      case 2: return mfma_launch<128, 128, 2, 2>(g, s);
-      case 3: return mfma_launch<64, 256, 1, 4>(g, s);
-      case 4: return mfma_launch<64, 64, 2, 2>(g, s);
+    switch (best_tile(g, false)) {
+      case kQuad: return quad_launch(g, s);
+      case k256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
+      case k128x128Ring: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
+      case k128x128: return mfma_launch<128, 128, 2, 2>(g, s);
+      case k128x64: return ring_launch<128, 64, 2, 2, 64, 3>(g, s);
+      // (a CU that holds one such block has nothing else to hide behind while operands come from memory: five buffers
+      // instead of three.  1000 x 1024 x 4096 inside a model 25.9 -> 21 us; but 512 x 3072 x 768, 384 tiles, 10.4 -> 15 us: the
+      // second block no longer fits)
+      case k64x64:
+        return ((g.m + 63) / 64) * ((g.n + 63) / 64) * g.batch <= 256 ? ring_launch<64, 64, 2, 2, 64, 5>(g, s) : ring_launch<64, 64, 2, 2, 64, 3>(g, s);
       default: return mfma_launch<32, 64, 1, 2>(g, s);
     }
   }

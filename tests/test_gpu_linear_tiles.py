@@ -1,0 +1,56 @@
+"""GPU parity of the bf16 GEMM's tile shapes at their edges: k of one to seven tiles (shorter than, equal to and longer than the ring of
+LDS buffers), rows and columns that end inside a tile, batched products, and equal bits whatever shape a launch takes."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import transformer as O
+from util import check, draw, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2401_10652_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("m,n", [
+    (5000, 5000),      # 256x256
+    (8100, 1020),      # 256x128
+    (4000, 760),       # 128x128 with a ring
+    (1000, 640),       # 64x64, at most one per CU
+    (1990, 2040),      # 64x64 / 128x64 in several rounds
+    (100, 100),        # 32x64
+])
+@pytest.mark.parametrize("k", [64, 128, 192, 320, 448])
+def test_linear_tiles(B, m, n, k):
+    """One launch against fp64 on sampled rows, and against the same rows in launches of other tile shapes, bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    a = torch.randn((m, k), generator=g, device="cuda").bfloat16()
+    w = (torch.randn((n, k), generator=g, device="cuda") / math.sqrt(k)).bfloat16()
+    res = torch.randn((m, n), generator=g, device="cuda").bfloat16()
+    out = torch.full((m, n), float("nan"), device="cuda", dtype=torch.bfloat16)
+    B.ac_op_linear(a, w, out, residual=res)
+    rows = np.unique(np.concatenate([np.arange(min(m, 40)), np.arange(max(0, m - 40), m), np.arange(0, m, 61)]))
+    t = torch.from_numpy(rows).cuda()
+    check(host(out[t]), O.linear(host(a[t]), host(w)) + host(res[t]), "bf16")
+    part = torch.full((m, n), float("nan"), device="cuda", dtype=torch.bfloat16)
+    for r0 in range(0, m, 1017):
+        r1 = min(m, r0 + 1017)
+        B.ac_op_linear(a[r0:r1], w, part[r0:r1], residual=res[r0:r1])
+    assert torch.equal(part, out)
+
+
+@pytest.mark.parametrize("c,ni,nj,nk", [(16, 64, 1024, 1024), (3, 700, 900, 192), (5, 40, 72, 64)])
+def test_batched_products(B, c, ni, nj, nk):
+    import torch
+    a, b = draw((c, ni, nk), 140, "bf16"), draw((c, nj, nk), 141, "bf16", 1 / math.sqrt(nk))
+    out = torch.full((c, ni, nj), float("nan"), device="cuda", dtype=torch.bfloat16)
+    B.ac_op_triangle_contract(B.to_device(a, "bf16"), B.to_device(b, "bf16"), out)
+    torch.cuda.synchronize()
+    check(host(out), np.matmul(a.astype(np.float64), b.astype(np.float64).transpose(0, 2, 1)), "bf16")
