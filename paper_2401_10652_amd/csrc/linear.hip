@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(256) linear_fma(LinearArgs g) {
 
 // ------------------------------------------------------------------------------------
 // bf16 MFMA kernel, tiles staged through registers (128x128 on four waves, two blocks per CU, whose prologues and epilogues
-// overlap; 32x64 on two, for launches that would leave CUs without a tile).
+// overlap; 64x64 and 32x64 for launches of at most one block per CU).
 // ------------------------------------------------------------------------------------
 constexpr int kBK = 64;            // k extent of one LDS stage
 constexpr int kLdsRow = kBK + 8;   // padded row, in elements (144 bytes)
@@ -711,7 +711,7 @@ __device__ __forceinline__ void finish_tile(const LinearArgs& g, f32x16 (&acc)[B
   }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(LinearArgs g) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
@@ -773,7 +773,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     auto buffer_to_lds = [](__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, uint32_t tile_off, unsigned char* lds) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, lane_off, tile_off, 0, 0);
     };
-    if (x >= A_I) {
+    if (RAGGED_K && kt * BK + BK > (int)g.k) {   // the last tile: chunks past the end of k are zeros in both operands
+      const bool in = kt * BK + src_chunk * 8 < (int)g.k;
+      const unsigned char* src = x >= A_I ? w_base + (int64_t)kt * ROWB + w_off[x >= A_I ? x - A_I : 0] : a_base + (int64_t)kt * ROWB + a_off[x < A_I ? x : 0];
+      to_lds(in ? src : (const unsigned char*)kZeroRow, dst);
+    } else if (x >= A_I) {
       buffer_to_lds(w_rsrc, w_off[x - A_I], kt * ROWB, dst);
     } else if (CONV) {
       const int koff = kt * BK, tap = koff / g.conv_c, c0 = koff % g.conv_c;   // a tile lies inside one window position
@@ -820,7 +824,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     if (x < TN) fw_[ks][x] = *reinterpret_cast<const bf16x8*>(sW + base + frag_off[ks] + x * 32 * ROWB);
     else fa_[ks][x - TN] = *reinterpret_cast<const bf16x8*>(sA + base + frag_off[ks] + (x - TN) * 32 * ROWB);
   };
-  const int kt_count = (int)(g.k / BK);
+  const int kt_count = (int)((g.k + (RAGGED_K ? BK - 1 : 0)) / BK);
   // Step kt: multiply tile kt (its fragments are in registers), read tile kt + 1's, and load tile kt + STAGES into the
   // buffer tile kt lay in.  `stage` = kt % STAGES.
   int kt = 0, stage = 0;
@@ -1008,9 +1012,9 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
   finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false>
 static hipError_t ring_launch(const LinearArgs& g, hipStream_t s) {
-  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV>;
+  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV, RAGGED_K>;
   constexpr size_t ring = ring_lds_bytes(BM, BN, BK, STAGES);
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(ring + kGeluTableBytes));
@@ -1331,7 +1335,7 @@ static bool aligned_to(const void* p, uintptr_t a) { return p == nullptr || ((ui
 
 static bool mfma_eligible(const LinearArgs& g) {
   if (g.dtype != AC_BF16) return false;
-  if (g.k < kBK || g.k % kBK != 0) return false;
+  if (g.k % 8 != 0) return false;
   if (g.n % 4 != 0 || g.n_split % 4 != 0) return false;
   if (g.lda % 8 != 0 || g.ldw % 8 != 0 || g.lda >= (1 << 22) || g.ldw >= (1 << 22)) return false;   // (32-bit byte offsets inside a tile)
   if (!aligned_to(g.a, 16) || !aligned_to(g.w, 16)) return false;
@@ -1366,7 +1370,7 @@ static TileShape best_tile(const LinearArgs& g, bool conv) {
     const int64_t tiles = ((g.m + costs[c].bm - 1) / costs[c].bm) * ((g.n + costs[c].bn - 1) / costs[c].bn) * g.batch;
     const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
     const double rounds = whole <= 1 ? 1 : 0.5 * (exact + whole);
-    const double t = rounds * ((double)(g.k / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
+    const double t = rounds * ((double)((g.k + kBK - 1) / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   return (TileShape)best;
@@ -1421,17 +1425,24 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     }
   }
   if (mfma_eligible(g)) {
-    switch (best_tile(g, false)) {
+    const TileShape shape = best_tile(g, false);
+    if (g.k % kBK != 0) {
+      // a depth that is no multiple of a tile's 64 (whole rows of 16-byte chunks all the same): the products over the positions of
+      // a pair tensor, whose size is a sequence's length.  128 products of 40 x 200 x 200: 42 us in the FMA kernel, 8.9 us here.
+      if (shape == kQuad || shape == k256x128) return ring_launch<256, 128, 4, 2, 64, 3, false, true>(g, s);
+      return ring_launch<64, 64, 2, 2, 64, 3, false, true>(g, s);
+    }
+    switch (shape) {
       case kQuad: return quad_launch(g, s);
       case k256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
       case k128x128Ring: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
       case k128x128: return mfma_launch<128, 128, 2, 2>(g, s);
       case k128x64: return ring_launch<128, 64, 2, 2, 64, 3>(g, s);
-      // (a CU that holds one such block has nothing else to hide behind while operands come from memory: five buffers
-      // instead of three.  1000 x 1024 x 4096 inside a model 25.9 -> 21 us; but 512 x 3072 x 768, 384 tiles, 10.4 -> 15 us: the
-      // second block no longer fits)
+      // (alone on its CU such a block gains nothing from direct loads and the register-staged loop, which also keeps a whole tile's
+      // fragments in registers, is ahead: 512 x 1024 x 4096 18.1 against 20.7 us, 1000 x 1024 x 4096 inside a model 22 against 26;
+      // with two or three blocks per CU it is behind: 512 x 3072 x 768 11.3 against 10.4)
       case k64x64:
-        return ((g.m + 63) / 64) * ((g.n + 63) / 64) * g.batch <= 256 ? ring_launch<64, 64, 2, 2, 64, 5>(g, s) : ring_launch<64, 64, 2, 2, 64, 3>(g, s);
+        return ((g.m + 63) / 64) * ((g.n + 63) / 64) * g.batch <= 256 ? mfma_launch<64, 64, 2, 2>(g, s) : ring_launch<64, 64, 2, 2, 64, 3>(g, s);
       default: return mfma_launch<32, 64, 1, 2>(g, s);
     }
   }

@@ -54,3 +54,22 @@ def test_batched_products(B, c, ni, nj, nk):
     B.ac_op_triangle_contract(B.to_device(a, "bf16"), B.to_device(b, "bf16"), out)
     torch.cuda.synchronize()
     check(host(out), np.matmul(a.astype(np.float64), b.astype(np.float64).transpose(0, 2, 1)), "bf16")
+
+
+@pytest.mark.parametrize("c,ni,nj,nk", [(6, 40, 200, 200), (3, 70, 72, 8), (2, 100, 136, 72), (128, 33, 328, 328), (4, 2000, 2100, 1000)])
+def test_depth_that_is_no_multiple_of_a_tile(B, c, ni, nj, nk):
+    """k of whole 16-byte chunks that ends inside a tile of 64 (64x64 and 256x128 tiles): what lies past the end of a row must not
+    count, so the operands are column blocks of tensors whose other columns hold NaN."""
+    import torch
+    a, b = draw((c, ni, nk), 150, "bf16"), draw((c, nj, nk), 151, "bf16", 1 / math.sqrt(nk))
+    wide_a = torch.full((c, ni, nk + 64), float("nan"), device="cuda", dtype=torch.bfloat16)
+    wide_b = torch.full((c, nj, nk + 64), float("nan"), device="cuda", dtype=torch.bfloat16)
+    wide_a[..., :nk], wide_b[..., :nk] = B.to_device(a, "bf16"), B.to_device(b, "bf16")
+    out = torch.full((c, ni, nj), float("nan"), device="cuda", dtype=torch.bfloat16)
+    B.ac_op_triangle_contract(wide_a[..., :nk], wide_b[..., :nk], out)
+    torch.cuda.synchronize()
+    check(host(out), np.matmul(a.astype(np.float64), b.astype(np.float64).transpose(0, 2, 1)), "bf16")
+    part = torch.full_like(out, float("nan"))
+    B.ac_op_triangle_contract(wide_a[:, :17, :nk], wide_b[..., :nk], part[:, :17])
+    torch.cuda.synchronize()
+    assert torch.equal(part[:, :17], out[:, :17])
