@@ -1087,6 +1087,8 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
   // consecutive row tiles go to one XCD, so that neighbouring runs of a strided output meet in one L2
   const int64_t m0 = xcd_run(blockIdx.x, gridDim.x) * BM;
   if (ka.any_gelu) gelu_table_fill(gelu_tab, tid, NT);
+  // blocks of the same rows share out the weight tiles
+  const int t_lo = ka.n_tiles * (int)blockIdx.y / (int)gridDim.y, t_hi = ka.n_tiles * ((int)blockIdx.y + 1) / (int)gridDim.y;
 
   // ---- LayerNorm of the block's rows (G lanes per row, the row in registers, fp32 statistics)
   {
@@ -1170,8 +1172,8 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
     return bv;
   };
 
-  load_first(0, tid);
-  for (int t = 0; t < ka.n_tiles; ++t) {
+  load_first(t_lo, tid);
+  for (int t = t_lo; t < t_hi; ++t) {
     const ProjPart& pp = p.part[ka.tile_part[t]];
     const int64_t n0 = ka.tile_n0[t];
     const bool gated = pp.gated != 0;
@@ -1182,7 +1184,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
     __syncthreads();                         // the tile (and, the first time, the normalised rows) is in LDS
     // the next weight tile is in flight while this one is multiplied and stored
     if (gated) load_w(pp.w, pp.n, n0, w_tid);
-    else if (t + 1 < ka.n_tiles) load_first(t + 1, w_tid);
+    else if (t + 1 < t_hi) load_first(t + 1, w_tid);
     multiply();
     __syncthreads();                         // every wave is done reading the weight tile
     if (gated) {
@@ -1200,7 +1202,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
         }
       store_w(w_tid);
       __syncthreads();
-      if (t + 1 < ka.n_tiles) load_first(t + 1, w_tid);
+      if (t + 1 < t_hi) load_first(t + 1, w_tid);
       multiply();
       __syncthreads();
 #pragma unroll
@@ -1296,7 +1298,12 @@ static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
   // the GELU table is only there when a part needs it
   const size_t lds = lds_max - (ka.any_gelu ? 0 : kGeluTableBytes);
   const int64_t blocks = (ka.a.rows + kLnProjRows - 1) / kLnProjRows;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s, ka);
+  // Four blocks fit a CU.  A launch of few rows would leave places empty and walk all its weight tiles one after
+  // another: the tiles are then shared out over as many blocks per 64 rows as there is room for, each of which
+  // normalises the rows again (8000 rows of 128, q, k, v, gate of the triangle attention: 19 -> 8.4 us).
+  const int64_t room = 1024 / blocks;
+  const unsigned shares = (unsigned)(room < 1 ? 1 : room < ka.n_tiles ? room : ka.n_tiles);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, shares), dim3(256), lds, s, ka);
   return hipGetLastError();
 }
 
