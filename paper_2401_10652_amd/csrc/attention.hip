@@ -419,23 +419,30 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
   }
   bf16x8 k_reg[K_CHUNKS], v_reg[V_CHUNKS], b_reg[B_CHUNKS];
 
+  // A ragged last tile is loaded like any other from clamped addresses when its key count is a multiple of the 16-byte
+  // vector (values past the end become zeros on the way to LDS, so that 0 * v stays 0; keys and bias past the end are masked
+  // later) and element by element when it is not.
+  const bool sk_vec = !RAGGED || sk % 8 == 0;
   auto load_tile = [&](int k0) {
+    const bool whole = !RAGGED || k0 + kKB <= sk;
 #pragma unroll
     for (int i = 0; i < K_CHUNKS; ++i) {
-      if (RAGGED) {
+      if (whole) {
+        k_reg[i] = *reinterpret_cast<const bf16x8*>(k_src[i] + (int64_t)k0 * a.ldk);
+      } else {
         int key = k0 + k_row[i]; if (key > sk - 1) key = sk - 1;
         k_reg[i] = *reinterpret_cast<const bf16x8*>(kbase + (int64_t)key * a.ldk + k_col[i]);
-      } else {
-        k_reg[i] = *reinterpret_cast<const bf16x8*>(k_src[i] + (int64_t)k0 * a.ldk);
       }
     }
 #pragma unroll
     for (int i = 0; i < V_CHUNKS; ++i) {
       const bf16_t* src = v_src[i] + k0;
-      if (!RAGGED) {
+      const int key = k0 + v_col[i];
+      if (whole) {
         v_reg[i] = *reinterpret_cast<const bf16x8*>(src);
-      } else {   // zero-fill past the end so that 0 * v stays 0
-        const int key = k0 + v_col[i];
+      } else if (sk_vec) {
+        v_reg[i] = *reinterpret_cast<const bf16x8*>(key < sk ? src : src - (key - (sk - 8)));
+      } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) v_reg[i][j] = key + j < sk ? src[j] : (bf16_t)0.0f;
       }
@@ -444,19 +451,27 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
 #pragma unroll
       for (int i = 0; i < B_CHUNKS; ++i) {
         const bf16_t* src = b_src[i] + k0;
-        if (!RAGGED) {
+        const int key = k0 + b_col[i];
+        if (whole) {
           b_reg[i] = *reinterpret_cast<const bf16x8*>(src);
-        } else {   // keys past the end are masked later; stage zeros for them
-          const int key = k0 + b_col[i];
+        } else if (sk_vec) {
+          b_reg[i] = *reinterpret_cast<const bf16x8*>(key < sk ? src : src - (key - (sk - 8)));
+        } else {
 #pragma unroll
           for (int j = 0; j < 8; ++j) b_reg[i][j] = key + j < sk ? src[j] : (bf16_t)0.0f;
         }
       }
     }
   };
-  auto store_tile = [&](int buf) {
+  auto store_tile = [&](int buf, int k0) {
     bf16_t* dk = sK + buf * kKB * KROW;
     bf16_t* dv = sV + buf * DH * VROW;
+    if (RAGGED && k0 + kKB > sk && sk_vec) {
+      const bf16x8 zero8 = {};
+#pragma unroll
+      for (int i = 0; i < V_CHUNKS; ++i)
+        if (k0 + v_col[i] >= sk) v_reg[i] = zero8;
+    }
 #pragma unroll
     for (int i = 0; i < K_CHUNKS; ++i) *reinterpret_cast<bf16x8*>(dk + k_dst[i]) = k_reg[i];
 #pragma unroll
@@ -488,7 +503,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
   const float scale2 = rsqrtf((float)DH) * kLog2e;
 
   if constexpr (!PIPE) {
-    if (tile_lo < tile_hi) { load_tile(tile_lo * kKB); store_tile(tile_lo & 1); }
+    if (tile_lo < tile_hi) { load_tile(tile_lo * kKB); store_tile(tile_lo & 1, tile_lo * kKB); }
     __syncthreads();
 
     for (int kt = tile_lo; kt < tile_hi; ++kt) {
@@ -578,7 +593,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
             }
       }
       if (BIAS && more) __syncthreads();   // the single bias buffer is overwritten next: every wave has read it
-      if (more) store_tile(buf ^ 1);
+      if (more) store_tile(buf ^ 1, k0 + kKB);
       __syncthreads();
     }
 
