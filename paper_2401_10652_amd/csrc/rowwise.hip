@@ -801,15 +801,10 @@ group_norm_partials_rows(const T* x, float* part, int64_t positions, int channel
   }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256)
-group_norm_apply(const T* x, const float* part, const T* gain, const T* shift, T* y, int64_t positions, int channels,
-                 int groups, float eps, int act) {
-  __shared__ float s_mean[kGnMaxGroups], s_rstd[kGnMaxGroups];
-  const int64_t image = blockIdx.y;
-  const int tid = threadIdx.x;
-  // a wave merges the 64 partials of a group as a tree (lane l holds part l; fixed shape, so the result does
-  // not depend on timing): a thread that walked them one after the other cost more than the pass itself
+// Mean and reciprocal deviation of every group of an image, by the block: a wave merges the 64 partials of a group as a tree
+// (lane l holds part l; fixed shape, so the result does not depend on timing): a thread that walked them one after the other
+// cost more than the pass itself.
+__device__ __forceinline__ void group_norm_merge(const float* part, int64_t image, int groups, float eps, int tid, float* s_mean, float* s_rstd) {
   static_assert(kGnParts == kWave, "one partial per lane");
   constexpr int GB = 8;                            // groups whose partials a wave has in flight at a time
   for (int g0 = tid / kWave; g0 < groups; g0 += GB * (256 / kWave)) {
@@ -841,6 +836,66 @@ group_norm_apply(const T* x, const float* part, const T* gain, const T* shift, T
       }
     }
   }
+}
+
+// The pass of rows of at most 256 16-byte runs: a thread keeps one run of channels and walks down the rows, so its eight groups'
+// statistics and its gain and shift are looked up once (a division by the group size per element, and the rows'
+// loads behind the merge instead of under it, had the launch of 2 x 4096 x 320 at 13.5 us; 11.5 us here).
+template <typename T>
+__global__ void __launch_bounds__(256)
+group_norm_apply_rows(const T* x, const float* part, const T* gain, const T* shift, T* y, int64_t positions, int channels,
+                      int groups, float eps, int act) {
+  constexpr int V = Elem<T>::kVec;
+  __shared__ float s_mean[kGnMaxGroups], s_rstd[kGnMaxGroups];
+  const int64_t image = blockIdx.y;
+  const int tid = threadIdx.x;
+  const int vpr = channels / V, rpp = 256 / vpr;   // 16-byte runs per row, rows per pass of the block
+  const int run = tid % vpr, r = tid / vpr;
+  const int64_t p0 = (int64_t)blockIdx.x * (rpp * kGnApplyChunks) + r;
+  const bool live = r < rpp;
+  const T* src = x + image * positions * channels + run * V;
+  T* dst = y + image * positions * channels + run * V;
+  float v[kGnApplyChunks][V], gg[V], sh[V];
+#pragma unroll
+  for (int k = 0; k < kGnApplyChunks; ++k) {       // in flight during the merge; past the end a valid row, not stored
+    const int64_t p = p0 + (int64_t)k * rpp;
+    load_vec(src + (p < positions ? p : positions - 1) * channels, v[k]);
+  }
+  load_vec(gain + run * V, gg);
+  load_vec(shift + run * V, sh);
+  group_norm_merge(part, image, groups, eps, tid, s_mean, s_rstd);
+  __syncthreads();
+  if (!live) return;
+  const int cg = channels / groups;
+  float mean[V], rstd[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const int g = (run * V + i) / cg;
+    mean[i] = s_mean[g];
+    rstd[i] = s_rstd[g];
+  }
+#pragma unroll
+  for (int k = 0; k < kGnApplyChunks; ++k) {
+    const int64_t p = p0 + (int64_t)k * rpp;
+    if (p >= positions) break;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const float t = (v[k][i] - mean[i]) * rstd[i] * gg[i] + sh[i];
+      v[k][i] = act == AC_ACT_SILU ? t * sigmoidf(t) : t;
+    }
+    store_vec(dst + p * channels, v[k]);
+  }
+}
+
+// (rows wider than that)
+template <typename T>
+__global__ void __launch_bounds__(256)
+group_norm_apply(const T* x, const float* part, const T* gain, const T* shift, T* y, int64_t positions, int channels,
+                 int groups, float eps, int act) {
+  __shared__ float s_mean[kGnMaxGroups], s_rstd[kGnMaxGroups];
+  const int64_t image = blockIdx.y;
+  const int tid = threadIdx.x;
+  group_norm_merge(part, image, groups, eps, tid, s_mean, s_rstd);
   __syncthreads();
   constexpr int V = Elem<T>::kVec;                          // channels per lane and access: 16 bytes
   const int cg = channels / groups;
@@ -882,18 +937,29 @@ hipError_t launch_group_norm(const void* x, const void* gain, const void* shift,
     return hipErrorInvalidValue;
   const bool by_rows = channels / (dtype == AC_BF16 ? 8 : 4) <= 256;
   const dim3 g1 = by_rows ? dim3((unsigned)images, kGnParts) : dim3((unsigned)(images * groups), kGnParts);
-  const int64_t chunks = positions * (channels / (dtype == AC_BF16 ? 8 : 4));
-  const dim3 g2((unsigned)((chunks + 256 * kGnApplyChunks - 1) / (256 * kGnApplyChunks)), (unsigned)images);
+  const int64_t runs = channels / (dtype == AC_BF16 ? 8 : 4), chunks = positions * runs;
+  const int64_t per_block = by_rows ? 256 / runs * kGnApplyChunks : 256 * kGnApplyChunks;   // rows, or 16-byte runs
+  const dim3 g2((unsigned)(((by_rows ? positions : chunks) + per_block - 1) / per_block), (unsigned)images);
   if (dtype == AC_BF16) {
-    if (by_rows) hipLaunchKernelGGL((group_norm_partials_rows<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
-    else hipLaunchKernelGGL((group_norm_partials<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
-    hipLaunchKernelGGL((group_norm_apply<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
-                       (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
+    if (by_rows) {
+      hipLaunchKernelGGL((group_norm_partials_rows<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
+      hipLaunchKernelGGL((group_norm_apply_rows<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
+                         (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
+    } else {
+      hipLaunchKernelGGL((group_norm_partials<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
+      hipLaunchKernelGGL((group_norm_apply<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
+                         (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
+    }
   } else {
-    if (by_rows) hipLaunchKernelGGL((group_norm_partials_rows<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
-    else hipLaunchKernelGGL((group_norm_partials<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
-    hipLaunchKernelGGL((group_norm_apply<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
-                       (const float*)shift, (float*)y, positions, channels, groups, eps, act);
+    if (by_rows) {
+      hipLaunchKernelGGL((group_norm_partials_rows<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
+      hipLaunchKernelGGL((group_norm_apply_rows<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
+                         (const float*)shift, (float*)y, positions, channels, groups, eps, act);
+    } else {
+      hipLaunchKernelGGL((group_norm_partials<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
+      hipLaunchKernelGGL((group_norm_apply<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
+                         (const float*)shift, (float*)y, positions, channels, groups, eps, act);
+    }
   }
   return hipGetLastError();
 }
