@@ -719,7 +719,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   constexpr int A_I = BM / RPI / NW, W_I = BN / RPI / NW, PER = A_I + W_I;   // load instructions of a wave per tile
   constexpr int KSTEPS = BK / 16, READS = KSTEPS * (TM + TN), MMAS = KSTEPS * TM * TN;
   constexpr int STAGE = (BM + BN) * ROWB;
-  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && STAGES >= 3 && (NW * RPI) % 32 == 0 && MMAS >= PER, "tile / wave layout mismatch");
+  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && STAGES >= 3 && (NW * RPI) % 16 == 0, "tile / wave layout mismatch");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   float* gelu_tab = reinterpret_cast<float*>(smem_raw + ring_lds_bytes(BM, BN, BK, STAGES));
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -734,10 +734,16 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   // Sources: a wave-uniform base that advances with k plus a 32-bit byte offset per lane and instruction (rows past the end
   // shadow the last one; their results are never stored).
   const int64_t lda = CONV ? (int64_t)g.conv_c : g.lda;
-  const unsigned char* a_base = (const unsigned char*)((const bf16_t*)g.a + product * g.sa_b + m0 * lda);
+  // CONV: the A operand is gathered from channels-last images as the 3x3 convolution needs it (implicit GEMM).  A tile of BK
+  // lies inside one window position (conv_c is a multiple of 64), so it is the same channels of the pixel shifted by that
+  // position for every row, or zeros where the shifted pixel falls outside its image.  The base is the first window
+  // position's pixel of the first row, so that the positions' offsets are not negative; a lane whose pixel is outside
+  // asks for an offset past the buffer's range, for which the hardware delivers zeros and touches no memory (two 64x64x320
+  // images: 39.5 us with a 64-bit address per lane and a page of zeros, 30 us so).
+  const unsigned char* a_base = (const unsigned char*)((const bf16_t*)g.a + product * g.sa_b + m0 * lda - (CONV ? (int64_t)(g.conv_w + 1) * g.conv_c : 0));
   const unsigned char* w_base = (const unsigned char*)((const bf16_t*)g.w + product * g.sw_b + n0 * g.ldw);
   const int row_in = lane / CPR;                                        // row of the instruction this lane moves
-  const int src_chunk = (lane % CPR) ^ ring_swizzle<BK>(wave * RPI + row_in);   // (NW instructions apart is a multiple of 32 rows)
+  const int src_chunk = (lane % CPR) ^ ring_swizzle<BK>(wave * RPI + row_in);   // (NW instructions apart is a multiple of 16 rows)
   uint32_t a_off[A_I], w_off[W_I];
   int a_taps[A_I];   // CONV: bit t set = window position t of this row's pixel lies inside the image
 #pragma unroll
@@ -761,13 +767,15 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     const int row = (wave + NW * i) * RPI + row_in;
     w_off[i] = (uint32_t)((row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
   }
-  // (addresses: base and tile offset in scalar registers, 32 bits per lane; every lane's address is valid, so the range is open)
-  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, -1, 0x00027000);
+  // (addresses: base and tile offset in scalar registers, 32 bits per lane; but for CONV's outside pixels every address is valid)
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, CONV ? 0x7fffffff : -1, 0x00027000);
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(w_base), 0, -1, 0x00027000);
   auto to_lds = [](const unsigned char* src, unsigned char* dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
   };
-  // load instruction x of the PER that bring in this wave's share of tile kt
+  // load instruction x of the PER that bring in this wave's share of tile kt; called tile after tile (CONV: the tile to
+  // come lies inside window position `tap`, from channel tap_c on)
+  int tap = 0, tap_c = 0;
   auto load_part = [&](int kt, int stage, int x) {
     unsigned char* dst = smem_raw + stage * STAGE + (x < A_I ? x * NW * 1024 : BM * ROWB + (x - A_I) * NW * 1024) + wave * 1024;
     auto buffer_to_lds = [](__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, uint32_t tile_off, unsigned char* lds) {
@@ -780,11 +788,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     } else if (x >= A_I) {
       buffer_to_lds(w_rsrc, w_off[x - A_I], kt * ROWB, dst);
     } else if (CONV) {
-      const int koff = kt * BK, tap = koff / g.conv_c, c0 = koff % g.conv_c;   // a tile lies inside one window position
-      const int64_t shift = (((int64_t)(tap / 3 - 1) * g.conv_w + (tap % 3 - 1)) * g.conv_c + c0) * 2;
-      to_lds((a_taps[x] >> tap) & 1 ? a_base + shift + a_off[x] : (const unsigned char*)kZeroRow, dst);
+      buffer_to_lds(a_rsrc, (a_taps[x] >> tap) & 1 ? a_off[x] : 0x80000000u, (((tap / 3) * g.conv_w + tap % 3) * g.conv_c + tap_c) * 2, dst);
     } else {
       buffer_to_lds(a_rsrc, a_off[x], kt * ROWB, dst);
+    }
+    if (CONV && x == PER - 1) {
+      tap_c += BK;
+      if (tap_c == g.conv_c) { tap_c = 0; ++tap; }
     }
   };
   // this wave's loads of all but the youngest `tiles` tiles have landed and its LDS reads are done, then every wave's
@@ -846,8 +856,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
         if (done < READS && done * (3 * MMAS) < (x + 1) * 4 * READS) read_frag(na, nw, base, done++);
       // the loads are spread too: issued together after a barrier, those of all waves queue up at the one address
       // unit and hold back the matrix instructions behind them
-      if (x % (MMAS / PER) == 0 && x / (MMAS / PER) < PER) {
-        if (more) load_part(kt + STAGES, free_stage, x / (MMAS / PER));
+#pragma unroll
+      for (int c = x * PER / MMAS; c < (x + 1) * PER / MMAS; ++c) {
+        if (more) load_part(kt + STAGES, free_stage, c);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
