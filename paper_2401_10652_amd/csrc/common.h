@@ -197,6 +197,8 @@ hipError_t launch_layernorm(const void* x, int64_t ldx, const void* gain, const 
                             hipStream_t s);
 hipError_t launch_bias_act(const void* x, int64_t ldx, const void* bias, void* y, int64_t ldy,
                            int64_t rows, int64_t cols, int act, int dtype, hipStream_t s);
+// y = a + b (op 0), a * b (op 1) or a * act(b) (op kOpGate + act)
+constexpr int kOpGate = 16;
 hipError_t launch_binary(const void* a, int64_t lda, const void* b, int64_t ldb, void* y, int64_t ldy,
                          int64_t rows, int64_t cols, int op, int dtype, hipStream_t s);
 hipError_t launch_linear(const LinearArgs& g, hipStream_t s);

@@ -168,6 +168,11 @@ bias_act_scalar(const T* x, int64_t ldx, const T* bias, T* y,
   }
 }
 
+// op 0: a + b; 1: a * b; kOpGate + act: a * act(b)
+__device__ __forceinline__ float binary_op(float u, float v, int op) {
+  return op == 0 ? u + v : op == 1 ? u * v : u * apply_act_rt(v, op - kOpGate);
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256)
 binary_vec(const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, T* __restrict__ y,
@@ -180,7 +185,7 @@ binary_vec(const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_
     load_vec(a + r * lda + c, u);
     load_vec(b + r * ldb + c, v);
 #pragma unroll
-    for (int j = 0; j < V; ++j) u[j] = op == 0 ? u[j] + v[j] : u[j] * v[j];
+    for (int j = 0; j < V; ++j) u[j] = binary_op(u[j], v[j], op);
     store_vec(y + r * ldy + c, u);
   }
 }
@@ -193,7 +198,7 @@ binary_scalar(const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
     const int64_t r = i / cols, c = i % cols;
     const float u = Elem<T>::ld(a + r * lda + c), v = Elem<T>::ld(b + r * ldb + c);
-    Elem<T>::st(y + r * ldy + c, op == 0 ? u + v : u * v);
+    Elem<T>::st(y + r * ldy + c, binary_op(u, v, op));
   }
 }
 

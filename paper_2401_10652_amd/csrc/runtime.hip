@@ -1091,8 +1091,9 @@ void Walk::res_stack(const void* x, void* y) {
       if (gated) {
         proj(u, C, W(AB_W_1), C, W(AB_B_1), AC_ACT_NONE, nullptr, 0, hid, 2 * F, T, 2 * F);
         void* gate = atw(hid, F);
-        bias_act(gate, 2 * F, nullptr, gate, 2 * F, T, F, m.activation);
-        binary(hid, 2 * F, gate, 2 * F, act, F, T, F, 1);
+        // one pass over both halves (activation and product apart, the activated gate rounded and stored in between:
+        // 11.4 + 9.5 us on 8192 rows of 2 x 1280, 13.3 together)
+        binary(hid, 2 * F, gate, 2 * F, act, F, T, F, kOpGate + m.activation);
       } else {
         proj(u, C, W(AB_W_1), C, W(AB_B_1), m.activation, nullptr, 0, hid, F, T, F);
       }
