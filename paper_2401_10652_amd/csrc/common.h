@@ -75,12 +75,19 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 }
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
-template <int ACT> __device__ __forceinline__ float apply_act(float x) {
+// The same for results that are stored as bf16: the hardware reciprocal (1 ulp, as much as __expf is off by itself) in place
+// of the division's ten instructions, and the tanh form of GELU as x sigmoid(2u), which it is, without a tanh.
+__device__ __forceinline__ float sigmoid_rcp(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+__device__ __forceinline__ float gelu_tanh_rcp(float x) {
+  return x * sigmoid_rcp(1.59576912160573072f * (x + 0.044715f * x * x * x));
+}
+
+template <int ACT> __device__ __forceinline__ float apply_act_bf16(float x) {
   if (ACT == AC_ACT_GELU_ERF) return gelu_erf(x);
-  if (ACT == AC_ACT_GELU_TANH) return gelu_tanh(x);
+  if (ACT == AC_ACT_GELU_TANH) return gelu_tanh_rcp(x);
   if (ACT == AC_ACT_RELU) return fmaxf(x, 0.0f);
-  if (ACT == AC_ACT_SIGMOID) return sigmoidf(x);
-  if (ACT == AC_ACT_SILU) return x * sigmoidf(x);
+  if (ACT == AC_ACT_SIGMOID) return sigmoid_rcp(x);
+  if (ACT == AC_ACT_SILU) return x * sigmoid_rcp(x);
   return x;
 }
 __device__ __forceinline__ float apply_act_rt(float x, int act) {

@@ -381,7 +381,7 @@ __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj) {
             const float pre = v[jj] + bf2f(bias_v[j][q][jj]);
-            v[jj] = ACT == AC_ACT_GELU_ERF ? gelu_table(pre, gelu_tab) : apply_act<ACT>(pre);
+            v[jj] = ACT == AC_ACT_GELU_ERF ? gelu_table(pre, gelu_tab) : apply_act_bf16<ACT>(pre);
           }
           if (g.mul) {
 #pragma unroll
@@ -1209,7 +1209,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
 #pragma unroll
           for (int i = 0; i < 1; ++i)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) sg[i][j][4 * q + jj] = sigmoidf(acc[i][j][4 * q + jj] + bf2f(bv[jj]));
+            for (int jj = 0; jj < 4; ++jj) sg[i][j][4 * q + jj] = sigmoid_rcp(acc[i][j][4 * q + jj] + bf2f(bv[jj]));
         }
       store_w(w_tid);
       __syncthreads();
@@ -1254,7 +1254,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
 #pragma unroll
           for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = sigmoidf(acc[i][j][r]);
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = sigmoid_rcp(acc[i][j][r]);
       } else if (act == AC_ACT_RELU) {
 #pragma unroll
         for (int i = 0; i < 1; ++i)
@@ -1268,7 +1268,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
 #pragma unroll
           for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = gelu_tanh(acc[i][j][r]);
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = gelu_tanh_rcp(acc[i][j][r]);
       }
     }
     LinearArgs g{};
