@@ -767,15 +767,16 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     const int row = (wave + NW * i) * RPI + row_in;
     w_off[i] = (uint32_t)((row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
   }
-  // (addresses: base and tile offset in scalar registers, 32 bits per lane; but for CONV's outside pixels every address is valid)
-  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, CONV ? 0x7fffffff : -1, 0x00027000);
+  // (addresses: base and tile offset in scalar registers, 32 bits per lane; every lane's address is valid, so the range is open but for CONV's outside pixels)
+  constexpr int kARange = CONV ? 0x7fffffff : -1;
+  __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, kARange, 0x00027000);
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(w_base), 0, -1, 0x00027000);
   auto to_lds = [](const unsigned char* src, unsigned char* dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
   };
   // load instruction x of the PER that bring in this wave's share of tile kt; called tile after tile (CONV: the tile to
-  // come lies inside window position `tap`, from channel tap_c on)
-  int tap = 0, tap_c = 0;
+  // come lies inside window position `tap`, tap_off bytes from the first position of its row of the window on)
+  int tap = 0, tap_off = 0, tap_end = g.conv_c * 2;
   auto load_part = [&](int kt, int stage, int x) {
     unsigned char* dst = smem_raw + stage * STAGE + (x < A_I ? x * NW * 1024 : BM * ROWB + (x - A_I) * NW * 1024) + wave * 1024;
     auto buffer_to_lds = [](__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, uint32_t tile_off, unsigned char* lds) {
@@ -788,13 +789,21 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     } else if (x >= A_I) {
       buffer_to_lds(w_rsrc, w_off[x - A_I], kt * ROWB, dst);
     } else if (CONV) {
-      buffer_to_lds(a_rsrc, (a_taps[x] >> tap) & 1 ? a_off[x] : 0x80000000u, (((tap / 3) * g.conv_w + tap % 3) * g.conv_c + tap_c) * 2, dst);
+      buffer_to_lds(a_rsrc, (a_taps[x] >> tap) & 1 ? a_off[x] : 0x80000000u, tap_off, dst);
     } else {
       buffer_to_lds(a_rsrc, a_off[x], kt * ROWB, dst);
     }
     if (CONV && x == PER - 1) {
-      tap_c += BK;
-      if (tap_c == g.conv_c) { tap_c = 0; ++tap; }
+      tap_off += ROWB;
+      if (tap_off == tap_end) {
+        tap_end += g.conv_c * 2;
+        if (++tap % 3 == 0) {   // the next row of the window: a base of its own, as an image's rows may be large
+          a_base += (int64_t)g.conv_w * g.conv_c * 2;
+          a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, kARange, 0x00027000);
+          tap_off = 0;
+          tap_end = g.conv_c * 2;
+        }
+      }
     }
   };
   // this wave's loads of all but the youngest `tiles` tiles have landed and its LDS reads are done, then every wave's
@@ -1366,28 +1375,29 @@ static bool mfma_eligible(const LinearArgs& g) {
   return true;
 }
 
-// Tile shapes of the bf16 GEMM, and the one with the least estimated time.  A launch is tiles / 256 rounds of the CUs (a last
-// round that is partly empty runs faster: half of it is counted) of k / 64 steps plus a prologue and an epilogue per tile, plus
-// what is paid once; the three times of a shape, in us, are fitted to 67 launches of 512 to 65536 rows x 64 to 4096
-// columns x 64 to 4096 deep, batched ones among them, on which the choice is within 5 % of the best shape but for three (7 %).  Shapes whose blocks
+// Tile shapes of the bf16 GEMM, and the one with the least estimated time.  A launch is tiles / 256 rounds of the CUs of k / 64
+// steps plus a prologue and an epilogue per tile, plus what is paid once.  A last round that is partly empty counts whole
+// for the shapes that have a CU to themselves (1.25 rounds of 256x256 tiles of 8192 x 2560 x 320 take 39.7 us, two take 37) and half
+// for those that share it.  The three times of a shape, in us, are fitted to 68 launches of 512 to 65536 rows x 64 to
+// 4096 columns x 64 to 4096 deep, batched ones among them, on which the choice is within 5 % of the best shape.  Shapes whose blocks
 // share a CU pay little per tile and more per step.  Examples (us; 256x256 / 256x128 / 128x128 ring / 128x128 / 128x64 /
 // 64x64 / 32x64):  65536x1024x1024  144 / 181 / 230 / 182 / 236 / 251 / 359;  6400x1024x1024  27 / 20 / 23 / 23 / 26 / 27 / 35;
 // 4000x1024x4096  78 / 56 / 42 / 46 / 52 / 64 / 83;  512x1024x4096  72 / 43 / 27 / 40 / 29 / 21 / 14.5.
 // The k order is the same for all of them, and so are the bits.
 enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x64, kTileShapes };
 static TileShape best_tile(const LinearArgs& g, bool conv) {
-  struct Cost { int bm, bn; double step, tile, once; bool conv; };
-  static const Cost costs[kTileShapes] = {{256, 256, 1.09, 11.7, 0.0, false}, {256, 128, 0.68, 8.1, 0.0, false},
-                                          {128, 128, 0.45, 5.1, 0.3, true},   {128, 128, 0.54, 2.6, 4.3, false},
-                                          {128, 64, 0.36, 1.4, 4.3, true},    {64, 64, 0.17, 0.8, 4.8, true},
-                                          {32, 64, 0.13, 0.65, 5.3, false}};
+  struct Cost { int bm, bn; double step, tile, once; bool alone, conv; };
+  static const Cost costs[kTileShapes] = {{256, 256, 1.06, 11.9, 0.0, true, false}, {256, 128, 0.65, 8.1, 0.0, true, false},
+                                          {128, 128, 0.46, 4.4, 1.0, true, true},   {128, 128, 0.52, 2.7, 4.4, false, false},
+                                          {128, 64, 0.36, 1.4, 4.3, false, true},   {64, 64, 0.17, 0.8, 4.8, false, true},
+                                          {32, 64, 0.13, 0.65, 5.4, false, false}};
   int best = -1;
   double best_t = 0;
   for (int c = 0; c < kTileShapes; ++c) {
     if (conv && !costs[c].conv) continue;
     const int64_t tiles = ((g.m + costs[c].bm - 1) / costs[c].bm) * ((g.n + costs[c].bn - 1) / costs[c].bn) * g.batch;
     const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
-    const double rounds = whole <= 1 ? 1 : 0.5 * (exact + whole);
+    const double rounds = whole <= 1 ? 1 : costs[c].alone ? whole : 0.5 * (exact + whole);
     const double t = rounds * ((double)((g.k + kBK - 1) / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
@@ -1456,11 +1466,11 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
       case k128x128Ring: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
       case k128x128: return mfma_launch<128, 128, 2, 2>(g, s);
       case k128x64: return ring_launch<128, 64, 2, 2, 64, 3>(g, s);
-      // (alone on its CU such a block gains nothing from direct loads and the register-staged loop, which also keeps a whole tile's
+      // (alone on its CU and with a long k such a block gains nothing from direct loads and the register-staged loop, which also keeps a whole tile's
       // fragments in registers, is ahead: 512 x 1024 x 4096 18.1 against 20.7 us, 1000 x 1024 x 4096 inside a model 22 against 26;
       // with two or three blocks per CU it is behind: 512 x 3072 x 768 11.3 against 10.4)
       case k64x64:
-        return ((g.m + 63) / 64) * ((g.n + 63) / 64) * g.batch <= 256 ? mfma_launch<64, 64, 2, 2>(g, s) : ring_launch<64, 64, 2, 2, 64, 3>(g, s);
+        return g.k >= 512 && ((g.m + 63) / 64) * ((g.n + 63) / 64) * g.batch <= 256 ? mfma_launch<64, 64, 2, 2>(g, s) : ring_launch<64, 64, 2, 2, 64, 3>(g, s);
       default: return mfma_launch<32, 64, 1, 2>(g, s);
     }
   }
