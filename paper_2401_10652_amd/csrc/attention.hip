@@ -639,19 +639,22 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
     };
     const unsigned char* const kg_base = uniform(kbase);
     const unsigned char* const vg_base = uniform(vbase);
+    // (buffer loads: base and row offset in scalar registers, 32 bits per lane)
+    auto dma = [&](const unsigned char* src, uint32_t lane_off, uint32_t row_off, unsigned char* dst) {
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src), 0, -1, 0x00027000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, lane_off, row_off, 0, 0);
+    };
     auto dma_k = [&](int kt, int buf) {
       const unsigned char* src = kg_base + (int64_t)kt * kKB * a.ldk * 2;
 #pragma unroll
       for (int j = 0; j < KG / NW; ++j)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)swap23(j * NW) * a.ldk * 2 + kg_off),
-                                         (__attribute__((address_space(3))) void*)(sKb + buf * KBUF + (wave_u + NW * j) * GB), 16, 0, 0);
+        dma(src, kg_off, (uint32_t)(swap23(j * NW) * (int)a.ldk) * 2u, sKb + buf * KBUF + (wave_u + NW * j) * GB);
     };
     auto dma_v = [&](int kt, int buf) {
       const unsigned char* src = vg_base + (int64_t)kt * kKB * 2;
 #pragma unroll
       for (int j = 0; j < VG / NW; ++j)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)j * NW * a.ldv * 2 + vg_off),
-                                         (__attribute__((address_space(3))) void*)(sVb + buf * VBUF + (wave_u + NW * j) * GB), 16, 0, 0);
+        dma(src, vg_off, (uint32_t)(j * NW * (int)a.ldv) * 2u, sVb + buf * VBUF + (wave_u + NW * j) * GB);
     };
     auto arrived = [&]() {   // this wave's loads have landed, then every wave's
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
