@@ -684,7 +684,8 @@ static hipError_t mfma_launch(const LinearArgs& g, hipStream_t s) {
 // Same matrix instructions on the same operands in the same k order as the kernel above: equal bits.
 // ------------------------------------------------------------------------------------
 template <int BK> __device__ __forceinline__ int ring_swizzle(int r) {
-  return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3;
+  static_assert(BK == 64, "rows of eight chunks");
+  return (r >> 1) & 7;
 }
 constexpr int ring_lds_bytes(int bm, int bn, int bk, int stages) {
   const int ring = stages * (bm + bn) * bk * 2;
@@ -692,7 +693,7 @@ constexpr int ring_lds_bytes(int bm, int bn, int bk, int stages) {
   const int most = out > out_t ? out : out_t;
   return ring > most ? ring : most;
 }
-__device__ const bf16_t kZeroRow[64] __attribute__((aligned(128))) = {};   // source of the chunks of pixels outside their image
+__device__ const bf16_t kZeroRow[64] __attribute__((aligned(128))) = {};   // source of the chunks past the end of k
 
 // After the k loop (every load landed, every wave past its last LDS read): one branch per launch, so the activation is
 // inlined without a per-element switch.
@@ -815,9 +816,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
       __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | kNoExp);
     };
     asm volatile("" ::: "memory");
-    if (STAGES >= 5 && tiles >= 3) wait(std::integral_constant<int, STAGES >= 5 ? 3 * PER : 0>{});
-    else if (STAGES >= 4 && tiles >= 2) wait(std::integral_constant<int, STAGES >= 4 ? 2 * PER : 0>{});
-    else if (tiles >= 1) wait(std::integral_constant<int, PER>{});
+    if (tiles >= STAGES - 2) wait(std::integral_constant<int, (STAGES - 2) * PER>{});
     else wait(std::integral_constant<int, 0>{});
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
