@@ -151,10 +151,13 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
   const float* kb = (const float*)a.k + b * a.sk_b + h * DH + 4 * grp;
   const float* vb = (const float*)a.v + b * a.sv_b + h * DH + NV * l16;
   const float* bias = a.bias ? (const float*)a.bias + h * a.s_bias_h + (int64_t)rowc * a.ld_bias : nullptr;
+  // Scores stay in their own units and log2(e) is multiplied into differences from the maximum only: a bias of the type's
+  // lowest value (how masks are often written) stays finite, and a row of nothing else averages its values.
+  const float scale = rsqrtf((float)DH);
   f32x4 qf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
-    qf[ks] = *reinterpret_cast<const f32x4*>((const float*)a.q + b * a.sq_b + (int64_t)rowc * a.ldq + h * DH + 16 * ks + 4 * grp);
+    qf[ks] = *reinterpret_cast<const f32x4*>((const float*)a.q + b * a.sq_b + (int64_t)rowc * a.ldq + h * DH + 16 * ks + 4 * grp) * scale;
 
   int kv_end = sk;
   if (a.causal) {
@@ -193,9 +196,7 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
   };
 #pragma unroll
   for (int i = 0; i < NV; ++i) acc_o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // running maximum (of the scaled scores in the log2 domain) and this lane's share of the sum
-  float m_run = -INFINITY, l_run = 0.f;
-  const float scale2 = rsqrtf((float)DH) * kLog2e;
+  float m_run = -INFINITY, l_run = 0.f;   // running maximum and this lane's share of the sum
 
   if (wave < n_tiles) { load_k(wave); load_v(wave); }
   for (int t = wave; t < n_tiles; t += NW) {
@@ -216,9 +217,9 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int key = 32 * t + 16 * u + 4 * grp + r;
-        float v = s[u][r] * scale2;
+        float v = s[u][r];
         if (key >= sk || (a.causal && key > qpos)) v = -INFINITY;
-        else if (bias) v = fmaf(bias[key], kLog2e, v);
+        else if (bias) v += bias[key];
         s[u][r] = v;
         mx = fmaxf(mx, v);
       }
@@ -226,7 +227,7 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float m_new = fmaxf(m_run, mx);
     const float m_exp = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp2(-inf) = 0, not NaN
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_exp);
+    const float alpha = __builtin_amdgcn_exp2f((m_run - m_exp) * kLog2e);
     m_run = m_new;
     l_run *= alpha;
 #pragma unroll
@@ -237,7 +238,7 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = __builtin_amdgcn_exp2f(s[u][r] - m_exp);
+        const float p = __builtin_amdgcn_exp2f((s[u][r] - m_exp) * kLog2e);
         l_run += p;
 #pragma unroll
         for (int i = 0; i < NV; ++i) acc_o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[u][r][i], p, acc_o[i], 0, 0, 0);
@@ -264,7 +265,7 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       if (s_ml[w][rl][0] == -INFINITY) continue;   // this wave saw no key of the row
-      const float f = __builtin_amdgcn_exp2f(s_ml[w][rl][0] - M);
+      const float f = __builtin_amdgcn_exp2f((s_ml[w][rl][0] - M) * kLog2e);
       L += s_ml[w][rl][1] * f;
       o += s_o[w][rl][d] * f;
     }

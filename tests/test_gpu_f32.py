@@ -66,3 +66,29 @@ def test_attention_f32(B, dh, sq, sk, causal, off):
         B.ac_op_attention(views[0][r0:r1], views[1], views[2], part[r0:r1], heads, dh, causal=causal, q_offset=off + r0)
     torch.cuda.synchronize()
     assert torch.equal(part, ctx)
+
+
+@pytest.mark.parametrize("dh", [16, 64, 128])
+def test_attention_f32_mask_values(B, dh):
+    """An additive mask written with the type's lowest value: masked keys have no weight beside others (also where they are all the
+    keys of a wave), and a row of nothing but masked keys averages its values.  A mask of -inf drops its keys likewise."""
+    import torch
+    heads, sq, sk = 2, 40, 200
+    d, low = heads * dh, np.finfo(np.float32).min
+    q, k, v = draw((sq, d), 130, "f32"), draw((sk, d), 131, "f32"), draw((sk, d), 132, "f32")
+    bias = draw((heads, sq, sk), 133, "f32").astype(np.float32)
+    bias[:, 0] = low                                            # nothing but masked keys
+    bias[:, 1, 5:] = low                                        # five visible ones, all in one wave's tile
+    bias[:, 2, 32:64] = low                                     # one wave's tile masked
+    bias[:, 3, 32:64] = -np.inf
+    ctx = torch.full((sq, d), float("nan"), device="cuda")
+    B.ac_op_attention(*(B.to_device(t, "f32") for t in (q, k, v)), ctx, heads, dh, bias=B.to_device(bias, "f32"))
+    torch.cuda.synchronize()
+    ref = np.empty((sq, d))
+    for h in range(heads):
+        c = slice(h * dh, (h + 1) * dh)
+        # (scores and the mask meet in fp32, where lowest + score is lowest; everything else in fp64)
+        s = ((q[:, c].astype(np.float64) @ k[:, c].astype(np.float64).T / math.sqrt(dh)).astype(np.float32) + bias[h]).astype(np.float64)
+        p = np.exp(s - s.max(-1, keepdims=True))
+        ref[:, c] = p / p.sum(-1, keepdims=True) @ v[:, c].astype(np.float64)
+    check(host(ctx), ref, "f32")
