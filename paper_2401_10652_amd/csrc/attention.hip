@@ -263,8 +263,7 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
     for (int w = 0; w < NW; ++w) M = fmaxf(M, s_ml[w][rl][0]);
     float L = 0.f, o = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      if (s_ml[w][rl][0] == -INFINITY) continue;   // this wave saw no key of the row
+    for (int w = 0; w < NW; ++w) {   // (a wave that saw no key of the row adds 0 * 0; one whose scores are all NaN adds NaN)
       const float f = __builtin_amdgcn_exp2f((s_ml[w][rl][0] - M) * kLog2e);
       L += s_ml[w][rl][1] * f;
       o += s_o[w][rl][d] * f;

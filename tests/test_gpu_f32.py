@@ -92,3 +92,21 @@ def test_attention_f32_mask_values(B, dh):
         p = np.exp(s - s.max(-1, keepdims=True))
         ref[:, c] = p / p.sum(-1, keepdims=True) @ v[:, c].astype(np.float64)
     check(host(ctx), ref, "f32")
+
+
+@pytest.mark.parametrize("dh", [16, 64])
+@pytest.mark.parametrize("tile", [1, 3, 6])
+def test_attention_f32_nan_keys(B, dh, tile):
+    """NaN in every key of one 32-key tile (all that one wave sees, or the last, ragged one) reaches every row that sees the tile, and no other."""
+    import torch
+    heads, s = 2, 200
+    q, k, v = (draw((s, heads * dh), 140 + i, "f32") for i in range(3))
+    k[32 * tile:32 * tile + 32] = np.nan
+    ctx = torch.zeros((s, heads * dh), device="cuda")
+    B.ac_op_attention(*(B.to_device(t, "f32") for t in (q, k, v)), ctx, heads, dh)
+    torch.cuda.synchronize()
+    assert torch.isnan(ctx).all()
+    B.ac_op_attention(*(B.to_device(t, "f32") for t in (q, k, v)), ctx, heads, dh, causal=True)
+    torch.cuda.synchronize()
+    assert torch.isnan(ctx[32 * tile:]).all()
+    check(host(ctx[:32 * tile]), O.attention(q, k, v, heads, True)[:32 * tile], "f32")
