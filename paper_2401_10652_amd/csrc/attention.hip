@@ -996,16 +996,20 @@ static bool mfma_attn_eligible(const AttnArgs& a) {
   return true;
 }
 
-// fp32 problems whose q, k and v rows can be read 16 bytes at a time
+// Blocks of the fp32 matrix-core kernel, in a grid of one dimension (whose threads the launch counts in 32 bits).
+static int64_t mfma_f32_attn_blocks(const AttnArgs& a) { return (a.sq + 15) / 16 * a.heads * a.batch; }
+
+// fp32 problems whose q, k and v rows can be read 16 bytes at a time and whose grid can be launched (the generic kernel's has
+// three dimensions)
 static bool mfma_f32_attn_eligible(const AttnArgs& a) {
   if (a.dtype != AC_F32 || a.v_transposed) return false;
   if (a.head_dim != 16 && a.head_dim != 32 && a.head_dim != 64 && a.head_dim != 128) return false;
   if (a.ldq % 4 || a.ldk % 4 || a.ldv % 4 || a.sq_b % 4 || a.sk_b % 4 || a.sv_b % 4) return false;
-  return al(a.q, 16) && al(a.k, 16) && al(a.v, 16);
+  return al(a.q, 16) && al(a.k, 16) && al(a.v, 16) && mfma_f32_attn_blocks(a) <= 0xffffffffLL / 256;
 }
 
 static hipError_t mfma_f32_attn_dispatch(const AttnArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)(((a.sq + 15) / 16) * a.heads * a.batch));
+  const dim3 grid((unsigned)mfma_f32_attn_blocks(a));
   switch (a.head_dim) {
     case 16: hipLaunchKernelGGL((attention_mfma_f32<16>), grid, dim3(256), 0, s, a); break;
     case 32: hipLaunchKernelGGL((attention_mfma_f32<32>), grid, dim3(256), 0, s, a); break;

@@ -110,3 +110,16 @@ def test_attention_f32_nan_keys(B, dh, tile):
     torch.cuda.synchronize()
     assert torch.isnan(ctx[32 * tile:]).all()
     check(host(ctx[:32 * tile]), O.attention(q, k, v, heads, True)[:32 * tile], "f32")
+
+
+def test_attention_f32_many_blocks(B):
+    """257 heads x 65535 problems of 16 queries: as blocks of 256 threads per 16 rows more threads than a grid of one dimension can have."""
+    import torch
+    heads, dh, batch, sq, sk = 257, 16, 65535, 16, 4
+    d = heads * dh
+    q, k, v = draw((sq, d), 150, "f32"), draw((sk, d), 151, "f32"), draw((sk, d), 152, "f32")
+    ctx = torch.zeros((batch, sq, d), device="cuda")
+    B.ac_op_attention(*(B.to_device(t, "f32") for t in (q, k, v)), ctx[0], heads, dh, batch=batch, strides=(0, 0, 0, 0, sq * d))
+    torch.cuda.synchronize()
+    check(host(ctx[0]), O.attention(q, k, v, heads, False), "f32")
+    assert all(torch.equal(ctx[i:i + 1], ctx[:1]) for i in range(1, batch, 1093)) and torch.equal(ctx[-1], ctx[0])
