@@ -296,6 +296,14 @@ int ac_op_linear(const void* a, int64_t lda, const void* w, int64_t ldw, const v
                  void* stream);
 
 /*
+ * Name of the kernel and output tile that a product of `batch` times [m, k] x [n, k] with row strides lda and ldw runs on
+ * (conv: the 3x3 convolution, m pixels, k = 9 * c_in), operands aligned as above, e.g. "quad 256x256".  For tests and
+ * profiles: computed on the host, no device is needed.  NULL for arguments that no such call takes.
+ */
+const char* ac_linear_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch,
+                             int conv, int dtype);
+
+/*
  * LayerNorm of `rows` short rows (k = 64 or 128 columns, bf16) followed by up to 5 projections of
  * the normalised rows t = LN(x), in one kernel: t never reaches memory.  The pair-stack modules
  * project each LayerNorm output several times (gated operands a and b of the triangle update;

@@ -125,6 +125,7 @@ SIGNATURES = {
     "ac_op_ln_linear": (INT, [VP, I64, VP, VP, C.c_float, I64, I64, C.POINTER(ac_proj_part), INT, INT, VP]),
     "ac_op_linear": (INT, [VP, I64, VP, I64, VP, VP, I64, VP, I64, VP, I64, VP, I64, I64, I64, I64, I64,
                            I64, I64, I64, INT, INT, VP]),
+    "ac_linear_kernel": (C.c_char_p, [I64, I64, I64, I64, I64, I64, INT, INT]),
     "ac_op_attention": (INT, [VP, I64, I64, VP, I64, I64, VP, I64, I64, INT, VP, I64, I64, VP, I64, I64,
                               VP, I64, I64, I64, I64, I64, INT, INT, INT, I64, INT, VP, U64, INT, VP]),
     "ac_op_attention_static_scratch": (INT, [VP, I64, I64, VP, I64, I64, VP, I64, I64, INT, VP, I64, I64, VP, I64, I64,
@@ -326,6 +327,12 @@ def ac_op_linear(a, w, out, bias=None, mul=None, residual=None, activation=AC_AC
         _ptr(out), 0 if out is None else out.stride(0),
         _ptr(out_t), n_split, t_period, t_s1, t_s2, t_s3, m, n, k, activation, _dt(a), _stream()),
         "ac_op_linear")
+
+
+def ac_linear_kernel(m, n, k, dtype, lda=0, ldw=0, batch=1, conv=False):
+    """Kernel and output tile of a product [m, k] x [n, k] (host only); dtype "f32" or "bf16"."""
+    name = lib().ac_linear_kernel(m, n, k, lda or k, ldw or k, batch, int(conv), AC_BF16 if dtype == "bf16" else AC_F32)
+    return name.decode() if name else None
 
 
 def ac_op_ln_linear(x, gain, shift, parts, eps=1e-5):

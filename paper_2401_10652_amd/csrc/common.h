@@ -209,6 +209,7 @@ constexpr int kOpGate = 16;
 hipError_t launch_binary(const void* a, int64_t lda, const void* b, int64_t ldb, void* y, int64_t ldy,
                          int64_t rows, int64_t cols, int op, int dtype, hipStream_t s);
 hipError_t launch_linear(const LinearArgs& g, hipStream_t s);
+const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);
 hipError_t launch_group_norm(const void* x, const void* gain, const void* shift, void* y, void* partials, int64_t images,

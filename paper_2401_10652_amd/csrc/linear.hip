@@ -1384,23 +1384,27 @@ static bool mfma_eligible(const LinearArgs& g) {
 // 4000x1024x4096  78 / 56 / 42 / 46 / 52 / 64 / 83;  512x1024x4096  72 / 43 / 27 / 40 / 29 / 21 / 14.5.
 // The k order is the same for all of them, and so are the bits.
 enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x64, kTileShapes };
+// A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
+static bool grid_fits(int64_t tiles, int threads) { return tiles <= 0xffffffffLL / threads; }
+static int64_t tiles_of(const LinearArgs& g, int bm, int bn) { return ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn); }
 static TileShape best_tile(const LinearArgs& g, bool conv) {
-  struct Cost { int bm, bn; double step, tile, once; bool alone, conv; };
-  static const Cost costs[kTileShapes] = {{256, 256, 1.06, 11.9, 0.0, true, false}, {256, 128, 0.65, 8.1, 0.0, true, false},
-                                          {128, 128, 0.46, 4.4, 1.0, true, true},   {128, 128, 0.52, 2.7, 4.4, false, false},
-                                          {128, 64, 0.36, 1.4, 4.3, false, true},   {64, 64, 0.17, 0.8, 4.8, false, true},
-                                          {32, 64, 0.13, 0.65, 5.4, false, false}};
+  struct Cost { int bm, bn, threads; double step, tile, once; bool alone, conv; };
+  static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, false}, {256, 128, 512, 0.65, 8.1, 0.0, true, false},
+                                          {128, 128, 512, 0.46, 4.4, 1.0, true, true},   {128, 128, 256, 0.52, 2.7, 4.4, false, false},
+                                          {128, 64, 256, 0.36, 1.4, 4.3, false, true},   {64, 64, 256, 0.17, 0.8, 4.8, false, true},
+                                          {32, 64, 128, 0.13, 0.65, 5.4, false, false}};
   int best = -1;
   double best_t = 0;
   for (int c = 0; c < kTileShapes; ++c) {
     if (conv && !costs[c].conv) continue;
-    const int64_t tiles = ((g.m + costs[c].bm - 1) / costs[c].bm) * ((g.n + costs[c].bn - 1) / costs[c].bn) * g.batch;
+    if (!grid_fits(tiles_of(g, costs[c].bm, costs[c].bn), costs[c].threads)) continue;
+    const int64_t tiles = tiles_of(g, costs[c].bm, costs[c].bn) * g.batch;
     const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
     const double rounds = whole <= 1 ? 1 : costs[c].alone ? whole : 0.5 * (exact + whole);
     const double t = rounds * ((double)((g.k + kBK - 1) / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
-  return (TileShape)best;
+  return best < 0 ? (conv ? k128x128Ring : kQuad) : (TileShape)best;
 }
 
 // fp32 products whose rows can be read 16 bytes at a time
@@ -1426,6 +1430,71 @@ static hipError_t mfma_f32_launch(const LinearArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The kernel a product runs on: a function of sizes, types, strides and alignment, decided on the host.
+enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kRouteQuad, kRing256x128, kRing128x128, kStaged128x128, kRing128x64, kRing64x64,
+             kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x64, kConv64x64, kRoutes };
+static const char* const kRouteName[kRoutes] = {
+    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "quad 256x256", "ring 256x128", "ring 128x128", "staged 128x128", "ring 128x64", "ring 64x64",
+    "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x64", "conv 64x64"};
+
+static Route bf16_route(const LinearArgs& g) {
+  const TileShape shape = best_tile(g, false);
+  if (g.k % kBK != 0) {
+    // a depth that is no multiple of a tile's 64 (whole rows of 16-byte chunks all the same): the products over the positions of
+    // a pair tensor, whose size is a sequence's length.  128 products of 40 x 200 x 200: 42 us in the FMA kernel, 8.9 us here.
+    return shape == kQuad || shape == k256x128 || !grid_fits(tiles_of(g, 64, 64), 256) ? kRagged256x128 : kRagged64x64;
+  }
+  switch (shape) {
+    case kQuad: return kRouteQuad;
+    case k256x128: return kRing256x128;
+    case k128x128Ring: return kRing128x128;
+    case k128x128: return kStaged128x128;
+    case k128x64: return kRing128x64;
+    // (alone on its CU and with a long k such a block gains nothing from direct loads and the register-staged loop, which also keeps a whole tile's
+    // fragments in registers, is ahead: 512 x 1024 x 4096 18.1 against 20.7 us, 1000 x 1024 x 4096 inside a model 22 against 26;
+    // with two or three blocks per CU it is behind: 512 x 3072 x 768 11.3 against 10.4)
+    case k64x64: return g.k >= 512 && tiles_of(g, 64, 64) * g.batch <= 256 ? kStaged64x64 : kRing64x64;
+    default: return kStaged32x64;
+  }
+}
+
+static Route f32_route(const LinearArgs& g) {
+  // Rounds of 256 tiles (one per CU) x area of the tile; on a tie the larger tile, which reads less per output.
+  // 256 x 512 x 2048: 27 / 19 / 15 / 18 us with tiles of 32x64 / 32x32 / 32x16 / 16x16 (64, 128, 256 and 512 of them),
+  // 256 x 2048 x 512: 11.5 / 12.9 / 17.5 / 22 us (256 of 32x64).
+  static const int shapes[4][2] = {{32, 64}, {32, 32}, {32, 16}, {16, 16}};
+  int best = -1;
+  int64_t best_t = INT64_MAX;
+  for (int c = 0; c < 4; ++c) {
+    const int64_t tiles = tiles_of(g, shapes[c][0], shapes[c][1]);
+    if (!grid_fits(tiles, 256)) continue;
+    const int64_t t = (tiles * g.batch + 255) / 256 * shapes[c][0] * shapes[c][1];
+    if (t < best_t) { best = c; best_t = t; }
+  }
+  return best < 0 ? kFma : (Route)(kF32_32x64 + best);
+}
+
+static Route linear_route(const LinearArgs& g) {
+  if (g.conv_c > 0) {
+    switch (best_tile(g, true)) {
+      case k128x128Ring: return kConv128x128;
+      case k128x64: return kConv128x64;
+      default: return kConv64x64;
+    }
+  }
+  if (mfma_eligible(g)) return bf16_route(g);
+  if (g.dtype == AC_F32 && mfma_f32_eligible(g)) return f32_route(g);
+  return kFma;
+}
+
+const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype) {
+  LinearArgs g{};
+  g.m = m; g.n = g.n_split = g.ldo = n; g.k = k; g.lda = lda; g.ldw = ldw; g.batch = batch; g.dtype = dtype; g.o_period = g.t_period = INT64_MAX;
+  g.sa_b = m * lda; g.sw_b = n * ldw; g.so_b = m * n;
+  if (conv) g.conv_c = (int)(k / 9);
+  return kRouteName[linear_route(g)];
+}
+
 hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
   LinearArgs g = g_in;
   if (g.m <= 0 || g.n <= 0) return hipSuccess;
@@ -1445,53 +1514,26 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
       return hipErrorInvalidValue;
     g.lda = g.conv_c;
     if (!mfma_eligible(g)) return hipErrorInvalidValue;
-    switch (best_tile(g, true)) {
-      case k128x128Ring: return ring_launch<128, 128, 2, 4, 64, 3, true>(g, s);
-      case k128x64: return ring_launch<128, 64, 2, 2, 64, 3, true>(g, s);
-      default: return ring_launch<64, 64, 2, 2, 64, 3, true>(g, s);
-    }
   }
-  if (mfma_eligible(g)) {
-    const TileShape shape = best_tile(g, false);
-    if (g.k % kBK != 0) {
-      // a depth that is no multiple of a tile's 64 (whole rows of 16-byte chunks all the same): the products over the positions of
-      // a pair tensor, whose size is a sequence's length.  128 products of 40 x 200 x 200: 42 us in the FMA kernel, 8.9 us here.
-      if (shape == kQuad || shape == k256x128) return ring_launch<256, 128, 4, 2, 64, 3, false, true>(g, s);
-      return ring_launch<64, 64, 2, 2, 64, 3, false, true>(g, s);
-    }
-    switch (shape) {
-      case kQuad: return quad_launch(g, s);
-      case k256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
-      case k128x128Ring: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
-      case k128x128: return mfma_launch<128, 128, 2, 2>(g, s);
-      case k128x64: return ring_launch<128, 64, 2, 2, 64, 3>(g, s);
-      // (alone on its CU and with a long k such a block gains nothing from direct loads and the register-staged loop, which also keeps a whole tile's
-      // fragments in registers, is ahead: 512 x 1024 x 4096 18.1 against 20.7 us, 1000 x 1024 x 4096 inside a model 22 against 26;
-      // with two or three blocks per CU it is behind: 512 x 3072 x 768 11.3 against 10.4)
-      case k64x64:
-        return g.k >= 512 && ((g.m + 63) / 64) * ((g.n + 63) / 64) * g.batch <= 256 ? mfma_launch<64, 64, 2, 2>(g, s) : ring_launch<64, 64, 2, 2, 64, 3>(g, s);
-      default: return mfma_launch<32, 64, 1, 2>(g, s);
-    }
-  }
-  if (g.dtype == AC_F32 && mfma_f32_eligible(g)) {
-    // Rounds of 256 tiles (one per CU) x area of the tile; on a tie the larger tile, which reads less per output.
-    // 256 x 512 x 2048: 27 / 19 / 15 / 18 us with tiles of 32x64 / 32x32 / 32x16 / 16x16 (64, 128, 256 and 512 of them),
-    // 256 x 2048 x 512: 11.5 / 12.9 / 17.5 / 22 us (256 of 32x64).
-    static const int shapes[4][2] = {{2, 4}, {2, 2}, {2, 1}, {1, 1}};
-    int best = 0;
-    int64_t best_t = INT64_MAX;
-    for (int c = 0; c < 4; ++c) {
-      const int64_t bm = 16 * shapes[c][0], bn = 16 * shapes[c][1];
-      const int64_t tiles = ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn) * g.batch;
-      const int64_t t = (tiles + 255) / 256 * bm * bn;
-      if (t < best_t) { best = c; best_t = t; }
-    }
-    switch (best) {
-      case 0: return mfma_f32_launch<2, 4>(g, s);
-      case 1: return mfma_f32_launch<2, 2>(g, s);
-      case 2: return mfma_f32_launch<2, 1>(g, s);
-      default: return mfma_f32_launch<1, 1>(g, s);
-    }
+  switch (linear_route(g)) {
+    case kF32_32x64: return mfma_f32_launch<2, 4>(g, s);
+    case kF32_32x32: return mfma_f32_launch<2, 2>(g, s);
+    case kF32_32x16: return mfma_f32_launch<2, 1>(g, s);
+    case kF32_16x16: return mfma_f32_launch<1, 1>(g, s);
+    case kRouteQuad: return quad_launch(g, s);
+    case kRing256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
+    case kRing128x128: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
+    case kStaged128x128: return mfma_launch<128, 128, 2, 2>(g, s);
+    case kRing128x64: return ring_launch<128, 64, 2, 2, 64, 3>(g, s);
+    case kRing64x64: return ring_launch<64, 64, 2, 2, 64, 3>(g, s);
+    case kStaged64x64: return mfma_launch<64, 64, 2, 2>(g, s);
+    case kStaged32x64: return mfma_launch<32, 64, 1, 2>(g, s);
+    case kRagged256x128: return ring_launch<256, 128, 4, 2, 64, 3, false, true>(g, s);
+    case kRagged64x64: return ring_launch<64, 64, 2, 2, 64, 3, false, true>(g, s);
+    case kConv128x128: return ring_launch<128, 128, 2, 4, 64, 3, true>(g, s);
+    case kConv128x64: return ring_launch<128, 64, 2, 2, 64, 3, true>(g, s);
+    case kConv64x64: return ring_launch<64, 64, 2, 2, 64, 3, true>(g, s);
+    default: break;
   }
   dim3 grid((unsigned)((g.n + 63) / 64), (unsigned)((g.m + 63) / 64), (unsigned)g.batch);
   if (g.dtype == AC_BF16) hipLaunchKernelGGL((linear_fma<bf16_t>), grid, dim3(256), 0, s, g);

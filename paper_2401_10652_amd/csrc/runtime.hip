@@ -1700,6 +1700,11 @@ int ac_op_linear(const void* a, int64_t lda, const void* w, int64_t ldw, const v
   return hip_status(launch_linear(g, (hipStream_t)stream), "linear");
 }
 
+const char* ac_linear_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, int conv, int dtype) {
+  if (m < 1 || n < 1 || k < 1 || batch < 1 || !dtype_ok(dtype) || (conv && (k % 9 != 0 || dtype != AC_BF16))) return nullptr;
+  return linear_kernel_name(m, n, k, lda, ldw, batch, conv != 0, dtype);
+}
+
 int ac_op_attention(const void* q, int64_t ldq, int64_t stride_q_batch, const void* k, int64_t ldk,
                     int64_t stride_k_batch, const void* v, int64_t ldv, int64_t stride_v_batch, int v_transposed,
                     const void* bias, int64_t ld_bias, int64_t stride_bias_head, const void* gate, int64_t ldg,

@@ -1,0 +1,36 @@
+"""Which kernel and tile a product takes: the rule runs on the host, so it is checked without a GPU."""
+import pytest
+
+from paper_2401_10652_amd import binding as B
+from paper_2401_10652_amd.build import ensure_built
+
+THREADS = {"fma": 256, "f32": 256, "staged 32x64": 128, "staged": 256, "quad": 512, "ring 256x128": 512, "ring 128x128": 512, "ring": 256,
+           "ragged 256x128": 512, "ragged": 256, "conv 128x128": 512, "conv": 256}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    ensure_built()
+
+
+def grid_threads(name, m, n):
+    """Threads in the first dimension of the launch."""
+    kind, tile = name.split()
+    bm, bn = (int(t) for t in tile.split("x"))
+    per_block = THREADS.get(name, THREADS[kind])
+    return -(-n // bn) * per_block if kind == "fma" else -(-m // bm) * -(-n // bn) * per_block
+
+
+@pytest.mark.parametrize("dtype,m,n,k", [
+    ("f32", 65537, 65536, 64), ("f32", 66000, 70000, 512), ("f32", 1 << 20, 1 << 15, 64), ("f32", (1 << 30) + 1, 16, 4),
+    ("bf16", 1 << 21, 1 << 16, 72), ("bf16", 1 << 21, 1 << 15, 8), ("bf16", 1 << 21, 1 << 16, 64), ("bf16", (1 << 30) - 1, 64, 200),
+])
+def test_large_products_fit_a_grid_dimension(dtype, m, n, k):
+    assert grid_threads(B.ac_linear_kernel(m, n, k, dtype), m, n) < 1 << 32
+
+
+@pytest.mark.parametrize("c", [64, 128, 256])
+def test_many_pixels_fit_a_grid_dimension(c):
+    """8 output channels of a little under 2^30 pixels."""
+    m = (1 << 30) - 64
+    assert grid_threads(B.ac_linear_kernel(m, 8, 9 * c, "bf16", lda=c, conv=True), m, 8) < 1 << 32
