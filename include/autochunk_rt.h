@@ -316,7 +316,8 @@ const char* ac_linear_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64
  * if out_t != NULL, strided like ac_op_linear's second output:
  *   out_t[(m / t_period) * t_s1 + (m % t_period) * t_s2 + col * t_s3]   (t_period <= 0: no period).
  * n must be a multiple of 4.  Shapes outside these return AC_ERR_UNSUPPORTED (use ac_op_layernorm
- * and ac_op_linear).  A row's result does not depend on which launch or block computes it.
+ * and ac_op_linear).  A row's result does not depend on which launch or block computes it.  Results
+ * may be written over x if every row's results lie on that row alone (a projection in place).
  */
 typedef struct ac_proj_part {
   const void* w; const void* bias;

@@ -1305,6 +1305,26 @@ bool ln_proj_shapes_ok(int dtype, int64_t k, const int64_t* n, int n_parts) {
   return tiles <= kMaxProjTiles;
 }
 
+// Whether some part's results may lie on top of the input rows (by the ranges of addresses that they span).
+static bool ln_proj_overlaps(const LnProjArgs& p) {
+  auto span = [&](int64_t period, int64_t s1, int64_t s2, int64_t n, int64_t sn, int64_t& lo, int64_t& hi) {
+    const int64_t q = (p.rows - 1) / period * s1, r = ((p.rows < period ? p.rows : period) - 1) * s2, c = (n - 1) * sn;
+    lo = (q < 0 ? q : 0) + (r < 0 ? r : 0) + (c < 0 ? c : 0);
+    hi = (q > 0 ? q : 0) + (r > 0 ? r : 0) + (c > 0 ? c : 0);
+  };
+  const bf16_t *x_lo = (const bf16_t*)p.x, *x_hi = x_lo + (p.rows - 1) * p.ldx + p.k;
+  for (int i = 0; i < p.n_parts; ++i) {
+    const ProjPart& pp = p.part[i];
+    const bf16_t* out = (const bf16_t*)(pp.out_t ? pp.out_t : pp.out);
+    int64_t lo, hi;
+    if (pp.out_t) span(pp.t_period, pp.t_s1, pp.t_s2, pp.n, pp.t_s3, lo, hi);
+    else if (pp.o_period == INT64_MAX) span(INT64_MAX, 0, pp.ldo, pp.n, 1, lo, hi);
+    else span(pp.o_period, pp.o_s1, pp.o_s2, pp.n, 1, lo, hi);
+    if (out + lo < x_hi && x_lo < out + hi + 1) return true;
+  }
+  return false;
+}
+
 template <int K, int BN>
 static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
   auto kern = ln_multi_proj_bf16<K, BN>;
@@ -1319,8 +1339,9 @@ static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
   const int64_t blocks = (ka.a.rows + kLnProjRows - 1) / kLnProjRows;
   // Four blocks fit a CU.  A launch of few rows would leave places empty and walk all its weight tiles one after
   // another: the tiles are then shared out over as many blocks per 64 rows as there is room for, each of which
-  // normalises the rows again (8000 rows of 128, q, k, v, gate of the triangle attention: 19 -> 8.4 us).
-  const int64_t room = 1024 / blocks;
+  // normalises the rows again (8000 rows of 128, q, k, v, gate of the triangle attention: 19 -> 8.4 us).  Where results may
+  // lie on the rows (a projection in place) one block has to have read them all before it writes, as without shares.
+  const int64_t room = ln_proj_overlaps(ka.a) ? 1 : 1024 / blocks;
   const unsigned shares = (unsigned)(room < 1 ? 1 : room < ka.n_tiles ? room : ka.n_tiles);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks, shares), dim3(256), lds, s, ka);
   return hipGetLastError();

@@ -406,3 +406,24 @@ def test_ln_linear_parts(B, rows, k):
         B.ac_op_ln_linear(dev(B, draw((8, 96), 1, "bf16"), "bf16"), dev(B, g[:96], "bf16"), dev(B, b[:96], "bf16"),
                           [dict(w=dev(B, draw((8, 96), 2, "bf16"), "bf16"), out=out_p)])
     assert ei.value.status == B.AC_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("rows", [1, 64, 130, 1000, 8000])
+@pytest.mark.parametrize("k", [64, 128])
+def test_ln_linear_in_place(B, rows, k):
+    """The projection written over its input rows, the row counts at which the weight tiles of one row block would otherwise be shared out."""
+    import torch
+    x, w = dev(B, draw((rows, k), 430, "bf16"), "bf16"), dev(B, draw((k, k), 431, "bf16", k ** -0.5), "bf16")
+    g, b = dev(B, 1.0 + draw((k,), 432, "bf16", 0.1), "bf16"), dev(B, draw((k,), 433, "bf16", 0.1), "bf16")
+    ref = torch.full_like(x, float("nan"))
+    B.ac_op_ln_linear(x, g, b, [dict(w=w, out=ref)])
+    for _ in range(5):
+        buf = x.clone()
+        B.ac_op_ln_linear(buf, g, b, [dict(w=w, out=buf)])
+        torch.cuda.synchronize()
+        assert torch.equal(buf, ref)
+    # beside the rows, in the same buffer: also one block per row block, and the same bits
+    wide = torch.cat([x, torch.zeros_like(x)], 1)
+    B.ac_op_ln_linear(wide[:, :k], g, b, [dict(w=w, out=wide[:, k:])])
+    torch.cuda.synchronize()
+    assert torch.equal(wide[:, k:], ref) and torch.equal(wide[:, :k], x)
