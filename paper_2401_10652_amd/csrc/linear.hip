@@ -1217,7 +1217,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
 #pragma unroll
           for (int i = 0; i < 1; ++i)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) sg[i][j][4 * q + jj] = sigmoid_rcp(acc[i][j][4 * q + jj] + bf2f(bv[jj]));
+            for (int jj = 0; jj < 4; ++jj) sg[i][j][4 * q + jj] = sigmoid_newton(acc[i][j][4 * q + jj] + bf2f(bv[jj]));
         }
       store_w(w_tid);
       __syncthreads();
@@ -1262,7 +1262,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
 #pragma unroll
           for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = sigmoid_rcp(acc[i][j][r]);
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = sigmoid_newton(acc[i][j][r]);
       } else if (act == AC_ACT_RELU) {
 #pragma unroll
         for (int i = 0; i < 1; ++i)
