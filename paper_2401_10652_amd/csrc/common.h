@@ -84,15 +84,10 @@ __device__ __forceinline__ float sigmoid_newton(float x) {
   const float d = fmaf(0.25f, __expf(-x), 0.25f), r = __builtin_amdgcn_rcpf(d);
   return 0.25f * fmaf(__builtin_amdgcn_fmed3f(fmaf(-d, r, 1.0f), -1.0f, 1.0f), r, r);
 }
-// The tanh form of GELU as x sigmoid(2u), which it is, without a tanh; for results that are stored as bf16.
-__device__ __forceinline__ float sigmoid_rcp(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-__device__ __forceinline__ float gelu_tanh_rcp(float x) {
-  return x * sigmoid_rcp(1.59576912160573072f * (x + 0.044715f * x * x * x));
-}
 
 template <int ACT> __device__ __forceinline__ float apply_act_bf16(float x) {
   if (ACT == AC_ACT_GELU_ERF) return gelu_erf(x);
-  if (ACT == AC_ACT_GELU_TANH) return gelu_tanh_rcp(x);
+  if (ACT == AC_ACT_GELU_TANH) return gelu_tanh(x);
   if (ACT == AC_ACT_RELU) return fmaxf(x, 0.0f);
   if (ACT == AC_ACT_SIGMOID) return sigmoid_newton(x);
   if (ACT == AC_ACT_SILU) return x * sigmoid_newton(x);

@@ -1276,7 +1276,7 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
 #pragma unroll
           for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = gelu_tanh_rcp(acc[i][j][r]);
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = gelu_tanh(acc[i][j][r]);
       }
     }
     LinearArgs g{};

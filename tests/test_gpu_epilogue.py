@@ -35,3 +35,10 @@ def test_sigmoid_of_a_bf16_product(B, std):
     import torch
     out, ref = below_bf16(B, B.AC_ACT_SIGMOID, std)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("std", [0.02, 0.5, 2.0])
+def test_tanh_gelu_of_a_bf16_product(B, std):
+    import torch
+    out, ref = below_bf16(B, B.AC_ACT_GELU_TANH, std)
+    assert torch.equal(out, ref)
