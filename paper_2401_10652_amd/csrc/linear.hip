@@ -312,8 +312,9 @@ __device__ __forceinline__ float gelu_table(float x, const float* tab) {
 // The epilogue of one block.  A tile that lies wholly in the row-major part of the output
 // is rounded to bf16 into LDS (free after the k loop) and written out with 16-byte stores
 // whose lanes walk along rows; other tiles (strided store, narrow or misaligned outputs)
-// store 8 bytes per lane straight from the registers.
-template <int ACT, int BM, int BN, int WAVES_M, int WAVES_N>
+// store 8 bytes per lane straight from the registers.  GELU_TABLE: erf GELU from the table at gelu_tab, up to
+// 9e-6 off at |x| = 1.4, and not by its formula (1.5e-7), which products of ragged depth keep from the FMA kernel.
+template <int ACT, int BM, int BN, int WAVES_M, int WAVES_N, bool GELU_TABLE = true>
 __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32],
                                               bf16_t* lds, const float* gelu_tab, int64_t m0, int64_t n0,
                                               int wave_m, int wave_n, int l32, int half, int tid) {
@@ -381,7 +382,7 @@ __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj) {
             const float pre = v[jj] + bf2f(bias_v[j][q][jj]);
-            v[jj] = ACT == AC_ACT_GELU_ERF ? gelu_table(pre, gelu_tab) : apply_act_bf16<ACT>(pre);
+            v[jj] = ACT == AC_ACT_GELU_ERF && GELU_TABLE ? gelu_table(pre, gelu_tab) : apply_act_bf16<ACT>(pre);
           }
           if (g.mul) {
 #pragma unroll
@@ -697,18 +698,18 @@ __device__ const bf16_t kZeroRow[64] __attribute__((aligned(128))) = {};   // so
 
 // After the k loop (every load landed, every wave past its last LDS read): one branch per launch, so the activation is
 // inlined without a per-element switch.
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU_TABLE = true>
 __device__ __forceinline__ void finish_tile(const LinearArgs& g, f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32],
                                             unsigned char* smem, float* gelu_tab, int64_t m0, int64_t n0, int wave_m, int wave_n,
                                             int l32, int half, int tid) {
   bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
-  if (g.act == AC_ACT_GELU_ERF) { gelu_table_fill(gelu_tab, tid, 64 * WAVES_M * WAVES_N); __syncthreads(); }
+  if (GELU_TABLE && g.act == AC_ACT_GELU_ERF) { gelu_table_fill(gelu_tab, tid, 64 * WAVES_M * WAVES_N); __syncthreads(); }
   switch (g.act) {
-    case AC_ACT_GELU_ERF: epilogue_tile<AC_ACT_GELU_ERF, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
-    case AC_ACT_GELU_TANH: epilogue_tile<AC_ACT_GELU_TANH, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
-    case AC_ACT_RELU: epilogue_tile<AC_ACT_RELU, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
-    case AC_ACT_SIGMOID: epilogue_tile<AC_ACT_SIGMOID, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
-    default: epilogue_tile<AC_ACT_NONE, BM, BN, WAVES_M, WAVES_N>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_GELU_ERF: epilogue_tile<AC_ACT_GELU_ERF, BM, BN, WAVES_M, WAVES_N, GELU_TABLE>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_GELU_TANH: epilogue_tile<AC_ACT_GELU_TANH, BM, BN, WAVES_M, WAVES_N, GELU_TABLE>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_RELU: epilogue_tile<AC_ACT_RELU, BM, BN, WAVES_M, WAVES_N, GELU_TABLE>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    case AC_ACT_SIGMOID: epilogue_tile<AC_ACT_SIGMOID, BM, BN, WAVES_M, WAVES_N, GELU_TABLE>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
+    default: epilogue_tile<AC_ACT_NONE, BM, BN, WAVES_M, WAVES_N, GELU_TABLE>(g, acc, lds, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid); break;
   }
 }
 
@@ -889,7 +890,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     step(fa[1], fw[1], fa[0], fw[0]);
     if (kt >= kt_count) break;
   }
-  finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
+  finish_tile<BM, BN, WAVES_M, WAVES_N, !RAGGED_K>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1040,7 +1041,7 @@ static hipError_t ring_launch(const LinearArgs& g, hipStream_t s) {
   if (attr_status != hipSuccess) return attr_status;
   const int64_t tiles = ((g.m + BM - 1) / BM) * ((g.n + BN - 1) / BN);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)g.batch), dim3(64 * WAVES_M * WAVES_N),
-                     ring + (g.act == AC_ACT_GELU_ERF ? kGeluTableBytes : 0), s, g);
+                     ring + (g.act == AC_ACT_GELU_ERF && !RAGGED_K ? kGeluTableBytes : 0), s, g);
   return hipGetLastError();
 }
 

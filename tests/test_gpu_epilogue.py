@@ -42,3 +42,11 @@ def test_tanh_gelu_of_a_bf16_product(B, std):
     import torch
     out, ref = below_bf16(B, B.AC_ACT_GELU_TANH, std)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("k,m", [(136, 8192), (136, 100), (200, 8192)])
+def test_erf_gelu_of_a_bf16_product_of_ragged_depth(B, k, m):
+    """(A depth of whole tiles takes the table, whose error a bf16 result hides.)"""
+    import torch
+    out, ref = below_bf16(B, B.AC_ACT_GELU_ERF, 1.0, k=k, m=m)
+    assert torch.equal(out, ref)
