@@ -1385,7 +1385,7 @@ static bool mfma_eligible(const LinearArgs& g) {
   if (g.dtype != AC_BF16) return false;
   if (g.k % 8 != 0) return false;
   if (g.n % 4 != 0 || g.n_split % 4 != 0) return false;
-  if (g.lda % 8 != 0 || g.ldw % 8 != 0 || g.lda >= (1 << 22) || g.ldw >= (1 << 22)) return false;   // (32-bit byte offsets inside a tile)
+  if (g.lda % 8 != 0 || g.ldw % 8 != 0) return false;
   if (!aligned_to(g.a, 16) || !aligned_to(g.w, 16)) return false;
   if (g.n_split > 0 && (g.ldo % 4 != 0 || !aligned_to(g.out, 8))) return false;
   if (g.o_period != INT64_MAX && (g.o_s1 % 4 != 0 || g.o_s2 % 4 != 0)) return false;
@@ -1409,16 +1409,19 @@ enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x6
 // A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
 static bool grid_fits(int64_t tiles, int threads) { return tiles <= 0xffffffffLL / threads; }
 static int64_t tiles_of(const LinearArgs& g, int bm, int bn) { return ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn); }
-static TileShape best_tile(const LinearArgs& g, bool conv) {
-  struct Cost { int bm, bn, threads; double step, tile, once; bool alone, conv; };
-  static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, false}, {256, 128, 512, 0.65, 8.1, 0.0, true, false},
-                                          {128, 128, 512, 0.46, 4.4, 1.0, true, true},   {128, 128, 256, 0.52, 2.7, 4.4, false, false},
-                                          {128, 64, 256, 0.36, 1.4, 4.3, false, true},   {64, 64, 256, 0.17, 0.8, 4.8, false, true},
-                                          {32, 64, 128, 0.13, 0.65, 5.4, false, false}};
+// The loops that exist for a shape: kPlain any k of whole tiles, kConv the convolution, kWide row strides of 2^22 elements and more (8 MB:
+// the ring and quad loops address a tile's rows with 32-bit byte offsets; the register-staged ones with 64-bit pointers).
+enum Form { kPlain = 1, kConv = 2, kWide = 4 };
+static TileShape best_tile(const LinearArgs& g, Form form) {
+  struct Cost { int bm, bn, threads; double step, tile, once; bool alone; int forms; };
+  static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain},
+                                          {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 128, 256, 0.52, 2.7, 4.4, false, kPlain | kWide},
+                                          {128, 64, 256, 0.36, 1.4, 4.3, false, kPlain | kConv},  {64, 64, 256, 0.17, 0.8, 4.8, false, kPlain | kConv | kWide},
+                                          {32, 64, 128, 0.13, 0.65, 5.4, false, kPlain | kWide}};
   int best = -1;
   double best_t = 0;
   for (int c = 0; c < kTileShapes; ++c) {
-    if (conv && !costs[c].conv) continue;
+    if (!(costs[c].forms & form)) continue;
     if (!grid_fits(tiles_of(g, costs[c].bm, costs[c].bn), costs[c].threads)) continue;
     const int64_t tiles = tiles_of(g, costs[c].bm, costs[c].bn) * g.batch;
     const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
@@ -1426,7 +1429,7 @@ static TileShape best_tile(const LinearArgs& g, bool conv) {
     const double t = rounds * ((double)((g.k + kBK - 1) / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
-  return best < 0 ? (conv ? k128x128Ring : kQuad) : (TileShape)best;
+  return best < 0 ? (form == kConv ? k128x128Ring : form == kWide ? k128x128 : kQuad) : (TileShape)best;
 }
 
 // fp32 products whose rows can be read 16 bytes at a time
@@ -1459,8 +1462,15 @@ static const char* const kRouteName[kRoutes] = {
     "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "quad 256x256", "ring 256x128", "ring 128x128", "staged 128x128", "ring 128x64", "ring 64x64",
     "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x64", "conv 64x64"};
 
+static bool wide_rows(const LinearArgs& g) { return g.lda >= (1 << 22) || g.ldw >= (1 << 22); }
+
 static Route bf16_route(const LinearArgs& g) {
-  const TileShape shape = best_tile(g, false);
+  if (wide_rows(g)) {
+    if (g.k % kBK != 0) return kFma;
+    const TileShape staged = best_tile(g, kWide);
+    return staged == k128x128 ? kStaged128x128 : staged == k64x64 ? kStaged64x64 : kStaged32x64;
+  }
+  const TileShape shape = best_tile(g, kPlain);
   if (g.k % kBK != 0) {
     // a depth that is no multiple of a tile's 64 (whole rows of 16-byte chunks all the same): the products over the positions of
     // a pair tensor, whose size is a sequence's length.  128 products of 40 x 200 x 200: 42 us in the FMA kernel, 8.9 us here.
@@ -1498,7 +1508,7 @@ static Route f32_route(const LinearArgs& g) {
 
 static Route linear_route(const LinearArgs& g) {
   if (g.conv_c > 0) {
-    switch (best_tile(g, true)) {
+    switch (best_tile(g, kConv)) {
       case k128x128Ring: return kConv128x128;
       case k128x64: return kConv128x64;
       default: return kConv64x64;
@@ -1535,7 +1545,7 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
         g.m % ((int64_t)g.conv_h * g.conv_w) != 0 || g.batch != 1)
       return hipErrorInvalidValue;
     g.lda = g.conv_c;
-    if (!mfma_eligible(g)) return hipErrorInvalidValue;
+    if (!mfma_eligible(g) || wide_rows(g)) return hipErrorInvalidValue;
   }
   switch (linear_route(g)) {
     case kF32_32x64: return mfma_f32_launch<2, 4>(g, s);

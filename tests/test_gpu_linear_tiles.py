@@ -73,3 +73,20 @@ def test_depth_that_is_no_multiple_of_a_tile(B, c, ni, nj, nk):
     B.ac_op_triangle_contract(wide_a[:, :17, :nk], wide_b[..., :nk], part[:, :17])
     torch.cuda.synchronize()
     assert torch.equal(part[:, :17], out[:, :17])
+
+
+@pytest.mark.parametrize("m,n", [(70, 60), (200, 520)])
+@pytest.mark.parametrize("side", ["a", "w"])
+def test_long_row_strides(B, m, n, side):
+    """Operand rows 2^22 elements apart: equal bits to the same rows side by side."""
+    import torch
+    k = 192
+    a, w = B.to_device(draw((m, k), 160, "bf16"), "bf16"), B.to_device(draw((n, k), 161, "bf16", 1 / math.sqrt(k)), "bf16")
+    ref, out = (torch.full((m, n), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    B.ac_op_linear(a, w, ref)
+    near = a if side == "a" else w
+    far = torch.empty(((near.shape[0] - 1) << 22) + k, device="cuda", dtype=torch.bfloat16).as_strided(near.shape, (1 << 22, 1))
+    far.copy_(near)
+    B.ac_op_linear(*((far, w) if side == "a" else (a, far)), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)

@@ -34,3 +34,12 @@ def test_many_pixels_fit_a_grid_dimension(c):
     """8 output channels of a little under 2^30 pixels."""
     m = (1 << 30) - 64
     assert grid_threads(B.ac_linear_kernel(m, 8, 9 * c, "bf16", lda=c, conv=True), m, 8) < 1 << 32
+
+
+@pytest.mark.parametrize("m,n,k", [(1000, 1024, 1024), (100, 768, 768), (8192, 4096, 64), (16, 64, 1 << 22)])
+@pytest.mark.parametrize("side", ["lda", "ldw"])
+def test_long_row_strides_keep_the_matrix_cores(m, n, k, side):
+    """Rows 2^22 elements apart and more: the loops with 64-bit addresses, not the FMA kernel."""
+    for stride in (1 << 22, 1 << 33):
+        assert B.ac_linear_kernel(m, n, k, "bf16", **{side: stride}).startswith("staged")
+    assert not B.ac_linear_kernel(m, n, min(k, 1024), "bf16", **{side: (1 << 22) - 8}).startswith("fma")
