@@ -713,7 +713,9 @@ __device__ __forceinline__ void finish_tile(const LinearArgs& g, f32x16 (&acc)[B
   }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false>
+// WIDE: a convolution whose rows are too long for 32-bit offsets inside a tile (2^20 channels and more): 64 bits per lane, outside
+// pixels from a row of zeros.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false, bool WIDE = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(LinearArgs g) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
@@ -722,6 +724,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   constexpr int KSTEPS = BK / 16, READS = KSTEPS * (TM + TN), MMAS = KSTEPS * TM * TN;
   constexpr int STAGE = (BM + BN) * ROWB;
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && STAGES >= 3 && (NW * RPI) % 16 == 0, "tile / wave layout mismatch");
+  static_assert(!WIDE || CONV, "only the convolution has a form for long rows");
+  using Off = std::conditional_t<WIDE, int64_t, uint32_t>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   float* gelu_tab = reinterpret_cast<float*>(smem_raw + ring_lds_bytes(BM, BN, BK, STAGES));
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -746,14 +750,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   const unsigned char* w_base = (const unsigned char*)((const bf16_t*)g.w + product * g.sw_b + n0 * g.ldw);
   const int row_in = lane / CPR;                                        // row of the instruction this lane moves
   const int src_chunk = (lane % CPR) ^ ring_swizzle<BK>(wave * RPI + row_in);   // (NW instructions apart is a multiple of 16 rows)
-  uint32_t a_off[A_I], w_off[W_I];
+  Off a_off[A_I], w_off[W_I];
   int a_taps[A_I];   // CONV: bit t set = window position t of this row's pixel lies inside the image
 #pragma unroll
   for (int i = 0; i < A_I; ++i) {
     const int64_t last = g.m - 1 - m0;
     const int row = (wave + NW * i) * RPI + row_in;
     const int64_t rc = row < last ? row : last;
-    a_off[i] = (uint32_t)(rc * lda * 2) + src_chunk * 16;
+    a_off[i] = (Off)(rc * lda * 2) + src_chunk * 16;
     a_taps[i] = 0;
     if (CONV) {
       const int pix = (int)((m0 + rc) % ((int64_t)g.conv_h * g.conv_w)), ph = pix / g.conv_w, pw = pix % g.conv_w;
@@ -767,7 +771,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   for (int i = 0; i < W_I; ++i) {
     const int64_t last = g.n - 1 - n0;
     const int row = (wave + NW * i) * RPI + row_in;
-    w_off[i] = (uint32_t)((row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
+    w_off[i] = (Off)((row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
   }
   // (addresses: base and tile offset in scalar registers, 32 bits per lane; every lane's address is valid, so the range is open but for CONV's outside pixels)
   constexpr int kARange = CONV ? 0x7fffffff : -1;
@@ -778,7 +782,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   };
   // load instruction x of the PER that bring in this wave's share of tile kt; called tile after tile (CONV: the tile to
   // come lies inside window position `tap`, tap_off bytes from the first position of its row of the window on)
-  int tap = 0, tap_off = 0, tap_end = g.conv_c * 2;
+  int tap = 0;
+  std::conditional_t<WIDE, int64_t, int> tap_off = 0, tap_end = (decltype(tap_off))g.conv_c * 2;
   auto load_part = [&](int kt, int stage, int x) {
     unsigned char* dst = smem_raw + stage * STAGE + (x < A_I ? x * NW * 1024 : BM * ROWB + (x - A_I) * NW * 1024) + wave * 1024;
     auto buffer_to_lds = [](__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, uint32_t tile_off, unsigned char* lds) {
@@ -788,6 +793,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
       const bool in = kt * BK + src_chunk * 8 < (int)g.k;
       const unsigned char* src = x >= A_I ? w_base + (int64_t)kt * ROWB + w_off[x >= A_I ? x - A_I : 0] : a_base + (int64_t)kt * ROWB + a_off[x < A_I ? x : 0];
       to_lds(in ? src : (const unsigned char*)kZeroRow, dst);
+    } else if (WIDE) {
+      const unsigned char* src = x >= A_I ? w_base + (int64_t)kt * ROWB + w_off[x >= A_I ? x - A_I : 0] : a_base + tap_off + a_off[x < A_I ? x : 0];
+      to_lds(x >= A_I || ((a_taps[x < A_I ? x : 0] >> tap) & 1) ? src : (const unsigned char*)kZeroRow, dst);
     } else if (x >= A_I) {
       buffer_to_lds(w_rsrc, w_off[x - A_I], kt * ROWB, dst);
     } else if (CONV) {
@@ -798,12 +806,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     if (CONV && x == PER - 1) {
       tap_off += ROWB;
       if (tap_off == tap_end) {
-        tap_end += g.conv_c * 2;
+        tap_end += (decltype(tap_off))g.conv_c * 2;
         if (++tap % 3 == 0) {   // the next row of the window: a base of its own, as an image's rows may be large
           a_base += (int64_t)g.conv_w * g.conv_c * 2;
           a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a_base), 0, kARange, 0x00027000);
           tap_off = 0;
-          tap_end = g.conv_c * 2;
+          tap_end = (decltype(tap_off))g.conv_c * 2;
         }
       }
     }
@@ -1032,9 +1040,9 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
   finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false, bool WIDE = false>
 static hipError_t ring_launch(const LinearArgs& g, hipStream_t s) {
-  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV, RAGGED_K>;
+  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV, RAGGED_K, WIDE>;
   constexpr size_t ring = ring_lds_bytes(BM, BN, BK, STAGES);
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(ring + kGeluTableBytes));
@@ -1457,10 +1465,10 @@ static hipError_t mfma_f32_launch(const LinearArgs& g, hipStream_t s) {
 
 // The kernel a product runs on: a function of sizes, types, strides and alignment, decided on the host.
 enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kRouteQuad, kRing256x128, kRing128x128, kStaged128x128, kRing128x64, kRing64x64,
-             kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x64, kConv64x64, kRoutes };
+             kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x64, kConv64x64, kConvWide64x64, kRoutes };
 static const char* const kRouteName[kRoutes] = {
     "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "quad 256x256", "ring 256x128", "ring 128x128", "staged 128x128", "ring 128x64", "ring 64x64",
-    "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x64", "conv 64x64"};
+    "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x64", "conv 64x64", "conv-wide 64x64"};
 
 static bool wide_rows(const LinearArgs& g) { return g.lda >= (1 << 22) || g.ldw >= (1 << 22); }
 
@@ -1508,6 +1516,7 @@ static Route f32_route(const LinearArgs& g) {
 
 static Route linear_route(const LinearArgs& g) {
   if (g.conv_c > 0) {
+    if (g.conv_c >= (1 << 20)) return kConvWide64x64;   // (128 weight rows of 9 * 2^20 channels are 2.4e9 bytes)
     switch (best_tile(g, kConv)) {
       case k128x128Ring: return kConv128x128;
       case k128x64: return kConv128x64;
@@ -1545,7 +1554,7 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
         g.m % ((int64_t)g.conv_h * g.conv_w) != 0 || g.batch != 1)
       return hipErrorInvalidValue;
     g.lda = g.conv_c;
-    if (!mfma_eligible(g) || wide_rows(g)) return hipErrorInvalidValue;
+    if (!mfma_eligible(g)) return hipErrorInvalidValue;
   }
   switch (linear_route(g)) {
     case kF32_32x64: return mfma_f32_launch<2, 4>(g, s);
@@ -1565,6 +1574,7 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     case kConv128x128: return ring_launch<128, 128, 2, 4, 64, 3, true>(g, s);
     case kConv128x64: return ring_launch<128, 64, 2, 2, 64, 3, true>(g, s);
     case kConv64x64: return ring_launch<64, 64, 2, 2, 64, 3, true>(g, s);
+    case kConvWide64x64: return ring_launch<64, 64, 2, 2, 64, 3, true, false, true>(g, s);
     default: break;
   }
   dim3 grid((unsigned)((g.n + 63) / 64), (unsigned)((g.m + 63) / 64), (unsigned)g.batch);

@@ -68,6 +68,21 @@ def test_conv3x3(B, images, h, w, ci, co, per_image, resid):
     check(host(out), ref, "bf16")
 
 
+@pytest.mark.parametrize("c", [466048, 1 << 20, (1 << 20) + 64])
+def test_conv3x3_many_channels(B, c):
+    """Window rows of 2^22 elements and more, and pixels too long for 32-bit offsets inside a tile."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(c)
+    x = torch.randn((1, 3, 2, c), generator=g, device="cuda").bfloat16()
+    wt = torch.randn((8, 3, 3, c), generator=g, device="cuda").div_(np.sqrt(9 * c)).bfloat16()
+    out = torch.full((1, 3, 2, 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.ac_op_conv3x3(x, wt, out)
+    torch.cuda.synchronize()
+    xp = torch.nn.functional.pad(x[0].double(), (0, 0, 1, 1, 1, 1))
+    ref = sum(xp[i:i + 3, j:j + 2].reshape(6, c) @ wt[:, i, j].double().T.contiguous() for i in range(3) for j in range(3))
+    check(host(out), ref.view(1, 3, 2, 8).cpu().numpy(), "bf16")
+
+
 def test_conv3x3_refuses_what_it_cannot_do(B):
     import torch
     x = torch.zeros((1, 4, 4, 32), dtype=torch.bfloat16, device="cuda")

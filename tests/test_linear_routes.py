@@ -5,7 +5,8 @@ from paper_2401_10652_amd import binding as B
 from paper_2401_10652_amd.build import ensure_built
 
 THREADS = {"fma": 256, "f32": 256, "staged 32x64": 128, "staged": 256, "quad": 512, "ring 256x128": 512, "ring 128x128": 512, "ring": 256,
-           "ragged 256x128": 512, "ragged": 256, "conv 128x128": 512, "conv": 256}
+           "ragged 256x128": 512, "ragged": 256, "conv 128x128": 512, "conv": 256,
+           "conv-wide": 256}
 
 
 @pytest.fixture(scope="module", autouse=True)
