@@ -1499,17 +1499,24 @@ static Route bf16_route(const LinearArgs& g) {
 }
 
 static Route f32_route(const LinearArgs& g) {
-  // Rounds of 256 tiles (one per CU) x area of the tile; on a tie the larger tile, which reads less per output.
-  // 256 x 512 x 2048: 27 / 19 / 15 / 18 us with tiles of 32x64 / 32x32 / 32x16 / 16x16 (64, 128, 256 and 512 of them),
-  // 256 x 2048 x 512: 11.5 / 12.9 / 17.5 / 22 us (256 of 32x64).
-  static const int shapes[4][2] = {{32, 64}, {32, 32}, {32, 16}, {16, 16}};
+  // Many columns of at most 64 terms: what is left is the store of the output, at which the FMA kernel's 64x64 tiles are ahead once there are
+  // rows for it (16000 x 1024 x 64 61 against 77 us, 16000 x 8192 x 32 278 against 360) and behind before (256 x 1024 x 64 12.5 against 4.9).
+  // By k and n alone, as the two kernels sum in different orders and a row's bits must not depend on the launch's rows.
+  if (g.k <= 64 && g.n >= 1024) return kFma;
+  // The tile of least estimated time: rounds of 256 tiles x (k / 64 steps + prologue and epilogue), plus what is paid once, in us; fitted to 172 products
+  // of 1 to 20000 rows x 4 to 8192 columns x 36 to 8192 deep, most of them no multiples of a tile, on which the choice is within 1 % of the
+  // best of the four on average and 12 % at worst (by area alone it was 11 % off on average: a row past a multiple of the large tiles had sent
+  // 777 x 512 x 512 to 16x16, 21.9 us, where 32x64 takes 12.7).
+  struct Cost { int bm, bn; double step, tile, once; };
+  static const Cost costs[4] = {{32, 64, 0.77, 1.9, 2.5}, {32, 32, 0.38, 0.9, 3.0}, {32, 16, 0.27, 0.5, 3.1}, {16, 16, 0.18, 0.25, 3.2}};
   int best = -1;
-  int64_t best_t = INT64_MAX;
+  double best_t = 0;
   for (int c = 0; c < 4; ++c) {
-    const int64_t tiles = tiles_of(g, shapes[c][0], shapes[c][1]);
+    const int64_t tiles = tiles_of(g, costs[c].bm, costs[c].bn);
     if (!grid_fits(tiles, 256)) continue;
-    const int64_t t = (tiles * g.batch + 255) / 256 * shapes[c][0] * shapes[c][1];
-    if (t < best_t) { best = c; best_t = t; }
+    const double rounds = (double)((tiles * g.batch + 255) / 256);
+    const double t = rounds * ((double)((g.k + 63) / 64) * costs[c].step + costs[c].tile) + costs[c].once;
+    if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   return best < 0 ? kFma : (Route)(kF32_32x64 + best);
 }

@@ -44,3 +44,15 @@ def test_long_row_strides_keep_the_matrix_cores(m, n, k, side):
     for stride in (1 << 22, 1 << 33):
         assert B.ac_linear_kernel(m, n, k, "bf16", **{side: stride}).startswith("staged")
     assert not B.ac_linear_kernel(m, n, min(k, 1024), "bf16", **{side: (1 << 22) - 8}).startswith("fma")
+
+
+@pytest.mark.parametrize("m,n,k", [(1024, 2048, 512), (1024, 1536, 512), (768, 512, 512), (1500, 2048, 512), (200, 1536, 512)])
+def test_a_row_more_does_not_send_an_fp32_product_to_the_smallest_tile(m, n, k):
+    for rows in (m, m + 1, m + 9):
+        assert B.ac_linear_kernel(rows, n, k, "f32") in ("f32 32x64", "f32 32x32")
+
+
+def test_short_fp32_sums_of_many_columns_take_one_kernel_whatever_the_rows():
+    for m in (1, 100, 1000, 20000):
+        assert B.ac_linear_kernel(m, 1024, 64, "f32") == "fma 64x64"
+        assert B.ac_linear_kernel(m, 1020, 64, "f32").startswith("f32") and B.ac_linear_kernel(m, 4096, 68, "f32").startswith("f32")
