@@ -1417,14 +1417,14 @@ enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x6
 // A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
 static bool grid_fits(int64_t tiles, int threads) { return tiles <= 0xffffffffLL / threads; }
 static int64_t tiles_of(const LinearArgs& g, int bm, int bn) { return ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn); }
-// The loops that exist for a shape: kPlain any k of whole tiles, kConv the convolution, kWide row strides of 2^22 elements and more (8 MB:
+// The loops that exist for a shape: kPlain any k of whole tiles, kRagged k that ends inside one, kConv the convolution, kWide row strides of 2^22 elements and more (8 MB:
 // the ring and quad loops address a tile's rows with 32-bit byte offsets; the register-staged ones with 64-bit pointers).
-enum Form { kPlain = 1, kConv = 2, kWide = 4 };
+enum Form { kPlain = 1, kConv = 2, kWide = 4, kRagged = 8 };
 static TileShape best_tile(const LinearArgs& g, Form form) {
   struct Cost { int bm, bn, threads; double step, tile, once; bool alone; int forms; };
-  static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain},
+  static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain | kRagged},
                                           {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 128, 256, 0.52, 2.7, 4.4, false, kPlain | kWide},
-                                          {128, 64, 256, 0.36, 1.4, 4.3, false, kPlain | kConv},  {64, 64, 256, 0.17, 0.8, 4.8, false, kPlain | kConv | kWide},
+                                          {128, 64, 256, 0.36, 1.4, 4.3, false, kPlain | kConv},  {64, 64, 256, 0.17, 0.8, 4.8, false, kPlain | kConv | kWide | kRagged},
                                           {32, 64, 128, 0.13, 0.65, 5.4, false, kPlain | kWide}};
   int best = -1;
   double best_t = 0;
@@ -1437,7 +1437,7 @@ static TileShape best_tile(const LinearArgs& g, Form form) {
     const double t = rounds * ((double)((g.k + kBK - 1) / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
-  return best < 0 ? (form == kConv ? k128x128Ring : form == kWide ? k128x128 : kQuad) : (TileShape)best;
+  return best < 0 ? (form == kConv ? k128x128Ring : form == kWide ? k128x128 : form == kRagged ? k256x128 : kQuad) : (TileShape)best;
 }
 
 // fp32 products whose rows can be read 16 bytes at a time
@@ -1478,13 +1478,13 @@ static Route bf16_route(const LinearArgs& g) {
     const TileShape staged = best_tile(g, kWide);
     return staged == k128x128 ? kStaged128x128 : staged == k64x64 ? kStaged64x64 : kStaged32x64;
   }
-  const TileShape shape = best_tile(g, kPlain);
   if (g.k % kBK != 0) {
     // a depth that is no multiple of a tile's 64 (whole rows of 16-byte chunks all the same): the products over the positions of
     // a pair tensor, whose size is a sequence's length.  128 products of 40 x 200 x 200: 42 us in the FMA kernel, 8.9 us here.
-    return shape == kQuad || shape == k256x128 || !grid_fits(tiles_of(g, 64, 64), 256) ? kRagged256x128 : kRagged64x64;
+    // Chosen among the two shapes that are built for it (4 products of 2000 x 2100 x 1000: 72 us on 256x128, 87 on 64x64).
+    return best_tile(g, kRagged) == k64x64 ? kRagged64x64 : kRagged256x128;
   }
-  switch (shape) {
+  switch (best_tile(g, kPlain)) {
     case kQuad: return kRouteQuad;
     case k256x128: return kRing256x128;
     case k128x128Ring: return kRing128x128;

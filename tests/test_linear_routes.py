@@ -56,3 +56,11 @@ def test_short_fp32_sums_of_many_columns_take_one_kernel_whatever_the_rows():
     for m in (1, 100, 1000, 20000):
         assert B.ac_linear_kernel(m, 1024, 64, "f32") == "fma 64x64"
         assert B.ac_linear_kernel(m, 1020, 64, "f32").startswith("f32") and B.ac_linear_kernel(m, 4096, 68, "f32").startswith("f32")
+
+
+def test_ragged_depths_are_priced_among_the_tiles_that_exist():
+    """(2000 x 2100 and 720 x 616 are fastest on the 128x128 tile by estimate, which ragged depths do not have.)"""
+    for m, n, k, batch in ((2000, 2100, 1000, 4), (720, 616, 280, 128), (200, 200, 200, 128)):
+        assert B.ac_linear_kernel(m, n, k, "bf16", batch=batch) == "ragged 256x128"
+    for m, n, k, batch in ((40, 200, 200, 128), (64, 328, 328, 128), (24, 208, 3048, 1)):
+        assert B.ac_linear_kernel(m, n, k, "bf16", batch=batch) == "ragged 64x64"
