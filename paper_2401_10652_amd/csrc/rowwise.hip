@@ -843,6 +843,12 @@ __device__ __forceinline__ void group_norm_merge(const float* part, int64_t imag
   }
 }
 
+// One element, the same in both passes below, so that which of them a launch takes does not change its bits.
+__device__ __forceinline__ float group_norm_one(float v, float mean, float rstd, float gain, float shift, int act) {
+  const float t = fmaf((v - mean) * rstd, gain, shift);
+  return act == AC_ACT_SILU ? t * sigmoidf(t) : t;
+}
+
 // The pass of rows of at most 256 16-byte runs: a thread keeps one run of channels and walks down the rows, so its eight groups'
 // statistics and its gain and shift are looked up once (a division by the group size per element, and the rows'
 // loads behind the merge instead of under it, had the launch of 2 x 4096 x 320 at 13.5 us; 11.5 us here).
@@ -884,15 +890,12 @@ group_norm_apply_rows(const T* x, const float* part, const T* gain, const T* shi
     const int64_t p = p0 + (int64_t)k * rpp;
     if (p >= positions) break;
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const float t = (v[k][i] - mean[i]) * rstd[i] * gg[i] + sh[i];
-      v[k][i] = act == AC_ACT_SILU ? t * sigmoidf(t) : t;
-    }
+    for (int i = 0; i < V; ++i) v[k][i] = group_norm_one(v[k][i], mean[i], rstd[i], gg[i], sh[i], act);
     store_vec(dst + p * channels, v[k]);
   }
 }
 
-// (rows wider than that)
+// The pass of wider rows, and of those that would leave the threads of the one above idle: a thread takes runs 256 apart.
 template <typename T>
 __global__ void __launch_bounds__(256)
 group_norm_apply(const T* x, const float* part, const T* gain, const T* shift, T* y, int64_t positions, int channels,
@@ -925,8 +928,7 @@ group_norm_apply(const T* x, const float* part, const T* gain, const T* shift, T
 #pragma unroll
     for (int i = 0; i < V; ++i) {
       const int g = (ch0[k] + i) / cg;
-      const float t = (v[k][i] - s_mean[g]) * s_rstd[g] * gg[i] + sh[i];
-      v[k][i] = act == AC_ACT_SILU ? t * sigmoidf(t) : t;
+      v[k][i] = group_norm_one(v[k][i], s_mean[g], s_rstd[g], gg[i], sh[i], act);
     }
     store_vec(y + off[k], v[k]);
   }
@@ -943,28 +945,26 @@ hipError_t launch_group_norm(const void* x, const void* gain, const void* shift,
   const bool by_rows = channels / (dtype == AC_BF16 ? 8 : 4) <= 256;
   const dim3 g1 = by_rows ? dim3((unsigned)images, kGnParts) : dim3((unsigned)(images * groups), kGnParts);
   const int64_t runs = channels / (dtype == AC_BF16 ? 8 : 4), chunks = positions * runs;
-  const int64_t per_block = by_rows ? 256 / runs * kGnApplyChunks : 256 * kGnApplyChunks;   // rows, or 16-byte runs
-  const dim3 g2((unsigned)(((by_rows ? positions : chunks) + per_block - 1) / per_block), (unsigned)images);
+  // Whole rows per block leave 256 mod `runs` threads idle.  A launch that fills the chip is bound by the rows it has in flight and
+  // wants at least seven of eight threads at work (8 x 4096 x 640 in fp32, 160 of 256: 80 us by rows, 62 by runs); a smaller one
+  // gains from the rows' earlier loads all the same (2 x 1024 x 640: 13.5 against 14.9; two blocks per CU and less).
+  const int64_t row_blocks = by_rows ? (positions + 256 / runs * kGnApplyChunks - 1) / (256 / runs * kGnApplyChunks) : 0;
+  const bool apply_rows = by_rows && (256 / runs * runs >= 224 || row_blocks * images <= 512);
+  const dim3 g2((unsigned)(apply_rows ? row_blocks : (chunks + 256 * kGnApplyChunks - 1) / (256 * kGnApplyChunks)), (unsigned)images);
   if (dtype == AC_BF16) {
-    if (by_rows) {
-      hipLaunchKernelGGL((group_norm_partials_rows<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
-      hipLaunchKernelGGL((group_norm_apply_rows<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
-                         (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
-    } else {
-      hipLaunchKernelGGL((group_norm_partials<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
-      hipLaunchKernelGGL((group_norm_apply<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
-                         (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
-    }
+    if (by_rows) hipLaunchKernelGGL((group_norm_partials_rows<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
+    else hipLaunchKernelGGL((group_norm_partials<bf16_t>), g1, dim3(256), 0, s, (const bf16_t*)x, (float*)partials, positions, channels, groups);
+    if (apply_rows) hipLaunchKernelGGL((group_norm_apply_rows<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
+                                       (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
+    else hipLaunchKernelGGL((group_norm_apply<bf16_t>), g2, dim3(256), 0, s, (const bf16_t*)x, (const float*)partials, (const bf16_t*)gain,
+                            (const bf16_t*)shift, (bf16_t*)y, positions, channels, groups, eps, act);
   } else {
-    if (by_rows) {
-      hipLaunchKernelGGL((group_norm_partials_rows<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
-      hipLaunchKernelGGL((group_norm_apply_rows<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
-                         (const float*)shift, (float*)y, positions, channels, groups, eps, act);
-    } else {
-      hipLaunchKernelGGL((group_norm_partials<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
-      hipLaunchKernelGGL((group_norm_apply<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
-                         (const float*)shift, (float*)y, positions, channels, groups, eps, act);
-    }
+    if (by_rows) hipLaunchKernelGGL((group_norm_partials_rows<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
+    else hipLaunchKernelGGL((group_norm_partials<float>), g1, dim3(256), 0, s, (const float*)x, (float*)partials, positions, channels, groups);
+    if (apply_rows) hipLaunchKernelGGL((group_norm_apply_rows<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
+                                       (const float*)shift, (float*)y, positions, channels, groups, eps, act);
+    else hipLaunchKernelGGL((group_norm_apply<float>), g2, dim3(256), 0, s, (const float*)x, (const float*)partials, (const float*)gain,
+                            (const float*)shift, (float*)y, positions, channels, groups, eps, act);
   }
   return hipGetLastError();
 }

@@ -47,6 +47,25 @@ def test_group_norm(B, dtype, images, h, w, c, groups, act):
     assert ei.value.status == B.AC_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("dtype,c", [("f32", 640), ("bf16", 1280)])
+def test_group_norm_does_not_depend_on_the_pass(B, dtype, c):
+    """Rows of 160 runs of 16 bytes: an image alone takes the pass by rows, three of them the pass by runs (the other would leave
+    96 of 256 threads idle), with equal bits."""
+    import torch
+    images, h, w, groups = 3, 32, 31, 32
+    x = draw((images, h, w, c), 53, dtype)
+    gain, shift = (I.round_to_storage(draw((c,), 54 + i, dtype) * 0.3 + 1.0 - i, dtype) for i in range(2))
+    dx, dg, ds = (B.to_device(t, dtype) for t in (x, gain, shift))
+    ws = torch.empty((B.ac_group_norm_workspace_bytes(images, groups),), dtype=torch.uint8, device="cuda")
+    y, one = torch.full_like(dx, float("nan")), torch.full_like(dx, float("nan"))
+    B.ac_op_group_norm(dx, dg, ds, y, ws, groups, activation=B.AC_ACT_SILU)
+    for i in range(images):
+        B.ac_op_group_norm(dx[i:i + 1], dg, ds, one[i:i + 1], ws, groups, activation=B.AC_ACT_SILU)
+    torch.cuda.synchronize()
+    check(host(y), U.silu(U.group_norm(x, gain, shift, groups)), dtype)
+    assert torch.equal(one, y)
+
+
 @pytest.mark.parametrize("images,h,w,ci,co,per_image,resid", [(2, 5, 7, 64, 72, True, False), (1, 16, 16, 128, 320, False, True),
                                                               (3, 8, 8, 64, 64, True, True), (1, 1, 1, 64, 8, False, False),
                                                               (2, 13, 1, 192, 136, True, True)])
