@@ -21,9 +21,13 @@ def B():
     (1, 4, 4),                       # one row, less than one step of k: three of the four runs of k empty
     (15, 20, 12), (17, 16, 68),      # 16x16 tiles; a run that ends inside a step
     (64, 33, 64),                    # columns that end inside a 16-byte store
-    (250, 520, 2052),                # 32x16 tiles, ragged last run
+    (250, 520, 2052),                # 32x32 tiles, ragged last run
     (700, 1020, 260),                # 32x32 tiles, ragged both ways
-    (1100, 2100, 100),               # 32x64 tiles, ragged both ways
+    (1100, 2100, 100),
+    (204, 449, 200),                 # 32x16 tiles, ragged all ways
+    (859, 65, 72),
+    (745, 602, 232),                 # 32x64 tiles, ragged all ways
+    (274, 929, 68),
 ])
 def test_linear_f32(B, m, n, k):
     import torch
@@ -34,7 +38,10 @@ def test_linear_f32(B, m, n, k):
     B.ac_op_linear(da, dw, out, bias=db, residual=dr)
     torch.cuda.synchronize()
     check(host(out), O.linear(a, w, bias) + res, "f32")
-    # a row's bits do not depend on the launch it falls in (nor on the tile shape that takes)
+    # a row's bits do not depend on the launch it falls in (nor on the tile shape: launches of 33 rows take 16x16)
+    tile = {(250, 520): "32x32", (700, 1020): "32x32", (1100, 2100): "32x32", (204, 449): "32x16", (859, 65): "32x16",
+            (745, 602): "32x64", (274, 929): "32x64"}.get((m, n), "16x16")
+    assert B.ac_linear_kernel(m, n, k, "f32") == "f32 " + tile and B.ac_linear_kernel(min(m, 33), n, k, "f32") == "f32 16x16"
     part = torch.full((m, n), float("nan"), device="cuda")
     for r0 in range(0, m, 33):
         r1 = min(m, r0 + 33)

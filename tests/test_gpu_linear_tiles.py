@@ -19,12 +19,12 @@ def B():
 
 
 @pytest.mark.parametrize("m,n", [
-    (5000, 5000),      # 256x256
+    (5000, 5000),      # 256x256 (one tile of k: 128x128 through registers)
     (8100, 1020),      # 256x128
     (4000, 760),       # 128x128 with a ring
     (1000, 640),       # 64x64, at most one per CU
-    (1990, 2040),      # 64x64 / 128x64 in several rounds
-    (100, 100),        # 32x64
+    (1990, 2040),      # 128x128 with a ring, its 1017-row launches also 128x64
+    (100, 100),        # 64x64
 ])
 @pytest.mark.parametrize("k", [64, 128, 192, 320, 448])
 def test_linear_tiles(B, m, n, k):
@@ -46,6 +46,35 @@ def test_linear_tiles(B, m, n, k):
     assert torch.equal(part, out)
 
 
+@pytest.mark.parametrize("tile,m,n,k", [
+    ("quad 256x256", 1684, 5708, 64), ("quad 256x256", 1445, 5780, 128), ("quad 256x256", 7215, 1096, 256),
+    ("ring 256x128", 773, 5000, 64), ("ring 256x128", 5473, 708, 192),
+    ("ring 128x128", 8267, 68, 64), ("ring 128x128", 291, 5448, 256),
+    ("staged 128x128", 1314, 5464, 64), ("staged 128x128", 2371, 3408, 192),
+    ("ring 128x64", 8270, 408, 64), ("ring 128x64", 4785, 196, 256),
+    ("ring 64x64", 150, 8, 64), ("ring 64x64", 1000, 644, 448),
+    ("staged 64x64", 502, 516, 512), ("staged 64x64", 950, 1020, 1024),
+    ("staged 32x64", 500, 1020, 4096), ("staged 32x64", 201, 500, 2048),
+])
+def test_every_tile(B, tile, m, n, k):
+    """Each kernel and tile, one and more tiles of k, rows and columns that end inside a tile: against fp64 on sampled rows and bit for
+    bit against launches of 97 rows, which take other tiles (GELU and the residual in the epilogue)."""
+    import torch
+    assert B.ac_linear_kernel(m, n, k, "bf16") == tile
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    a = torch.randn((m, k), generator=g, device="cuda").bfloat16()
+    w = (torch.randn((n, k), generator=g, device="cuda") / math.sqrt(k)).bfloat16()
+    res = torch.randn((m, n), generator=g, device="cuda").bfloat16()
+    out, part = (torch.full((m, n), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    B.ac_op_linear(a, w, out, residual=res, activation=B.AC_ACT_GELU_ERF)
+    rows = np.unique(np.concatenate([np.arange(min(m, 40)), np.arange(max(0, m - 40), m), np.arange(0, m, 61)]))
+    t = torch.from_numpy(rows).cuda()
+    check(host(out[t]), O.gelu_erf(O.linear(host(a[t]), host(w))) + host(res[t]), "bf16")
+    for r0 in range(0, m, 97):
+        B.ac_op_linear(a[r0:r0 + 97], w, part[r0:r0 + 97], residual=res[r0:r0 + 97], activation=B.AC_ACT_GELU_ERF)
+    assert torch.equal(part, out)
+
+
 @pytest.mark.parametrize("c,ni,nj,nk", [(16, 64, 1024, 1024), (3, 700, 900, 192), (5, 40, 72, 64)])
 def test_batched_products(B, c, ni, nj, nk):
     import torch
@@ -56,11 +85,12 @@ def test_batched_products(B, c, ni, nj, nk):
     check(host(out), np.matmul(a.astype(np.float64), b.astype(np.float64).transpose(0, 2, 1)), "bf16")
 
 
-@pytest.mark.parametrize("c,ni,nj,nk", [(6, 40, 200, 200), (3, 70, 72, 8), (2, 100, 136, 72), (128, 33, 328, 328), (4, 2000, 2100, 1000)])
+@pytest.mark.parametrize("c,ni,nj,nk", [(6, 40, 200, 200), (3, 70, 72, 8), (2, 100, 136, 72), (128, 33, 328, 328), (4, 2000, 2100, 1000), (128, 197, 200, 200), (128, 200, 200, 72)])
 def test_depth_that_is_no_multiple_of_a_tile(B, c, ni, nj, nk):
-    """k of whole 16-byte chunks that ends inside a tile of 64 (64x64 and 256x128 tiles): what lies past the end of a row must not
+    """k of whole 16-byte chunks that ends inside a tile of 64 (64x64 tiles, the last three 256x128): what lies past the end of a row must not
     count, so the operands are column blocks of tensors whose other columns hold NaN."""
     import torch
+    assert B.ac_linear_kernel(ni, nj, nk, "bf16", lda=nk + 64, ldw=nk + 64, batch=c) == ("ragged 256x128" if c * ni >= 8000 else "ragged 64x64")
     a, b = draw((c, ni, nk), 150, "bf16"), draw((c, nj, nk), 151, "bf16", 1 / math.sqrt(nk))
     wide_a = torch.full((c, ni, nk + 64), float("nan"), device="cuda", dtype=torch.bfloat16)
     wide_b = torch.full((c, nj, nk + 64), float("nan"), device="cuda", dtype=torch.bfloat16)

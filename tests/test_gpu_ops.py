@@ -39,9 +39,9 @@ def test_layernorm(B, dtype, rows, cols):
 
 
 @pytest.mark.parametrize("dtype,m,n,k", [
-    ("bf16", 300, 200, 192),      # 32x64 tiles, ragged m and n
+    ("bf16", 300, 200, 192),      # 64x64 tiles, ragged m and n
     ("bf16", 500, 2040, 192),     # 64x64 tiles (256 of them), ragged m and n
-    ("bf16", 520, 3000, 128),     # 64x64 tiles in two rounds, ragged m and n
+    ("bf16", 520, 3000, 128),     # 128x128 tiles, ragged m and n
     ("bf16", 2048, 2048, 256),    # 128x128 tiles
     ("bf16", 1100, 3072, 128),    # 128x128 tiles, ragged m
     ("bf16", 77, 37, 100),        # odd shape -> generic kernel
@@ -87,7 +87,7 @@ def test_linear(B, dtype, m, n, k, epi):
 @pytest.mark.parametrize("m,n,k,epi", [(8184, 8168, 2048, "none"), (8184, 8168, 2048, "bias_gelu"),
                                        (8184, 8168, 4096, "bias_resid"), (8192, 8192, 1024, "bias_gelu")])
 def test_linear_large_tiles_on_sampled_rows(B, m, n, k, epi):
-    """Shapes that take the 256x256 tiles (both kernels: k >= 2048 and below), with ragged last
+    """Shapes that take the 256x256 tiles, with ragged last
     tiles in both directions; the oracle computes every column of a sample of rows (the first
     and the last tile's rows among them)."""
     import torch

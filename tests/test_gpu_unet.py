@@ -68,11 +68,14 @@ def test_group_norm_does_not_depend_on_the_pass(B, dtype, c):
 
 @pytest.mark.parametrize("images,h,w,ci,co,per_image,resid", [(2, 5, 7, 64, 72, True, False), (1, 16, 16, 128, 320, False, True),
                                                               (3, 8, 8, 64, 64, True, True), (1, 1, 1, 64, 8, False, False),
-                                                              (2, 13, 1, 192, 136, True, True)])
+                                                              (2, 13, 1, 192, 136, True, True), (13, 29, 44, 64, 72, True, True),
+                                                              (3, 43, 101, 64, 72, True, True), (1, 1, 13029, 64, 72, False, True)])
 def test_conv3x3(B, images, h, w, ci, co, per_image, resid):
-    """Borders on every side, one-pixel and one-column images (most window positions outside), output channels that
-    end inside a tile, a bias per image, the skip."""
+    """Borders on every side, one-pixel, one-column and one-row images (most window positions outside), pixels and output
+    channels that end inside a tile (of 64x64, and of 128x128 and 128x64 for the larger ones), a bias per image, the skip."""
     import torch
+    assert B.ac_linear_kernel(images * h * w, co, 9 * ci, "bf16", lda=ci, conv=True) == (
+        "conv 128x128" if images == 13 else "conv 128x64" if images * h * w > 10000 else "conv 64x64")
     x = draw((images, h, w, ci), 60, "bf16")
     wt = draw((co, 3, 3, ci), 61, "bf16", std=1.0 / np.sqrt(9 * ci))
     bias = draw((images, co) if per_image else (co,), 62, "bf16", std=0.5)
