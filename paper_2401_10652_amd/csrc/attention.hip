@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(128) attention_rows(AttnArgs a) {
 // registers = 4 consecutive keys) which is the operand layout of the second product, and value rows are
 // read whole, lane l16 holding d = NV l16 .. NV l16 + NV - 1.
 // Measured (1024 x 1024 causal, 8 heads of 64 / 256 x 256, 4 heads of 16): 916 / 71 us with one thread per
-// row (the kernel above), 35 / 5.7 us here.
+// row (the kernel above), 34 / 5.2 us here.
 // ------------------------------------------------------------------------------------
 template <int DH>
 __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {

@@ -75,7 +75,8 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 }
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
-// The same by the hardware reciprocal and one Newton step, for the GEMM epilogues: 8 instructions where the division takes 13.
+// The same by the hardware reciprocal and one Newton step, for the GEMM epilogues: 8 instructions where the division takes 13
+// (q, k, v, gate and bias of 65536 rows of 128: 26.7 us; 27.7 with the division, 26.1 with the bare reciprocal).
 // A quarter of the denominator is inverted, so that all of its range up to 2^128 has a normal reciprocal; the residual's clamp is
 // for an infinite denominator (0 * inf) and lets NaN through.  Equal to sigmoidf for every fp32 input but for 33945 between
 // -87.3 and -88.8, whose subnormal result is rounded twice (all 2^32 inputs compared; the bare reciprocal differs for 33

@@ -9,10 +9,9 @@
 // The K loop order does not depend on the tile's position in m, so a row's result is
 // bitwise the same for every chunk length.
 //
-// fp32 path and odd shapes: an LDS-tiled FMA kernel with full bounds checks.
+// fp32 path: v_mfma_f32_16x16x4_f32 on rows that can be read 16 bytes at a time.
+// Odd shapes and strides of either type, and short fp32 sums of many columns: an LDS-tiled FMA kernel with full bounds checks.
 #include "common.h"
-
-#include <type_traits>
 
 #include <type_traits>
 
@@ -680,8 +679,8 @@ static hipError_t mfma_launch(const LinearArgs& g, hipStream_t s) {
 // LDS rows are BK elements without padding (a direct load writes 1 KB of consecutive LDS); the 16-byte chunks
 // of a row are permuted instead: chunk c of row r lies at position c ^ swz(r).  A 128-bit read serves 16 lanes at a time over
 // 256 bytes of banks, lanes 0-3, 12-15, 20-23, 24-27 together and the other sixteen of a half-wave together; swz gives
-// either set sixteen different slots (SQ_LDS_BANK_CONFLICT 1 % of SQ_LDS_IDX_ACTIVE; a rule for runs of 16 or 32 consecutive lanes
-// left 50 % on 64-byte rows).  The permutation is applied to the lane's global address, inside one cache line.
+// either set sixteen different slots (SQ_LDS_BANK_CONFLICT 1.1 % of SQ_LDS_IDX_ACTIVE at k = 8192 and 7.5 % at k = 1024: the epilogue's
+// staging, none of it the k loop's).  The permutation is applied to the lane's global address, inside one cache line.
 // Same matrix instructions on the same operands in the same k order as the kernel above: equal bits.
 // ------------------------------------------------------------------------------------
 template <int BK> __device__ __forceinline__ int ring_swizzle(int r) {
@@ -723,7 +722,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   constexpr int A_I = BM / RPI / NW, W_I = BN / RPI / NW, PER = A_I + W_I;   // load instructions of a wave per tile
   constexpr int KSTEPS = BK / 16, READS = KSTEPS * (TM + TN), MMAS = KSTEPS * TM * TN;
   constexpr int STAGE = (BM + BN) * ROWB;
-  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && STAGES >= 3 && (NW * RPI) % 16 == 0, "tile / wave layout mismatch");
+  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && STAGES == 3 && (NW * RPI) % 16 == 0, "tile / wave layout mismatch");   // (arrived() has the waits of three)
   static_assert(!WIDE || CONV, "only the convolution has a form for long rows");
   using Off = std::conditional_t<WIDE, int64_t, uint32_t>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -919,7 +918,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
 // Same matrix instructions in the same k order per output as the kernels above: equal bits.
 // ------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
-  constexpr int BM = 256, BN = 256, WAVES_M = 2, WAVES_N = 4, NW = 8, TM = 4, TN = 2, BK = 64, ROWB = 128;
+  constexpr int BM = 256, BN = 256, WAVES_M = 2, WAVES_N = 4, TM = 4, TN = 2, BK = 64, ROWB = 128;
   constexpr int BUF = (BM + BN) * ROWB;                                 // bytes of one tile
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   float* gelu_tab = reinterpret_cast<float*>(smem_raw + ring_lds_bytes(BM, BN, BK, 2));
