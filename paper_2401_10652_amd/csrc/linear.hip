@@ -1411,6 +1411,8 @@ static bool mfma_eligible(const LinearArgs& g) {
 // share a CU pay little per tile and more per step.  Examples (us; 256x256 / 256x128 / 128x128 ring / 128x128 / 128x64 /
 // 64x64 / 32x64):  65536x1024x1024  144 / 181 / 230 / 182 / 236 / 251 / 359;  6400x1024x1024  27 / 20 / 23 / 23 / 26 / 27 / 35;
 // 4000x1024x4096  78 / 56 / 42 / 46 / 52 / 64 / 83;  512x1024x4096  72 / 43 / 27 / 40 / 29 / 21 / 14.5.
+// What 32x64 pays once is set by launches of one round inside models, whose operands another kernel has just written: 128x2048x512 takes
+// 7.0 us on it and 8.1 on 64x64 (which 5.4 us instead of 5.0 had preferred), 128x1536x384 6.7 and 7.7, 240x2048x512 (320 tiles) 10.0 and 9.0.
 // The k order is the same for all of them, and so are the bits.
 enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x64, kTileShapes };
 // A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
@@ -1424,7 +1426,7 @@ static TileShape best_tile(const LinearArgs& g, Form form) {
   static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain | kRagged},
                                           {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 128, 256, 0.52, 2.7, 4.4, false, kPlain | kWide},
                                           {128, 64, 256, 0.36, 1.4, 4.3, false, kPlain | kConv},  {64, 64, 256, 0.17, 0.8, 4.8, false, kPlain | kConv | kWide | kRagged},
-                                          {32, 64, 128, 0.13, 0.65, 5.4, false, kPlain | kWide}};
+                                          {32, 64, 128, 0.13, 0.65, 5.0, false, kPlain | kWide}};
   int best = -1;
   double best_t = 0;
   for (int c = 0; c < kTileShapes; ++c) {

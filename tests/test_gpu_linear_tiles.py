@@ -24,7 +24,7 @@ def B():
     (4000, 760),       # 128x128 with a ring
     (1000, 640),       # 64x64, at most one per CU
     (1990, 2040),      # 128x128 with a ring, its 1017-row launches also 128x64
-    (100, 100),        # 64x64
+    (100, 100),        # 32x64 (one tile of k: 64x64)
 ])
 @pytest.mark.parametrize("k", [64, 128, 192, 320, 448])
 def test_linear_tiles(B, m, n, k):
@@ -53,7 +53,7 @@ def test_linear_tiles(B, m, n, k):
     ("staged 128x128", 1314, 5464, 64), ("staged 128x128", 2371, 3408, 192),
     ("ring 128x64", 8270, 408, 64), ("ring 128x64", 4785, 196, 256),
     ("ring 64x64", 150, 8, 64), ("ring 64x64", 1000, 644, 448),
-    ("staged 64x64", 502, 516, 512), ("staged 64x64", 950, 1020, 1024),
+    ("staged 64x64", 1000, 644, 512), ("staged 64x64", 950, 1020, 1024),
     ("staged 32x64", 500, 1020, 4096), ("staged 32x64", 201, 500, 2048),
 ])
 def test_every_tile(B, tile, m, n, k):

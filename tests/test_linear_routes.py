@@ -64,3 +64,8 @@ def test_ragged_depths_are_priced_among_the_tiles_that_exist():
         assert B.ac_linear_kernel(m, n, k, "bf16", batch=batch) == "ragged 256x128"
     for m, n, k, batch in ((40, 200, 200, 128), (64, 328, 328, 128), (24, 208, 3048, 1)):
         assert B.ac_linear_kernel(m, n, k, "bf16", batch=batch) == "ragged 64x64"
+
+
+@pytest.mark.parametrize("m,n,k", [(128, 2048, 512), (128, 1536, 384), (96, 2048, 512), (128, 3072, 768), (256, 512, 2048), (512, 768, 3072)])
+def test_launches_of_one_round_of_small_tiles_take_the_smallest(m, n, k):
+    assert B.ac_linear_kernel(m, n, k, "bf16") == "staged 32x64"
