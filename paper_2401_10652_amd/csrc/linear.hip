@@ -1407,12 +1407,13 @@ static bool mfma_eligible(const LinearArgs& g) {
 // steps plus a prologue and an epilogue per tile, plus what is paid once.  A last round that is partly empty counts whole
 // for the shapes that have a CU to themselves (1.25 rounds of 256x256 tiles of 8192 x 2560 x 320 take 39.7 us, two take 37) and half
 // for those that share it.  The three times of a shape, in us, are fitted to 68 launches of 512 to 65536 rows x 64 to
-// 4096 columns x 64 to 4096 deep, batched ones among them, on which the choice is within 5 % of the best shape.  Shapes whose blocks
-// share a CU pay little per tile and more per step.  Examples (us; 256x256 / 256x128 / 128x128 ring / 128x128 / 128x64 /
+// 4096 columns x 64 to 4096 deep, batched ones among them, on which the choice is within 5 % of the best shape; on 140 others of 1 to 70000 rows
+// and ragged sizes it is 2 % off on average and 23 % at worst.  Shapes whose blocks share a CU pay little per tile and more per step.  Examples (us; 256x256 / 256x128 / 128x128 ring / 128x128 / 128x64 /
 // 64x64 / 32x64):  65536x1024x1024  144 / 181 / 230 / 182 / 236 / 251 / 359;  6400x1024x1024  27 / 20 / 23 / 23 / 26 / 27 / 35;
 // 4000x1024x4096  78 / 56 / 42 / 46 / 52 / 64 / 83;  512x1024x4096  72 / 43 / 27 / 40 / 29 / 21 / 14.5.
 // What 32x64 pays once is set by launches of one round inside models, whose operands another kernel has just written: 128x2048x512 takes
-// 7.0 us on it and 8.1 on 64x64 (which 5.4 us instead of 5.0 had preferred), 128x1536x384 6.7 and 7.7, 240x2048x512 (320 tiles) 10.0 and 9.0.
+// 7.0 us on it and 8.1 on 64x64 (which 5.4 us instead of 5.0 had preferred), 128x1536x384 6.7 and 7.7, 152x4096x1024 (320 tiles)
+// 10.0 and 9.0.
 // The k order is the same for all of them, and so are the bits.
 enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x64, kTileShapes };
 // A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
