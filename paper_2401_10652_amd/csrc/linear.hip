@@ -1506,8 +1506,9 @@ static Route f32_route(const LinearArgs& g) {
   // By k and n alone, as the two kernels sum in different orders and a row's bits must not depend on the launch's rows.
   if (g.k <= 64 && g.n >= 1024) return kFma;
   // The tile of least estimated time: rounds of 256 tiles x (k / 64 steps + prologue and epilogue), plus what is paid once, in us; fitted to 172 products
-  // of 1 to 20000 rows x 4 to 8192 columns x 36 to 8192 deep, most of them no multiples of a tile, on which the choice is within 1 % of the
-  // best of the four on average and 12 % at worst (by area alone it was 11 % off on average: a row past a multiple of the large tiles had sent
+  // of 1 to 20000 rows x 4 to 8192 columns x 36 to 8192 deep, most of them no multiples of a tile.  Within 4 % the larger tile, which reads less per
+  // output: 1024 x 1536 x 512 inside a model takes 35 us on 32x64 and 37 on 32x32, 16000 x 2048 x 128 157 and 224.  The choice is 1 % off the
+  // best of the four on average and 32 % at worst (by area alone 11 % on average: a row past a multiple of the large tiles had sent
   // 777 x 512 x 512 to 16x16, 21.9 us, where 32x64 takes 12.7).
   struct Cost { int bm, bn; double step, tile, once; };
   static const Cost costs[4] = {{32, 64, 0.77, 1.9, 2.5}, {32, 32, 0.38, 0.9, 3.0}, {32, 16, 0.27, 0.5, 3.1}, {16, 16, 0.18, 0.25, 3.2}};
@@ -1518,7 +1519,7 @@ static Route f32_route(const LinearArgs& g) {
     if (!grid_fits(tiles, 256)) continue;
     const double rounds = (double)((tiles * g.batch + 255) / 256);
     const double t = rounds * ((double)((g.k + 63) / 64) * costs[c].step + costs[c].tile) + costs[c].once;
-    if (best < 0 || t < best_t) { best = c; best_t = t; }
+    if (best < 0 || t < 0.96 * best_t) { best = c; best_t = t; }
   }
   return best < 0 ? kFma : (Route)(kF32_32x64 + best);
 }

@@ -23,7 +23,7 @@ def B():
     (64, 33, 64),                    # columns that end inside a 16-byte store
     (250, 520, 2052),                # 32x32 tiles, ragged last run
     (700, 1020, 260),                # 32x32 tiles, ragged both ways
-    (1100, 2100, 100),
+    (1100, 2100, 100),               # 32x64 tiles, ragged both ways
     (204, 449, 200),                 # 32x16 tiles, ragged all ways
     (859, 65, 72),
     (745, 602, 232),                 # 32x64 tiles, ragged all ways
@@ -39,7 +39,7 @@ def test_linear_f32(B, m, n, k):
     torch.cuda.synchronize()
     check(host(out), O.linear(a, w, bias) + res, "f32")
     # a row's bits do not depend on the launch it falls in (nor on the tile shape: launches of 33 rows take 16x16)
-    tile = {(250, 520): "32x32", (700, 1020): "32x32", (1100, 2100): "32x32", (204, 449): "32x16", (859, 65): "32x16",
+    tile = {(250, 520): "32x32", (700, 1020): "32x32", (1100, 2100): "32x64", (204, 449): "32x16", (859, 65): "32x16",
             (745, 602): "32x64", (274, 929): "32x64"}.get((m, n), "16x16")
     assert B.ac_linear_kernel(m, n, k, "f32") == "f32 " + tile and B.ac_linear_kernel(min(m, 33), n, k, "f32") == "f32 16x16"
     part = torch.full((m, n), float("nan"), device="cuda")

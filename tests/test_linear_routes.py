@@ -52,6 +52,11 @@ def test_a_row_more_does_not_send_an_fp32_product_to_the_smallest_tile(m, n, k):
         assert B.ac_linear_kernel(rows, n, k, "f32") in ("f32 32x64", "f32 32x32")
 
 
+def test_near_ties_of_fp32_tiles_go_to_the_larger():
+    for m, n, k in ((1024, 1536, 512), (4000, 2048, 128), (4000, 2048, 96)):
+        assert B.ac_linear_kernel(m, n, k, "f32") == "f32 32x64"
+
+
 def test_short_fp32_sums_of_many_columns_take_one_kernel_whatever_the_rows():
     for m in (1, 100, 1000, 20000):
         assert B.ac_linear_kernel(m, 1024, 64, "f32") == "fma 64x64"
