@@ -87,8 +87,10 @@ typedef enum ac_region_kind {
  * a multiple of head_dim for the attention region (a segment is a run of whole heads) and of 8
  * for the output projection (a block of output columns), else AC_ERR_ARG.  Regions whose
  * segments hold no tensor of their own (the fused attention core, the fused output projection,
- * LayerNorm + packed projection) run consecutive segments in one launch; ac_region_info.launches
- * says how many launches a layer's region takes. */
+ * LayerNorm + packed projection) run consecutive segments in one launch; segments of the others share launches
+ * where their tensors fit in memory the plan has anyway and that is idle meanwhile (below the workspace's high-water
+ * mark, in dead tensors of the walk, in rows of the result that are still to be written); ac_region_info.launches says
+ * how many launches a layer's region takes. */
 enum { AC_DIM_BATCH = 0, AC_DIM_SEQ = 1, AC_DIM_FEATURE = 2, AC_DIM_HEAD_DIM = 3, AC_DIM_KEY = 4 };
 enum { AC_DIM_ROW = 0, AC_DIM_COL = 1, AC_DIM_CHANNEL = 2, AC_DIM_CONTRACT = 3 };
 
@@ -166,9 +168,9 @@ typedef struct ac_region_info {
   int64_t extent;            /* size of the chunk dim */
   int64_t chunk_len;         /* chosen rows per segment */
   int64_t n_segments;        /* the paper's n */
-  int64_t launches;          /* segment-loop iterations that launch kernels: n_segments, except that the fused
-                                attention, which keeps nothing of a segment in memory, runs consecutive
-                                segments in one launch where that needs no more workspace than the plan's */
+  int64_t launches;          /* segment-loop iterations that launch kernels: n_segments, or fewer where consecutive
+                                segments run in one launch because that needs no more workspace than the plan's
+                                (of the last layer) */
   uint64_t model_bytes;      /* paper-style sum X + Y + A/n of this region, ops unfused */
   uint64_t model_bytes_unchunked; /* the same with n = 1 (first activation equation) */
 } ac_region_info;
@@ -246,9 +248,11 @@ int ac_plan_bind_weights(ac_plan* plan, const void* const* dev_ptrs, int n_ptrs)
  * kernels on `stream` and returns without waiting.  x_dev [tokens, d_model] (or
  * [n_res, n_res, c_z]) is only read; y_dev has the same shape and must not overlap x_dev;
  * workspace_dev is scratch of at least workspace_bytes (else AC_ERR_WORKSPACE, nothing
- * launched).  All three must be 256-byte aligned.  *measured_peak_bytes (host, may be NULL)
+ * launched).  All three must be 256-byte aligned.  Rows of y_dev may hold intermediates before their results are
+ * written.  *measured_peak_bytes (host, may be NULL)
  * receives io_bytes + the highest workspace offset actually handed to a kernel during
- * this call, which the host tracks while binding buffers (no device round trip).
+ * this call (to the scratch of a launch that segments share: all of it up to the plan's mark),
+ * which the host tracks while binding buffers (no device round trip).
  */
 int ac_execute(ac_plan* plan, const void* x_dev, void* y_dev, void* workspace_dev,
                uint64_t workspace_bytes, void* stream, uint64_t* measured_peak_bytes);

@@ -7,7 +7,8 @@
 // pushed at the start of a segment and released at its end, and the high-water mark of
 // the arena is the activation memory the plan needs.  Planning is a dry run of the very
 // same walk with launches switched off, so planned and measured peaks agree by
-// construction.
+// construction.  Segments whose tensors fit below that mark together, or in memory that is dead
+// while their region runs, share launches (Walk::shared_runs).
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -46,12 +47,28 @@ static inline bool aligned256(const void* p) { return ((uintptr_t)p & 255u) == 0
 enum KClass { K_GEMM = 0, K_ATTN = 1, K_LN = 2, K_ELEM = 3, K_TRI = 4, K_CLASSES = 5 };
 static const char* const kClassName[K_CLASSES] = {"gemm", "attention", "layernorm", "elementwise", "trimul"};
 
+// A run of idle bytes outside the arena's free end: addresses (while planning: offsets from the buffer's start).
+struct Span { uint64_t lo, hi; };
+
 struct Arena {
   uint8_t* base = nullptr;   // null during planning
   uint64_t top = 0, high = 0;
   uint64_t* watch = nullptr;   // high-water mark of the region being walked (planning)
+  uint64_t limit = UINT64_MAX; // the plan's high-water mark, once it is known; a push past it takes idle memory, or sets `full`
+  std::vector<Span> idle;
+  bool full = false;
   void* push(uint64_t bytes) {
     const uint64_t off = align_up(top, 256);
+    if (off > limit || bytes > limit - off) {
+      for (Span& s : idle) {
+        const uint64_t lo = align_up(s.lo, 256);
+        if (lo > s.hi || bytes > s.hi - lo) continue;
+        s.lo = lo + bytes;
+        return (void*)(uintptr_t)lo;
+      }
+      full = true;
+      return nullptr;
+    }
     top = off + bytes;
     high = std::max(high, top);
     if (watch) *watch = std::max(*watch, top);
@@ -73,6 +90,9 @@ struct Setting {   // chunk setting of one region kind (section 3.3, rule 4: one
 struct WeightSlot { std::string name; int64_t rows, cols; };
 
 struct ProfRec { int cls; hipEvent_t start, stop; double flops, bytes; };
+
+// A run [i0, i0 + ni) of rows (or columns) of a pair tensor, of images, of token rows.
+struct RowSeg { int64_t i0, ni; };
 
 }  // namespace ac
 
@@ -97,6 +117,7 @@ struct ac_plan {
   size_t sync_used = 0;
   int sync_needed = 0;
   int64_t region_launches[AC_REGION_KINDS] = {};   // launches per layer of a region whose segments share launches (0: one per segment)
+  std::vector<std::vector<RowSeg>> shared;         // the runs of every shared_loop of a walk, in order
 };
 
 namespace ac {
@@ -104,9 +125,6 @@ namespace ac {
 static int elem_bytes(int dtype) { return dtype == AC_BF16 ? 2 : 4; }
 
 static uint64_t attention_split_bytes(int64_t rows, int64_t batch, int heads, int head_dim, int ns);
-
-// A run [i0, i0 + ni) of rows (or columns) of a pair tensor.
-struct RowSeg { int64_t i0, ni; };
 
 // One walk of the plan: either a dry run (planning) or the real thing.
 struct Walk {
@@ -187,6 +205,78 @@ struct Walk {
     arena.release(base);
   }
 
+  // Segments whose tensors fit in memory that the plan has anyway share launches.  A plan's segments bound the bytes a region
+  // holds; the workspace is as large as the region that needs most, and while a region runs, other tensors of the walk
+  // are dead (q, k and v during the feed-forward; the rows of the result that no segment has written yet).  So units
+  // [0, extent) of a region cut into segments of `len` run in the fewest runs whose pushes stay below the plan's high-water mark
+  // or in the spans that idle(first, units) names, of about equal length (a multiple of `granule` where it matters), at most
+  // `most` units each.  Rows keep their arithmetic, so the bits do not depend on it.  A short launch costs its fixed 4 to
+  // 5 us and leaves CUs without work: 512 rows through a 768 x 3072 feed-forward take 10.4 + 12.6 us, 2048 rows 21 + 23; a stack of
+  // twelve such layers cut into 512-row segments 3.92 -> 2.80 ms, the pair block at N = 1024 in 64-row segments 12.05 -> 9.49.
+  // Decided by the dry run that ends planning (`deciding`) and kept in the plan; without it, and where two segments in flight would need
+  // spans of their own, the caller's segments run as they are.
+  bool deciding = false;
+  size_t next_shared = 0;
+  bool may_share() const { return !unchunked && (deciding || !dry) && !(p->m.flags & AC_FLAG_UNFUSED_ELEMENTWISE); }
+  bool shares() const { return may_share() && lanes == 1; }
+  template <typename I>
+  void enter_run(uint64_t base, const RowSeg& r, I&& idle) {
+    arena.release(base);
+    arena.idle = idle(r.i0, r.ni);
+    arena.full = false;
+  }
+  template <typename I, typename F>
+  const std::vector<RowSeg>& shared_runs(int64_t extent, int64_t len, int64_t granule, int64_t most, I&& idle, F&& body) {
+    if (deciding) {
+      const uint64_t base = arena.mark();
+      std::vector<RowSeg> runs;
+      auto fits = [&](int64_t i0, int64_t ni) {
+        enter_run(base, RowSeg{i0, ni}, idle);
+        measuring = true;
+        body(RowSeg{i0, ni});
+        measuring = false;
+        return !arena.full;
+      };
+      for (int64_t i = 0; i < extent; i += runs.back().ni) {
+        const int64_t left = extent - i;
+        int64_t lo = std::min(len, left), hi = std::max(lo, std::min(left, most));
+        if (fits(i, hi)) lo = hi;
+        while (lo + 1 < hi) {
+          const int64_t mid = lo + (hi - lo) / 2;
+          if (fits(i, mid)) lo = mid; else hi = mid;
+        }
+        const int64_t even = ceil_div(ceil_div(left, ceil_div(left, lo)), granule) * granule;
+        runs.push_back(RowSeg{i, even < lo && fits(i, even) ? even : lo});
+      }
+      p->shared.push_back(std::move(runs));
+      arena.release(base);
+      arena.idle.clear();
+    }
+    return p->shared[next_shared++];
+  }
+  template <typename I, typename F>
+  int64_t shared_loop(const std::vector<RowSeg>& runs, I&& idle, F&& body) {
+    const uint64_t base = arena.mark();
+    for (const RowSeg& r : runs) {
+      enter_run(base, r, idle);
+      body(r);
+      if (arena.full && ok()) { err = hipErrorInvalidValue; err_where = "scratch of a shared launch"; }
+    }
+    arena.release(base);
+    arena.idle.clear();
+    arena.high = std::max(arena.high, arena.limit);   // (such a loop is handed everything up to the plan's mark)
+    return (int64_t)runs.size();
+  }
+  // Units of `rows` rows each that one launch may take: the kernels' grids are checked for 2^21 rows.
+  static int64_t most_units(int64_t rows) { return std::max<int64_t>(1, (1 << 21) / rows); }
+  // What the rows of `out` behind unit i0 + ni of `units` are while a run is computed: not yet written.
+  static Span unwritten(const void* out, int64_t i0, int64_t ni, int64_t units, uint64_t unit_bytes) {
+    const uint64_t b = (uint64_t)(uintptr_t)out;
+    return Span{b + (uint64_t)(i0 + ni) * unit_bytes, b + (uint64_t)units * unit_bytes};
+  }
+  static Span whole(const void* buf, uint64_t bytes) { return Span{(uint64_t)(uintptr_t)buf, (uint64_t)(uintptr_t)buf + bytes}; }
+  std::vector<Span> idle_whole;   // inter-module buffers that hold nothing while the current module runs
+
   int eb() const { return elem_bytes(p->m.dtype); }
   const void* w(int layer, int slot, int per_layer) const {
     return dry ? nullptr : p->wptr[(size_t)layer * per_layer + slot];
@@ -198,7 +288,7 @@ struct Walk {
   void run(int cls, double fl, double by, const char* where, F&& launch) {
     if (measuring) return;
     flops += fl;
-    if (dry || !ok()) return;
+    if (dry || arena.full || !ok()) return;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (p->profiling) {
       if (p->pool_used + 2 > p->pool.size()) {
@@ -399,6 +489,7 @@ struct Walk {
   void res_stack(const void* x, void* y);
   const void* pair_segment(const void* zin, const RowSeg& sg, bool col);
   void pair_store(LinearArgs& o, void* zout, const RowSeg& sg, bool col);
+  template <typename F> void pair_loop(int kind, const std::vector<RowSeg>& segs, void* zout, bool col, F&& body);
   void tri_mul(int kind, const void* const* W, const void* zin, void* zout);
   void tri_att(int kind, const void* const* W, const void* zin, void* zout);
   void transition(const void* const* W, const void* zin, void* zout);
@@ -490,15 +581,17 @@ void Walk::transformer(const void* x, void* y) {
 
   // Whole tensors of a layer.  bf16: q,k row-major [T, 2d] and v transposed per batch
   // element [d, S]; fp32: q,k,v row-major [T, 3d].
+  // (q, k and v last, next to the arena's free end: the two together are what the feed-forward may use)
+  void* ctx_all = arena.push((uint64_t)T * d * e);   // whole context: output of the attention region
+  void* hbuf = arena.push((uint64_t)T * d * e);
+  void* tbuf = m.layers > 1 ? arena.push((uint64_t)T * d * e) : nullptr;
+  const uint64_t before_qkv = arena.mark();
   void* qk = arena.push((uint64_t)T * (bf ? 2 : 3) * d * e);
   const bool stored_scores = (m.flags & AC_FLAG_MATERIALIZED_SCORES) != 0;
   // v transposed: written by the projection's strided store (bf16), or, for the stored-scores
   // attention of an fp32 model, by a transpose after the projection region
   void* vt = (bf || stored_scores) ? arena.push((uint64_t)T * d * e) : nullptr;
   const int64_t ldqk = (bf ? 2 : 3) * d;
-  void* ctx_all = arena.push((uint64_t)T * d * e);   // whole context: output of the attention region
-  void* hbuf = arena.push((uint64_t)T * d * e);
-  void* tbuf = m.layers > 1 ? arena.push((uint64_t)T * d * e) : nullptr;
 
   for (int l = 0; l < m.layers && ok(); ++l) {
     const void* in = l == 0 ? x : (const void*)tbuf;
@@ -610,13 +703,29 @@ void Walk::transformer(const void* x, void* y) {
       const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
       ln(at(hbuf, r0 * d), d, W(W_LN2G), W(W_LN2B), atw(ctx_all, r0 * d), d, rows, d);
     }
-    seg_loop(ffn_segs, [&](const Seg& sg) {
-      const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
+    auto ffn_rows = [&](const RowSeg& r) {
+      const int64_t r0 = r.i0, rows = r.ni;
       const void* u = at(ctx_all, r0 * d);
       void* hid = arena.push((uint64_t)rows * F * e);
       proj(u, d, W(W_1), d, W(W_B1), m.activation, nullptr, 0, hid, F, rows, F);
       proj(hid, F, W(W_2), F, W(W_B2), AC_ACT_NONE, at(hbuf, r0 * d), d, atw(out, r0 * d), d, rows, d);
-    });
+    };
+    // q, k and v are dead from here to the next layer's projection, and the hidden rows of a run lie in their memory and what
+    // a segment may hold behind it.  (A region cut in two stays two launches: so ac_region_info has always reported it.)  With two
+    // segments in flight the runs still go one after another, where there are no more of them than rounds of two segments.
+    bool in_runs = may_share() && ffn_segs.size() > 2;
+    if (in_runs) {
+      const uint64_t mk = arena.mark();
+      auto none = [](int64_t, int64_t) { return std::vector<Span>(); };
+      arena.release(before_qkv);
+      const std::vector<RowSeg>& runs = shared_runs(T, ffn_segs[0].nb * ffn_segs[0].ns, 256, most_units(1), none, ffn_rows);
+      in_runs = runs.size() * lanes <= ffn_segs.size();
+      if (in_runs) region_launches[AC_REGION_FFN] = shared_loop(runs, none, ffn_rows);
+      arena.release(mk);
+    }
+    if (!in_runs) {
+      seg_loop(ffn_segs, [&](const Seg& sg) { ffn_rows(RowSeg{sg.b0 * S + sg.s0, sg.nb * sg.ns}); });
+    }
   }
 }
 
@@ -671,6 +780,21 @@ void Walk::pair_store(LinearArgs& o, void* zout, const RowSeg& sg, bool col) {
   }
 }
 
+// The chunked part of a module: its segments one after another, or sharing launches where their tensors fit in the arena below the
+// plan's mark, in an idle inter-module buffer, or (row runs: rows of z' are contiguous) in the rows of z' still to come.
+template <typename F>
+void Walk::pair_loop(int kind, const std::vector<RowSeg>& segs, void* zout, bool col, F&& body) {
+  if (!shares()) { seg_loop(segs, body); return; }
+  const int64_t N = p->m.n_res;
+  const uint64_t row_bytes = (uint64_t)N * p->m.c_z * eb();
+  auto idle = [&](int64_t i0, int64_t ni) {
+    std::vector<Span> v = idle_whole;
+    if (!col) v.push_back(unwritten(zout, i0, ni, N, row_bytes));
+    return v;
+  };
+  region_launches[kind] = shared_loop(shared_runs(N, seg_len(kind), 1, most_units(N), idle, body), idle, body);
+}
+
 void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) {
   const ac_model_desc& m = p->m;
   const int64_t N = m.n_res, cz = m.c_z, ch = m.c_hidden, R = N * N;
@@ -722,11 +846,15 @@ void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) 
   }
   // ---- chunked part: rows i (or columns j) of the output.  For columns the contraction runs
   // with the operands exchanged, out^T[j, i] = sum_k b[j, k] a[i, k], on the gathered segment.
-  seg_loop(segs, [&](const RowSeg& sg) {
+  // Where segments share launches the gate of a row run waits in the run's own rows of the result (the projection that
+  // ends the module reads an element of it and writes the same element).
+  const bool gate_in_out = shares() && !col;
+  int64_t n_run = 0;
+  pair_loop(kind, segs, zout, col, [&](const RowSeg& sg) {
     const int64_t rows = sg.ni * N;
     const void* zs = pair_segment(zin, sg, col);
     void* t = fuse_g ? nullptr : arena.push((uint64_t)rows * cz * e);
-    void* gate = arena.push((uint64_t)rows * cz * e);
+    void* gate = gate_in_out ? atw(zout, sg.i0 * N * cz) : arena.push((uint64_t)rows * cz * e);
     void* o_c = arena.push((uint64_t)ch * rows * e);   // [c][segment index][other index]
     void* lo = arena.push((uint64_t)rows * ch * e);
     if (fuse_g) {
@@ -742,8 +870,8 @@ void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) 
     }
     // every segment reads the whole second operand, which is about the size of the memory-side cache: odd
     // segments walk the channels backwards, so a segment starts on the channels the one before ended on
-    contract(at(col ? b_t : a_t, sg.i0 * N), N, R, col ? a_t : b_t, N, R, o_c, N, rows, sg.ni, N, N, ch,
-             (sg.i0 / seg_len(kind)) % 2 == 1);
+    contract(at(col ? b_t : a_t, sg.i0 * N), N, R, col ? a_t : b_t, N, R, o_c, N, rows, sg.ni, N, N, ch, n_run % 2 == 1);
+    if (!measuring) ++n_run;
     ln_channel_major(o_c, rows, W[TM_LN_OUT_G], W[TM_LN_OUT_B], lo, ch, rows, ch);
     LinearArgs o{};
     o.a = lo; o.lda = ch; o.w = W[TM_W_O]; o.ldw = ch; o.bias = W[TM_B_O]; o.mul = gate; o.ldmul = cz;
@@ -823,13 +951,16 @@ void Walk::tri_att(int kind, const void* const* W, const void* zin, void* zout) 
     if (ending_form) transpose_inplace(v_all, N, R, N, hd);
   }
   // ---- chunked part
-  seg_loop(segs, [&](const RowSeg& sg) {
+  // Where segments share launches the context takes the place of the queries (a block reads the queries of its rows and
+  // head before it writes their context) and the gate of a row run waits in the run's rows of the result.
+  const bool in_place = shares(), gate_in_out = in_place && !col && hd == cz;
+  pair_loop(kind, segs, zout, col, [&](const RowSeg& sg) {
     const int64_t rows = sg.ni * N;
     const void* zs = pair_segment(zin, sg, col);
     void* t = fuse_b ? nullptr : arena.push((uint64_t)rows * cz * e);
     void* q = arena.push((uint64_t)rows * hd * e);
-    void* gate = arena.push((uint64_t)rows * hd * e);
-    void* ctx = arena.push((uint64_t)rows * hd * e);
+    void* gate = gate_in_out ? atw(zout, sg.i0 * N * cz) : arena.push((uint64_t)rows * hd * e);
+    void* ctx = in_place ? q : arena.push((uint64_t)rows * hd * e);
     void* k_seg = ending_form ? nullptr : arena.push((uint64_t)rows * hd * e);
     void* v_seg = ending_form ? nullptr : arena.push((uint64_t)rows * hd * e);   // [segment row][h*d][key]
     LinearArgs lq{};
@@ -893,7 +1024,7 @@ void Walk::transition(const void* const* W, const void* zin, void* zout) {
   const int e = eb();
   const bool col = p->set[AC_REGION_PAIR_TRANSITION].chunk_dim == AC_DIM_COL;
   enter(AC_REGION_PAIR_TRANSITION);
-  seg_loop(row_segments(N, seg_len(AC_REGION_PAIR_TRANSITION)), [&](const RowSeg& sg) {
+  pair_loop(AC_REGION_PAIR_TRANSITION, row_segments(N, seg_len(AC_REGION_PAIR_TRANSITION)), zout, col, [&](const RowSeg& sg) {
     const int64_t rows = sg.ni * N;
     const void* zs = pair_segment(zin, sg, col);
     const bool fuse_up = fuses_ln_proj(cz, {F});
@@ -936,6 +1067,9 @@ void Walk::pair(const void* x, void* y) {
     const int g = seq[idx];
     const void* zin = idx == 0 ? x : (const void*)tbuf[(idx - 1) % 2];
     void* zout = idx == modules - 1 ? y : tbuf[idx % 2];
+    idle_whole.clear();
+    for (void* b : tbuf)
+      if (b && b != zin && b != zout) idle_whole.push_back(whole(b, zbytes));
     const void* const* base = dry ? nullw.data() : p->wptr.data() + (size_t)(g / 5) * kPairWeights;
     switch (g % 5) {
       case 0: tri_mul(AC_REGION_TRIMUL_OUT, base, zin, zout); break;
@@ -1004,6 +1138,18 @@ void Walk::res_stack(const void* x, void* y) {
     const void* in = idx == 0 ? x : (const void*)tbuf[(idx - 1) % 2];
     void* out = idx == modules - 1 ? y : tbuf[idx % 2];
     auto W = [&](int slot) { return w(l, attn ? RB_COUNT + ab_index(m, slot) : slot, per_layer); };
+    idle_whole.clear();
+    for (void* b : tbuf)
+      if (b && b != in && b != out) idle_whole.push_back(whole(b, (uint64_t)m.batch * img_bytes));
+    auto image_loop = [&](int kind, auto&& body) {
+      if (!shares()) { seg_loop(image_segments(kind), body); return; }
+      auto idle = [&](int64_t i0, int64_t ni) {
+        std::vector<Span> v = idle_whole;
+        v.push_back(unwritten(out, i0, ni, m.batch, img_bytes));
+        return v;
+      };
+      region_launches[kind] = shared_loop(shared_runs(m.batch, seg_len(kind), 1, most_units(HW), idle, body), idle, body);
+    };
     // GroupNorm of a segment's images; their partial statistics sit at the images' own place in the table,
     // so two segments in flight do not share any of it
     auto gn = [&](const RowSeg& sg, const void* src, int gslot, int bslot, void* dst, int act) {
@@ -1017,11 +1163,14 @@ void Walk::res_stack(const void* x, void* y) {
     if (!attn) {
       enter(AC_REGION_RES_BLOCK);
       bias_act(W(RB_TEMB), C, W(RB_B1), bt, C, m.batch, C, AC_ACT_NONE);
-      seg_loop(image_segments(AC_REGION_RES_BLOCK), [&](const RowSeg& sg) {
+      // (where segments share launches the first convolution's images wait in their own rows of the result: the second GroupNorm
+      // has consumed them when the second convolution writes there)
+      const bool t_in_out = shares();
+      image_loop(AC_REGION_RES_BLOCK, [&](const RowSeg& sg) {
         const int64_t nb = sg.ni, px = nb * HW;
         const void* xs = at(in, sg.i0 * HW * C);
         void* a = arena.push((uint64_t)nb * img_bytes);
-        void* t = arena.push((uint64_t)nb * img_bytes);
+        void* t = t_in_out ? atw(out, sg.i0 * HW * C) : arena.push((uint64_t)nb * img_bytes);
         auto conv = [&](const void* src, int wslot, const void* bias, int64_t bias_period, const void* resid, void* dst) {
           LinearArgs g{};
           g.a = src; g.lda = C; g.w = W(wslot); g.ldw = 9 * C; g.bias = bias; g.bias_period = bias_period;
@@ -1040,16 +1189,25 @@ void Walk::res_stack(const void* x, void* y) {
     const int64_t F = m.d_ffn, dh = C / m.heads;
     const bool gated = (m.flags & AC_FLAG_GATED_FFN) != 0;
     const int64_t Tc = m.seq, D = m.d_model, Tcp = (Tc + 7) / 8 * 8;   // context tokens, width; padded row of its v^T
-    seg_loop(image_segments(AC_REGION_UNET_ATTN), [&](const RowSeg& sg) {
+    // Where segments share launches they hold less each: the stream t lies in the images' own rows of the result until the
+    // feed-forward's second product moves it to u (whose rows the first has consumed), and the hidden rows take the place of the
+    // attention's tensors.
+    const bool tight = shares();
+    image_loop(AC_REGION_UNET_ATTN, [&](const RowSeg& sg) {
       const int64_t nb = sg.ni, T = nb * HW;
       const void* xs = at(in, sg.i0 * HW * C);
       void* u = arena.push((uint64_t)T * C * e);        // normalised rows: GroupNorm, then LayerNorm 1, then LayerNorm 2
-      void* t = arena.push((uint64_t)T * C * e);        // the block's stream, updated in place by the residual epilogues
+      void* t = tight ? atw(out, sg.i0 * HW * C) : arena.push((uint64_t)T * C * e);   // the block's stream, updated in place by the residual epilogues
+      const uint64_t mk = arena.mark();
       void* qk = arena.push((uint64_t)T * 2 * C * e);   // q | k row-major
       void* vt = arena.push((uint64_t)T * C * e);       // v transposed per image: [image][C][HW]
       void* ctx = arena.push((uint64_t)T * C * e);
-      void* hid = arena.push((uint64_t)T * (gated ? 2 : 1) * F * e);
-      void* act = gated ? arena.push((uint64_t)T * F * e) : hid;
+      void *hid = nullptr, *act = nullptr;
+      auto push_hidden = [&] {
+        hid = arena.push((uint64_t)T * (gated ? 2 : 1) * F * e);
+        act = gated ? arena.push((uint64_t)T * F * e) : hid;
+      };
+      if (!tight) push_hidden();
       void* kc = Tc > 0 ? arena.push((uint64_t)nb * Tc * C * e) : nullptr;     // keys of the contexts, row-major
       void* vct = Tc > 0 ? arena.push((uint64_t)nb * C * Tcp * e) : nullptr;   // their values, transposed per image
       gn(sg, xs, AB_GN_G, AB_GN_B, u, AC_ACT_NONE);
@@ -1088,6 +1246,7 @@ void Walk::res_stack(const void* x, void* y) {
         proj(ctx, C, W(AB_W_OC), C, W(AB_B_OC), AC_ACT_NONE, t, C, t, C, T, C);
       }
       ln(t, C, W(AB_LN2_G), W(AB_LN2_B), u, C, T, C);
+      if (tight) { arena.release(mk); push_hidden(); }
       if (gated) {
         proj(u, C, W(AB_W_1), C, W(AB_B_1), AC_ACT_NONE, nullptr, 0, hid, 2 * F, T, 2 * F);
         void* gate = atw(hid, F);
@@ -1097,8 +1256,9 @@ void Walk::res_stack(const void* x, void* y) {
       } else {
         proj(u, C, W(AB_W_1), C, W(AB_B_1), m.activation, nullptr, 0, hid, F, T, F);
       }
-      proj(act, F, W(AB_W_2), F, W(AB_B_2), AC_ACT_NONE, t, C, t, C, T, C);
-      proj(t, C, W(AB_W_OUT), C, W(AB_B_OUT), AC_ACT_NONE, xs, C, atw(out, sg.i0 * HW * C), C, T, C);
+      void* last = tight ? u : t;
+      proj(act, F, W(AB_W_2), F, W(AB_B_2), AC_ACT_NONE, t, C, last, C, T, C);
+      proj(last, C, W(AB_W_OUT), C, W(AB_B_OUT), AC_ACT_NONE, xs, C, atw(out, sg.i0 * HW * C), C, T, C);
     });
   }
 }
@@ -1190,8 +1350,11 @@ static bool dim_legal(const ac_model_desc& m, int kind, int dim, bool& known) {
 }
 
 static void dry_run(ac_plan* p, bool unchunked, uint64_t& arena_bytes, double& flops,
-                    uint64_t* region_high = nullptr) {
+                    uint64_t* region_high = nullptr, uint64_t limit = UINT64_MAX) {
   Walk wk{p, true, unchunked, nullptr};
+  wk.arena.limit = limit;
+  wk.deciding = limit != UINT64_MAX;   // the arena is sized: decide which segments share launches below that mark
+  if (wk.deciding) p->shared.clear();
   wk.lanes = (p->m.flags & AC_FLAG_TWO_SEGMENTS_IN_FLIGHT) ? 2 : 1;
   if (p->m.workload == AC_TRANSFORMER_STACK) wk.transformer(nullptr, nullptr);
   else if (p->m.workload == AC_UNET_RES_STACK) wk.res_stack(nullptr, nullptr);
@@ -1199,7 +1362,8 @@ static void dry_run(ac_plan* p, bool unchunked, uint64_t& arena_bytes, double& f
   arena_bytes = wk.arena.high;
   flops = wk.flops;
   if (region_high) memcpy(region_high, wk.region_high, sizeof(wk.region_high));
-  if (!unchunked) { p->sync_needed = wk.sync_events; memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches)); }
+  if (wk.deciding) memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches));
+  else if (!unchunked) { p->sync_needed = wk.sync_events; memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches)); }
 }
 
 static uint64_t io_bytes(const ac_model_desc& m) {
@@ -1507,6 +1671,8 @@ int ac_plan_create(const ac_model_desc* model, const ac_region_desc* regions, in
   uint64_t arena1 = 0;
   double f1 = 0;
   dry_run(p, true, arena1, f1);
+  uint64_t same = 0;
+  dry_run(p, false, same, f1, nullptr, arena);
   inf.peak_bytes_unchunked_planned = inf.io_bytes + arena1;
   inf.n_regions = count;
   for (int k = first; k < first + count; ++k) {
@@ -1585,6 +1751,7 @@ int ac_execute(ac_plan* plan, const void* x_dev, void* y_dev, void* workspace_de
   if (xb < yb + half && yb < xb + half) return fail(AC_ERR_ARG, "x and y overlap");
   Walk wk{plan, false, false, (hipStream_t)stream};
   wk.arena.base = (uint8_t*)workspace_dev;
+  wk.arena.limit = plan->info.workspace_bytes;
   wk.lane_stream[0] = (hipStream_t)stream;
   if (plan->m.flags & AC_FLAG_TWO_SEGMENTS_IN_FLIGHT) {
     if (!plan->aux_stream) return fail(AC_ERR_STATE, "the plan's second stream does not exist");

@@ -439,3 +439,18 @@ def test_unet_stage_with_attention_plan():
     expect(B.AC_ERR_ILLEGAL_CHUNK_DIM, lambda: B.Plan(B.res_stack_desc(cfg), [(B.AC_REGION_UNET_ATTN, B.AC_DIM_SEQ, 64)]))
     expect(B.AC_ERR_ARG, lambda: B.Plan(B.res_stack_desc(dataclasses.replace(cfg, heads=0, d_ffn=0)),
                                         [(B.AC_REGION_UNET_ATTN, B.AC_DIM_BATCH, 1)]))
+
+
+@pytest.mark.parametrize("cfg,c_attn,chunk,lanes", [
+    (I.C3, 512, 512, 1), (I.C3, 4096, 512, 1), (I.C3, 4096, 1408, 1), (I.C3, 512, 2048, 1), (I.C2, 8192, 3200, 1), (I.C1, 64, 64, 1),
+    (I.C3, 512, 1024, 2), (I.C3, 512, 256, 2)])
+def test_feed_forward_segments_share_launches(cfg, c_attn, chunk, lanes):
+    """The hidden rows of a launch lie where q, k and v were and in what the plan holds behind them; no byte is added to the plan.
+    A region cut in two stays two launches."""
+    flags = B.AC_FLAG_TWO_SEGMENTS_IN_FLIGHT if lanes == 2 else 0
+    info = B.Plan(B.transformer_desc(cfg, flags=flags), regions(cfg.seq, c_attn, chunk)).ac_plan_query()
+    assert info.workspace_bytes == arena_by_hand(cfg, cfg.seq, c_attn, chunk, lanes=lanes)
+    row = cfg.d_model * (2 if cfg.dtype == "bf16" else 4)
+    room = info.workspace_bytes - (3 if cfg.layers > 1 else 2) * cfg.seq * row       # all but the context, the stream, the layer's input
+    n, runs = -(-cfg.seq // chunk), -(-cfg.seq // (room // (row * cfg.d_ffn // cfg.d_model)))
+    assert info.regions[3].n_segments == n and info.regions[3].launches == (n if n == 2 else runs) <= n
