@@ -280,24 +280,25 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
 constexpr int kQB = 128;   // query rows per block of the 4-wave kernel (32 per wave)
 constexpr int kKB = 64;    // keys per LDS tile
 
-// Which instantiations run the software-pipelined loop with direct global-to-LDS staging: no bias tile to
-// stage, whole key tiles only (a direct load cannot zero-fill), heads of 64 or 128.  The loop needs two
-// score tiles in registers, which leaves two waves per SIMD where the plain loop has three at 64-wide
-// heads; a causal launch at that width (many short blocks, three per CU co-resident) measured faster plain.
-constexpr bool attention_pipelined(int dh, bool causal, bool bias, bool ragged) {
-  return !bias && !ragged && (dh == 128 || (dh == 64 && !causal));
-}
-constexpr size_t attention_lds_bytes(int dh, bool causal, bool bias, bool ragged, int nw) {
-  return attention_pipelined(dh, causal, bias, ragged)
+// Key counts: whole tiles, whole 16-byte chunks of V^T (the last tile's chunks past the end are zeros), or any.
+enum Keys { kWholeTiles, kWholeChunks, kAnyKeys };
+
+// Which instantiations run the software-pipelined loop with direct global-to-LDS staging: no bias tile to stage, keys in whole
+// chunks (a direct load can zero 16 bytes, not fewer), heads of 64 or 128.  (It needs two score tiles in registers, which leaves two
+// waves per SIMD where the plain loop has three at 64-wide heads, and is ahead all the same: 8192 causal, 16 heads of 64, 190 us
+// plain and 176 pipelined, two problems of 2048 33 and 26.)
+constexpr bool attention_pipelined(int dh, bool bias, Keys keys) { return !bias && keys != kAnyKeys && dh >= 64; }
+constexpr size_t attention_lds_bytes(int dh, bool bias, Keys keys, int nw) {
+  return attention_pipelined(dh, bias, keys)
              ? (size_t)2 * 1040 * (kKB * dh * 2 / 1024 + dh * kKB * 2 / 1024)
              : ((size_t)2 * (kKB * (dh + 8) + dh * (kKB + 8)) + (bias ? 32 * nw * (kKB + 4) : 0)) * sizeof(bf16_t);
 }
 
-// RAGGED: the key count is not a multiple of the tile (or of the 16-byte vector): loads are
-// guarded and keys past the end are masked.  The other instantiation has no bounds work in
-// its main loop.
-template <int DH, bool CAUSAL, bool BIAS, bool RAGGED, int NW>
-__global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS, RAGGED) ? 2 : 1) attention_mfma_bf16(AttnArgs a) {
+// KEYS: beyond whole tiles, loads of the last tile are guarded and keys past the end are masked; whole tiles have no bounds
+// work in their main loop.
+template <int DH, bool CAUSAL, bool BIAS, Keys KEYS, int NW>
+__global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ? 2 : 1) attention_mfma_bf16(AttnArgs a) {
+  constexpr bool RAGGED = KEYS != kWholeTiles;
   constexpr int NT = 64 * NW;         // threads
   constexpr int QB = 32 * NW;         // query rows per block
   constexpr int KROW = DH + 8;        // padded K row (elements): conflict-free 128-bit reads
@@ -307,7 +308,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
   constexpr int K_CHUNKS = kKB * (DH / 8) / NT;   // 16-byte chunks per thread, K tile
   constexpr int V_CHUNKS = DH * (kKB / 8) / NT;   // and V^T tile
   static_assert(K_CHUNKS >= 1 && V_CHUNKS >= 1, "tile too small for the block");
-  constexpr bool PIPE = attention_pipelined(DH, CAUSAL, BIAS, RAGGED);
+  constexpr bool PIPE = attention_pipelined(DH, BIAS, KEYS);
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);     // [2][kKB][KROW]
   bf16_t* sV = sK + 2 * kKB * KROW;                      // [2][DH][VROW]
@@ -392,6 +393,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
   wave_last += q_offset;
   const int wave_first = q_offset + q0 + wave * 32;
   const bool wave_active = q0 + wave * 32 < sq;   // waves past the last query row only help staging
+  const int keys_seen = CAUSAL && qpos < sk ? qpos + 1 : sk;   // by this lane's query
 
   // staging: which chunks of a K tile / V^T tile this thread moves.  A V^T chunk (8 keys of
   // one d row) is stored as two 8-byte halves, permuted inside its 16-key group to the slot
@@ -498,9 +500,31 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
   for (int i = 0; i < DT; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_o[i][r] = 0.f;
-  // running maximum (of scale2 * score [+ bias]) and sum, both in the log2 domain
+  // Reference of a row's exponents (log2 domain) and the sum of its probabilities so far.  The reference is the largest score of
+  // the first tile in which the row sees a key, and follows the running maximum only where that has grown by more than 2^kLag:
+  // probabilities up to there lose nothing in bf16 or fp32, the sums stay below 2^127, and a tile is spared the exchange
+  // between the half-waves and, while any of the wave's 32 rows still finds new maxima (most tiles of a few thousand keys), the
+  // rescaling of its accumulators.  A row's reference depends on its own scores alone.  (16384 causal, 16 heads of 128: 1122 -> 1033 us;
+  // 4096, 8 heads of 128: 80.1 -> 72.7; 4096, 12 heads of 64: 78.5 -> 70.1; 8192 causal, 16 heads of 64, plain loop: 203 -> 190.)
   float m_run = -INFINITY, l_run = 0.f;
+  float m_exp = 0.f;   // m_run, or 0 while the row has seen no key: exp2(-inf - m_exp) is then 0, not NaN
+  constexpr float kLag = 40.f;
   const float scale2 = rsqrtf((float)DH) * kLog2e;
+  const float unit = BIAS ? 1.f : scale2;                // of the scores a tile is left with: a bias is added in the log2 domain
+  // the reference against a tile's largest score per lane
+  auto new_max = [&](float mx) {
+    if (__builtin_amdgcn_ballot_w64(mx * unit > m_run + kLag) == 0) return;   // (a row that has seen no key: -inf + kLag)
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * unit;                            // unit > 0: max commutes with the scaling
+    const bool up = mx > m_run + kLag;
+    const float alpha = !up ? 1.f : m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mx);
+    m_run = up ? mx : m_run;
+    m_exp = m_run == -INFINITY ? 0.f : m_run;
+    l_run *= alpha;
+#pragma unroll
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc_o[i][r] *= alpha;
+  };
 
   if constexpr (!PIPE) {
     if (tile_lo < tile_hi) { load_tile(tile_lo * kKB); store_tile(tile_lo & 1, tile_lo * kKB); }
@@ -527,7 +551,8 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
           }
         }
         // ---- lane holds keys k0 + tt*32 + 8*(r/4) + 4*half + r%4.  Scores go to the log2 domain
-        // only where needed: with a bias right away, otherwise folded into the exponent below.
+        // only where needed: with a bias right away (so that equal biases of any size, as masks are, differ by exactly zero),
+        // otherwise folded into the exponent below.
         if (BIAS) {
           const bf16_t* cb = sB + (wave * 32 + l32) * BROW + 4 * half;
   #pragma unroll
@@ -536,46 +561,31 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
             for (int g4 = 0; g4 < 4; ++g4) {
               const bf16x4 bb = *reinterpret_cast<const bf16x4*>(cb + tt * 32 + 8 * g4);
   #pragma unroll
-              for (int j = 0; j < 4; ++j)
-                acc_s[tt][4 * g4 + j] = fmaf(acc_s[tt][4 * g4 + j], scale2, bf2f(bb[j]) * kLog2e);
+              for (int j = 0; j < 4; ++j) acc_s[tt][4 * g4 + j] = fmaf(acc_s[tt][4 * g4 + j], scale2, bf2f(bb[j]) * kLog2e);
             }
         }
         const bool need_mask = (RAGGED && k0 + kKB > sk) || (CAUSAL && k0 + kKB - 1 > wave_first);
         if (need_mask) {
+          const int seen = keys_seen - k0 - 4 * half;
   #pragma unroll
           for (int tt = 0; tt < 2; ++tt)
   #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int kj = k0 + tt * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-              if ((RAGGED && kj >= sk) || (CAUSAL && kj > qpos)) acc_s[tt][r] = -INFINITY;
-            }
+            for (int r = 0; r < 16; ++r)
+              if (tt * 32 + 8 * (r / 4) + (r % 4) >= seen) acc_s[tt][r] = -INFINITY;
         }
         float mx = acc_s[0][0];
   #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
   #pragma unroll
           for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc_s[tt][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        if (!BIAS) mx *= scale2;                       // scale2 > 0: max commutes with the scaling
-        // rescale only when some row of the wave saw a new maximum
-        if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
-          const float m_new = fmaxf(m_run, mx);
-          const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-          m_run = m_new;
-          l_run *= alpha;
-  #pragma unroll
-          for (int i = 0; i < DT; ++i)
-  #pragma unroll
-            for (int r = 0; r < 16; ++r) acc_o[i][r] *= alpha;
-        }
+        new_max(mx);
         float psum = 0.f;
         bf16x8 pf[2][2];
   #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
   #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float e = BIAS ? acc_s[tt][r] - m_run : fmaf(acc_s[tt][r], scale2, -m_run);
-            const float p = __builtin_amdgcn_exp2f(e);
+            const float p = __builtin_amdgcn_exp2f(BIAS ? acc_s[tt][r] - m_exp : fmaf(acc_s[tt][r], scale2, -m_exp));
             psum += p;
             pf[tt][r / 8][r % 8] = f2bf(p);
           }
@@ -639,22 +649,33 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
     };
     const unsigned char* const kg_base = uniform(kbase);
     const unsigned char* const vg_base = uniform(vbase);
-    // (buffer loads: base and row offset in scalar registers, 32 bits per lane)
+    // (buffer loads: base and row offset in scalar registers, 32 bits per lane.  A lane of the last tile whose key or chunk of keys
+    // lies past the end asks for an offset past the buffer's range, for which the hardware delivers zeros and touches no memory.)
+    constexpr uint32_t kPastRange = 0x80000000u;
     auto dma = [&](const unsigned char* src, uint32_t lane_off, uint32_t row_off, unsigned char* dst) {
-      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src), 0, -1, 0x00027000);
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src), 0, RAGGED ? 0x7fffffff : -1, 0x00027000);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, lane_off, row_off, 0, 0);
     };
+    // (the last tile's comparisons on an opaque copy of the lane: hoisted, they would hold registers that the loop does not have)
     auto dma_k = [&](int kt, int buf) {
       const unsigned char* src = kg_base + (int64_t)kt * kKB * a.ldk * 2;
+      const bool last = RAGGED && (kt + 1) * kKB > sk;
+      int ln = lane;
+      if (last) asm volatile("" : "+v"(ln));
+      const int past = last ? sk - kt * kKB - swap23((ln / (KRB / 16)) * KG + wave_u) : kKB;   // this lane's first key outside, counted from its first
 #pragma unroll
       for (int j = 0; j < KG / NW; ++j)
-        dma(src, kg_off, (uint32_t)(swap23(j * NW) * (int)a.ldk) * 2u, sKb + buf * KBUF + (wave_u + NW * j) * GB);
+        dma(src, !RAGGED || swap23(j * NW) < past ? kg_off : kPastRange, (uint32_t)(swap23(j * NW) * (int)a.ldk) * 2u, sKb + buf * KBUF + (wave_u + NW * j) * GB);
     };
     auto dma_v = [&](int kt, int buf) {
       const unsigned char* src = vg_base + (int64_t)kt * kKB * 2;
+      const bool last = RAGGED && (kt + 1) * kKB > sk;
+      int ln = lane;
+      if (last) asm volatile("" : "+v"(ln));
+      const uint32_t off = !last || kt * kKB + (ln % (VRB / 16)) * 8 < sk ? vg_off : kPastRange;
 #pragma unroll
       for (int j = 0; j < VG / NW; ++j)
-        dma(src, vg_off, (uint32_t)(j * NW * (int)a.ldv) * 2u, sVb + buf * VBUF + (wave_u + NW * j) * GB);
+        dma(src, off, (uint32_t)(j * NW * (int)a.ldv) * 2u, sVb + buf * VBUF + (wave_u + NW * j) * GB);
     };
     auto arrived = [&]() {   // this wave's loads have landed, then every wave's
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
@@ -673,8 +694,6 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
     int w_hi = tile_hi;                               // this wave computes tiles [tile_lo, w_hi)
     if (CAUSAL) { const int vis = wave_last / kKB + 1; if (vis < w_hi) w_hi = vis; }
     if (!wave_active) w_hi = tile_lo;
-    float m_exp = 0.f;   // m_run, or 0 while the row has seen no key: exp2(-inf - m_exp) is then 0, not NaN
-
     // S^T = K Q^T of the tile in K buffer `buf`, one 32-key half after the other
     auto scores = [&](f32x16 (&s)[2], int buf) {
 #pragma unroll
@@ -689,33 +708,15 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, CAUSAL, BIAS,
           s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[tt], 0, 0, 0);
         }
     };
-    auto needs_mask = [&](int kt) { return CAUSAL && kt * kKB + kKB - 1 > wave_first; };
+    auto needs_mask = [&](int kt) { return (CAUSAL && kt * kKB + kKB - 1 > wave_first) || (RAGGED && kt * kKB + kKB > sk); };
     auto mask = [&](f32x16 (&s)[2], int kt) {
-      const int k0 = kt * kKB;
+      int seen = keys_seen - kt * kKB - 8 * half;
+      asm volatile("" : "+v"(seen));
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kj = k0 + tt * 32 + 16 * (r / 8) + 8 * half + 4 * ((r / 4) % 2) + (r % 4);
-          if (kj > qpos) s[tt][r] = -INFINITY;
-        }
-    };
-    // the running maximum takes in a tile's largest score per lane; the accumulators are rescaled only when
-    // some row of the wave saw a new maximum
-    auto new_max = [&](float mx) {
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      mx *= scale2;                                  // scale2 > 0: max commutes with the scaling
-      if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        m_exp = m_new == -INFINITY ? 0.f : m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int i = 0; i < DT; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc_o[i][r] *= alpha;
-      }
+        for (int r = 0; r < 16; ++r)
+          if (tt * 32 + 16 * (r / 8) + 4 * ((r / 4) % 2) + (r % 4) >= seen) s[tt][r] = -INFINITY;
     };
     auto take_max = [&](const f32x16 (&s)[2]) {
       float mx = s[0][0];
@@ -938,10 +939,10 @@ __global__ void __launch_bounds__(256) attention_merge_splits(AttnArgs a) {
   *reinterpret_cast<bf16x4*>((bf16_t*)a.ctx + b * a.sc_b + row * a.ldc + h * a.head_dim + d) = o;
 }
 
-template <int DH, bool CAUSAL, bool BIAS, bool RAGGED, int NW>
+template <int DH, bool CAUSAL, bool BIAS, Keys KEYS, int NW>
 static hipError_t mfma_attn_launch(const AttnArgs& a, hipStream_t s) {
-  auto kern = attention_mfma_bf16<DH, CAUSAL, BIAS, RAGGED, NW>;
-  constexpr size_t lds = attention_lds_bytes(DH, CAUSAL, BIAS, RAGGED, NW);
+  auto kern = attention_mfma_bf16<DH, CAUSAL, BIAS, KEYS, NW>;
+  constexpr size_t lds = attention_lds_bytes(DH, BIAS, KEYS, NW);
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr_status != hipSuccess) return attr_status;
@@ -956,20 +957,34 @@ static hipError_t mfma_attn_launch(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int DH, bool CAUSAL, bool BIAS>
-static hipError_t mfma_attn_ragged(const AttnArgs& a, hipStream_t s) {
+template <int DH, bool CAUSAL, bool BIAS, Keys KEYS>
+static hipError_t mfma_attn_rows(const AttnArgs& a, hipStream_t s) {
   // 64-row blocks (2 waves) when a problem has at most 64 query rows, so that no wave idles
-  if (a.sq <= 64) {
-    if (a.sk % kKB != 0) return mfma_attn_launch<DH, CAUSAL, BIAS, true, 2>(a, s);
-    return mfma_attn_launch<DH, CAUSAL, BIAS, false, 2>(a, s);
-  }
-  if (a.sk % kKB != 0) return mfma_attn_launch<DH, CAUSAL, BIAS, true, 4>(a, s);
+  if (a.sq <= 64) return mfma_attn_launch<DH, CAUSAL, BIAS, KEYS, 2>(a, s);
   // 256-row blocks (8 waves, one block per CU) when the launch has rounds of them to spare: a K / V^T tile
   // then serves twice the query rows, which halves the tile loads of the pipelined loop (measured +2.5 %)
-  if constexpr (attention_pipelined(DH, CAUSAL, BIAS, false)) {
-    if (a.n_splits <= 1 && ((a.sq + 255) / 256) * a.heads * a.batch >= 1024) return mfma_attn_launch<DH, CAUSAL, BIAS, false, 8>(a, s);
+  if constexpr (attention_pipelined(DH, BIAS, KEYS)) {
+    if (a.n_splits <= 1 && ((a.sq + 255) / 256) * a.heads * a.batch >= 1024) return mfma_attn_launch<DH, CAUSAL, BIAS, KEYS, 8>(a, s);
   }
-  return mfma_attn_launch<DH, CAUSAL, BIAS, false, 4>(a, s);
+  return mfma_attn_launch<DH, CAUSAL, BIAS, KEYS, 4>(a, s);
+}
+
+// Fewest keys for the pipelined loop with a ragged last tile: its first scores wait for a load and nothing hides them, which shorter
+// 64-wide rows do not make up for (3072 causal heads of 200 rows 19.0 us plain, 19.3 pipelined, of 136 18.6 and 21.5, of 392 24.8 and
+// 23.7; 40 heads of 4096 x 160 20.6 and 23.1).  128-wide heads gain from 72 keys on (8 heads of 1032 31.0 and 23.5, of 3080 79.7 and 57.9).
+constexpr int64_t pipelined_from(int dh) { return dh == 64 ? 320 : 0; }
+template <int DH, bool CAUSAL, bool BIAS>
+static hipError_t mfma_attn_ragged(const AttnArgs& a, hipStream_t s) {
+  if (a.sk % kKB == 0) return mfma_attn_rows<DH, CAUSAL, BIAS, kWholeTiles>(a, s);
+  if constexpr (attention_pipelined(DH, BIAS, kWholeChunks)) {
+    if (a.sk % 8 == 0 && a.sk >= pipelined_from(DH)) {
+      // (one instantiation: without a mask the queries stand behind all keys)
+      AttnArgs c = a;
+      if (!CAUSAL) { c.causal = 1; c.q_offset = a.sk - 1; }
+      return mfma_attn_rows<DH, true, BIAS, kWholeChunks>(c, s);
+    }
+  }
+  return mfma_attn_rows<DH, CAUSAL, BIAS, kAnyKeys>(a, s);
 }
 
 template <int DH>

@@ -1,0 +1,85 @@
+"""The attention kernel's exponent reference, which lags behind the running maximum, and the pipelined loop with a ragged last tile:
+against the fp64 oracle, with NaN in whatever lies behind the keys."""
+import numpy as np
+import pytest
+
+from oracle import transformer as O
+from util import check, draw, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2401_10652_amd import binding
+    binding.lib()
+    return binding
+
+
+def run(B, q, k, v, heads, causal, q_offset=0, bias=None, n_splits=1):
+    """One problem; k [sk, d] and v [sk, d] handed over in buffers whose rest is NaN."""
+    import torch
+    sq, sk, d = q.shape[0], k.shape[0], q.shape[1]
+    kb = torch.full((sk + 80, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    vb = torch.full((d + 1, sk + (-sk) % 8 + 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    kb[:sk], vb[:d, :sk] = B.to_device(k, "bf16"), B.to_device(v, "bf16").T
+    ctx = torch.full((sq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = B.empty_workspace(max(256, B.ac_attention_split_workspace_bytes(sq, heads, 1, d // heads, n_splits)))
+    db = None
+    if bias is not None:
+        db = torch.full((heads, sq, sk + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+        db[:, :, :sk] = B.to_device(bias, "bf16")
+    B.ac_op_attention(B.to_device(q, "bf16"), kb[:sk], vb[:d], ctx, heads, d // heads, causal=causal, q_offset=q_offset, bias=db,
+                      v_transposed=True, n_splits=n_splits, split_workspace=ws)
+    torch.cuda.synchronize()
+    return host(ctx)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("sq,sk,causal,q_offset,n_splits", [
+    (100, 328, False, 0, 1), (33, 520, True, 487, 1), (300, 1032, False, 0, 2), (64, 72, True, 8, 1), (200, 392, True, 150, 1),
+    (130, 1096, True, 966, 3), (129, 320, True, 0, 1), (40, 312, False, 0, 1)])
+@pytest.mark.parametrize("growth", [1.0, 40.0])
+def test_ragged_key_tiles(B, dh, sq, sk, causal, q_offset, n_splits, growth):
+    heads = 2
+    q, k, v = (draw((n, heads * dh), 300 + i, "bf16") for i, n in enumerate((sq, sk, sk)))
+    # the scores' spread grows along the keys to `growth` units: hundreds of binary orders, raised several times over
+    k = (k * (growth / 2 * np.linspace(0.05, 1.0, sk)[:, None] if growth > 1 else k * 0 + 1)).astype(np.float32)
+    from paper_2401_10652_amd.inputs import round_to_storage
+    k = round_to_storage(k, "bf16")
+    check(run(B, q, k, v, heads, causal, q_offset, None, n_splits), O.attention(q, k, v, heads, causal, q_offset=q_offset), "bf16")
+
+
+@pytest.mark.parametrize("dh,sq,sk,batch", [(64, 264, 328, 256), (128, 260, 136, 256)])
+def test_ragged_key_tiles_in_256_row_blocks(B, dh, sq, sk, batch):
+    import torch
+    heads, d = 2, 2 * dh
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((batch, n, d), generator=gen, device="cuda").bfloat16() for n in (sq, sk, sk))
+    vt = v.transpose(1, 2).contiguous()
+    ctx = torch.full_like(q, float("nan"))
+    B.ac_op_attention(q[0], k[0], vt[0], ctx[0], heads, dh, v_transposed=True, batch=batch, strides=(sq * d, sk * d, d * sk, 0, sq * d))
+    torch.cuda.synchronize()
+    for b in (0, 100, batch - 1):
+        check(host(ctx[b]), O.attention(host(q[b]), host(k[b]), host(v[b]), heads, False), "bf16")
+
+
+@pytest.mark.parametrize("dh", [32, 64])
+@pytest.mark.parametrize("sk", [192, 200])
+@pytest.mark.parametrize("mask", [-1e30, float("-inf"), float(np.finfo(np.float32).min)])
+def test_masks_over_the_first_tiles(B, dh, sk, mask):
+    """Rows whose first tiles are masked altogether, and later tiles far above the first ones."""
+    heads, sq = 2, 70
+    q, k, v = (draw((n, heads * dh), 310 + i, "bf16") for i, n in enumerate((sq, sk, sk)))
+    bias = draw((heads, sq, sk), 313, "bf16", 3.0)
+    bias[:, :, 128:] += 90.0
+    from paper_2401_10652_amd.inputs import round_to_storage
+    bias = round_to_storage(bias, "bf16").astype(np.float64)
+    if np.isfinite(mask):   # the largest bf16 below: what such a mask is in storage
+        mask = max(mask, -3.3895313892515355e38)
+    bias[:, 10:40, :130] = mask
+    bias[:, 50:, 64:] = mask
+    if mask == -1e30:
+        bias[:, 45:48] = mask          # a row of nothing else averages its values
+    b32 = round_to_storage(bias.astype(np.float32), "bf16")
+    check(run(B, q, k, v, heads, False, bias=b32), O.attention(q, k, v, heads, False, bias=b32), "bf16")
