@@ -1414,8 +1414,11 @@ static bool mfma_eligible(const LinearArgs& g) {
 // What 32x64 pays once is set by launches of one round inside models, whose operands another kernel has just written: 128x2048x512 takes
 // 7.0 us on it and 8.1 on 64x64 (which 5.4 us instead of 5.0 had preferred), 128x1536x384 6.7 and 7.7, 152x4096x1024 (320 tiles)
 // 10.0 and 9.0.
+// 128x192 fills rounds that the others leave half empty or padded (6400x768x3072 46.8 us on 256x128, 41.9 on it); at few steps it is priced a
+// little above what it takes by itself (2048x3072x768 19.9 against 20.2 us): with every CU loading, twelve layers of it run
+// back to back 3 % slower than on 192 tiles of 256x128.
 // The k order is the same for all of them, and so are the bits.
-enum TileShape { kQuad, k256x128, k128x128Ring, k128x128, k128x64, k64x64, k32x64, kTileShapes };
+enum TileShape { kQuad, k256x128, k128x128Ring, k128x192, k128x128, k128x64, k64x64, k32x64, kTileShapes };
 // A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
 static bool grid_fits(int64_t tiles, int threads) { return tiles <= 0xffffffffLL / threads; }
 static int64_t tiles_of(const LinearArgs& g, int bm, int bn) { return ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn); }
@@ -1425,7 +1428,8 @@ enum Form { kPlain = 1, kConv = 2, kWide = 4, kRagged = 8 };
 static TileShape best_tile(const LinearArgs& g, Form form) {
   struct Cost { int bm, bn, threads; double step, tile, once; bool alone; int forms; };
   static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain | kRagged},
-                                          {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 128, 256, 0.52, 2.7, 4.4, false, kPlain | kWide},
+                                          {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 192, 512, 0.60, 7.4, 1.8, true, kPlain},
+                                          {128, 128, 256, 0.52, 2.7, 4.4, false, kPlain | kWide},
                                           {128, 64, 256, 0.36, 1.4, 4.3, false, kPlain | kConv},  {64, 64, 256, 0.17, 0.8, 4.8, false, kPlain | kConv | kWide | kRagged},
                                           {32, 64, 128, 0.13, 0.65, 5.0, false, kPlain | kWide}};
   int best = -1;
@@ -1440,6 +1444,31 @@ static TileShape best_tile(const LinearArgs& g, Form form) {
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   return best < 0 ? (form == kConv ? k128x128Ring : form == kWide ? k128x128 : form == kRagged ? k256x128 : kQuad) : (TileShape)best;
+}
+
+// The convolution's tile: its sums are long (9 C_in) and its columns few, so the time per step decides, and that depends on how many CUs load
+// at once.  A launch takes the larger of what one block needs by itself (`step1`, `once1`) and what the rounds need with every CU busy
+// (a lone block's rounds count whole); between an empty and a full first round the two are mixed.  Times in us of
+// 49 launches (256 to 64000 pixels, 128 to 640 channels).  Four 64x64 images of 320 channels: 51.9 on 128x128 and 128x64 (whose last
+// columns are half padding), 47.8 on 64x64, 39.2 on 128x192; eight of 192: 37.8 / 35.9 / 36.8 / 26.8; four of 512: 84.5 / 94.8 / 110.9 / 97.5.
+// (64 input channels: nine steps, as short as a product, and priced as one.)
+static TileShape best_conv_tile(const LinearArgs& g) {
+  if (g.conv_c == 64) return best_tile(g, kConv);
+  struct Cost { TileShape shape; int bm, bn, threads; double step, tile, once, step1, once1; bool alone; };
+  static const Cost costs[] = {{k128x192, 128, 192, 512, 0.66, 6.5, 2.0, 0.467, 8.8, true}, {k128x128Ring, 128, 128, 512, 0.505, 4.8, 1.0, 0.385, 6.5, true},
+                               {k128x64, 128, 64, 256, 0.29, 1.7, 4.3, 0.356, 6.9, false},  {k64x64, 64, 64, 256, 0.178, 0.5, 4.8, 0.278, 5.4, false}};
+  TileShape best = k128x128Ring;
+  double best_t = 0;
+  for (const Cost& c : costs) {
+    const int64_t tiles = tiles_of(g, c.bm, c.bn);
+    if (!grid_fits(tiles, c.threads)) continue;
+    const double steps = (double)(g.k / kBK), exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
+    const double rounds = whole <= 1 ? 1 : c.alone ? whole : 0.5 * (exact + whole);
+    const double one = steps * c.step1 + c.once1, busy = rounds * (steps * c.step + c.tile) + c.once;
+    const double t = busy <= one ? one : one + (busy - one) * (exact < 1 ? exact : 1);
+    if (best_t == 0 || t < best_t) { best = c.shape; best_t = t; }
+  }
+  return best;
 }
 
 // fp32 products whose rows can be read 16 bytes at a time
@@ -1466,11 +1495,11 @@ static hipError_t mfma_f32_launch(const LinearArgs& g, hipStream_t s) {
 }
 
 // The kernel a product runs on: a function of sizes, types, strides and alignment, decided on the host.
-enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kRouteQuad, kRing256x128, kRing128x128, kStaged128x128, kRing128x64, kRing64x64,
-             kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x64, kConv64x64, kConvWide64x64, kRoutes };
+enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kRouteQuad, kRing256x128, kRing128x128, kRing128x192, kStaged128x128, kRing128x64, kRing64x64,
+             kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x192, kConv128x64, kConv64x64, kConvWide64x64, kRoutes };
 static const char* const kRouteName[kRoutes] = {
-    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "quad 256x256", "ring 256x128", "ring 128x128", "staged 128x128", "ring 128x64", "ring 64x64",
-    "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x64", "conv 64x64", "conv-wide 64x64"};
+    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
+    "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x192", "conv 128x64", "conv 64x64", "conv-wide 64x64"};
 
 static bool wide_rows(const LinearArgs& g) { return g.lda >= (1 << 22) || g.ldw >= (1 << 22); }
 
@@ -1490,6 +1519,7 @@ static Route bf16_route(const LinearArgs& g) {
     case kQuad: return kRouteQuad;
     case k256x128: return kRing256x128;
     case k128x128Ring: return kRing128x128;
+    case k128x192: return kRing128x192;
     case k128x128: return kStaged128x128;
     case k128x64: return kRing128x64;
     // (alone on its CU and with a long k such a block gains nothing from direct loads and the register-staged loop, which also keeps a whole tile's
@@ -1527,8 +1557,9 @@ static Route f32_route(const LinearArgs& g) {
 static Route linear_route(const LinearArgs& g) {
   if (g.conv_c > 0) {
     if (g.conv_c >= (1 << 20)) return kConvWide64x64;   // (128 weight rows of 9 * 2^20 channels are 2.4e9 bytes)
-    switch (best_tile(g, kConv)) {
+    switch (best_conv_tile(g)) {
       case k128x128Ring: return kConv128x128;
+      case k128x192: return kConv128x192;
       case k128x64: return kConv128x64;
       default: return kConv64x64;
     }
@@ -1574,6 +1605,7 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     case kRouteQuad: return quad_launch(g, s);
     case kRing256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
     case kRing128x128: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
+    case kRing128x192: return ring_launch<128, 192, 4, 2, 64, 3>(g, s);
     case kStaged128x128: return mfma_launch<128, 128, 2, 2>(g, s);
     case kRing128x64: return ring_launch<128, 64, 2, 2, 64, 3>(g, s);
     case kRing64x64: return ring_launch<64, 64, 2, 2, 64, 3>(g, s);
@@ -1582,6 +1614,7 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     case kRagged256x128: return ring_launch<256, 128, 4, 2, 64, 3, false, true>(g, s);
     case kRagged64x64: return ring_launch<64, 64, 2, 2, 64, 3, false, true>(g, s);
     case kConv128x128: return ring_launch<128, 128, 2, 4, 64, 3, true>(g, s);
+    case kConv128x192: return ring_launch<128, 192, 4, 2, 64, 3, true>(g, s);
     case kConv128x64: return ring_launch<128, 64, 2, 2, 64, 3, true>(g, s);
     case kConv64x64: return ring_launch<64, 64, 2, 2, 64, 3, true>(g, s);
     case kConvWide64x64: return ring_launch<64, 64, 2, 2, 64, 3, true, false, true>(g, s);

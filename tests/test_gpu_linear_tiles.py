@@ -120,3 +120,30 @@ def test_long_row_strides(B, m, n, side):
     B.ac_op_linear(*((far, w) if side == "a" else (a, far)), out)
     torch.cuda.synchronize()
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("m,n,k", [(6399, 764, 1600), (3001, 1500, 1664), (6273, 708, 3072)])
+def test_192_column_tiles(B, m, n, k):
+    """Rows and columns that end inside a 128x192 tile: as test_every_tile."""
+    test_every_tile(B, "ring 128x192", m, n, k)
+
+
+@pytest.mark.parametrize("images,h,w,ci,co", [(5, 57, 56, 128, 320), (2, 91, 90, 128, 320), (1, 1, 16003, 192, 320)])
+def test_192_column_tiles_of_the_convolution(B, images, h, w, ci, co):
+    """Against fp64 on sampled pixels, and bit for bit against launches of one image or of fewer columns (64x64 tiles)."""
+    import torch
+    assert B.ac_linear_kernel(images * h * w, co, 9 * ci, "bf16", lda=ci, conv=True) == "conv 128x192"
+    g = torch.Generator(device="cuda").manual_seed(co)
+    x = torch.randn((images, h, w, ci), generator=g, device="cuda").bfloat16()
+    wt = (torch.randn((co, 3, 3, ci), generator=g, device="cuda") / math.sqrt(9 * ci)).bfloat16()
+    res = torch.randn((images, h, w, co), generator=g, device="cuda").bfloat16()
+    out = torch.full((images, h, w, co), float("nan"), device="cuda", dtype=torch.bfloat16)
+    B.ac_op_conv3x3(x, wt, out, residual=res)
+    pad = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    ref = sum(pad[:, i:i + h, j:j + w] @ wt[:, i, j].double().T.contiguous() for i in range(3) for j in range(3)) + res.double()
+    check(host(out), ref.cpu().numpy(), "bf16")
+    for i in range(images):
+        for n0 in range(0, co, 40):
+            part = torch.full((1, h, w, 40), float("nan"), device="cuda", dtype=torch.bfloat16)
+            B.ac_op_conv3x3(x[i:i + 1], wt[n0:n0 + 40].contiguous(), part, residual=res[i:i + 1, ..., n0:n0 + 40].contiguous())
+            assert torch.equal(part[0], out[i, ..., n0:n0 + 40])
