@@ -126,6 +126,7 @@ template <int G> __device__ __forceinline__ float group_sum(float v) {
 // Launch interface used by the executor and by the ac_op_* entry points.
 // ---------------------------------------------------------------------------------------
 
+enum { kCausalColumns = 1, kCausalDepth = 2 };
 struct LinearArgs {
   const void* a; int64_t lda;        // [m, k]
   const void* w; int64_t ldw;        // [n, k]
@@ -152,6 +153,10 @@ struct LinearArgs {
   // product is their 3x3 convolution (stride 1, zero padding 1): row m is a pixel, k = 9 * conv_c runs over
   // (window row, window column, input channel), w is [n][3][3][conv_c].  lda is ignored (= conv_c).
   int conv_h, conv_w, conv_c;
+  // causal (bf16 matrix-core kernels only: linear_takes_causal): row m stands at position q_offset + m.  kCausalColumns: columns past a row's
+  // position may be left unwritten; kCausalDepth: a's terms past a row's position are zeros and may be left out.
+  int causal;
+  int64_t q_offset;
   // bias_period > 0: row m takes bias row m / bias_period (bias is [m / bias_period][n]): one bias vector per image
   int64_t bias_period;
 };
@@ -213,15 +218,17 @@ constexpr int kOpGate = 16;
 hipError_t launch_binary(const void* a, int64_t lda, const void* b, int64_t ldb, void* y, int64_t ldy,
                          int64_t rows, int64_t cols, int op, int dtype, hipStream_t s);
 hipError_t launch_linear(const LinearArgs& g, hipStream_t s);
+bool linear_takes_causal(const LinearArgs& g);
 const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);
 hipError_t launch_group_norm(const void* x, const void* gain, const void* shift, void* y, void* partials, int64_t images,
                              int64_t positions, int channels, int groups, float eps, int act, int dtype, hipStream_t s);
 // p = softmax(scale * s [causal]) over stored rows; row r is query r mod period at position
-// q_offset + (r mod period).
+// q_offset + (r mod period).  A causal row's zeros are written up to the end of the row, or (row_tile > 0) as far as a
+// kCausalDepth product of tiles of at most row_tile rows reads them.
 hipError_t launch_softmax_rows(const void* src, int64_t lds, void* dst, int64_t ldd, int64_t rows, int64_t cols,
-                               float scale, int causal, int64_t q_offset, int64_t period, int dtype, hipStream_t s);
+                               float scale, int causal, int64_t q_offset, int64_t period, int row_tile, int dtype, hipStream_t s);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
 int attention_key_splits(int64_t sq, int64_t sk, int heads, int64_t batch, int head_dim, int dtype, int v_transposed);
 uint64_t attention_split_workspace_bytes(int64_t sq, int heads, int64_t batch, int head_dim, int n_splits);

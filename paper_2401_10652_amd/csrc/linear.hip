@@ -112,10 +112,11 @@ constexpr int kXcds = 8;
 // Block id -> tile.  Consecutive block ids go round-robin to the 8 XCDs, each with its own
 // L2; give every XCD a contiguous run of tiles, ordered in groups of 4 tile-rows so that
 // tiles resident together share activation and weight panels.
-__device__ __forceinline__ void tile_of_block(int64_t tiles_m, int64_t tiles_n, int64_t& tm, int64_t& tn) {
+// (`turn` rotates the runs among the XCDs: products whose tiles differ in work do not all give the same XCD the most.)
+__device__ __forceinline__ void tile_of_block(int64_t tiles_m, int64_t tiles_n, int64_t& tm, int64_t& tn, int64_t turn = 0) {
   const int64_t nb = gridDim.x, pid = blockIdx.x;
   const int64_t q = nb / kXcds, r = nb % kXcds;
-  const int64_t x = pid % kXcds, idx = pid / kXcds;
+  const int64_t x = r == 0 ? (pid + turn) % kXcds : pid % kXcds, idx = pid / kXcds;
   const int64_t t = x * q + (x < r ? x : r) + idx;
   constexpr int64_t GM = 4;
   const int64_t width = GM * tiles_n;
@@ -274,6 +275,18 @@ __global__ void __launch_bounds__(256) linear_mfma_f32(LinearArgs g, int vec) {
     }
     epilogue_store_f32x4(g, vec, product, m0 + rl, n0 + cl, v);
   }
+}
+
+// Products over stored causal scores and probabilities: a tile whose columns lie past the positions of all its rows has nothing to do,
+// and one whose rows stop seeing terms stops there (in whole steps).  16 heads of 1024 queries against 4096 keys, segment by segment: scores
+// 55 -> 35 us on average, context 35 -> 20, the softmax between them 37 -> 32.
+__device__ __forceinline__ bool tile_unseen(const LinearArgs& g, int64_t m0, int64_t n0, int bm) {
+  return g.causal == kCausalColumns && n0 >= g.q_offset + m0 + bm;
+}
+__device__ __forceinline__ int64_t tile_depth(const LinearArgs& g, int64_t m0, int bm) {
+  if (g.causal != kCausalDepth) return g.k;
+  const int64_t seen = (g.q_offset + m0 + bm + kBK - 1) / kBK * kBK;
+  return seen < g.k ? seen : g.k;
 }
 
 // Block id -> position in a 1-D list of work items such that each XCD gets a contiguous run.
@@ -465,8 +478,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(Linea
   const int l32 = lane % 32, half = lane / 32;
   const int64_t tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
   int64_t tm_, tn_;
-  tile_of_block(tiles_m, tiles_n, tm_, tn_);
+  tile_of_block(tiles_m, tiles_n, tm_, tn_, g.causal ? blockIdx.y : 0);
   const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  if (tile_unseen(g, m0, n0, BM)) return;
   const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
   const bf16_t* a = (const bf16_t*)g.a + product * g.sa_b;
   const bf16_t* w = (const bf16_t*)g.w + product * g.sw_b;
@@ -512,7 +526,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_mfma_bf16(Linea
   // inside a model their operands were written by the kernel before (another XCD's L2, so they
   // come from memory), and a 512 x 768 x 3072 product on 32x64 tiles went from 15.6 to 12.3 us;
   // with operands that are already in L2 the depth makes no difference.
-  const int64_t kt_count = g.k / kBK;
+  const int64_t kt_count = tile_depth(g, m0, BM) / kBK;
   constexpr int KSTEPS = kBK / 16;
   // register sets of the staging ring (registers allow four only in the small tiles)
   constexpr int S = TM * TN < 4 ? 4 : 2;
@@ -731,8 +745,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
   const int l32 = lane % 32, half = lane / 32;
   int64_t tm_, tn_;
-  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_);
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_, g.causal ? blockIdx.y : 0);
   const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  if (tile_unseen(g, m0, n0, BM)) return;
   const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
   g.out = (bf16_t*)g.out + product * g.so_b;
 
@@ -850,7 +865,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     if (x < TN) fw_[ks][x] = *reinterpret_cast<const bf16x8*>(sW + base + frag_off[ks] + x * 32 * ROWB);
     else fa_[ks][x - TN] = *reinterpret_cast<const bf16x8*>(sA + base + frag_off[ks] + (x - TN) * 32 * ROWB);
   };
-  const int kt_count = (int)((g.k + (RAGGED_K ? BK - 1 : 0)) / BK);
+  const int kt_count = (int)((tile_depth(g, m0, BM) + (RAGGED_K ? BK - 1 : 0)) / BK);
   // Step kt: multiply tile kt (its fragments are in registers), read tile kt + 1's, and load tile kt + STAGES into the
   // buffer tile kt lay in.  `stage` = kt % STAGES.
   int kt = 0, stage = 0;
@@ -926,8 +941,9 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
   const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
   const int l32 = lane % 32, half = lane / 32;
   int64_t tm_, tn_;
-  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_);
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_, g.causal ? blockIdx.y : 0);
   const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  if (tile_unseen(g, m0, n0, BM)) return;
   const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
   g.out = (bf16_t*)g.out + product * g.so_b;
 
@@ -985,7 +1001,7 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
   auto read_w = [&](bf16x8 (&f)[4], int kt, int h, int x) {             // fragment x of 4
     f[x] = *reinterpret_cast<const bf16x8*>(sW + (kt & 1) * BUF + h * 32 * ROWB + frag_off[x]);
   };
-  const int kt_count = (int)(g.k / BK);
+  const int kt_count = (int)(tile_depth(g, m0, BM) / BK);
   // Both steps: 16 matrix instructions, 12 fragment reads among the first 12 of them, 4 loads spread evenly.  (Past the last
   // tile the reads fetch what an older one left; nothing uses it.)
   auto step_x = [&](int kt, bf16x8 (&w0)[4], bf16x8 (&w1)[4]) {
@@ -1567,6 +1583,12 @@ static Route linear_route(const LinearArgs& g) {
   if (mfma_eligible(g)) return bf16_route(g);
   if (g.dtype == AC_F32 && mfma_f32_eligible(g)) return f32_route(g);
   return kFma;
+}
+
+bool linear_takes_causal(const LinearArgs& g_in) {
+  LinearArgs g = g_in;
+  g.o_period = g.t_period = INT64_MAX;
+  return g.dtype == AC_BF16 && linear_route(g) != kFma;
 }
 
 const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype) {

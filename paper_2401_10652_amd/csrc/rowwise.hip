@@ -584,7 +584,7 @@ softmax_rows(const T* src, int64_t lds_, T* dst, int64_t ldd, int64_t cols, floa
 template <typename T, int NV>
 __global__ void __launch_bounds__(256)
 softmax_rows_vec(const T* src, int64_t lds_, T* dst, int64_t ldd, int64_t cols, float scale,
-                 int causal, int64_t q_offset, int64_t period) {
+                 int causal, int64_t q_offset, int64_t period, int row_tile) {
   constexpr int V = Elem<T>::kVec;
   constexpr int R = NV > 0 ? NV : 1;
   __shared__ float red[4];
@@ -596,8 +596,13 @@ softmax_rows_vec(const T* src, int64_t lds_, T* dst, int64_t ldd, int64_t cols, 
     const int64_t last = q_offset + r % period;
     if (last + 1 < vis) vis = last + 1;
   }
+  int64_t written = cols;     // (a product's row tile reads up to the position of its last row, in whole steps of 64)
+  if (causal && row_tile > 0) {
+    const int64_t end = (q_offset + ((r % period) / row_tile + 1) * row_tile + 63) / 64 * 64;
+    if (end < written) written = end;
+  }
   const int tid = threadIdx.x;
-  const int64_t nvec = cols / V;
+  const int64_t nvec = written / V;
   float v[R][V];
   float m = -INFINITY;
   if (NV > 0) {
@@ -661,12 +666,12 @@ softmax_rows_vec(const T* src, int64_t lds_, T* dst, int64_t ldd, int64_t cols, 
 
 template <typename T>
 static hipError_t softmax_rows_vec_launch(const void* src, int64_t lds_, void* dst, int64_t ldd, int64_t rows, int64_t cols,
-                                          float scale, int causal, int64_t q_offset, int64_t period, hipStream_t s) {
+                                          float scale, int causal, int64_t q_offset, int64_t period, int row_tile, hipStream_t s) {
   const int64_t nvec = cols / Elem<T>::kVec;
   const dim3 grid((unsigned)rows);
 #define AC_SOFTMAX_VEC(NV)                                                                                        \
   hipLaunchKernelGGL((softmax_rows_vec<T, NV>), grid, dim3(256), 0, s, (const T*)src, lds_, (T*)dst, ldd, cols, scale, \
-                     causal, q_offset, period)
+                     causal, q_offset, period, row_tile)
   if (nvec <= 256) AC_SOFTMAX_VEC(1);
   else if (nvec <= 512) AC_SOFTMAX_VEC(2);
   else if (nvec <= 1024) AC_SOFTMAX_VEC(4);
@@ -677,13 +682,13 @@ static hipError_t softmax_rows_vec_launch(const void* src, int64_t lds_, void* d
 }
 
 hipError_t launch_softmax_rows(const void* src, int64_t lds_, void* dst, int64_t ldd, int64_t rows, int64_t cols,
-                               float scale, int causal, int64_t q_offset, int64_t period, int dtype, hipStream_t s) {
+                               float scale, int causal, int64_t q_offset, int64_t period, int row_tile, int dtype, hipStream_t s) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   if (period <= 0 || !(scale > 0.f) || rows > 0x7fffffffLL) return hipErrorInvalidValue;
   const int64_t vec = dtype == AC_BF16 ? 8 : 4;
   if (cols % vec == 0 && lds_ % vec == 0 && ldd % vec == 0 && ((uintptr_t)src % 16) == 0 && ((uintptr_t)dst % 16) == 0) {
-    if (dtype == AC_BF16) return softmax_rows_vec_launch<bf16_t>(src, lds_, dst, ldd, rows, cols, scale, causal, q_offset, period, s);
-    return softmax_rows_vec_launch<float>(src, lds_, dst, ldd, rows, cols, scale, causal, q_offset, period, s);
+    if (dtype == AC_BF16) return softmax_rows_vec_launch<bf16_t>(src, lds_, dst, ldd, rows, cols, scale, causal, q_offset, period, row_tile, s);
+    return softmax_rows_vec_launch<float>(src, lds_, dst, ldd, rows, cols, scale, causal, q_offset, period, row_tile, s);
   }
   if (dtype == AC_BF16)
     hipLaunchKernelGGL((softmax_rows<bf16_t>), dim3((unsigned)rows), dim3(256), 0, s, (const bf16_t*)src, lds_,

@@ -367,6 +367,9 @@ struct Walk {
     const int e = eb();
     const int64_t c = a.sq, S = a.sk, H = a.heads, dh = a.head_dim;
     const uint64_t mk = arena.mark();
+    // A causal segment's rows see keys up to the last one's position: the columns behind are neither computed nor read, and of
+    // those before only the tiles that some row of theirs sees.
+    const int64_t seen = a.causal ? std::min<int64_t>(S, align_up((uint64_t)(a.q_offset + c), 64)) : S;
     uint8_t* scores = (uint8_t*)arena.push((uint64_t)a.batch * H * c * S * e);
     uint8_t* probs = (uint8_t*)arena.push((uint64_t)a.batch * H * c * S * e);
     const float scale = 1.0f / sqrtf((float)dh);
@@ -377,20 +380,25 @@ struct Walk {
       g1.w = (const uint8_t*)a.k + b * a.sk_b * e; g1.ldw = a.ldk; g1.sw_b = dh;
       g1.out = dry ? nullptr : scores + off; g1.ldo = S; g1.so_b = c * S;
       g1.m = c; g1.n = S; g1.k = dh; g1.n_split = S; g1.batch = H; g1.act = AC_ACT_NONE; g1.dtype = dt;
+      LinearArgs g2{};
+      g2.a = dry ? nullptr : probs + off; g2.lda = S; g2.sa_b = c * S;
+      g2.w = (const uint8_t*)a.v + b * a.sv_b * e; g2.ldw = a.ldv; g2.sw_b = dh * a.ldv;
+      g2.out = (uint8_t*)a.ctx + b * a.sc_b * e; g2.ldo = a.ldc; g2.so_b = dh;
+      g2.m = c; g2.n = dh; g2.k = S; g2.n_split = dh; g2.batch = H; g2.act = AC_ACT_NONE; g2.dtype = dt;
+      LinearArgs s1 = g1, s2 = g2;
+      s1.n = s1.n_split = s2.k = seen;
+      s1.causal = kCausalColumns; s2.causal = kCausalDepth; s1.q_offset = s2.q_offset = a.q_offset;
+      const bool skips = a.causal && linear_takes_causal(s1) && linear_takes_causal(s2);
+      if (skips) { g1 = s1; g2 = s2; }
       run(K_GEMM, 2.0 * c * S * dh * H, ((double)c * dh + (double)S * dh + (double)c * S) * H * e, "scores",
           [&] { return launch_linear(g1, stream); });
       const void* sp = dry ? nullptr : scores + off;
       void* pp = dry ? nullptr : probs + off;
-      const int causal = a.causal;
-      const int64_t qo = a.q_offset;
+      const int causal = a.causal, row_tile = skips ? 256 : 0;
+      const int64_t qo = a.q_offset, cols = skips ? seen : S;
       hipStream_t st = stream;
       run(K_ELEM, 5.0 * c * S * H, 4.0 * c * S * H * e, "softmax",
-          [&] { return launch_softmax_rows(sp, S, pp, S, H * c, S, scale, causal, qo, c, dt, st); });
-      LinearArgs g2{};
-      g2.a = pp; g2.lda = S; g2.sa_b = c * S;
-      g2.w = (const uint8_t*)a.v + b * a.sv_b * e; g2.ldw = a.ldv; g2.sw_b = dh * a.ldv;
-      g2.out = (uint8_t*)a.ctx + b * a.sc_b * e; g2.ldo = a.ldc; g2.so_b = dh;
-      g2.m = c; g2.n = dh; g2.k = S; g2.n_split = dh; g2.batch = H; g2.act = AC_ACT_NONE; g2.dtype = dt;
+          [&] { return launch_softmax_rows(sp, S, pp, S, H * c, cols, scale, causal, qo, c, row_tile, dt, st); });
       run(K_GEMM, 2.0 * c * S * dh * H, ((double)c * S + (double)S * dh + (double)c * dh) * H * e, "context",
           [&] { return launch_linear(g2, stream); });
     }
@@ -2001,7 +2009,7 @@ int ac_op_softmax_rows(const void* s, int64_t lds, void* p, int64_t ldp, int64_t
   if (!s || !p || rows < 0 || cols < 1 || lds < cols || ldp < cols || !(scale > 0.f) || q_offset < 0 || period < 1 ||
       !dtype_ok(dtype))
     return fail(AC_ERR_ARG, "ac_op_softmax_rows: bad argument");
-  return hip_status(launch_softmax_rows(s, lds, p, ldp, rows, cols, scale, causal != 0, q_offset, period, dtype,
+  return hip_status(launch_softmax_rows(s, lds, p, ldp, rows, cols, scale, causal != 0, q_offset, period, 0, dtype,
                                         (hipStream_t)stream), "softmax_rows");
 }
 
