@@ -717,6 +717,7 @@ hipError_t launch_softmax_rows(const void* src, int64_t lds_, void* dst, int64_t
 constexpr int kGnParts = 64;          // position shares per (image, group): enough blocks to fill the chip at 2 images
 constexpr int kGnApplyChunks = 4;     // 16-byte runs per thread of the apply kernel (amortises the merge of the partials)
 constexpr int kGnMaxGroups = 128;
+constexpr int kGnLanes = 8;           // lanes that work on a group's sums
 
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -753,6 +754,22 @@ group_norm_partials(const T* x, float* part, int64_t positions, int channels, in
   }
 }
 
+// The group of each of V consecutive channels from c0 on: one division, then counting.
+template <int V>
+__device__ __forceinline__ void group_of_channels(int c0, int cg, int (&g)[V]) {
+  g[0] = c0 / cg;
+  int left = (g[0] + 1) * cg - c0;                 // channels of the current group still to come
+#pragma unroll
+  for (int j = 1; j < V; ++j) {
+    const bool next = --left == 0;
+    g[j] = g[j - 1] + (next ? 1 : 0);
+    left = next ? cg : left;
+  }
+}
+
+// What bounds it: besides the read, the sums of a block's lanes on the way to its groups.  They are added over the rows by a thread per
+// channel and over a group's channels by eight lanes: one thread per group, walking its 60 sums, had the launch of
+// 4 x 4096 x 320 at 8.8 us, 6.6 here.
 template <typename T>
 __global__ void __launch_bounds__(256)
 group_norm_partials_rows(const T* x, float* part, int64_t positions, int channels, int groups) {
@@ -773,10 +790,12 @@ group_norm_partials_rows(const T* x, float* part, int64_t positions, int channel
 #pragma unroll
   for (int j = 0; j < V; ++j) { k[j] = 0.f; s1[j] = 0.f; s2[j] = 0.f; }
   if (r < rpp && p0 + r < p1) {
+    int g[V];
+    group_of_channels<V>(v * V, cg, g);
 #pragma unroll
-    for (int j = 0; j < V; ++j) k[j] = Elem<T>::ld(img + p0 * channels + (v * V + j) / cg * cg);
+    for (int j = 0; j < V; ++j) k[j] = Elem<T>::ld(img + p0 * channels + g[j] * cg);
     const T* col = img + v * V;
-    constexpr int B = 8;     // rows in flight per thread: the rows were written by the kernel before and come from memory
+    constexpr int B = 4;     // rows in flight per thread (eight: two blocks fewer per CU, 4 x 4096 x 320 15.1 instead of 14.5 us with the pass after it)
     for (int64_t base = p0 + r; base < p1; base += (int64_t)B * rpp) {
       float val[B][V];
 #pragma unroll
@@ -795,13 +814,27 @@ group_norm_partials_rows(const T* x, float* part, int64_t positions, int channel
 #pragma unroll
   for (int j = 0; j < V; ++j) { s_s1[tid][j] = s1[j]; s_s2[tid][j] = s2[j]; }
   __syncthreads();
-  for (int g = tid; g < groups; g += 256) {
+  for (int c = tid; c < channels; c += 256) {        // (fixed orders: the result does not depend on timing)
+    float a1 = s_s1[c / V][c % V], a2 = s_s2[c / V][c % V];
+    for (int rr = 1; rr < rpp; ++rr) {
+      a1 += s_s1[rr * vpr + c / V][c % V];
+      a2 += s_s2[rr * vpr + c / V][c % V];
+    }
+    s_s1[c / V][c % V] = a1;                         // (read by this thread alone until the barrier)
+    s_s2[c / V][c % V] = a2;
+  }
+  __syncthreads();
+  for (int g0 = 0; g0 < groups; g0 += 256 / kGnLanes) {
+    const int g = g0 + tid / kGnLanes, lane = tid % kGnLanes;
+    if (g >= groups) break;                          // (whole sets of eight lanes)
     float a1 = 0.f, a2 = 0.f;
-    for (int c = g * cg; c < (g + 1) * cg; ++c)
-      for (int rr = 0; rr < rpp; ++rr) {             // fixed order: the result does not depend on timing
-        a1 += s_s1[rr * vpr + c / V][c % V];
-        a2 += s_s2[rr * vpr + c / V][c % V];
-      }
+    for (int c = g * cg + lane; c < (g + 1) * cg; c += kGnLanes) {
+      a1 += s_s1[c / V][c % V];
+      a2 += s_s2[c / V][c % V];
+    }
+    a1 = group_sum<kGnLanes>(a1);
+    a2 = group_sum<kGnLanes>(a2);
+    if (lane > 0) continue;
     const float cnt = p1 > p0 ? (float)((p1 - p0) * cg) : 0.f;
     const float kg = p1 > p0 ? Elem<T>::ld(img + p0 * channels + g * cg) : 0.f;
     float* o = part + ((image * groups + g) * kGnParts + part_i) * 3;
@@ -811,52 +844,48 @@ group_norm_partials_rows(const T* x, float* part, int64_t positions, int channel
   }
 }
 
-// Mean and reciprocal deviation of every group of an image, by the block: a wave merges the 64 partials of a group as a tree
-// (lane l holds part l; fixed shape, so the result does not depend on timing): a thread that walked them one after the other
-// cost more than the pass itself.
+// Mean and reciprocal deviation of every group of an image, by the block: eight lanes per group, eight partials each, first the mean, then the
+// deviations from it (fixed shape, so the result does not depend on timing).  Every block of the pass does this before it can
+// store a row: as a tree over one partial per lane, three exchanges a step, it was most of the pass (4 x 4096 x 320: 17.0 us, 10.1 here).
 __device__ __forceinline__ void group_norm_merge(const float* part, int64_t image, int groups, float eps, int tid, float* s_mean, float* s_rstd) {
-  static_assert(kGnParts == kWave, "one partial per lane");
-  constexpr int GB = 8;                            // groups whose partials a wave has in flight at a time
-  for (int g0 = tid / kWave; g0 < groups; g0 += GB * (256 / kWave)) {
-    float n[GB], mean[GB], m2[GB];
+  static_assert(kGnParts == kGnLanes * kGnLanes, "eight partials per lane");
+  typedef float run_t __attribute__((ext_vector_type(4), aligned(4)));     // (the table may start at any float)
+  for (int g0 = 0; g0 < groups; g0 += 256 / kGnLanes) {
+    const int g = g0 + tid / kGnLanes, lane = tid % kGnLanes;
+    const float* pp = part + ((image * groups + (g < groups ? g : groups - 1)) * kGnParts + lane * kGnLanes) * 3;
+    float v[3 * kGnLanes];
 #pragma unroll
-    for (int i = 0; i < GB; ++i) {
-      const int g = g0 + i * (256 / kWave);
-      const float* pp = part + ((image * groups + (g < groups ? g : groups - 1)) * kGnParts + tid % kWave) * 3;
-      n[i] = pp[0]; mean[i] = pp[1]; m2[i] = pp[2];
+    for (int i = 0; i < 3 * kGnLanes / 4; ++i) {
+      const run_t t = *reinterpret_cast<const run_t*>(pp + 4 * i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * i + e] = t[e];
     }
+    float n = 0.f, sum = 0.f, m2 = 0.f;
 #pragma unroll
-    for (int off = kWave / 2; off >= 1; off /= 2) {
+    for (int i = 0; i < kGnLanes; ++i) { n += v[3 * i]; sum += v[3 * i] * v[3 * i + 1]; }
+    n = group_sum<kGnLanes>(n);
+    const float mean = group_sum<kGnLanes>(sum) / n;
 #pragma unroll
-      for (int i = 0; i < GB; ++i) {                 // (the groups' chains are independent: their exchanges overlap)
-        const float nb = __shfl_down(n[i], off, kWave), mb = __shfl_down(mean[i], off, kWave), m2b = __shfl_down(m2[i], off, kWave);
-        const float tot = n[i] + nb;
-        const float delta = mb - mean[i], f = nb > 0.f ? nb * __builtin_amdgcn_rcpf(tot) : 0.f;   // (a weight, good to 1 ulp)
-        mean[i] += delta * f;
-        m2[i] += m2b + delta * delta * (n[i] * f);
-        n[i] = tot;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < GB; ++i) {
-      const int g = g0 + i * (256 / kWave);
-      if (g < groups && tid % kWave == 0) {
-        s_mean[g] = mean[i];
-        s_rstd[g] = rsqrtf(m2[i] / n[i] + eps);
-      }
+    for (int i = 0; i < kGnLanes; ++i) { const float d = v[3 * i + 1] - mean; m2 += v[3 * i + 2] + v[3 * i] * d * d; }
+    m2 = group_sum<kGnLanes>(m2);
+    if (g < groups && lane == 0) {
+      s_mean[g] = mean;
+      s_rstd[g] = rsqrtf(m2 / n + eps);
     }
   }
 }
 
 // One element, the same in both passes below, so that which of them a launch takes does not change its bits.
+// (bf16: sigmoid by reciprocal and Newton step, the division's value wherever a bf16 result tells them apart.)
+template <typename T>
 __device__ __forceinline__ float group_norm_one(float v, float mean, float rstd, float gain, float shift, int act) {
   const float t = fmaf((v - mean) * rstd, gain, shift);
-  return act == AC_ACT_SILU ? t * sigmoidf(t) : t;
+  return act == AC_ACT_SILU ? t * (sizeof(T) == 2 ? sigmoid_newton(t) : sigmoidf(t)) : t;
 }
 
 // The pass of rows of at most 256 16-byte runs: a thread keeps one run of channels and walks down the rows, so its eight groups'
 // statistics and its gain and shift are looked up once (a division by the group size per element, and the rows'
-// loads behind the merge instead of under it, had the launch of 2 x 4096 x 320 at 13.5 us; 11.5 us here).
+// loads behind the merge instead of under it, had the launch of 2 x 4096 x 320 at 13.5 us; 11.5 without).
 template <typename T>
 __global__ void __launch_bounds__(256)
 group_norm_apply_rows(const T* x, const float* part, const T* gain, const T* shift, T* y, int64_t positions, int channels,
@@ -882,20 +911,17 @@ group_norm_apply_rows(const T* x, const float* part, const T* gain, const T* shi
   group_norm_merge(part, image, groups, eps, tid, s_mean, s_rstd);
   __syncthreads();
   if (!live) return;
-  const int cg = channels / groups;
   float mean[V], rstd[V];
+  int g[V];
+  group_of_channels<V>(run * V, channels / groups, g);
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int g = (run * V + i) / cg;
-    mean[i] = s_mean[g];
-    rstd[i] = s_rstd[g];
-  }
+  for (int i = 0; i < V; ++i) { mean[i] = s_mean[g[i]]; rstd[i] = s_rstd[g[i]]; }
 #pragma unroll
   for (int k = 0; k < kGnApplyChunks; ++k) {
     const int64_t p = p0 + (int64_t)k * rpp;
     if (p >= positions) break;
 #pragma unroll
-    for (int i = 0; i < V; ++i) v[k][i] = group_norm_one(v[k][i], mean[i], rstd[i], gg[i], sh[i], act);
+    for (int i = 0; i < V; ++i) v[k][i] = group_norm_one<T>(v[k][i], mean[i], rstd[i], gg[i], sh[i], act);
     store_vec(dst + p * channels, v[k]);
   }
 }
@@ -930,11 +956,10 @@ group_norm_apply(const T* x, const float* part, const T* gain, const T* shift, T
     float gg[V], sh[V];
     load_vec(gain + ch0[k], gg);
     load_vec(shift + ch0[k], sh);
+    int g[V];
+    group_of_channels<V>(ch0[k], cg, g);
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const int g = (ch0[k] + i) / cg;
-      v[k][i] = group_norm_one(v[k][i], s_mean[g], s_rstd[g], gg[i], sh[i], act);
-    }
+    for (int i = 0; i < V; ++i) v[k][i] = group_norm_one<T>(v[k][i], s_mean[g[i]], s_rstd[g[i]], gg[i], sh[i], act);
     store_vec(y + off[k], v[k]);
   }
 }
