@@ -326,8 +326,10 @@ __device__ __forceinline__ float gelu_table(float x, const float* tab) {
 // whose lanes walk along rows; other tiles (strided store, narrow or misaligned outputs)
 // store 8 bytes per lane straight from the registers.  GELU_TABLE: erf GELU from the table at gelu_tab, up to
 // 9e-6 off at |x| = 1.4, and not by its formula (1.5e-7), which products of ragged depth keep from the FMA kernel.
-template <int ACT, int BM, int BN, int WAVES_M, int WAVES_N, bool GELU_TABLE = true>
-__device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32],
+constexpr int64_t kNearRow = 1 << 22;   // row strides below: 256 rows span less than 2^31 bytes
+// LDS_FREE: nobody reads `lds` any more.  Returns whether the block met at a barrier.
+template <int ACT, int BM, int BN, int WAVES_M, int WAVES_N, bool GELU_TABLE = true, bool LDS_FREE = false>
+__device__ __forceinline__ bool epilogue_tile(const LinearArgs& g, f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32],
                                               bf16_t* lds, const float* gelu_tab, int64_t m0, int64_t n0,
                                               int wave_m, int wave_n, int l32, int half, int tid) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
@@ -340,7 +342,102 @@ __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)
   constexpr int TROW = BM + 8;
   const bool tstaged = !staged && n0 >= g.n_split && g.t_s2 == 1 && g.m % 8 == 0 && g.t_s1 % 8 == 0 && g.t_s3 % 8 == 0 &&
                        ((uintptr_t)g.out_t % 16) == 0 && (g.t_period == INT64_MAX || (g.t_period % BM == 0));
-  if (staged || tstaged) __syncthreads();   // every wave is done reading the k-loop buffers
+  if (!LDS_FREE && (staged || tstaged)) __syncthreads();   // every wave is done reading the k-loop buffers
+  // Whole tiles of ordinary operands: no clamps, no predicates, and a wave-uniform base plus 32 bits per lane for every access.  What
+  // bounds an epilogue is vector work, and the general form below spends most of its own on 64-bit addresses (34
+  // instructions per four elements).  16384x4096x1024 144.6 -> 141.9 us, 12288x2560x320 37.8 -> 35.5, 524288x128x128 112.7 -> 106.5.
+  const bool whole = m0 + BM <= g.m && n0 + BN <= g.n && ((staged && g.o_period == INT64_MAX && g.ldo < kNearRow) || (tstaged && g.t_s3 < kNearRow)) &&
+                     (!g.mul || g.ldmul < kNearRow) && (!g.resid || g.ldr < kNearRow) &&
+                     (g.bias_period <= 0 || (uint32_t)m0 / (uint32_t)g.bias_period == (uint32_t)(m0 + BM - 1) / (uint32_t)g.bias_period);
+  if (whole) {
+    constexpr int JF = WAVES_M * WAVES_N == 8 ? TN : 1;      // (operands a wave has in flight at a time, as below)
+    auto near4 = [](const bf16_t* base, uint32_t bytes, int imm) { return *reinterpret_cast<const bf16x4*>((const unsigned char*)base + bytes + imm * 2); };
+    auto store8 = [](bf16_t* base, uint32_t bytes, const bf16_t* from) { *reinterpret_cast<bf16x8*>((unsigned char*)base + bytes) = *reinterpret_cast<const bf16x8*>(from); };
+    const bf16_t* const bias_b = g.bias ? (const bf16_t*)g.bias + (g.bias_period > 0 ? (int64_t)((uint32_t)m0 / (uint32_t)g.bias_period) * g.n : 0) + n0 : nullptr;
+    const bf16_t* const mul_b = (const bf16_t*)g.mul + m0 * g.ldmul + n0;
+    const bf16_t* const res_b = (const bf16_t*)g.resid + m0 * g.ldr + n0;
+    const uint32_t cl = wave_n * WN + 4 * half;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const uint32_t rl = wave_m * WM + i * 32 + l32;
+      const uint32_t mul_o = (rl * (uint32_t)g.ldmul + cl) * 2, res_o = (rl * (uint32_t)g.ldr + cl) * 2;   // bytes
+#pragma unroll
+      for (int jb = 0; jb < TN; jb += JF) {
+        bf16x4 bias_v[JF][4] = {}, mul_v[JF][4], res_v[JF][4];
+        if (bias_b) {
+#pragma unroll
+          for (int j = 0; j < JF; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bias_v[j][q] = near4(bias_b, cl * 2, (jb + j) * 32 + 8 * q);
+        }
+        if (g.mul) {
+#pragma unroll
+          for (int j = 0; j < JF; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) mul_v[j][q] = near4(mul_b, mul_o, (jb + j) * 32 + 8 * q);
+        }
+        if (g.resid) {
+#pragma unroll
+          for (int j = 0; j < JF; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) res_v[j][q] = near4(res_b, res_o, (jb + j) * 32 + 8 * q);
+        }
+#pragma unroll
+        for (int j = 0; j < JF; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float v[4];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+              const float pre = acc[i][jb + j][4 * q + jj] + bf2f(bias_v[j][q][jj]);
+              v[jj] = ACT == AC_ACT_GELU_ERF && GELU_TABLE ? gelu_table(pre, gelu_tab) : apply_act_bf16<ACT>(pre);
+            }
+            if (g.mul) {
+#pragma unroll
+              for (int jj = 0; jj < 4; ++jj) v[jj] *= bf2f(mul_v[j][q][jj]);
+            }
+            if (g.resid) {
+#pragma unroll
+              for (int jj = 0; jj < 4; ++jj) v[jj] += bf2f(res_v[j][q][jj]);
+            }
+            const bf16x4 o = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+            const uint32_t c = cl + (jb + j) * 32 + 8 * q;
+            if (staged) {
+              *reinterpret_cast<bf16x4*>(lds + rl * CROW + c) = o;
+            } else {
+#pragma unroll
+              for (int jj = 0; jj < 4; ++jj) lds[(c + jj) * TROW + rl] = o[jj];
+            }
+          }
+      }
+    }
+    __syncthreads();
+    if (staged) {
+      constexpr int CPR = BN / 8, RPT = NT / CPR;            // 16-byte chunks per tile row, rows per pass of the block
+      bf16_t* const out_b = (bf16_t*)g.out + m0 * g.ldo + n0;
+      if constexpr (NT % CPR == 0) {
+        const uint32_t r0 = tid / CPR, cc = tid % CPR * 8;
+        uint32_t off = (r0 * (uint32_t)g.ldo + cc) * 2;
+#pragma unroll 4
+        for (int r = 0; r < BM; r += RPT, off += RPT * (uint32_t)g.ldo * 2) store8(out_b, off, lds + (r0 + r) * CROW + cc);
+      } else {
+#pragma unroll 4
+        for (int c = tid; c < BM * CPR; c += NT)
+          store8(out_b, ((uint32_t)(c / CPR) * (uint32_t)g.ldo + c % CPR * 8) * 2, lds + c / CPR * CROW + c % CPR * 8);
+      }
+    } else {
+      constexpr int CPT = BM / 8, NPT = NT / CPT;
+      static_assert(NT % CPT == 0 && BN % NPT == 0, "columns per pass of the block");
+      int64_t tq, tr;
+      split_row(m0, g.t_period, tq, tr);
+      bf16_t* const out_b = (bf16_t*)g.out_t + tq * g.t_s1 + tr + (n0 - g.n_split) * g.t_s3;
+      const uint32_t nl = tid / CPT, mm = tid % CPT * 8;
+      uint32_t off = (nl * (uint32_t)g.t_s3 + mm) * 2;
+#pragma unroll 4
+      for (int n = 0; n < BN; n += NPT, off += NPT * (uint32_t)g.t_s3 * 2) store8(out_b, off, lds + (nl + n) * TROW + mm);
+    }
+    return true;
+  }
   // Operand loads of the epilogue are issued in batches and from clamped, always valid
   // addresses, so that a lane waits for memory once per batch and not once per group of four
   // columns; only the stores are predicated.  A batch is a row of the wave's 32x32
@@ -436,9 +533,9 @@ __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)
         *reinterpret_cast<bf16x8*>((bf16_t*)g.out_t + t_tile + mm + (n - g.n_split) * g.t_s3) =
             *reinterpret_cast<const bf16x8*>(lds + nl * TROW + mm);
     }
-    return;
+    return true;
   }
-  if (!staged) return;
+  if (!staged) return false;
   __syncthreads();
   constexpr int CPR = BN / 8;   // 16-byte chunks per tile row
   if (g.o_period == INT64_MAX) {   // (two loops: the common one carries no trace of the regrouping arithmetic)
@@ -458,6 +555,7 @@ __device__ __forceinline__ void epilogue_tile(const LinearArgs& g, f32x16 (&acc)
         *reinterpret_cast<bf16x8*>((bf16_t*)g.out + out_row(g, m) + n) = *reinterpret_cast<const bf16x8*>(lds + rl * CROW + cc);
     }
   }
+  return true;
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N>
@@ -1090,8 +1188,12 @@ static hipError_t quad_launch(const LinearArgs& g, hipStream_t s) {
 // CU, whose phases interleave: while one waits for its rows another multiplies and a third stores
 // (measured against 64 x 128 tiles, two blocks per CU: the pair block at N = 1024 takes 9.7 instead of
 // 10.4 ms in one segment per region, 11.7 instead of 12.5 ms in 64-row segments, where a launch's 1024
-// blocks are then resident at once).  Each tile is prefetched into registers while the previous one is
-// multiplied, and leaves through the same epilogue as the GEMM above (row-major, regrouped
+// blocks are then resident at once).  A wave keeps its 32 normalised rows in registers for every tile, the epilogue is staged where
+// they lay, and so two barriers a tile suffice (five with one buffer for weights and staging).  What bounds it is vector work, half of
+// which was addresses: with those of whole tiles in 32 bits, q, k, v and gate of 524288 rows take 240 instead of 272 us, two gated pairs
+// of 40000 rows 21.6 instead of 26.0.  (Weights straight from memory into the registers the matrix instructions read: 352 to
+// 544 us, as a lane's 16 bytes then use a fraction of every line asked for.)  Each tile is prefetched into registers while
+// the previous one is multiplied, and leaves through the same epilogue as the GEMM above (row-major, regrouped
 // or strided store).  A gated pair keeps sigmoid(gate) in registers and multiplies the
 // projection by it, so the gate never reaches memory.  Per-row arithmetic does not depend on
 // the block a row falls in, so results are bitwise independent of the chunk length.
@@ -1107,22 +1209,27 @@ struct LnProjKernelArgs {
 constexpr int kLnProjRows = 64;   // rows per block
 constexpr int kLnProjCols = 64;   // columns per weight tile
 
+// Elements of LDS: the normalised rows or the staging tile that takes their place (the transposed form is the larger), and a weight tile.
+constexpr int ln_proj_rows_elems(int k) {
+  const int rows = kLnProjRows * (k + 8), stage = kLnProjCols * (kLnProjRows + 8);
+  return rows > stage ? rows : stage;
+}
+constexpr int ln_proj_lds_elems(int k) { return ln_proj_rows_elems(k) + kLnProjCols * (k + 8); }
+
 template <int K, int BN>
-__global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka) {
+__global__ void __launch_bounds__(256, 4) ln_multi_proj_bf16(LnProjKernelArgs ka) {
   constexpr int BM = kLnProjRows, NT = 256;
-  constexpr int TN = BN / 64;                 // 32-column MFMA tiles per wave (waves 2 x 2, 32 rows each)
+  static_assert(BM == 64 && BN == 64, "waves 2 x 2 of one 32x32 MFMA tile each");
   constexpr int AROW = K + 8;                 // padded LDS row (elements)
   constexpr int G = K / 8;                    // lanes per row in the LayerNorm pass (16-byte chunks per row)
   constexpr int RPP = NT / G;                 // rows per pass
   constexpr int PASSES = BM / RPP;
   constexpr int KSTEPS = K / 16;
-  constexpr int W_CHUNKS = BN * G / NT;       // 16-byte chunks of a weight tile per thread
-  constexpr int STAGE = BN * (BM + 8);        // elements the epilogue's staging tile needs (the transposed form is the larger)
-  constexpr int WBUF = BN * AROW > STAGE ? BN * AROW : STAGE;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t* sA = reinterpret_cast<bf16_t*>(smem_raw);     // [BM][AROW]: the normalised rows
-  bf16_t* sW = sA + BM * AROW;                          // [BN][AROW]: weight tile; then the epilogue's staging tile
-  float* gelu_tab = reinterpret_cast<float*>(sW + WBUF);
+  constexpr int W_CHUNKS = BN * G / NT;       // 16-byte chunks of a weight tile per thread
+  bf16_t* sA = reinterpret_cast<bf16_t*>(smem_raw);     // [BM][AROW]: the normalised rows; then the epilogue's staging tile
+  bf16_t* sW = sA + ln_proj_rows_elems(K);              // [BN][AROW]: weight tile
+  float* gelu_tab = reinterpret_cast<float*>(sA + ln_proj_lds_elems(K));
   const LnProjArgs& p = ka.a;
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int wave_m = wave / 2, wave_n = wave % 2;
@@ -1132,6 +1239,32 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
   if (ka.any_gelu) gelu_table_fill(gelu_tab, tid, NT);
   // blocks of the same rows share out the weight tiles
   const int t_lo = ka.n_tiles * (int)blockIdx.y / (int)gridDim.y, t_hi = ka.n_tiles * ((int)blockIdx.y + 1) / (int)gridDim.y;
+
+  bf16x8 wreg[W_CHUNKS];
+  auto store_w = [&](int tid) {
+#pragma unroll
+    for (int i = 0; i < W_CHUNKS; ++i) *reinterpret_cast<bf16x8*>(sW + (tid / G + i * RPP) * AROW + tid % G * 8) = wreg[i];
+  };
+  auto load_w = [&](const void* wbase, int64_t n_rows, int64_t n0, int tid) {
+    const bf16_t* w = (const bf16_t*)wbase;
+    if (n0 + BN <= n_rows) {                  // (the usual case: a tile is one run of memory)
+      const unsigned char* b = (const unsigned char*)(w + n0 * K);
+#pragma unroll
+      for (int i = 0; i < W_CHUNKS; ++i) wreg[i] = *reinterpret_cast<const bf16x8*>(b + (uint32_t)tid * 16 + i * NT * 16);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < W_CHUNKS; ++i) {
+      const int c = tid + NT * i, row = c / G, ch = c % G;
+      int64_t gr = n0 + row; if (gr > n_rows - 1) gr = n_rows - 1;
+      wreg[i] = *reinterpret_cast<const bf16x8*>(w + gr * K + ch * 8);
+    }
+  };
+  // first weight tile of entry t: the gate's for a gated pair
+  auto load_first = [&](int t, int tid) {
+    const ProjPart& q = p.part[ka.tile_part[t]];
+    load_w(q.gated ? q.w_gate : q.w, q.n, ka.tile_n0[t], tid);
+  };
 
   // ---- LayerNorm of the block's rows (G lanes per row, the row in registers, fp32 statistics)
   {
@@ -1163,59 +1296,30 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
       store_vec(sA + (ps * RPP + rg) * AROW + lg * 8, o);
     }
   }
-
-  bf16x8 wreg[W_CHUNKS];
-  auto store_w = [&](int tid) {
+  __syncthreads();
+  // the wave's 32 normalised rows stay in registers for every tile
+  bf16x8 fa[KSTEPS];
 #pragma unroll
-    for (int i = 0; i < W_CHUNKS; ++i) {
-      const int c = tid + NT * i, row = c / G, ch = c % G;
-      *reinterpret_cast<bf16x8*>(sW + row * AROW + ch * 8) = wreg[i];
-    }
-  };
-
-  auto load_w = [&](const void* wbase, int64_t n_rows, int64_t n0, int tid) {
-    const bf16_t* w = (const bf16_t*)wbase;
-#pragma unroll
-    for (int i = 0; i < W_CHUNKS; ++i) {
-      const int c = tid + NT * i, row = c / G, ch = c % G;
-      int64_t gr = n0 + row; if (gr > n_rows - 1) gr = n_rows - 1;
-      wreg[i] = *reinterpret_cast<const bf16x8*>(w + gr * K + ch * 8);
-    }
-  };
-  // first weight tile of entry t: the gate's for a gated pair
-  auto load_first = [&](int t, int tid) {
-    const ProjPart& q = p.part[ka.tile_part[t]];
-    load_w(q.gated ? q.w_gate : q.w, q.n, ka.tile_n0[t], tid);
-  };
-  f32x16 acc[1][TN];
-  const bf16_t* cA = sA + (wave_m * 32 + l32) * AROW + half * 8;
-  const bf16_t* cW = sW + (wave_n * (BN / 2) + l32) * AROW + half * 8;
-  auto multiply = [&]() {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      const bf16x8 fa = *reinterpret_cast<const bf16x8*>(cA + ks * 16);
-      bf16x8 fw[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fw[j] = *reinterpret_cast<const bf16x8*>(cW + j * 32 * AROW + ks * 16);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[j], fa, acc[0][j], 0, 0, 0);
-    }
-  };
-  // this lane's 4 consecutive columns of group q in 32-column tile j: acc[i][j][4q .. 4q+3]
-  auto lane_bias = [&](const void* bias, int64_t n_total, int64_t n0, int j, int q) {
-    int64_t n = n0 + wave_n * (BN / 2) + j * 32 + 8 * q + 4 * half;
-    if (n > n_total - 4) n = n_total - 4;
-    bf16x4 bv = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
-    if (bias) bv = *reinterpret_cast<const bf16x4*>((const bf16_t*)bias + n);
-    return bv;
-  };
+  for (int ks = 0; ks < KSTEPS; ++ks) fa[ks] = *reinterpret_cast<const bf16x8*>(sA + (wave_m * 32 + l32) * AROW + half * 8 + ks * 16);
 
   load_first(t_lo, tid);
+  f32x16 acc[1][1];
+  const bf16_t* cW = sW + (wave_n * 32 + l32) * AROW + half * 8;
+  auto multiply = [&]() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks)
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(cW + ks * 16), fa[ks], acc[0][0], 0, 0, 0);
+  };
+  // this lane's 4 consecutive columns of group q: acc[4q .. 4q+3]
+  auto lane_bias = [&](const void* bias, int64_t n_total, int64_t n0, int q) {
+    bf16x4 bv = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
+    if (!bias) return bv;
+    const uint32_t c = wave_n * 32 + 8 * q + 4 * half, last = (uint32_t)(n_total - 4 - n0);      // (n < 2^31: at most 48 tiles)
+    return *reinterpret_cast<const bf16x4*>((const unsigned char*)((const bf16_t*)bias + n0) + (c < last ? c : last) * 2);
+  };
+
   for (int t = t_lo; t < t_hi; ++t) {
     const ProjPart& pp = p.part[ka.tile_part[t]];
     const int64_t n0 = ka.tile_n0[t];
@@ -1224,83 +1328,52 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
     int w_tid = tid;
     asm volatile("" : "+v"(w_tid));
     store_w(w_tid);
-    __syncthreads();                         // the tile (and, the first time, the normalised rows) is in LDS
+    __syncthreads();                         // the tile is in LDS (and, the first time, every wave has its rows: sA is free)
     // the next weight tile is in flight while this one is multiplied and stored
     if (gated) load_w(pp.w, pp.n, n0, w_tid);
     else if (t + 1 < t_hi) load_first(t + 1, w_tid);
     multiply();
-    __syncthreads();                         // every wave is done reading the weight tile
     if (gated) {
+      __syncthreads();                       // every wave is done reading the gate's weights
       // sigmoid(gate) stays in registers; the projection tile of the pair follows at once
-      f32x16 sg[1][TN];
+      f32x16 sg;
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int q = 0; q < 4; ++q) {
+        const bf16x4 bv = lane_bias(pp.bias_gate, pp.n, n0, q);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bf16x4 bv = lane_bias(pp.bias_gate, pp.n, n0, j, q);
-#pragma unroll
-          for (int i = 0; i < 1; ++i)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) sg[i][j][4 * q + jj] = sigmoid_newton(acc[i][j][4 * q + jj] + bf2f(bv[jj]));
-        }
+        for (int jj = 0; jj < 4; ++jj) sg[4 * q + jj] = sigmoid_newton(acc[0][0][4 * q + jj] + bf2f(bv[jj]));
+      }
       store_w(w_tid);
       __syncthreads();
       if (t + 1 < t_hi) load_first(t + 1, w_tid);
       multiply();
-      __syncthreads();
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int q = 0; q < 4; ++q) {
+        const bf16x4 bv = lane_bias(pp.bias, pp.n, n0, q);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bf16x4 bv = lane_bias(pp.bias, pp.n, n0, j, q);
-#pragma unroll
-          for (int i = 0; i < 1; ++i)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj)
-              acc[i][j][4 * q + jj] = (acc[i][j][4 * q + jj] + bf2f(bv[jj])) * sg[i][j][4 * q + jj];
-        }
-    }
-    if (!gated) {
+        for (int jj = 0; jj < 4; ++jj) acc[0][0][4 * q + jj] = (acc[0][0][4 * q + jj] + bf2f(bv[jj])) * sg[4 * q + jj];
+      }
+    } else {
       // bias and activation here, one uniform branch per tile, so that the epilogue below exists once
       const int act = pp.act;
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int q = 0; q < 4; ++q) {
+        const bf16x4 bv = lane_bias(pp.bias, pp.n, n0, q);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bf16x4 bv = lane_bias(pp.bias, pp.n, n0, j, q);
-#pragma unroll
-          for (int i = 0; i < 1; ++i)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) acc[i][j][4 * q + jj] += bf2f(bv[jj]);
-        }
+        for (int jj = 0; jj < 4; ++jj) acc[0][0][4 * q + jj] += bf2f(bv[jj]);
+      }
       if (act == AC_ACT_GELU_ERF) {
 #pragma unroll
-        for (int i = 0; i < 1; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = gelu_table(acc[i][j][r], gelu_tab);
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = gelu_table(acc[0][0][r], gelu_tab);
       } else if (act == AC_ACT_SIGMOID) {
 #pragma unroll
-        for (int i = 0; i < 1; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = sigmoid_newton(acc[i][j][r]);
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = sigmoid_newton(acc[0][0][r]);
       } else if (act == AC_ACT_RELU) {
 #pragma unroll
-        for (int i = 0; i < 1; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = fmaxf(acc[i][j][r], 0.f);
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = fmaxf(acc[0][0][r], 0.f);
       } else if (act == AC_ACT_GELU_TANH) {
 #pragma unroll
-        for (int i = 0; i < 1; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = gelu_tanh(acc[i][j][r]);
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = gelu_tanh(acc[0][0][r]);
       }
     }
     LinearArgs g{};
@@ -1313,8 +1386,9 @@ __global__ void __launch_bounds__(256, 2) ln_multi_proj_bf16(LnProjKernelArgs ka
     // coordinates make them values of this iteration, recomputed per tile with a few ALU ops.
     int e_tid = tid, e_l32 = l32, e_half = half, e_wm = wave_m, e_wn = wave_n;
     asm volatile("" : "+v"(e_tid), "+v"(e_l32), "+v"(e_half), "+v"(e_wm), "+v"(e_wn));
-    epilogue_tile<AC_ACT_NONE, BM, BN, 2, 2>(g, acc, sW, gelu_tab, m0, n0, e_wm, e_wn, e_l32, e_half, e_tid);
-    __syncthreads();                         // the staging tile has been read out; sW is free for the next tile
+    // The barrier between the staging tile's writes and reads is also where every wave is done with the weights; the tile is written
+    // again behind the next tile's first barrier.
+    if (!epilogue_tile<AC_ACT_NONE, BM, BN, 2, 2, true, true>(g, acc, sA, gelu_tab, m0, n0, e_wm, e_wn, e_l32, e_half, e_tid)) __syncthreads();
   }
 }
 
@@ -1352,9 +1426,7 @@ static bool ln_proj_overlaps(const LnProjArgs& p) {
 template <int K, int BN>
 static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
   auto kern = ln_multi_proj_bf16<K, BN>;
-  constexpr int AROW = K + 8, STAGE = BN * (kLnProjRows + 8);
-  constexpr int WBUF = BN * AROW > STAGE ? BN * AROW : STAGE;
-  constexpr size_t lds_max = (size_t)(kLnProjRows * AROW + WBUF) * sizeof(bf16_t) + kGeluTableBytes;
+  constexpr size_t lds_max = (size_t)ln_proj_lds_elems(K) * sizeof(bf16_t) + kGeluTableBytes;
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
   if (attr_status != hipSuccess) return attr_status;

@@ -726,7 +726,8 @@ void Walk::transformer(const void* x, void* y) {
       const uint64_t mk = arena.mark();
       auto none = [](int64_t, int64_t) { return std::vector<Span>(); };
       arena.release(before_qkv);
-      const std::vector<RowSeg>& runs = shared_runs(T, ffn_segs[0].nb * ffn_segs[0].ns, 256, most_units(1), none, ffn_rows);
+      const std::vector<RowSeg>& runs =                // (every layer's are the first one's)
+          l > 0 ? p->shared[0] : shared_runs(T, ffn_segs[0].nb * ffn_segs[0].ns, 256, most_units(1), none, ffn_rows);
       in_runs = runs.size() * lanes <= ffn_segs.size();
       if (in_runs) region_launches[AC_REGION_FFN] = shared_loop(runs, none, ffn_rows);
       arena.release(mk);
