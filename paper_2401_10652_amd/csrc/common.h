@@ -157,6 +157,8 @@ struct LinearArgs {
   // position may be left unwritten; kCausalDepth: a's terms past a row's position are zeros and may be left out.
   int causal;
   int64_t q_offset;
+  // gate > 0 (where linear_takes_gate: erf GELU): w and bias hold n = `gate` value rows and then as many gate rows, and out = value * act(gate).
+  int64_t gate;
   // bias_period > 0: row m takes bias row m / bias_period (bias is [m / bias_period][n]): one bias vector per image
   int64_t bias_period;
 };
@@ -219,6 +221,7 @@ hipError_t launch_binary(const void* a, int64_t lda, const void* b, int64_t ldb,
                          int64_t rows, int64_t cols, int op, int dtype, hipStream_t s);
 hipError_t launch_linear(const LinearArgs& g, hipStream_t s);
 bool linear_takes_causal(const LinearArgs& g);
+bool linear_takes_gate(const LinearArgs& g);
 const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);

@@ -824,10 +824,49 @@ __device__ __forceinline__ void finish_tile(const LinearArgs& g, f32x16 (&acc)[B
   }
 }
 
+// A gated product's tile: the 32-row blocks of its weight rows are value rows and the gate rows of the same columns in turn, so a wave's two
+// accumulator tiles of a row are both halves of 32 outputs, which meet here in fp32 (stored in between and multiplied by a pass of their own,
+// 2 x 1280 columns of 8192 rows took 16.9 + 13.3 us and rounded both halves to bf16).
+__device__ __forceinline__ int64_t gate_weight_row(const LinearArgs& g, int r, int64_t last) {   // relative to the tile's first column
+  const int64_t c = r / 64 * 32 + r % 32;
+  return (c < last ? c : last) + (r / 32 % 2) * g.gate;
+}
+template <int ACT, int TM>
+__device__ __forceinline__ void gate_tile(const LinearArgs& g, f32x16 (&acc)[TM][2], int64_t n) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bf16x4 zero4 = {};
+    const int64_t c = n + 8 * q < g.n ? n + 8 * q : g.n - 4;
+    const bf16x4 bv = g.bias ? *reinterpret_cast<const bf16x4*>((const bf16_t*)g.bias + c) : zero4;
+    const bf16x4 bg = g.bias ? *reinterpret_cast<const bf16x4*>((const bf16_t*)g.bias + g.gate + c) : zero4;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        acc[i][0][4 * q + jj] = (acc[i][0][4 * q + jj] + bf2f(bv[jj])) * apply_act_bf16<ACT>(acc[i][1][4 * q + jj] + bf2f(bg[jj]));
+    __builtin_amdgcn_sched_barrier(0);   // (a group of columns at a time: interleaved, their temporaries do not fit)
+  }
+}
+// (erf GELU, by its formula as the pass it replaces had it; the other activations keep that pass: tanhf alone spills 80 registers here)
+template <int BM, int BN, int WAVES_M, int WAVES_N>
+__device__ __forceinline__ void finish_gated(LinearArgs g, f32x16 (&acc)[BM / WAVES_M / 32][2], unsigned char* smem, int64_t m0, int64_t n0,
+                                             int wave_m, int wave_n, int l32, int half, int tid) {
+  static_assert(BN / WAVES_N == 64, "a value tile and a gate tile per wave");
+  constexpr int TM = BM / WAVES_M / 32;
+  const int64_t n = n0 + wave_n * 32 + 4 * half;
+  gate_tile<AC_ACT_GELU_ERF, TM>(g, acc, n);
+  g.bias = nullptr;
+  f32x16 out[TM][1];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) out[i][0] = acc[i][0];
+  epilogue_tile<AC_ACT_NONE, BM, BN / 2, WAVES_M, WAVES_N>(g, out, reinterpret_cast<bf16_t*>(smem), nullptr, m0, n0, wave_m, wave_n, l32, half, tid);
+}
+
 // WIDE: a convolution whose rows are too long for 32-bit offsets inside a tile (2^20 channels and more): 64 bits per lane, outside
 // pixels from a row of zeros.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false, bool WIDE = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false, bool WIDE = false, bool GATED = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(LinearArgs g) {
+  constexpr int BNO = GATED ? BN / 2 : BN;      // output columns of a tile
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   constexpr int ROWB = BK * 2, CPR = ROWB / 16, RPI = 1024 / ROWB;      // bytes and chunks per LDS row, rows per load instruction
@@ -843,8 +882,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
   const int l32 = lane % 32, half = lane / 32;
   int64_t tm_, tn_;
-  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_, g.causal ? blockIdx.y : 0);
-  const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BNO - 1) / BNO, tm_, tn_, g.causal ? blockIdx.y : 0);
+  const int64_t m0 = tm_ * BM, n0 = tn_ * BNO;
   if (tile_unseen(g, m0, n0, BM)) return;
   const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
   g.out = (bf16_t*)g.out + product * g.so_b;
@@ -883,7 +922,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
   for (int i = 0; i < W_I; ++i) {
     const int64_t last = g.n - 1 - n0;
     const int row = (wave + NW * i) * RPI + row_in;
-    w_off[i] = (Off)((row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
+    w_off[i] = (Off)((GATED ? gate_weight_row(g, row, last) : row < last ? row : last) * g.ldw * 2) + src_chunk * 16;
   }
   // (addresses: base and tile offset in scalar registers, 32 bits per lane; every lane's address is valid, so the range is open but for CONV's outside pixels)
   constexpr int kARange = CONV ? 0x7fffffff : -1;
@@ -1010,7 +1049,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
     step(fa[1], fw[1], fa[0], fw[0]);
     if (kt >= kt_count) break;
   }
-  finish_tile<BM, BN, WAVES_M, WAVES_N, !RAGGED_K>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
+  if constexpr (GATED) finish_gated<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, m0, n0, wave_m, wave_n, l32, half, tid);
+  else finish_tile<BM, BN, WAVES_M, WAVES_N, !RAGGED_K>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1030,7 +1070,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) linear_ring_bf16(Linea
 // (1337 TFLOP/s; 1811 and 1873), 65536 x 8192 x 2048 in 1836 (2041 and 2011), 4000 x 4096 x 1024 in 35.8 (38.3 and 38.1).
 // Same matrix instructions in the same k order per output as the kernels above: equal bits.
 // ------------------------------------------------------------------------------------
+template <bool GATED>
 __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
+  constexpr int BNO = GATED ? 128 : 256;                                // output columns of a tile
   constexpr int BM = 256, BN = 256, WAVES_M = 2, WAVES_N = 4, TM = 4, TN = 2, BK = 64, ROWB = 128;
   constexpr int BUF = (BM + BN) * ROWB;                                 // bytes of one tile
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -1039,8 +1081,8 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
   const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
   const int l32 = lane % 32, half = lane / 32;
   int64_t tm_, tn_;
-  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_, g.causal ? blockIdx.y : 0);
-  const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BNO - 1) / BNO, tm_, tn_, g.causal ? blockIdx.y : 0);
+  const int64_t m0 = tm_ * BM, n0 = tn_ * BNO;
   if (tile_unseen(g, m0, n0, BM)) return;
   const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
   g.out = (bf16_t*)g.out + product * g.so_b;
@@ -1062,7 +1104,7 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
       const int64_t la = g.m - 1 - m0, lw = g.n - 1 - n0;
       const int ra = a_row(h, j) + row_in, rw = w_row(h, j) + row_in;
       a_off[h][j] = (uint32_t)((ra < la ? ra : la) * g.lda * 2) + src_chunk * 16;
-      w_off[h][j] = (uint32_t)((rw < lw ? rw : lw) * g.ldw * 2) + src_chunk * 16;
+      w_off[h][j] = (uint32_t)((GATED ? gate_weight_row(g, rw, lw) : rw < lw ? rw : lw) * g.ldw * 2) + src_chunk * 16;
     }
   auto load_half = [&](int kt, int h, int x) {                          // instruction x of the four of half h of tile kt
     unsigned char* dst = smem_raw + (kt & 1) * BUF + (x < 2 ? a_row(h, x) : BM + w_row(h, x - 2)) * ROWB;
@@ -1150,30 +1192,33 @@ __global__ void __launch_bounds__(512) linear_quad_bf16(LinearArgs g) {
     step_y(kt + 1, wb, wa);
     if (kt + 2 >= kt_count) break;
   }
-  finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
+  if constexpr (GATED) finish_gated<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, m0, n0, wave_m, wave_n, l32, half, tid);
+  else finish_tile<BM, BN, WAVES_M, WAVES_N>(g, acc, smem_raw, gelu_tab, m0, n0, wave_m, wave_n, l32, half, tid);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false, bool WIDE = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool CONV = false, bool RAGGED_K = false, bool WIDE = false, bool GATED = false>
 static hipError_t ring_launch(const LinearArgs& g, hipStream_t s) {
-  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV, RAGGED_K, WIDE>;
+  constexpr int BNO = GATED ? BN / 2 : BN;
+  auto kern = linear_ring_bf16<BM, BN, WAVES_M, WAVES_N, BK, STAGES, CONV, RAGGED_K, WIDE, GATED>;
   constexpr size_t ring = ring_lds_bytes(BM, BN, BK, STAGES);
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(ring + kGeluTableBytes));
   if (attr_status != hipSuccess) return attr_status;
-  const int64_t tiles = ((g.m + BM - 1) / BM) * ((g.n + BN - 1) / BN);
+  const int64_t tiles = ((g.m + BM - 1) / BM) * ((g.n + BNO - 1) / BNO);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)g.batch), dim3(64 * WAVES_M * WAVES_N),
-                     ring + (g.act == AC_ACT_GELU_ERF && !RAGGED_K ? kGeluTableBytes : 0), s, g);
+                     ring + (g.act == AC_ACT_GELU_ERF && !RAGGED_K && !GATED ? kGeluTableBytes : 0), s, g);
   return hipGetLastError();
 }
 
+template <bool GATED>
 static hipError_t quad_launch(const LinearArgs& g, hipStream_t s) {
   constexpr size_t lds = ring_lds_bytes(256, 256, 64, 2);
   static const hipError_t attr_status = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(linear_quad_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds + kGeluTableBytes));
+      reinterpret_cast<const void*>(linear_quad_bf16<GATED>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds + kGeluTableBytes));
   if (attr_status != hipSuccess) return attr_status;
-  const int64_t tiles = ((g.m + 255) / 256) * ((g.n + 255) / 256);
-  hipLaunchKernelGGL(linear_quad_bf16, dim3((unsigned)tiles, (unsigned)g.batch), dim3(512),
-                     lds + (g.act == AC_ACT_GELU_ERF ? kGeluTableBytes : 0), s, g);
+  const int64_t tiles = ((g.m + 255) / 256) * (GATED ? (g.n + 127) / 128 : (g.n + 255) / 256);
+  hipLaunchKernelGGL(linear_quad_bf16<GATED>, dim3((unsigned)tiles, (unsigned)g.batch), dim3(512),
+                     lds + (g.act == AC_ACT_GELU_ERF && !GATED ? kGeluTableBytes : 0), s, g);
   return hipGetLastError();
 }
 
@@ -1663,6 +1708,14 @@ bool linear_takes_causal(const LinearArgs& g_in) {
   return g.dtype == AC_BF16 && linear_route(g) != kFma;
 }
 
+// A gated product: erf GELU, whole k tiles, no other epilogue operand, and its weight rows within 32-bit byte offsets of a tile.
+bool linear_takes_gate(const LinearArgs& g_in) {
+  LinearArgs g = g_in;
+  g.o_period = g.t_period = INT64_MAX;
+  return g.dtype == AC_BF16 && g.act == AC_ACT_GELU_ERF && g.k % kBK == 0 && g.n == g.gate && g.n_split == g.n && g.batch <= 1 && !g.mul && !g.resid && g.conv_c == 0 && g.bias_period == 0 &&
+         !wide_rows(g) && (g.gate + 256) * g.ldw < (1ll << 30) && g.m <= 0x7fffffffLL && aligned_to(g.bias, 8) && mfma_eligible(g);
+}
+
 const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype) {
   LinearArgs g{};
   g.m = m; g.n = g.n_split = g.ldo = n; g.k = k; g.lda = lda; g.ldw = ldw; g.batch = batch; g.dtype = dtype; g.o_period = g.t_period = INT64_MAX;
@@ -1691,12 +1744,19 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     g.lda = g.conv_c;
     if (!mfma_eligible(g)) return hipErrorInvalidValue;
   }
+  if (g.gate > 0) {
+    if (!linear_takes_gate(g_in)) return hipErrorInvalidValue;
+    // (of the two shapes whose waves hold 64 columns, by the same prices: 256x256 where its rounds are full)
+    LinearArgs both = g;
+    both.n = 2 * g.n;
+    return best_tile(both, kPlain) == kQuad ? quad_launch<true>(g, s) : ring_launch<256, 128, 4, 2, 64, 3, false, false, false, true>(g, s);
+  }
   switch (linear_route(g)) {
     case kF32_32x64: return mfma_f32_launch<2, 4>(g, s);
     case kF32_32x32: return mfma_f32_launch<2, 2>(g, s);
     case kF32_32x16: return mfma_f32_launch<2, 1>(g, s);
     case kF32_16x16: return mfma_f32_launch<1, 1>(g, s);
-    case kRouteQuad: return quad_launch(g, s);
+    case kRouteQuad: return quad_launch<false>(g, s);
     case kRing256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
     case kRing128x128: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);
     case kRing128x192: return ring_launch<128, 192, 4, 2, 64, 3>(g, s);

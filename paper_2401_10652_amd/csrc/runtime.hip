@@ -1212,8 +1212,13 @@ void Walk::res_stack(const void* x, void* y) {
       void* vt = arena.push((uint64_t)T * C * e);       // v transposed per image: [image][C][HW]
       void* ctx = arena.push((uint64_t)T * C * e);
       void *hid = nullptr, *act = nullptr;
+      // The gated product multiplies its halves where it makes them; the plan counts the first layer's rows all the same.
+      LinearArgs up{};
+      up.a = u; up.lda = C; up.w = W(AB_W_1); up.ldw = C; up.bias = W(AB_B_1); up.act = m.activation; up.m = T; up.n = up.n_split = up.ldo = up.gate = F; up.k = C;
+      up.dtype = dt;
+      const bool one_pass = gated && linear_takes_gate(up);
       auto push_hidden = [&] {
-        hid = arena.push((uint64_t)T * (gated ? 2 : 1) * F * e);
+        if (!tight || !one_pass) hid = arena.push((uint64_t)T * (gated ? 2 : 1) * F * e);
         act = gated ? arena.push((uint64_t)T * F * e) : hid;
       };
       if (!tight) push_hidden();
@@ -1256,7 +1261,11 @@ void Walk::res_stack(const void* x, void* y) {
       }
       ln(t, C, W(AB_LN2_G), W(AB_LN2_B), u, C, T, C);
       if (tight) { arena.release(mk); push_hidden(); }
-      if (gated) {
+      if (one_pass) {
+        up.out = act;
+        const double by = ((double)T * C + 2.0 * F * C + (double)T * F) * e;
+        run(K_GEMM, 2.0 * T * 2 * F * C + 1.0 * T * F, by, "linear", [&] { return launch_linear(up, stream); });
+      } else if (gated) {
         proj(u, C, W(AB_W_1), C, W(AB_B_1), AC_ACT_NONE, nullptr, 0, hid, 2 * F, T, 2 * F);
         void* gate = atw(hid, F);
         // one pass over both halves (activation and product apart, the activated gate rounded and stored in between:
