@@ -210,7 +210,8 @@ struct Walk {
   // are dead (q, k and v during the feed-forward; the rows of the result that no segment has written yet).  So units
   // [0, extent) of a region cut into segments of `len` run in the fewest runs whose pushes stay below the plan's high-water mark
   // or in the spans that idle(first, units) names, of about equal length (a multiple of `granule` where it matters), at most
-  // `most` units each.  Rows keep their arithmetic, so the bits do not depend on it.  A short launch costs its fixed 4 to
+  // `most` units each.  Rows keep their arithmetic, so the bits do not depend on it, but where attention cuts the keys of one launch into
+  // more runs than of another (attention_key_splits): there results are equal to rounding.  A short launch costs its fixed 4 to
   // 5 us and leaves CUs without work: 512 rows through a 768 x 3072 feed-forward take 10.4 + 12.6 us, 2048 rows 21 + 23; a stack of
   // twelve such layers cut into 512-row segments 3.92 -> 2.80 ms, the pair block at N = 1024 in 64-row segments 12.05 -> 9.49.
   // Decided by the dry run that ends planning (`deciding`) and kept in the plan; without it, and where two segments in flight would need
@@ -237,16 +238,28 @@ struct Walk {
         measuring = false;
         return !arena.full;
       };
-      for (int64_t i = 0; i < extent; i += runs.back().ni) {
+      // A run is kept only if its own walk fitted.  Fewer units can need more scratch (the key splits' partial results), and the last run has
+      // no unwritten rows to borrow, so no length but the caller's own segments, which the plan was sized by, fits by construction.
+      const int64_t own = ceil_div(extent, len);
+      for (int64_t i = 0; i < extent && (int64_t)runs.size() < own; i += runs.back().ni) {
         const int64_t left = extent - i;
         int64_t lo = std::min(len, left), hi = std::max(lo, std::min(left, most));
-        if (fits(i, hi)) lo = hi;
-        while (lo + 1 < hi) {
-          const int64_t mid = lo + (hi - lo) / 2;
-          if (fits(i, mid)) lo = mid; else hi = mid;
+        if (fits(i, hi)) {
+          lo = hi;
+        } else {
+          while (lo + 1 < hi) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            if (fits(i, mid)) lo = mid; else hi = mid;
+          }
+          while (lo > 0 && !fits(i, lo)) --lo;
         }
+        if (lo == 0) break;
         const int64_t even = ceil_div(ceil_div(left, ceil_div(left, lo)), granule) * granule;
         runs.push_back(RowSeg{i, even < lo && fits(i, even) ? even : lo});
+      }
+      if (runs.empty() || runs.back().i0 + runs.back().ni < extent) {   // (no run of any length, or more of them than segments)
+        runs.clear();
+        for (int64_t i = 0; i < extent; i += len) runs.push_back(RowSeg{i, std::min(len, extent - i)});
       }
       p->shared.push_back(std::move(runs));
       arena.release(base);
@@ -1367,7 +1380,8 @@ static bool dim_legal(const ac_model_desc& m, int kind, int dim, bool& known) {
   return false;
 }
 
-static void dry_run(ac_plan* p, bool unchunked, uint64_t& arena_bytes, double& flops,
+// False if the walk needs more than `limit`.
+static bool dry_run(ac_plan* p, bool unchunked, uint64_t& arena_bytes, double& flops,
                     uint64_t* region_high = nullptr, uint64_t limit = UINT64_MAX) {
   Walk wk{p, true, unchunked, nullptr};
   wk.arena.limit = limit;
@@ -1382,6 +1396,7 @@ static void dry_run(ac_plan* p, bool unchunked, uint64_t& arena_bytes, double& f
   if (region_high) memcpy(region_high, wk.region_high, sizeof(wk.region_high));
   if (wk.deciding) memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches));
   else if (!unchunked) { p->sync_needed = wk.sync_events; memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches)); }
+  return wk.ok();
 }
 
 static uint64_t io_bytes(const ac_model_desc& m) {
@@ -1690,7 +1705,10 @@ int ac_plan_create(const ac_model_desc* model, const ac_region_desc* regions, in
   double f1 = 0;
   dry_run(p, true, arena1, f1);
   uint64_t same = 0;
-  dry_run(p, false, same, f1, nullptr, arena);
+  if (!dry_run(p, false, same, f1, nullptr, arena)) {   // (not while shared_runs falls back to the caller's segments)
+    delete p;
+    return fail(AC_ERR_STATE, "segments that share launches do not fit in %llu bytes", (unsigned long long)arena);
+  }
   inf.peak_bytes_unchunked_planned = inf.io_bytes + arena1;
   inf.n_regions = count;
   for (int k = first; k < first + count; ++k) {

@@ -1,0 +1,84 @@
+"""Plans whose segments share launches run to their end: the walk of ac_execute with the kernel launches stubbed out, so that no GPU
+is needed and no pointer is followed."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+STUB = """
+#include <stddef.h>
+typedef struct { unsigned x, y, z; } grid3;
+int hipLaunchKernel(const void* f, grid3 g, grid3 b, void** args, size_t lds, void* stream) { return 0; }
+int hipFuncSetAttribute(const void* f, int attribute, int value) { return 0; }
+int hipGetLastError(void) { return 0; }
+"""
+
+WALK = """
+import ctypes, random, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)          # before the library: its references go to the stubs
+from paper_2401_10652_amd import binding as B, inputs as I
+L = B.lib()
+
+def walk(what, desc, regions):
+    plan = B.Plan(desc, regions)
+    info = plan.ac_plan_query()
+    ptrs = (B.VP * info.n_weights)(*[(1 << 44) + 256 * i for i in range(info.n_weights)])
+    assert L.ac_plan_bind_weights(plan._h, ptrs, info.n_weights) == 0
+    peak = B.U64(0)
+    status = L.ac_execute(plan._h, 1 << 40, 1 << 41, 1 << 42, info.workspace_bytes, None, ctypes.byref(peak))
+    assert status == 0, (what, L.ac_last_error())
+    assert peak.value <= info.peak_bytes_planned, what
+    assert all(r.launches <= r.n_segments for r in info.regions[:info.n_regions]), what
+
+def unet(batch, h, w, c, heads, f, c_res, c_attn, gated=False, context=0, layers=1):
+    cfg = I.ResStackConfig("plan", 1, layers, batch, h, w, c, 16, heads=heads, d_ffn=f, gated=gated,
+                           context_tokens=context, context_dim=64 if context else 0)
+    walk(("unet", batch, h, w, c, heads, f, c_res, c_attn, gated, context, layers), B.res_stack_desc(cfg),
+         [(B.AC_REGION_RES_BLOCK, B.AC_DIM_BATCH, c_res), (B.AC_REGION_UNET_ATTN, B.AC_DIM_BATCH, c_attn)])
+
+def pair(n, c_z, heads, dh, settings):
+    cfg = I.PairConfig("plan", 1, n, c_z, 64, heads, dh, 2, "bf16")
+    walk(("pair", n, c_z, heads, dh, settings), B.pair_desc(cfg, flags=B.AC_FLAG_LISTED_REGIONS_ONLY), [(k, B.AC_DIM_ROW, c) for k, c in settings])
+
+exec(sys.argv[2])
+"""
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("stub")
+    source, lib = folder / "stub.c", folder / "stub.so"
+    source.write_text(STUB)
+    subprocess.run(["cc", "-shared", "-fPIC", "-o", str(lib), str(source)], check=True)
+
+    def run(calls):
+        r = subprocess.run([sys.executable, "-c", WALK, str(lib), calls], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert r.returncode == 0, r.stdout
+    return run
+
+
+@pytest.mark.parametrize("call", [
+    "unet(14, 72, 16, 320, 5, 320, 9, 9)", "unet(16, 72, 16, 320, 5, 64, 9, 9)", "unet(17, 64, 24, 640, 10, 320, 4, 4)",
+    "unet(21, 64, 24, 192, 3, 192, 13, 13)", "unet(18, 80, 16, 128, 4, 192, 4, 11)", "unet(48, 40, 96, 128, 1, 256, 22, 9)",
+    "unet(35, 72, 48, 64, 2, 64, 23, 8)", "pair(1088, 64, 2, 32, [(B.AC_REGION_TRIATT_START, 23)])"])
+def test_a_short_run_needs_more_scratch_than_a_long_one(walk, call):
+    """A launch of few problems cuts their keys into more runs, each with partial results, and the last run of a region has no rows of
+    the result left to borrow: such a run must not be taken for one that fits."""
+    walk(call)
+
+
+def test_drawn_plans(walk):
+    walk("""
+rng = random.Random(2)
+for i in range(12000):
+    if i % 2:
+        n, listed = 8 * rng.randint(3, 225), sorted(rng.sample(range(B.AC_REGION_TRIMUL_OUT, B.AC_REGION_PAIR_TRANSITION + 1), rng.randint(1, 5)))
+        pair(n, 64, rng.choice([1, 2, 4]), rng.choice([16, 32, 64]), [(k, rng.randint(1, rng.choice([n, 1 + n // 20]))) for k in listed])
+    else:
+        batch, c, dh = rng.randint(1, 50), rng.choice([64, 128, 192, 320, 640]), rng.choice([32, 64])
+        unet(batch, 8 * rng.randint(1, 12), 8 * rng.randint(1, 12), c, c // dh, 64 * rng.randint(1, max(1, c // 16)), rng.randint(1, batch),
+             rng.randint(1, batch), rng.random() < 0.3, rng.choice([0, 0, 13]), rng.choice([1, 1, 2, 3]))
+""")
