@@ -977,7 +977,10 @@ template <int DH, bool CAUSAL, bool BIAS>
 static hipError_t mfma_attn_ragged(const AttnArgs& a, hipStream_t s) {
   if (a.sk % kKB == 0) return mfma_attn_rows<DH, CAUSAL, BIAS, kWholeTiles>(a, s);
   if constexpr (attention_pipelined(DH, BIAS, kWholeChunks)) {
-    if (a.sk % 8 == 0 && a.sk >= pipelined_from(DH)) {
+    // (the range that gives the zeros past the end is 2^31 bytes: rows of V^T that reach further, 128 of 8454664 elements and more, take
+    // the plain loop's 64-bit addresses; K's 64 rows of less than 2^24 elements do not)
+    const bool in_range = (DH - 1) * a.ldv * 2 + 2 * kKB < (1ll << 31);
+    if (a.sk % 8 == 0 && a.sk >= pipelined_from(DH) && in_range) {
       // (one instantiation: without a mask the queries stand behind all keys)
       AttnArgs c = a;
       if (!CAUSAL) { c.causal = 1; c.q_offset = a.sk - 1; }

@@ -83,3 +83,17 @@ def test_masks_over_the_first_tiles(B, dh, sk, mask):
         bias[:, 45:48] = mask          # a row of nothing else averages its values
     b32 = round_to_storage(bias.astype(np.float32), "bf16")
     check(run(B, q, k, v, heads, False, bias=b32), O.attention(q, k, v, heads, False, bias=b32), "bf16")
+
+
+@pytest.mark.parametrize("ldv", [8454656, 8454664, 9437184])
+def test_values_in_far_rows(B, ldv):
+    """Rows of V^T up to the 2^31 bytes of the pipelined loop's buffer, and beyond."""
+    import torch
+    sq, sk, dh = 100, 328, 128
+    q, k, v = (draw((n, dh), 320 + i, "bf16") for i, n in enumerate((sq, sk, sk)))
+    vb = torch.empty((dh, ldv), dtype=torch.bfloat16, device="cuda")
+    vb[:, :sk], vb[:, sk:sk + 64] = B.to_device(v, "bf16").T, float("nan")
+    ctx = torch.full((sq, dh), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.ac_op_attention(B.to_device(q, "bf16"), B.to_device(k, "bf16"), vb, ctx, 1, dh, v_transposed=True)
+    torch.cuda.synchronize()
+    check(host(ctx), O.attention(q, k, v, 1, False), "bf16")

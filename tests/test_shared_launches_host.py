@@ -1,34 +1,17 @@
 """Plans whose segments share launches run to their end: the walk of ac_execute with the kernel launches stubbed out, so that no GPU
 is needed and no pointer is followed."""
-import os
-import subprocess
-import sys
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-
-STUB = """
-#include <stddef.h>
-typedef struct { unsigned x, y, z; } grid3;
-int hipLaunchKernel(const void* f, grid3 g, grid3 b, void** args, size_t lds, void* stream) { return 0; }
-int hipFuncSetAttribute(const void* f, int attribute, int value) { return 0; }
-int hipGetLastError(void) { return 0; }
-"""
+import launch_stub
 
 WALK = """
-import ctypes, random, sys
-ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)          # before the library: its references go to the stubs
-from paper_2401_10652_amd import binding as B, inputs as I
-L = B.lib()
-
 def walk(what, desc, regions):
     plan = B.Plan(desc, regions)
     info = plan.ac_plan_query()
     ptrs = (B.VP * info.n_weights)(*[(1 << 44) + 256 * i for i in range(info.n_weights)])
     assert L.ac_plan_bind_weights(plan._h, ptrs, info.n_weights) == 0
     peak = B.U64(0)
-    status = L.ac_execute(plan._h, 1 << 40, 1 << 41, 1 << 42, info.workspace_bytes, None, ctypes.byref(peak))
+    status = L.ac_execute(plan._h, X, Y, W, info.workspace_bytes, None, ctypes.byref(peak))
     assert status == 0, (what, L.ac_last_error())
     assert peak.value <= info.peak_bytes_planned, what
     assert all(r.launches <= r.n_segments for r in info.regions[:info.n_regions]), what
@@ -42,22 +25,13 @@ def unet(batch, h, w, c, heads, f, c_res, c_attn, gated=False, context=0, layers
 def pair(n, c_z, heads, dh, settings):
     cfg = I.PairConfig("plan", 1, n, c_z, 64, heads, dh, 2, "bf16")
     walk(("pair", n, c_z, heads, dh, settings), B.pair_desc(cfg, flags=B.AC_FLAG_LISTED_REGIONS_ONLY), [(k, B.AC_DIM_ROW, c) for k, c in settings])
-
-exec(sys.argv[2])
 """
 
 
 @pytest.fixture(scope="module")
 def walk(tmp_path_factory):
-    folder = tmp_path_factory.mktemp("stub")
-    source, lib = folder / "stub.c", folder / "stub.so"
-    source.write_text(STUB)
-    subprocess.run(["cc", "-shared", "-fPIC", "-o", str(lib), str(source)], check=True)
-
-    def run(calls):
-        r = subprocess.run([sys.executable, "-c", WALK, str(lib), calls], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        assert r.returncode == 0, r.stdout
-    return run
+    lib = launch_stub.build(str(tmp_path_factory.mktemp("stub")))
+    return lambda calls: launch_stub.run(lib, WALK + calls)
 
 
 @pytest.mark.parametrize("call", [
