@@ -975,6 +975,8 @@ static hipError_t mfma_attn_rows(const AttnArgs& a, hipStream_t s) {
 constexpr int64_t pipelined_from(int dh) { return dh == 64 ? 320 : 0; }
 template <int DH, bool CAUSAL, bool BIAS>
 static hipError_t mfma_attn_ragged(const AttnArgs& a, hipStream_t s) {
+  // (the pipelined loop adds row offsets of 32 bits without a sign: rows in descending order take the plain one)
+  if (attention_pipelined(DH, BIAS, kWholeTiles) && (a.ldk < 0 || a.ldv < 0)) return mfma_attn_rows<DH, CAUSAL, BIAS, kAnyKeys>(a, s);
   if (a.sk % kKB == 0) return mfma_attn_rows<DH, CAUSAL, BIAS, kWholeTiles>(a, s);
   if constexpr (attention_pipelined(DH, BIAS, kWholeChunks)) {
     // (the range that gives the zeros past the end is 2^31 bytes: rows of V^T that reach further, 128 of 8454664 elements and more, take

@@ -29,3 +29,10 @@ assert loop(200, 1000, {dh}, {dh}, {ldv}, {causal}) == "{route}"
 assert loop(200, 1000, {dh}, (1 << 24) - 8, {ldv}, {causal}) == "{route}"
 assert loop(200, 1024, {dh}, {dh}, {ldv}, {causal}) == "0"
 """)
+
+
+@pytest.mark.parametrize("dh,sk,causal", [(64, 1024, 1), (64, 1000, 0), (64, 1000, 1), (128, 1024, 0), (128, 1000, 1)])
+def test_rows_in_descending_order_take_addresses_of_64_bits(lib, dh, sk, causal):
+    launch_stub.run(lib, CALL + f"""
+assert loop(200, {sk}, {dh}, -{dh}, 4096, {causal}) == "2" and loop(200, {sk}, {dh}, {dh}, -4096, {causal}) == "2"
+""")

@@ -97,3 +97,28 @@ def test_values_in_far_rows(B, ldv):
     B.ac_op_attention(B.to_device(q, "bf16"), B.to_device(k, "bf16"), vb, ctx, 1, dh, v_transposed=True)
     torch.cuda.synchronize()
     check(host(ctx), O.attention(q, k, v, 1, False), "bf16")
+
+
+@pytest.mark.parametrize("dh,sk,causal", [(64, 384, True), (64, 392, False), (128, 384, False), (128, 392, True)])
+@pytest.mark.parametrize("which", ["k", "v"])
+def test_rows_in_descending_order(B, dh, sk, causal, which):
+    """A key or a value operand whose rows lie behind each other (a negative stride), in the middle of memory it must not reach beyond."""
+    import torch
+    sq = 150
+    q, k, v = (draw((n, dh), 330 + i, "bf16") for i, n in enumerate((sq, sk, sk)))
+    dq, dk, dv = B.to_device(q, "bf16"), B.to_device(k, "bf16"), B.to_device(v, "bf16").T.contiguous()
+
+    def placed(t, descending):
+        """(address of row 0, row stride, the buffer)"""
+        buf = torch.full((3, *t.shape), float("nan"), dtype=t.dtype, device="cuda")
+        buf[1] = t.flip(0) if descending else t
+        row = t.shape[1]
+        return buf[1, t.shape[0] - 1 if descending else 0].data_ptr(), -row if descending else row, buf
+    kp, ldk, kb = placed(dk, which == "k")
+    vp, ldv, vb = placed(dv, which == "v")
+    ctx = torch.full((sq, dh), float("nan"), dtype=torch.bfloat16, device="cuda")
+    status = B.lib().ac_op_attention(dq.data_ptr(), dh, 0, kp, ldk, 0, vp, ldv, 0, 1, None, 0, 0, None, 0, 0, ctx.data_ptr(), dh, 0, 1, sq, sk, 1, dh,
+                                     int(causal), sk - sq if causal else 0, 1, None, 0, B.AC_BF16, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert status == 0
+    check(host(ctx), O.attention(q, k, v, 1, causal, q_offset=sk - sq if causal else 0), "bf16")
