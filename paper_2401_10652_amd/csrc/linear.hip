@@ -326,7 +326,7 @@ __device__ __forceinline__ float gelu_table(float x, const float* tab) {
 // whose lanes walk along rows; other tiles (strided store, narrow or misaligned outputs)
 // store 8 bytes per lane straight from the registers.  GELU_TABLE: erf GELU from the table at gelu_tab, up to
 // 9e-6 off at |x| = 1.4, and not by its formula (1.5e-7), which products of ragged depth keep from the FMA kernel.
-constexpr int64_t kNearRow = 1 << 22;   // row strides below: 256 rows span less than 2^31 bytes
+constexpr int64_t kNearRow = 1 << 22;   // row strides from 0 to below: 256 rows span less than 2^31 bytes
 // LDS_FREE: nobody reads `lds` any more.  Returns whether the block met at a barrier.
 template <int ACT, int BM, int BN, int WAVES_M, int WAVES_N, bool GELU_TABLE = true, bool LDS_FREE = false>
 __device__ __forceinline__ bool epilogue_tile(const LinearArgs& g, f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32],
@@ -346,8 +346,10 @@ __device__ __forceinline__ bool epilogue_tile(const LinearArgs& g, f32x16 (&acc)
   // Whole tiles of ordinary operands: no clamps, no predicates, and a wave-uniform base plus 32 bits per lane for every access.  What
   // bounds an epilogue is vector work, and the general form below spends most of its own on 64-bit addresses (34
   // instructions per four elements).  16384x4096x1024 144.6 -> 141.9 us, 12288x2560x320 37.8 -> 35.5, 524288x128x128 112.7 -> 106.5.
-  const bool whole = m0 + BM <= g.m && n0 + BN <= g.n && ((staged && g.o_period == INT64_MAX && g.ldo < kNearRow) || (tstaged && g.t_s3 < kNearRow)) &&
-                     (!g.mul || g.ldmul < kNearRow) && (!g.resid || g.ldr < kNearRow) &&
+  // (Rows in descending order, a negative stride, are for the general form: its offsets have a sign.)
+  auto near_rows = [](int64_t stride) { return (uint64_t)stride < (uint64_t)kNearRow; };
+  const bool whole = m0 + BM <= g.m && n0 + BN <= g.n && ((staged && g.o_period == INT64_MAX && near_rows(g.ldo)) || (tstaged && near_rows(g.t_s3))) &&
+                     (!g.mul || near_rows(g.ldmul)) && (!g.resid || near_rows(g.ldr)) &&
                      (g.bias_period <= 0 || (uint32_t)m0 / (uint32_t)g.bias_period == (uint32_t)(m0 + BM - 1) / (uint32_t)g.bias_period);
   if (whole) {
     constexpr int JF = WAVES_M * WAVES_N == 8 ? TN : 1;      // (operands a wave has in flight at a time, as below)
