@@ -500,24 +500,26 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   for (int i = 0; i < DT; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_o[i][r] = 0.f;
-  // Reference of a row's exponents (log2 domain) and the sum of its probabilities so far.  The reference is the largest score of
-  // the first tile in which the row sees a key, and follows the running maximum only where that has grown by more than 2^kLag:
-  // probabilities up to there lose nothing in bf16 or fp32, the sums stay below 2^127, and a tile is spared the exchange
+  // Reference of a row's exponents (log2 domain) and the sum of its probabilities so far.  The reference lies 2^kLead above the largest
+  // score of the first tile in which the row sees a key and moves only when a score passes it, so that a tile is spared the exchange
   // between the half-waves and, while any of the wave's 32 rows still finds new maxima (most tiles of a few thousand keys), the
-  // rescaling of its accumulators.  A row's reference depends on its own scores alone.  (16384 causal, 16 heads of 128: 1122 -> 1033 us;
-  // 4096, 8 heads of 128: 80.1 -> 72.7; 4096, 12 heads of 64: 78.5 -> 70.1; 8192 causal, 16 heads of 64, plain loop: 203 -> 190.)
+  // rescaling of its accumulators.  Probabilities stay at 1 or below, so that no accumulator overflows where the values' own sums do not; the
+  // largest is 2^-kLead or more, as exact in bf16 and fp32 as 1, and a term of the result underflows below 2^-102, not 2^-126.
+  // A row's reference depends on its own scores alone.  (Against a reference at the running maximum: 16384 causal, 16 heads of 128, 1084 ->
+  // 999 us; 4096 causal, 8 heads of 128, 62.6 -> 59.2; 4096, 12 heads of 64, 77.1 -> 70.3.  A lead of 16 is as fast at scores of unit variance
+  // and 1 to 4 % slower at a deviation of 6; 24 is not.)
   float m_run = -INFINITY, l_run = 0.f;
   float m_exp = 0.f;   // m_run, or 0 while the row has seen no key: exp2(-inf - m_exp) is then 0, not NaN
-  constexpr float kLag = 40.f;
+  constexpr float kLead = 24.f;
   const float scale2 = rsqrtf((float)DH) * kLog2e;
   const float unit = BIAS ? 1.f : scale2;                // of the scores a tile is left with: a bias is added in the log2 domain
   // the reference against a tile's largest score per lane
   auto new_max = [&](float mx) {
-    if (__builtin_amdgcn_ballot_w64(mx * unit > m_run + kLag) == 0) return;   // (a row that has seen no key: -inf + kLag)
+    if (__builtin_amdgcn_ballot_w64(mx * unit > m_run) == 0) return;
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * unit;                            // unit > 0: max commutes with the scaling
-    const bool up = mx > m_run + kLag;
-    const float alpha = !up ? 1.f : m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mx);
-    m_run = up ? mx : m_run;
+    const bool up = mx > m_run;
+    const float alpha = !up ? 1.f : m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - (mx + kLead));
+    m_run = up ? mx + kLead : m_run;
     m_exp = m_run == -INFINITY ? 0.f : m_run;
     l_run *= alpha;
 #pragma unroll
@@ -844,7 +846,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   if (row >= sq) return;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if (ns > 1) {
-    // partial result of this key split: unnormalised O (fp32), running max and sum
+    // partial result of this key split: unnormalised O (fp32), exponent reference and sum
     const int64_t prow = ((int64_t)split * a.batch + b) * sq + row;
     float* po = (float*)a.part_o + (prow * a.heads + h) * DH;
 #pragma unroll

@@ -1,4 +1,4 @@
-"""The attention kernel's exponent reference, which lags behind the running maximum, and the pipelined loop with a ragged last tile:
+"""The attention kernel's exponent reference, which moves only when a score passes it, and the pipelined loop with a ragged last tile:
 against the fp64 oracle, with NaN in whatever lies behind the keys."""
 import numpy as np
 import pytest
@@ -48,6 +48,22 @@ def test_ragged_key_tiles(B, dh, sq, sk, causal, q_offset, n_splits, growth):
     from paper_2401_10652_amd.inputs import round_to_storage
     k = round_to_storage(k, "bf16")
     check(run(B, q, k, v, heads, causal, q_offset, None, n_splits), O.attention(q, k, v, heads, causal, q_offset=q_offset), "bf16")
+
+
+@pytest.mark.parametrize("dh,biased", [(32, False), (64, False), (64, True), (128, False)])
+@pytest.mark.parametrize("sk,n_splits", [(384, 1), (392, 1), (328, 1), (1096, 2)])
+@pytest.mark.parametrize("order", [100, 114, -100])
+def test_values_near_the_ends_of_the_range(B, dh, biased, sk, n_splits, order):
+    """Scores that grow along the keys, some of them by up to tens of binary orders between two moves of the reference: no product
+    or sum of probabilities and values may leave the range that the result stays in."""
+    from paper_2401_10652_amd.inputs import round_to_storage
+    heads, sq = 2, 100
+    q, k, v = (draw((n, heads * dh), 340 + i, "bf16") for i, n in enumerate((sq, sk, sk)))
+    k = round_to_storage((k * (6.0 * np.linspace(0.05, 1.0, sk)[:, None])).astype(np.float32), "bf16")
+    v = np.clip(v, -2, 2) * 2.0 ** order
+    bias = draw((heads, sq, sk), 343, "bf16") if biased else None
+    got = run(B, q, k, v.astype(np.float32), heads, False, bias=bias, n_splits=n_splits)
+    check(got * 2.0 ** -order, O.attention(q, k, v * 2.0 ** -order, heads, False, bias=bias), "bf16")
 
 
 @pytest.mark.parametrize("dh,sq,sk,batch", [(64, 264, 328, 256), (128, 260, 136, 256)])
