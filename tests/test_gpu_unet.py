@@ -47,6 +47,20 @@ def test_group_norm(B, dtype, images, h, w, c, groups, act):
     assert ei.value.status == B.AC_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("value", [1234.567, -3.1e7, 1e30, 1e35])
+@pytest.mark.parametrize("dtype,h,w,c,groups", [("f32", 30, 33, 64, 8), ("bf16", 64, 64, 320, 32), ("f32", 5, 3, 2304, 32), ("f32", 1, 37, 64, 2)])
+def test_group_norm_of_one_value(B, dtype, h, w, c, groups, value):
+    """Groups of a single value, whatever its size, have that mean exactly and no deviation: what is left is the shift."""
+    import torch
+    x = torch.full((2, h, w, c), value, device="cuda", dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    gain, shift = torch.full((c,), 3.0, device="cuda", dtype=x.dtype), torch.linspace(-1, 1, c, device="cuda").to(x.dtype)
+    y = torch.full_like(x, float("nan"))
+    ws = torch.empty((B.ac_group_norm_workspace_bytes(2, groups),), dtype=torch.uint8, device="cuda")
+    B.ac_op_group_norm(x, gain, shift, y, ws, groups)
+    torch.cuda.synchronize()
+    assert torch.equal(y, shift.expand_as(y))
+
+
 @pytest.mark.parametrize("dtype,c", [("f32", 640), ("bf16", 1280)])
 def test_group_norm_does_not_depend_on_the_pass(B, dtype, c):
     """Rows of 160 runs of 16 bytes: an image alone takes the pass by rows, three of them the pass by runs (the other would leave
