@@ -1560,6 +1560,12 @@ static int64_t tiles_of(const LinearArgs& g, int bm, int bn) { return ((g.m + bm
 // The loops that exist for a shape: kPlain any k of whole tiles, kRagged k that ends inside one, kConv the convolution, kWide row strides of 2^22 elements and more (8 MB:
 // the ring and quad loops address a tile's rows with 32-bit byte offsets; the register-staged ones with 64-bit pointers).
 enum Form { kPlain = 1, kConv = 2, kWide = 4, kRagged = 8 };
+// (blocks that have a CU to themselves pay whole rounds, those that share it half of the last one's empty part)
+static double estimate_us(int64_t tiles, double steps, double step, double tile, double once, bool alone) {
+  const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
+  const double rounds = whole <= 1 ? 1 : alone ? whole : 0.5 * (exact + whole);
+  return rounds * (steps * step + tile) + once;
+}
 static TileShape best_tile(const LinearArgs& g, Form form) {
   struct Cost { int bm, bn, threads; double step, tile, once; bool alone; int forms; };
   static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain | kRagged},
@@ -1573,9 +1579,7 @@ static TileShape best_tile(const LinearArgs& g, Form form) {
     if (!(costs[c].forms & form)) continue;
     if (!grid_fits(tiles_of(g, costs[c].bm, costs[c].bn), costs[c].threads)) continue;
     const int64_t tiles = tiles_of(g, costs[c].bm, costs[c].bn) * g.batch;
-    const double exact = (double)tiles / 256, whole = (double)((tiles + 255) / 256);
-    const double rounds = whole <= 1 ? 1 : costs[c].alone ? whole : 0.5 * (exact + whole);
-    const double t = rounds * ((double)((g.k + kBK - 1) / kBK) * costs[c].step + costs[c].tile) + costs[c].once;
+    const double t = estimate_us(tiles, (double)((g.k + kBK - 1) / kBK), costs[c].step, costs[c].tile, costs[c].once, costs[c].alone);
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   return best < 0 ? (form == kConv ? k128x128Ring : form == kWide ? k128x128 : form == kRagged ? k256x128 : kQuad) : (TileShape)best;
@@ -1601,6 +1605,25 @@ static TileShape best_conv_tile(const LinearArgs& g) {
     const double rounds = whole <= 1 ? 1 : c.alone ? whole : 0.5 * (exact + whole);
     const double one = steps * c.step1 + c.once1, busy = rounds * (steps * c.step + c.tile) + c.once;
     const double t = busy <= one ? one : one + (busy - one) * (exact < 1 ? exact : 1);
+    if (best_t == 0 || t < best_t) { best = c.shape; best_t = t; }
+  }
+  return best;
+}
+
+// A gated product's tile, of the three whose waves hold a value and a gate tile of the same columns.  Its epilogue evaluates erf by formula for half of its
+// accumulators, so it has prices of its own, fitted to 64 to 8192 rows x 2 * 256 to 2 * 5120 weight rows x 64 to 1280 deep; the choice is within 4 % of the
+// best of the three on all of those, and ahead of product and gating pass apart.  In us, 64x128 / 256x128 / 256x256 / apart: 64 x 2*5120 x 1280 12.7 / 20.4 /
+// 31.5 / 13.4; 512 of the same 30.7 / 25.3 / 36.0 / 32.6; 1024 50.1 / 49.4 / 39.1 / 47.0; 256 x 2*1280 x 320 6.8 / 11.1 / 16.5 / 10.0; 8192 of the same
+// 35.2 / 36.4 / 36.5 / 46.9.  (128x128 on four or eight waves is never the best of them.)
+static TileShape best_gated_tile(const LinearArgs& g) {
+  struct Cost { TileShape shape; int bm, bn, threads; double step, tile, once; bool alone; };
+  static const Cost costs[] = {{kQuad, 256, 128, 512, 1.5, 11.0, 0.0, true}, {k256x128, 256, 64, 512, 0.85, 8.0, 0.0, true}, {k64x64, 64, 64, 256, 0.32, 1.8, 4.0, false}};
+  TileShape best = kQuad;
+  double best_t = 0;
+  for (const Cost& c : costs) {                    // (bn: columns of the result)
+    const int64_t tiles = tiles_of(g, c.bm, c.bn);
+    if (!grid_fits(tiles, c.threads)) continue;
+    const double t = estimate_us(tiles, (double)(g.k / kBK), c.step, c.tile, c.once, c.alone);
     if (best_t == 0 || t < best_t) { best = c.shape; best_t = t; }
   }
   return best;
@@ -1748,10 +1771,11 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
   }
   if (g.gate > 0) {
     if (!linear_takes_gate(g_in)) return hipErrorInvalidValue;
-    // (of the two shapes whose waves hold 64 columns, by the same prices: 256x256 where its rounds are full)
-    LinearArgs both = g;
-    both.n = 2 * g.n;
-    return best_tile(both, kPlain) == kQuad ? quad_launch<true>(g, s) : ring_launch<256, 128, 4, 2, 64, 3, false, false, false, true>(g, s);
+    switch (best_gated_tile(g)) {
+      case kQuad: return quad_launch<true>(g, s);
+      case k256x128: return ring_launch<256, 128, 4, 2, 64, 3, false, false, false, true>(g, s);
+      default: return ring_launch<64, 128, 2, 2, 64, 3, false, false, false, true>(g, s);
+    }
   }
   switch (linear_route(g)) {
     case kF32_32x64: return mfma_f32_launch<2, 4>(g, s);

@@ -323,9 +323,10 @@ def test_stage_with_cross_attention_and_gate_equals_oracle(B, tc, d, gated):
     assert torch.equal(y3[0], y1[0]) and torch.equal(y3[2], y1[2]) and not torch.equal(y3[1], y1[1])
 
 
-@pytest.mark.parametrize("batch,h,w,c,f,quad", [(5, 8, 24, 64, 320, False), (5, 32, 30, 128, 960, True), (3, 8, 8, 128, 64, False)])
+@pytest.mark.parametrize("batch,h,w,c,f,quad", [(5, 8, 24, 64, 320, False), (5, 32, 30, 128, 960, True), (3, 8, 8, 128, 64, False),
+                                                       (19, 8, 24, 64, 576, False)])
 def test_gated_product(B, batch, h, w, c, f, quad):
-    """The gated first layer in one product: rows and value columns that end inside a tile of either shape it runs on, against the
+    """The gated first layer in one product: rows and value columns that end inside a tile of each shape it runs on, against the
     oracle, and the same bits image by image."""
     import torch
     assert (B.ac_linear_kernel(batch * h * w, 2 * f, c, "bf16") == "quad 256x256") == quad

@@ -74,3 +74,26 @@ def test_ragged_depths_are_priced_among_the_tiles_that_exist():
 @pytest.mark.parametrize("m,n,k", [(128, 2048, 512), (128, 1536, 384), (96, 2048, 512), (128, 3072, 768), (256, 512, 2048), (512, 768, 3072)])
 def test_launches_of_one_round_of_small_tiles_take_the_smallest(m, n, k):
     assert B.ac_linear_kernel(m, n, k, "bf16") == "staged 32x64"
+
+
+def test_the_gated_product_takes_small_tiles_where_it_is_small(tmp_path):
+    """The tile of the gated feed-forward's first product, by the kernels that one image's plan launches: of 64 rows and 2 * 5120 weight rows, 256-row
+    tiles would leave three quarters of the work as padding."""
+    import launch_stub
+    launch_stub.run(launch_stub.build(str(tmp_path)), """
+def gated_kernel(h, w, c, f):
+    cfg = I.ResStackConfig("plan", 1, 1, 1, h, w, c, 32, heads=c // 64, d_ffn=f, gated=True)
+    plan = B.Plan(B.res_stack_desc(cfg), [])
+    info = plan.ac_plan_query()
+    assert L.ac_plan_bind_weights(plan._h, (B.VP * info.n_weights)(*[(1 << 44) + 256 * i for i in range(info.n_weights)]), info.n_weights) == 0
+    assert L.ac_execute(plan._h, X, Y, W, info.workspace_bytes, None, None) == 0, L.ac_last_error()
+    (name,) = [k for k in kernels() if "linear_quad_bf16ILb1E" in k or ("linear_ring_bf16" in k and "ELb0ELb0ELb0ELb1E" in k)]
+    return "256x256" if "quad" in name else "x".join(name[name.index("ILi") + 3:].split("ELi")[:2])
+
+assert gated_kernel(8, 8, 1280, 5120) == "64x128"
+assert gated_kernel(16, 16, 1280, 5120) == "64x128"
+assert gated_kernel(16, 32, 1280, 5120) == "256x128"
+assert gated_kernel(32, 32, 1280, 5120) == "256x256"
+assert gated_kernel(32, 32, 320, 1280) == "64x128"
+assert gated_kernel(64, 64, 320, 1280) == "256x256"
+""")
