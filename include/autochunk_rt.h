@@ -113,8 +113,9 @@ enum {
                                       or mem(A)/n per segment, so the effect of chunking on memory can be
                                       measured and not only modelled.  Same result as the fused kernel up
                                       to the rounding of the stored scores and probabilities.  With a
-                                      causal mask the masked half is computed and discarded;
-                                      flops_per_execute counts what is executed. */
+                                      causal mask, bf16 products leave out the tiles that no row of theirs sees
+                                      and flops_per_execute counts visible pairs only; in fp32 the masked half
+                                      is computed and discarded, and counted. */
   AC_FLAG_BUDGET_PAPER_MODEL = 16, /* act_budget_bytes additionally bounds, for every region, the bytes
                                       the paper's two activation equations give for an unfused graph in
                                       which every op output is a tensor (ac_region_info.model_bytes:

@@ -337,20 +337,18 @@ struct Walk {
     if (g.resid) by += (double)g.m * g.n * eb();
     run(K_GEMM, 2.0 * g.m * g.n * g.k, by, "linear", [&] { return launch_linear(g, stream); });
   }
+  // (query, key) pairs per head and problem that the mask leaves
+  static double visible_pairs(const AttnArgs& a) {
+    if (!a.causal) return (double)a.sq * a.sk;
+    // rows r see min(sk, q_offset + r + 1) keys
+    const int64_t full_from = std::max<int64_t>(0, a.sk - 1 - a.q_offset);   // first r seeing all keys
+    const int64_t tri = std::min<int64_t>(a.sq, full_from);
+    return (double)tri * (a.q_offset + 1) + (double)tri * (tri - 1) / 2.0 + (double)(a.sq - tri) * a.sk;
+  }
   // max_split_bytes caps the fp32 partial results of the launch's key splits (fewer splits if needed)
   void attention(AttnArgs a, uint64_t max_split_bytes = UINT64_MAX) {
     a.dtype = p->m.dtype;
-    double pairs;   // visible (query, key) pairs per head and problem
-    if (a.causal) {
-      pairs = 0;
-      // rows r see min(sk, q_offset + r + 1) keys
-      const int64_t full_from = std::max<int64_t>(0, a.sk - 1 - a.q_offset);   // first r seeing all keys
-      const int64_t tri = std::min<int64_t>(a.sq, full_from);
-      pairs += (double)tri * (a.q_offset + 1) + (double)tri * (tri - 1) / 2.0;
-      pairs += (double)(a.sq - tri) * a.sk;
-    } else {
-      pairs = (double)a.sq * a.sk;
-    }
+    const double pairs = visible_pairs(a);
     const double fl = 4.0 * pairs * a.head_dim * a.heads * a.batch;
     // q and ctx rows of the segment, k and v rows any of them sees (causal: keys up to the last row)
     const int64_t keys_seen = a.causal ? std::min<int64_t>(a.sk, a.q_offset + a.sq) : a.sk;
@@ -403,16 +401,18 @@ struct Walk {
       s1.causal = kCausalColumns; s2.causal = kCausalDepth; s1.q_offset = s2.q_offset = a.q_offset;
       const bool skips = a.causal && linear_takes_causal(s1) && linear_takes_causal(s2);
       if (skips) { g1 = s1; g2 = s2; }
-      run(K_GEMM, 2.0 * c * S * dh * H, ((double)c * dh + (double)S * dh + (double)c * S) * H * e, "scores",
+      // (counted is what the mask leaves, or, where the masked part is computed and discarded, all of it)
+      const double pairs = skips ? visible_pairs(a) : (double)c * S, keys = (double)(skips ? seen : S);
+      run(K_GEMM, 2.0 * pairs * dh * H, ((double)c * dh + keys * dh + pairs) * H * e, "scores",
           [&] { return launch_linear(g1, stream); });
       const void* sp = dry ? nullptr : scores + off;
       void* pp = dry ? nullptr : probs + off;
       const int causal = a.causal, row_tile = skips ? 256 : 0;
       const int64_t qo = a.q_offset, cols = skips ? seen : S;
       hipStream_t st = stream;
-      run(K_ELEM, 5.0 * c * S * H, 4.0 * c * S * H * e, "softmax",
+      run(K_ELEM, 5.0 * pairs * H, 4.0 * pairs * H * e, "softmax",
           [&] { return launch_softmax_rows(sp, S, pp, S, H * c, cols, scale, causal, qo, c, row_tile, dt, st); });
-      run(K_GEMM, 2.0 * c * S * dh * H, ((double)c * S + (double)S * dh + (double)c * dh) * H * e, "context",
+      run(K_GEMM, 2.0 * pairs * dh * H, (pairs + keys * dh + (double)c * dh) * H * e, "context",
           [&] { return launch_linear(g2, stream); });
     }
     arena.release(mk);

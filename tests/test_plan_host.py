@@ -187,6 +187,20 @@ def test_flops_are_the_algorithmic_counts():
         assert abs(info2.flops_per_execute - info.flops_per_execute) <= 1e-9 * info.flops_per_execute
 
 
+@pytest.mark.parametrize("dtype,causal", [("bf16", True), ("bf16", False), ("f32", True)])
+@pytest.mark.parametrize("batch,chunk", [(1, 1024), (1, 392), (2, 1), (2, 1024)])
+def test_flops_of_stored_scores_count_what_the_mask_leaves(dtype, causal, batch, chunk):
+    """The fused kernel's count plus five per softmax element: visible pairs in bf16, whose products skip the others, all pairs in fp32."""
+    cfg = I.TransformerConfig("tfl", 75, 2, 1024, 128, 2, 256, causal, dtype, None, batch=batch)
+    dim = B.AC_DIM_BATCH if batch > 1 and chunk == 1 else B.AC_DIM_SEQ
+    fused, stored = (B.Plan(B.transformer_desc(cfg, flags=f), regions(chunk, chunk, chunk, dim=dim)).ac_plan_query().flops_per_execute
+                     for f in (0, B.AC_FLAG_MATERIALIZED_SCORES))
+    S, per_pair = cfg.seq, cfg.layers * batch * cfg.heads
+    visible = S * (S + 1) // 2 if causal else S * S
+    counted = visible if dtype == "bf16" else S * S
+    assert abs(stored - fused - per_pair * (4 * cfg.head_dim * (counted - visible) + 5 * counted)) <= 1e-9 * stored
+
+
 def expect(status, fn):
     with pytest.raises(B.AcError) as ei:
         fn()
