@@ -1263,8 +1263,10 @@ constexpr int ln_proj_rows_elems(int k) {
 }
 constexpr int ln_proj_lds_elems(int k) { return ln_proj_rows_elems(k) + kLnProjCols * (k + 8); }
 
+// (blocks per CU: four by registers at K = 128; at K = 64, where a launch is mostly loads and stores, five, which cost 96 registers and no spill: 73792
+// rows to 192, 512 and 512 columns 84 us with four, 66 with five, 67352 to 128, a gated 192 and twice 256 59 and 47; six spill)
 template <int K, int BN>
-__global__ void __launch_bounds__(256, 4) ln_multi_proj_bf16(LnProjKernelArgs ka) {
+__global__ void __launch_bounds__(256, K == 64 ? 5 : 4) ln_multi_proj_bf16(LnProjKernelArgs ka) {
   constexpr int BM = kLnProjRows, NT = 256;
   static_assert(BM == 64 && BN == 64, "waves 2 x 2 of one 32x32 MFMA tile each");
   constexpr int AROW = K + 8;                 // padded LDS row (elements)
@@ -1480,7 +1482,7 @@ static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
   // the GELU table is only there when a part needs it
   const size_t lds = lds_max - (ka.any_gelu ? 0 : kGeluTableBytes);
   const int64_t blocks = (ka.a.rows + kLnProjRows - 1) / kLnProjRows;
-  // Four blocks fit a CU.  A launch of few rows would leave places empty and walk all its weight tiles one after
+  // Four blocks fit a CU (five at K = 64).  A launch of few rows would leave places empty and walk all its weight tiles one after
   // another: the tiles are then shared out over as many blocks per 64 rows as there is room for, each of which
   // normalises the rows again (8000 rows of 128, q, k, v, gate of the triangle attention: 19 -> 8.4 us).  Where results may
   // lie on the rows (a projection in place) one block has to have read them all before it writes, as without shares.
