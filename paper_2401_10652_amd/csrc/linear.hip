@@ -1551,9 +1551,11 @@ static bool mfma_eligible(const LinearArgs& g) {
 // What 32x64 pays once is set by launches of one round inside models, whose operands another kernel has just written: 128x2048x512 takes
 // 7.0 us on it and 8.1 on 64x64 (which 5.4 us instead of 5.0 had preferred), 128x1536x384 6.7 and 7.7, 152x4096x1024 (320 tiles)
 // 10.0 and 9.0.
-// 128x192 fills rounds that the others leave half empty or padded (6400x768x3072 46.8 us on 256x128, 41.9 on it); at few steps it is priced a
-// little above what it takes by itself (2048x3072x768 19.9 against 20.2 us): with every CU loading, twelve layers of it run
-// back to back 3 % slower than on 192 tiles of 256x128.
+// 128x192 fills rounds that the others leave half empty or padded (6400x768x3072 47.2 us on 256x128, 43.8 on it; 2048x3072x768 19.1 and 17.0;
+// 1600x3072x768 17.0 and 14.7).  Its prices are fitted to 475 launches of 256 to 65536 rows whose operands another kernel has just written: the choice
+// among all seven is 1.8 % off the best on those on average, 1.6 % on 465 others and 34 % at worst (14105x576x512).  Inside stacks of twelve
+// layers, one after another without a pause, it is mostly ahead of 256x128 too: 3200 rows, d 768, in two launches a layer 2210 -> 2160 us, 6144 rows
+// 4235 -> 4115, 2048 rows in one 1219 -> 1212; 4096 rows in two, whose 256 tiles load every CU at once, 2447 -> 2500.
 // The k order is the same for all of them, and so are the bits.
 enum TileShape { kQuad, k256x128, k128x128Ring, k128x192, k128x128, k128x64, k64x64, k32x64, kTileShapes };
 // A grid dimension counts its threads in 32 bits: a shape whose blocks of a launch are more than that is not a choice.
@@ -1571,7 +1573,7 @@ static double estimate_us(int64_t tiles, double steps, double step, double tile,
 static TileShape best_tile(const LinearArgs& g, Form form) {
   struct Cost { int bm, bn, threads; double step, tile, once; bool alone; int forms; };
   static const Cost costs[kTileShapes] = {{256, 256, 512, 1.06, 11.9, 0.0, true, kPlain},         {256, 128, 512, 0.65, 8.1, 0.0, true, kPlain | kRagged},
-                                          {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 192, 512, 0.60, 7.4, 1.8, true, kPlain},
+                                          {128, 128, 512, 0.46, 4.4, 1.0, true, kPlain | kConv},  {128, 192, 512, 0.58, 6.5, 1.85, true, kPlain},
                                           {128, 128, 256, 0.52, 2.7, 4.4, false, kPlain | kWide},
                                           {128, 64, 256, 0.36, 1.4, 4.3, false, kPlain | kConv},  {64, 64, 256, 0.17, 0.8, 4.8, false, kPlain | kConv | kWide | kRagged},
                                           {32, 64, 128, 0.13, 0.65, 5.0, false, kPlain | kWide}};
