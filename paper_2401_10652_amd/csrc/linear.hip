@@ -1591,15 +1591,16 @@ static TileShape best_tile(const LinearArgs& g, Form form) {
 
 // The convolution's tile: its sums are long (9 C_in) and its columns few, so the time per step decides, and that depends on how many CUs load
 // at once.  A launch takes the larger of what one block needs by itself (`step1`, `once1`) and what the rounds need with every CU busy
-// (a lone block's rounds count whole); between an empty and a full first round the two are mixed.  Times in us of
-// 49 launches (256 to 64000 pixels, 128 to 640 channels).  Four 64x64 images of 320 channels: 51.9 on 128x128 and 128x64 (whose last
+// (a lone block's rounds count whole); between an empty and a full first round the two are mixed.  Fitted to 422
+// launches (up to 100000 pixels, 128 to 640 channels in, 64 to 640 out): the choice is 0.2 % off the best of four on those, 0.4 % on 434 others and 14 % at worst
+// (nine 55x89 images, 128 to 192).  Four 64x64 images of 320 channels: 51.9 on 128x128 and 128x64 (whose last
 // columns are half padding), 47.8 on 64x64, 39.2 on 128x192; eight of 192: 37.8 / 35.9 / 36.8 / 26.8; four of 512: 84.5 / 94.8 / 110.9 / 97.5.
 // (64 input channels: nine steps, as short as a product, and priced as one.)
 static TileShape best_conv_tile(const LinearArgs& g) {
   if (g.conv_c == 64) return best_tile(g, kConv);
   struct Cost { TileShape shape; int bm, bn, threads; double step, tile, once, step1, once1; bool alone; };
-  static const Cost costs[] = {{k128x192, 128, 192, 512, 0.66, 6.5, 2.0, 0.467, 8.8, true}, {k128x128Ring, 128, 128, 512, 0.505, 4.8, 1.0, 0.385, 6.5, true},
-                               {k128x64, 128, 64, 256, 0.29, 1.7, 4.3, 0.356, 6.9, false},  {k64x64, 64, 64, 256, 0.178, 0.5, 4.8, 0.278, 5.4, false}};
+  static const Cost costs[] = {{k128x192, 128, 192, 512, 0.67, 5.5, 1.5, 0.44, 9.6, true}, {k128x128Ring, 128, 128, 512, 0.506, 4.8, 1.1, 0.38, 7.2, true},
+                               {k128x64, 128, 64, 256, 0.32, 1.6, 4.3, 0.36, 7.3, false},  {k64x64, 64, 64, 256, 0.18, 0.47, 4.9, 0.278, 5.6, false}};
   TileShape best = k128x128Ring;
   double best_t = 0;
   for (const Cost& c : costs) {
