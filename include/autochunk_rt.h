@@ -101,7 +101,10 @@ enum {
   AC_FLAG_TWO_SEGMENTS_IN_FLIGHT = 4, /* segments of a region alternate between the caller's stream and a
                                       second stream owned by the plan, each with its own per-segment
                                       workspace (the plan's bytes account for both); all work is joined
-                                      back into the caller's stream at the end of every region */
+                                      back into the caller's stream at the end of every region.  Such segments
+                                      do not share launches outside the feed-forward region, so where those of
+                                      the plan without the flag do (ac_region_info.launches), that plan can be
+                                      the faster one */
   AC_FLAG_LISTED_REGIONS_ONLY = 2, /* pair stack only: the block consists of just the region kinds
                                       listed in ac_plan_create (each maps z to z), in canonical
                                       order; weights of the others are still bound but unused */

@@ -1056,9 +1056,11 @@ static hipError_t generic_attn_dispatch(const AttnArgs& a, hipStream_t s) {
 }
 
 // Key splits for a launch that would leave most of the 256 CUs idle: as many as still give
-// every block a place at once, which by register count is three blocks per CU, two with
-// 128-wide heads (a launch that spills into a second round leaves those blocks to run alone
-// at the end, at a fraction of the CU's rate), each split at least 512 keys long.  A pure
+// every block a place at once (a launch that spills into a second round leaves those blocks to run alone
+// at the end, at a fraction of the CU's rate): 512 places with 128-wide heads, whose blocks stand two to a
+// CU, 768 with others, three to a CU by the registers of the plain loop.  (The pipelined loop of 64-wide heads holds two, and a launch of
+// 513 to 768 of its blocks takes a second round; none of 400 drawn launches was slower for it than on the plain loop, and the rule is
+// the same for both, as the scratch of plans depends on it.)  Each split is at least 512 keys long.  A pure
 // function of the launch shape, so planning and execution agree.
 int attention_key_splits(int64_t sq, int64_t sk, int heads, int64_t batch, int head_dim, int dtype, int v_transposed) {
   if (dtype != AC_BF16 || !v_transposed) return 1;

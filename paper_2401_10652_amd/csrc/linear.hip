@@ -1719,7 +1719,7 @@ static Route f32_route(const LinearArgs& g) {
 
 static Route linear_route(const LinearArgs& g) {
   if (g.conv_c > 0) {
-    if (g.conv_c >= (1 << 20)) return kConvWide64x64;   // (128 weight rows of 9 * 2^20 channels are 2.4e9 bytes)
+    if (g.conv_c >= (1 << 20)) return kConvWide64x64;   // (192 weight rows of 9 * 2^20 channels are 3.6e9 bytes, the most that 32-bit offsets hold)
     switch (best_conv_tile(g)) {
       case k128x128Ring: return kConv128x128;
       case k128x192: return kConv128x192;
