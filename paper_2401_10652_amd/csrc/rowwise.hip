@@ -846,7 +846,7 @@ group_norm_partials_rows(const T* x, float* part, int64_t positions, int channel
 
 // Mean and reciprocal deviation of every group of an image, by the block: eight lanes per group, eight partials each, first the mean, then the
 // deviations from it (fixed shape, so the result does not depend on timing).  Every block of the pass does this before it can
-// store a row: as a tree over one partial per lane, three exchanges a step, it was most of the pass (4 x 4096 x 320: 17.0 us, 10.1 here).
+// store a row: as a tree over one partial per lane, three exchanges a step, it was most of the pass (4 x 4096 x 320: 17.0 us, 10.2 here).
 __device__ __forceinline__ void group_norm_merge(const float* part, int64_t image, int groups, float eps, int tid, float* s_mean, float* s_rstd) {
   static_assert(kGnParts == kGnLanes * kGnLanes, "eight partials per lane");
   typedef float run_t __attribute__((ext_vector_type(4), aligned(4)));     // (the table may start at any float)
