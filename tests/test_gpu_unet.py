@@ -327,7 +327,8 @@ def test_stage_with_cross_attention_and_gate_equals_oracle(B, tc, d, gated):
                                                        (19, 8, 24, 64, 576, False)])
 def test_gated_product(B, batch, h, w, c, f, quad):
     """The gated first layer in one product: rows and value columns that end inside a tile of each shape it runs on, against the
-    oracle, and the same bits image by image."""
+    oracle, and the same bits image by image.  (quad: what a plain product of both halves takes; the gated one chooses by prices of its own,
+    64x128, 256x256, 64x128 and 256x128 here.)"""
     import torch
     assert (B.ac_linear_kernel(batch * h * w, 2 * f, c, "bf16") == "quad 256x256") == quad
     cfg = I.ResStackConfig("tug", 54, 1, batch, h, w, c, 16, heads=c // 64, d_ffn=f, gated=True)
