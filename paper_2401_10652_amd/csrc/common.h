@@ -69,10 +69,6 @@ __device__ __forceinline__ float erf_as(float x) {
   return copysignf(fmaf(-p, e, 1.0f), x);
 }
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erf_as(x * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_tanh(float x) {
-  float u = 0.79788456080286536f * (x + 0.044715f * x * x * x);
-  return 0.5f * x * (1.0f + tanhf(u));
-}
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
 // The same by the hardware reciprocal and one Newton step, for the GEMM epilogues: 8 instructions where the division takes 13
@@ -84,6 +80,18 @@ __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + __exp
 __device__ __forceinline__ float sigmoid_newton(float x) {
   const float d = fmaf(0.25f, __expf(-x), 0.25f), r = __builtin_amdgcn_rcpf(d);
   return 0.25f * fmaf(__builtin_amdgcn_fmed3f(fmaf(-d, r, 1.0f), -1.0f, 1.0f), r, r);
+}
+
+// GELU, tanh form: x (1 + tanh u) / 2 = max(x, 0) - |x| / (1 + e^(2|u|)) with u = sqrt(2/pi) (x + 0.044715 x^3), the denominator inverted
+// as above.  14 instructions, where tanhf is a division, an exponential and two branches: what bounds the epilogue of a product is vector work
+// (4000 x 4096 x 1024 57 -> 48 us).  Against 64 bits over N(0, 1): 2.8e-8 in 2-norm and 2.4e-7 at most, with tanhf 3.8e-8
+// and 4.1e-7.  (From |x| = 16 on the second term is 0, and the clamp keeps inf * 0 out; x / 2 + |x| / 2 is NaN for -inf, as the product form is.)
+__device__ __forceinline__ float gelu_tanh(float x) {
+  const float a = fabsf(x);
+  const float t = a * fmaf(x * x, 0.102943240f, 2.302208198f);        // 2 |u| log2 e
+  const float d = fmaf(0.25f, __builtin_amdgcn_exp2f(t), 0.25f), r = __builtin_amdgcn_rcpf(d);
+  const float s = 0.25f * fmaf(__builtin_amdgcn_fmed3f(fmaf(-d, r, 1.0f), -1.0f, 1.0f), r, r);
+  return fmaf(-fminf(a, 16.0f), s, fmaf(0.5f, a, 0.5f * x));
 }
 
 template <int ACT> __device__ __forceinline__ float apply_act_bf16(float x) {

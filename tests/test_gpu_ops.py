@@ -266,6 +266,23 @@ def test_elementwise(B, dtype, rows, cols):
     check(host(y), x.astype(np.float64) * r, dtype)
 
 
+@pytest.mark.parametrize("std", [0.6, 1.0, 3.0, 8.0])
+def test_tanh_gelu_in_fp32(B, std):
+    """Within 4.5e-8 in 2-norm and 3 eps of the larger of 1 and the value (tanhf's form is 3.8e-8 and 3.5 eps off); the values at the ends of the range."""
+    import torch
+    x = draw((512, 1024), 46, "f32", std)
+    y = torch.empty(x.shape, device="cuda")
+    B.ac_op_bias_act(dev(B, x, "f32"), None, y, B.AC_ACT_GELU_TANH)
+    err, ref = host(y) - O.gelu_tanh(x.astype(np.float64)), O.gelu_tanh(x.astype(np.float64))
+    assert np.linalg.norm(err) <= 4.5e-8 * np.linalg.norm(ref)
+    assert (np.abs(err) <= 3 * 2.0 ** -23 * np.maximum(1, np.abs(ref))).all()
+    ends = torch.tensor([[math.inf, -math.inf, math.nan, 0.0, -0.0, 3e38, -3e38, 1e13, -1e13, 20.0, -20.0, 2e-38]], device="cuda")
+    out = torch.empty_like(ends)
+    B.ac_op_bias_act(ends, None, out, B.AC_ACT_GELU_TANH)
+    want = [math.inf, math.nan, math.nan, 0.0, 0.0, 3e38, 0.0, 1e13, 0.0, 20.0, 0.0, 1e-38]
+    assert np.allclose(host(out)[0], want, rtol=1e-6, atol=0, equal_nan=True)
+
+
 def test_bf16_store_rounds_to_nearest_even(B):
     """x + 0 through the kernel must equal the host generator's rounding, bit for bit."""
     import torch
