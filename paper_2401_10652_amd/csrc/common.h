@@ -113,6 +113,41 @@ __device__ __forceinline__ float apply_act_rt(float x, int act) {
   }
 }
 
+// GELU (erf form) from a table in LDS.  gelu(x) = x/2 + |x| h(|x|) with h(a) = erf(a / sqrt 2) / 2,
+// and h is read from 385 entries (value, step to the next) at a spacing of 1/64, interpolated
+// linearly: |error of h| <= (1/64)^2 / 8 * max|h''| = 7.4e-6, and from |x| = 6 on h is 1/2 to
+// fp32.  Nine instructions and one LDS read per element instead of a reciprocal, an exponential
+// and a dozen more, which matters because the epilogue of an 8-wave tile overlaps with nothing.
+constexpr int kGeluEntries = 385;
+constexpr size_t kGeluTableBytes = (size_t)kGeluEntries * 2 * sizeof(float);
+__device__ __forceinline__ void gelu_table_fill(float* tab, int tid, int nt) {
+  for (int i = tid; i < kGeluEntries; i += nt) {
+    const float h0 = 0.5f * erf_as((float)i * (0.70710678118654752f / 64.0f));
+    const float h1 = i + 1 < kGeluEntries ? 0.5f * erf_as((float)(i + 1) * (0.70710678118654752f / 64.0f)) : h0;
+    tab[2 * i] = h0;
+    tab[2 * i + 1] = h1 - h0;
+  }
+}
+__device__ __forceinline__ float gelu_table(float x, const float* tab) {
+  const float a = fabsf(x);
+  const float u = a * 64.0f;
+  unsigned idx = (unsigned)u;                       // saturating conversion
+  idx = idx < (unsigned)(kGeluEntries - 1) ? idx : (unsigned)(kGeluEntries - 1);
+  const f32x2 e = *reinterpret_cast<const f32x2*>(tab + 2 * idx);
+  const float h = fmaf(e[1], __builtin_amdgcn_fractf(u), e[0]);
+  return fmaf(a, h, 0.5f * x);
+}
+
+// m = q * period + r for a row index m < 2^31 (the launchers refuse more rows): a 32-bit division,
+// a fraction of the instructions and registers of the 64-bit one.  A period of 2^31 or more (the
+// "no period" value) gives q = 0, r = m.
+__device__ __forceinline__ void split_row(int64_t m, int64_t period, int64_t& q, int64_t& r) {
+  if (period > 0x7fffffffLL) { q = 0; r = m; return; }
+  const uint32_t qq = (uint32_t)m / (uint32_t)period;
+  q = qq;
+  r = (int64_t)((uint32_t)m - qq * (uint32_t)period);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -123,10 +158,23 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
-// Sum over groups of G consecutive lanes (G a power of two <= 64).
+// Sum over groups of G consecutive lanes (G a power of two <= 64).  Within sixteen lanes by rotations of the row: once lanes 8 apart hold the same sum
+// a rotation by 4 is an exchange of lanes 4 apart, and so on, the sums (and bits) of the exchanges at no trip through LDS.
+template <int N> __device__ __forceinline__ float rotate_row(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, true));
+}
 template <int G> __device__ __forceinline__ float group_sum(float v) {
+  if constexpr (G >= 64) v += __shfl_xor(v, 32, 64);
+  if constexpr (G >= 32) v += __shfl_xor(v, 16, 64);
+  if constexpr (G >= 16) {
+    v += rotate_row<8>(v);
+    v += rotate_row<4>(v);
+    v += rotate_row<2>(v);
+    v += rotate_row<1>(v);
+  } else {
 #pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  }
   return v;
 }
 
@@ -231,6 +279,17 @@ hipError_t launch_linear(const LinearArgs& g, hipStream_t s);
 bool linear_takes_causal(const LinearArgs& g);
 bool linear_takes_gate(const LinearArgs& g);
 const char* linear_kernel_name(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldw, int64_t batch, bool conv, int dtype);
+// The end of a triangle update of rows of z (contiguous, bf16): out = z + sigmoid(LN(z) w_g^T + b_g) * (LN(o) w_o^T + b_o) with o channel-major,
+// o[c * stride_c + row].  Row r of the result goes to (r / o_period) * o_s1 + (r % o_period) * o_s2 (o_period <= 0: r * c_z).
+struct TriMulOutArgs {
+  const void *z, *ln_in_g, *ln_in_b, *w_g, *b_g;
+  const void* o; int64_t stride_c; const void *ln_out_g, *ln_out_b, *w_o, *b_o;
+  void* out; int64_t o_period, o_s1, o_s2;
+  int64_t rows, c_z, c_hidden;
+  float eps;
+};
+bool trimul_out_shapes_ok(int dtype, int64_t c_z, int64_t c_hidden, int64_t row_unit);   // segments of whole multiples of `row_unit` rows
+hipError_t launch_trimul_out(const TriMulOutArgs& p, hipStream_t s);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);
 hipError_t launch_group_norm(const void* x, const void* gain, const void* shift, void* y, void* partials, int64_t images,

@@ -21,15 +21,6 @@ namespace ac {
 // Epilogue for one element (generic kernel) — bias, activation, multiplier, residual,
 // then the row-major or the strided ("transposed") store.
 // ------------------------------------------------------------------------------------
-// m = q * period + r for a row index m < 2^31 (the launchers refuse more rows): a 32-bit division,
-// a fraction of the instructions and registers of the 64-bit one.  A period of 2^31 or more (the
-// "no period" value) gives q = 0, r = m.
-__device__ __forceinline__ void split_row(int64_t m, int64_t period, int64_t& q, int64_t& r) {
-  if (period > 0x7fffffffLL) { q = 0; r = m; return; }
-  const uint32_t qq = (uint32_t)m / (uint32_t)period;
-  q = qq;
-  r = (int64_t)((uint32_t)m - qq * (uint32_t)period);
-}
 // Offset of row m in the row-major part of the output.
 __device__ __forceinline__ int64_t out_row(const LinearArgs& g, int64_t m) {
   if (g.o_period == INT64_MAX) return m * g.ldo;
@@ -294,31 +285,6 @@ __device__ __forceinline__ int64_t xcd_run(int64_t pid, int64_t nb) {
   const int64_t q = nb / kXcds, r = nb % kXcds;
   const int64_t x = pid % kXcds, idx = pid / kXcds;
   return x * q + (x < r ? x : r) + idx;
-}
-
-// GELU (erf form) from a table in LDS.  gelu(x) = x/2 + |x| h(|x|) with h(a) = erf(a / sqrt 2) / 2,
-// and h is read from 385 entries (value, step to the next) at a spacing of 1/64, interpolated
-// linearly: |error of h| <= (1/64)^2 / 8 * max|h''| = 7.4e-6, and from |x| = 6 on h is 1/2 to
-// fp32.  Nine instructions and one LDS read per element instead of a reciprocal, an exponential
-// and a dozen more, which matters because the epilogue of an 8-wave tile overlaps with nothing.
-constexpr int kGeluEntries = 385;
-constexpr size_t kGeluTableBytes = (size_t)kGeluEntries * 2 * sizeof(float);
-__device__ __forceinline__ void gelu_table_fill(float* tab, int tid, int nt) {
-  for (int i = tid; i < kGeluEntries; i += nt) {
-    const float h0 = 0.5f * erf_as((float)i * (0.70710678118654752f / 64.0f));
-    const float h1 = i + 1 < kGeluEntries ? 0.5f * erf_as((float)(i + 1) * (0.70710678118654752f / 64.0f)) : h0;
-    tab[2 * i] = h0;
-    tab[2 * i + 1] = h1 - h0;
-  }
-}
-__device__ __forceinline__ float gelu_table(float x, const float* tab) {
-  const float a = fabsf(x);
-  const float u = a * 64.0f;
-  unsigned idx = (unsigned)u;                       // saturating conversion
-  idx = idx < (unsigned)(kGeluEntries - 1) ? idx : (unsigned)(kGeluEntries - 1);
-  const f32x2 e = *reinterpret_cast<const f32x2*>(tab + 2 * idx);
-  const float h = fmaf(e[1], __builtin_amdgcn_fractf(u), e[0]);
-  return fmaf(a, h, 0.5f * x);
 }
 
 // The epilogue of one block.  A tile that lies wholly in the row-major part of the output

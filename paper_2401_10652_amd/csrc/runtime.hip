@@ -871,10 +871,26 @@ void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) 
   // Where segments share launches the gate of a row run waits in the run's own rows of the result (the projection that
   // ends the module reads an element of it and writes the same element).
   const bool gate_in_out = shares() && !col;
+  // Gate, LayerNorm over channels, projection and residual in one kernel: neither the gate nor the normalised rows exist in memory
+  // (the plan counts them all the same, and segments that share launches use their room).
+  const bool one_pass = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE) && trimul_out_shapes_ok(m.dtype, cz, ch, N);
   int64_t n_run = 0;
   pair_loop(kind, segs, zout, col, [&](const RowSeg& sg) {
     const int64_t rows = sg.ni * N;
     const void* zs = pair_segment(zin, sg, col);
+    if (one_pass) {
+      void* o = arena.push((uint64_t)ch * rows * e);   // [c][segment index][other index]
+      if (!shares()) { arena.push((uint64_t)rows * cz * e); arena.push((uint64_t)rows * ch * e); }
+      contract(at(col ? b_t : a_t, sg.i0 * N), N, R, col ? a_t : b_t, N, R, o, N, rows, sg.ni, N, N, ch, n_run % 2 == 1);
+      if (!measuring) ++n_run;
+      LinearArgs dst{};
+      pair_store(dst, zout, sg, col);
+      const TriMulOutArgs g{zs, W[TM_LN_IN_G], W[TM_LN_IN_B], W[TM_W_G], W[TM_B_G], o, rows, W[TM_LN_OUT_G], W[TM_LN_OUT_B], W[TM_W_O], W[TM_B_O],
+                            dst.out, dst.o_period, dst.o_s1, dst.o_s2, rows, cz, ch, m.ln_eps};
+      run(K_GEMM, rows * (8.0 * cz + 2.0 * cz * cz + 8.0 * ch + 2.0 * cz * ch), ((double)rows * (2 * cz + ch) + cz * (cz + ch)) * e, "trimul_out",
+          [&] { return launch_trimul_out(g, stream); });
+      return;
+    }
     void* t = fuse_g ? nullptr : arena.push((uint64_t)rows * cz * e);
     void* gate = gate_in_out ? atw(zout, sg.i0 * N * cz) : arena.push((uint64_t)rows * cz * e);
     void* o_c = arena.push((uint64_t)ch * rows * e);   // [c][segment index][other index]
