@@ -290,6 +290,16 @@ struct TriMulOutArgs {
 };
 bool trimul_out_shapes_ok(int dtype, int64_t c_z, int64_t c_hidden, int64_t row_unit);   // segments of whole multiples of `row_unit` rows
 hipError_t launch_trimul_out(const TriMulOutArgs& p, hipStream_t s);
+// out = z + act(LN(z) w_1^T + b_1) w_2^T + b_2 on rows of z, the hidden rows on chip; rows of the result as above.
+struct TransitionArgs {
+  const void *z, *ln_g, *ln_b, *w_1, *b_1, *w_2, *b_2;
+  void* out; int64_t o_period, o_s1, o_s2;
+  int64_t rows, c_z, hidden;
+  int act;
+  float eps;
+};
+bool transition_shapes_ok(int dtype, int64_t c_z, int64_t hidden, int act);
+hipError_t launch_transition(const TransitionArgs& p, hipStream_t s);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);
 hipError_t launch_group_norm(const void* x, const void* gain, const void* shift, void* y, void* partials, int64_t images,

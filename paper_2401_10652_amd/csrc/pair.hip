@@ -1,5 +1,6 @@
 // Modules of the pair stack whose intermediates of a row fit on chip: the end of a triangle update (output gate, LayerNorm over the
-// channels of the contraction, output projection, residual).  bf16, 64 or 128 channels.  A row's arithmetic does not depend on the launch it falls in.
+// channels of the contraction, output projection, residual) and the transition (LayerNorm, both layers, residual).  bf16, 64 or 128
+// channels.  A row's arithmetic does not depend on the launch it falls in.
 #include "common.h"
 
 namespace ac {
@@ -171,6 +172,171 @@ hipError_t launch_trimul_out(const TriMulOutArgs& p_in, hipStream_t s) {
   if (p.c_z == 128) p.c_hidden == 128 ? trimul_out_launch<128, 128>(p, s) : trimul_out_launch<128, 64>(p, s);
   else p.c_hidden == 128 ? trimul_out_launch<64, 128>(p, s) : trimul_out_launch<64, 64>(p, s);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------
+// Transition.  A wave owns 32 rows, normalised in registers, and walks the hidden columns 32 at a time: the product is taken transposed (weight rows
+// in the first operand), so that a lane holds hidden values of its own row, activated and rounded they are the second operand of the second product as
+// they stand, and no hidden value leaves the registers.  For that the first product takes weight row pi(m) as its row m (pi swaps bits 2 and 3),
+// which leaves a lane runs of eight consecutive hidden columns.  The weights of 64 hidden columns pass through LDS, twice buffered, one barrier each.
+// 524288 rows of 128 channels and 512 hidden: 224 + 198 us as two launches, 167 as one (820 TFLOP/s; 175 in the compiler's own order, which reads each
+// fragment right before its use); 40000 rows 31 and 23.  A CU's two blocks keep eight waves at two per SIMD.
+// ------------------------------------------------------------------------------------
+constexpr int kHiddenStep = 64;
+constexpr int transition_buffer_elems(int k) { return kHiddenStep * (k + 8) + k * (kHiddenStep + 8); }
+static size_t transition_lds(int k, int64_t hidden, int act) {
+  return (2 * (size_t)transition_buffer_elems(k) + hidden) * sizeof(bf16_t) + (act == AC_ACT_GELU_ERF ? kGeluTableBytes : 0);
+}
+
+template <int K, int ACT>
+__global__ void __launch_bounds__(256, 2) pair_transition_bf16(TransitionArgs p) {
+  constexpr int BM = 128, NT = 256, HS = kHiddenStep, AROW = K + 8, HROW = HS + 8, BUF = transition_buffer_elems(K);
+  constexpr int G = K / 8, RPP = NT / G, PASSES = BM / RPP;
+  constexpr int CHUNKS = HS * K / 8 / NT;                      // 16-byte chunks of either weight tile per thread
+  constexpr int NK = K / 16, NC = K / 32, AHEAD = 5;           // matrix instructions of 32 hidden columns in either product; 32-column tiles of the result
+  static_assert(BM * AROW <= BUF, "the normalised rows pass through the second buffer");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  bf16_t* buf = reinterpret_cast<bf16_t*>(smem_raw);           // [2]: w_1 rows [HS][K + 8], w_2 rows [K][HS + 8]
+  bf16_t* b1 = buf + 2 * BUF;                                  // [hidden]
+  float* gelu_tab = reinterpret_cast<float*>(b1 + p.hidden);
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, l32 = lane % 32, half = lane / 32;
+  const int64_t m0 = (int64_t)blockIdx.x * BM;
+  const bf16_t *z = (const bf16_t*)p.z, *w1 = (const bf16_t*)p.w_1, *w2 = (const bf16_t*)p.w_2;
+  const int hidden = (int)p.hidden, steps = hidden / HS;
+  if (ACT == AC_ACT_GELU_ERF) gelu_table_fill(gelu_tab, tid, NT);
+  for (int c = tid; c < hidden / 8; c += NT) *reinterpret_cast<bf16x8*>(b1 + c * 8) = ld8((const bf16_t*)p.b_1 + c * 8);
+
+  bf16x8 r1[CHUNKS], r2[CHUNKS];
+  auto load = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int c = tid + NT * i;
+      r1[i] = ld8(w1 + (int64_t)s * HS * K + c * 8);                             // (64 rows of w_1 are one run of memory)
+      r2[i] = ld8(w2 + (int64_t)(c / (HS / 8)) * hidden + s * HS + c % (HS / 8) * 8);
+    }
+  };
+  auto store = [&](bf16_t* b) {
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int c = tid + NT * i;
+      *reinterpret_cast<bf16x8*>(b + c / G * AROW + c % G * 8) = r1[i];
+      *reinterpret_cast<bf16x8*>(b + HS * AROW + c / (HS / 8) * HROW + c % (HS / 8) * 8) = r2[i];
+    }
+  };
+  load(0);
+  {
+    const int lg = tid % G, rg = tid / G;
+    const bf16x8 gain = ld8((const bf16_t*)p.ln_g + lg * 8), shift = ld8((const bf16_t*)p.ln_b + lg * 8);
+    bf16x8 x[PASSES];
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) {
+      int64_t r = m0 + ps * RPP + rg;
+      if (r > p.rows - 1) r = p.rows - 1;                      // rows past the end shadow the last one; never stored
+      x[ps] = ld8(z + r * K + lg * 8);
+    }
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) *reinterpret_cast<bf16x8*>(buf + BUF + (ps * RPP + rg) * AROW + lg * 8) = normalise<G>(x[ps], gain, shift, p.eps);
+  }
+  store(buf);
+  __syncthreads();
+  bf16x8 fa[K / 16];
+#pragma unroll
+  for (int ks = 0; ks < K / 16; ++ks) fa[ks] = ld8(buf + BUF + (wave * 32 + l32) * AROW + half * 8 + ks * 16);
+  __syncthreads();                                             // every wave has its rows: the second buffer is free
+  f32x16 acc[K / 32] = {};
+  const int pi = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
+  for (int s = 0; s < steps; ++s) {
+    if (s + 1 < steps) load(s + 1);
+    // The stage's matrix instructions in order: both 32-column halves of the first product, then of the second.  A fragment is read AHEAD
+    // instructions before it is used, and a half is activated between the instructions that do not need it; the barriers pin that order.
+    const bf16_t *b_1 = buf + (s & 1) * BUF + pi * AROW + half * 8, *b_2 = buf + (s & 1) * BUF + HS * AROW + l32 * HROW + half * 8;
+    auto fragment = [&](int i) {
+      const int u = i / NK % 2, j = i % NK;
+      return i < 2 * NK ? ld8(b_1 + u * 32 * AROW + j * 16) : ld8(b_2 + j % NC * 32 * HROW + u * 32 + j / NC * 16);
+    };
+    f32x16 h[2] = {};
+    bf16x8 bias[2][2], hv[2][2], f[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) f[i] = fragment(i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bias[i / 2][i % 2] = ld8(b1 + s * HS + i * 16 + half * 8);   // (hidden columns 16 i + 8 half + 0..7 of row l32)
+#pragma unroll
+    for (int i = 0; i < 4 * NK; ++i) {
+      const int part = i / NK, j = i % NK;
+      if (part < 2) h[part] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % AHEAD], fa[j], h[part], 0, 0, 0);
+      else acc[j % NC] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % AHEAD], hv[part - 2][j / NC], acc[j % NC], 0, 0, 0);
+      if (i + AHEAD < 4 * NK) f[i % AHEAD] = fragment(i + AHEAD);
+      if (part == 1 || part == 2) {
+#pragma unroll
+        for (int e = j * 16 / NK; e < (j + 1) * 16 / NK; ++e) {
+          const float x = h[part - 1][e] + bf2f(bias[part - 1][e / 8][e % 8]);
+          hv[part - 1][e / 8][e % 8] = f2bf(ACT == AC_ACT_GELU_ERF ? gelu_table(x, gelu_tab) : apply_act_bf16<ACT>(x));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (s + 1 < steps) store(buf + ((s + 1) & 1) * BUF);
+    __syncthreads();
+  }
+  // bias and residual: the rows of z (again, from L2) lie in LDS while a lane adds to its own elements of them
+  const int lg = tid % G, rg = tid / G;
+#pragma unroll
+  for (int ps = 0; ps < PASSES; ++ps) {
+    int64_t r = m0 + ps * RPP + rg;
+    if (r > p.rows - 1) r = p.rows - 1;
+    *reinterpret_cast<bf16x8*>(buf + (ps * RPP + rg) * AROW + lg * 8) = ld8(z + r * K + lg * 8);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < K / 32; ++c)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = c * 32 + 8 * q + 4 * half;
+      const bf16x4 bias = *reinterpret_cast<const bf16x4*>((const bf16_t*)p.b_2 + col);
+      bf16x4* at = reinterpret_cast<bf16x4*>(buf + (wave * 32 + l32) * AROW + col);
+      const bf16x4 zv = *at;
+      bf16x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = f2bf(acc[c][4 * q + j] + bf2f(bias[j]) + bf2f(zv[j]));
+      *at = v;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int ps = 0; ps < PASSES; ++ps) {
+    const int r = ps * RPP + rg;
+    if (m0 + r < p.rows)
+      *reinterpret_cast<bf16x8*>((bf16_t*)p.out + result_row(m0 + r, p.o_period, p.o_s1, p.o_s2, K) + lg * 8) = ld8(buf + r * AROW + lg * 8);
+  }
+}
+
+// (a hidden row of 1024 columns and the two buffers leave room for two blocks per CU)
+bool transition_shapes_ok(int dtype, int64_t c_z, int64_t hidden, int act) {
+  return dtype == AC_BF16 && (c_z == 64 || c_z == 128) && hidden > 0 && hidden % kHiddenStep == 0 && hidden <= 1024 &&
+         (act == AC_ACT_RELU || act == AC_ACT_GELU_ERF || act == AC_ACT_GELU_TANH);
+}
+
+template <int K, int ACT> static hipError_t transition_launch(const TransitionArgs& p, hipStream_t s) {
+  auto kern = pair_transition_bf16<K, ACT>;
+  static const hipError_t attr_status =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)transition_lds(K, 1024, ACT));
+  if (attr_status != hipSuccess) return attr_status;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((p.rows + 127) / 128)), dim3(256), transition_lds(K, p.hidden, ACT), s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_transition(const TransitionArgs& p_in, hipStream_t s) {
+  TransitionArgs p = p_in;
+  if (p.rows <= 0) return hipSuccess;
+  if (!transition_shapes_ok(AC_BF16, p.c_z, p.hidden, p.act) || p.rows > 0x7fffffffLL) return hipErrorInvalidValue;
+  for (const void* q : {p.z, p.ln_g, p.ln_b, p.w_1, p.b_1, p.w_2, p.b_2, (const void*)p.out})
+    if (!at16(q)) return hipErrorInvalidValue;
+  if (p.o_period <= 0) p.o_period = INT64_MAX;
+  else if (p.o_s1 % 8 != 0 || p.o_s2 % 8 != 0) return hipErrorInvalidValue;
+  if (p.c_z == 128)
+    return p.act == AC_ACT_RELU ? transition_launch<128, AC_ACT_RELU>(p, s)
+           : p.act == AC_ACT_GELU_ERF ? transition_launch<128, AC_ACT_GELU_ERF>(p, s) : transition_launch<128, AC_ACT_GELU_TANH>(p, s);
+  return p.act == AC_ACT_RELU ? transition_launch<64, AC_ACT_RELU>(p, s)
+         : p.act == AC_ACT_GELU_ERF ? transition_launch<64, AC_ACT_GELU_ERF>(p, s) : transition_launch<64, AC_ACT_GELU_TANH>(p, s);
 }
 
 }  // namespace ac

@@ -1062,9 +1062,19 @@ void Walk::transition(const void* const* W, const void* zin, void* zout) {
   const int e = eb();
   const bool col = p->set[AC_REGION_PAIR_TRANSITION].chunk_dim == AC_DIM_COL;
   enter(AC_REGION_PAIR_TRANSITION);
+  const bool one_pass = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE) && transition_shapes_ok(m.dtype, cz, F, m.activation);
   pair_loop(AC_REGION_PAIR_TRANSITION, row_segments(N, seg_len(AC_REGION_PAIR_TRANSITION)), zout, col, [&](const RowSeg& sg) {
     const int64_t rows = sg.ni * N;
     const void* zs = pair_segment(zin, sg, col);
+    if (one_pass) {   // (the plan counts the hidden rows all the same)
+      if (!shares()) arena.push((uint64_t)rows * F * e);
+      LinearArgs dst{};
+      pair_store(dst, zout, sg, col);
+      const TransitionArgs g{zs, W[PT_LN_G], W[PT_LN_B], W[PT_W_1], W[PT_B_1], W[PT_W_2], W[PT_B_2], dst.out, dst.o_period, dst.o_s1, dst.o_s2,
+                             rows, cz, F, m.activation, m.ln_eps};
+      run(K_GEMM, rows * (8.0 * cz + 4.0 * cz * F), (2.0 * rows * cz + 2.0 * cz * F) * e, "transition", [&] { return launch_transition(g, stream); });
+      return;
+    }
     const bool fuse_up = fuses_ln_proj(cz, {F});
     void* u = fuse_up ? nullptr : arena.push((uint64_t)rows * cz * e);
     void* hid = arena.push((uint64_t)rows * F * e);

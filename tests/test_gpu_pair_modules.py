@@ -1,5 +1,5 @@
-"""The one-kernel ends of the triangle updates against the oracle: row counts around their tiles of 64 rows, each channel count, row and column
-chunks; the bits do not depend on the chunks."""
+"""The one-kernel ends of the triangle updates and the one-kernel transition, module by module against the oracle: row counts around their tiles of
+64 and 128 rows, each channel count, activation and hidden width, row and column chunks; the bits do not depend on the chunks."""
 import pytest
 
 from oracle import pairstack as P
@@ -48,3 +48,12 @@ def test_triangle_update(B, n, c_z, c_hidden):
     for kind in (B.AC_REGION_TRIMUL_OUT, B.AC_REGION_TRIMUL_IN):
         y, ref = module(B, cfg, kind, settings(B, n))
         check(y, ref, "bf16", what=f"kind {kind}")
+
+
+@pytest.mark.parametrize("n,c_z,factor,activation", [
+    (8, 64, 1, "relu"), (8, 128, 1, "gelu_erf"), (16, 64, 4, "gelu_tanh"), (24, 128, 4, "relu"), (40, 128, 8, "gelu_tanh"), (48, 64, 3, "gelu_erf"),
+    (72, 128, 2, "gelu_tanh"), (104, 128, 4, "gelu_erf"), (16, 128, 9, "relu")])     # (nine times as wide: two launches)
+def test_transition(B, n, c_z, factor, activation):
+    cfg = I.PairConfig("tpt", 47, n, c_z, 64, 2, 32, factor, "bf16", activation=activation)
+    y, ref = module(B, cfg, B.AC_REGION_PAIR_TRANSITION, settings(B, n))
+    check(y, ref, "bf16")
