@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_NAME = "libautochunk_rt.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 
-SOURCES = ["rowwise.hip", "linear.hip", "pair.hip", "attention.hip", "runtime.hip", "search.hip"]
+SOURCES = ["rowwise.hip", "linear.hip", "pair.hip", "layer_f32.hip", "attention.hip", "runtime.hip", "search.hip"]
 
 # Per-file extras.  attention.hip: keep MFMA results in VGPRs; the softmax reads every score
 # right after the matrix op, and accumulator-register copies would double its VALU work.

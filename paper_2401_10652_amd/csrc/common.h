@@ -300,6 +300,14 @@ struct TransitionArgs {
 };
 bool transition_shapes_ok(int dtype, int64_t c_z, int64_t hidden, int act);
 hipError_t launch_transition(const TransitionArgs& p, hipStream_t s);
+// fp32 layers of 32, 64 or 128 channels; rows contiguous.  out[rows, n] = LN(x) w^T + bias, and
+// h = resid + ctx w_o^T + b_o; out = h + act(LN(h) w_1^T + b_1) w_2^T + b_2 with a feed-forward of 4 d columns.
+struct LnLinearF32Args { const void *x, *gain, *shift, *w, *bias; void* out; int64_t rows, d, n; float eps; };
+struct LayerTailF32Args { const void *ctx, *resid, *w_o, *b_o, *ln_g, *ln_b, *w_1, *b_1, *w_2, *b_2; void* out; int64_t rows, d; int act; float eps; };
+bool ln_linear_f32_shapes_ok(int dtype, int64_t d, int64_t n);
+hipError_t launch_ln_linear_f32(const LnLinearF32Args& p, hipStream_t s);
+bool layer_tail_f32_shapes_ok(int dtype, int64_t d, int64_t hidden);
+hipError_t launch_layer_tail_f32(const LayerTailF32Args& p, hipStream_t s);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);
 hipError_t launch_group_norm(const void* x, const void* gain, const void* shift, void* y, void* partials, int64_t images,

@@ -613,6 +613,10 @@ void Walk::transformer(const void* x, void* y) {
   // attention of an fp32 model, by a transpose after the projection region
   void* vt = (bf || stored_scores) ? arena.push((uint64_t)T * d * e) : nullptr;
   const int64_t ldqk = (bf ? 2 : 3) * d;
+  // fp32 layers of few channels: LayerNorm 1 and the projection in one launch, and all that follows the attention core in the feed-forward's launches (the
+  // plan counts the tensors between all the same)
+  const bool fused = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE);
+  const bool few_in = fused && ln_linear_f32_shapes_ok(m.dtype, d, 3 * d), few_out = fused && layer_tail_f32_shapes_ok(m.dtype, d, F);
 
   for (int l = 0; l < m.layers && ok(); ++l) {
     const void* in = l == 0 ? x : (const void*)tbuf;
@@ -629,6 +633,11 @@ void Walk::transformer(const void* x, void* y) {
     region_launches[AC_REGION_QKV] = (int64_t)qkv_segs.size();
     seg_loop(qkv_segs, [&](const Seg& sg) {
       const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
+      if (few_in) {
+        const LnLinearF32Args g{at(in, r0 * d), W(W_LN1G), W(W_LN1B), W(W_QKV), W(W_BQKV), atw(qk, r0 * ldqk), rows, d, 3 * d, m.ln_eps};
+        run(K_GEMM, 8.0 * rows * d + 2.0 * rows * 3 * d * d, ((double)rows * 4 * d + 3.0 * d * d) * e, "ln_linear", [&] { return launch_ln_linear_f32(g, stream); });
+        return;
+      }
       void* u = atw(ctx_all, r0 * d);
       ln(at(in, r0 * d), d, W(W_LN1G), W(W_LN1B), u, d, rows, d);
       LinearArgs g{};
@@ -711,6 +720,7 @@ void Walk::transformer(const void* x, void* y) {
     seg_loop(col_segs, [&](const ColSeg& cs) {
       const Seg& sg = cs.t;
       const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
+      if (few_out) return;
       proj(at(ctx_all, r0 * d), d, at(W(W_O), cs.n0 * d), d, at(W(W_BO), cs.n0), AC_ACT_NONE, at(in, r0 * d + cs.n0), d,
            atw(hbuf, r0 * d + cs.n0), d, rows, cs.nc);
     });
@@ -721,6 +731,7 @@ void Walk::transformer(const void* x, void* y) {
     enter(AC_REGION_FFN);
     const std::vector<Seg> ffn_segs = token_segments(m, p->set[AC_REGION_FFN].chunk_dim, seg_len(AC_REGION_FFN));
     for (const Seg& sg : merged_segments(m, ffn_segs)) {
+      if (few_out) break;
       const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
       ln(at(hbuf, r0 * d), d, W(W_LN2G), W(W_LN2B), atw(ctx_all, r0 * d), d, rows, d);
     }
@@ -728,6 +739,13 @@ void Walk::transformer(const void* x, void* y) {
       const int64_t r0 = r.i0, rows = r.ni;
       const void* u = at(ctx_all, r0 * d);
       void* hid = arena.push((uint64_t)rows * F * e);
+      if (few_out) {
+        const LayerTailF32Args g{u, at(in, r0 * d), W(W_O), W(W_BO), W(W_LN2G), W(W_LN2B), W(W_1), W(W_B1), W(W_2), W(W_B2), atw(out, r0 * d), rows, d,
+                                 m.activation, m.ln_eps};
+        run(K_GEMM, rows * (2.0 * d * d + 8.0 * d + 4.0 * d * F), (rows * 3.0 * d + d * (d + 2.0 * F)) * e, "layer_tail",
+            [&] { return launch_layer_tail_f32(g, stream); });
+        return;
+      }
       proj(u, d, W(W_1), d, W(W_B1), m.activation, nullptr, 0, hid, F, rows, F);
       proj(hid, F, W(W_2), F, W(W_B2), AC_ACT_NONE, at(hbuf, r0 * d), d, atw(out, r0 * d), d, rows, d);
     };
