@@ -1191,6 +1191,140 @@ static hipError_t quad_launch(const LinearArgs& g, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------
+// fp32 MFMA kernel, tiles by direct global-to-LDS loads through a ring of three buffers of 32 k.
+//
+// What bounds linear_mfma_f32 on larger products is its stream of operands: a step of 16 k asks for half a cache line of every row, a CU holds about a
+// hundred such requests in flight whatever they carry, and each wave fetches the whole tile's operands for itself.  Here a row's step is a whole line,
+// fetched once for the block's four waves, which hold a quarter of the tile each over all of k.  The loop is the bf16 ring's: loads three tiles ahead, the next
+// tile's fragments read between this one's matrix instructions, chunks of a row permuted so that a read meets every bank (lanes of sixteen rows and two chunks: the
+// same permutation serves).  The four parts of a sum over k that linear_mfma_f32 gives to four waves follow one another here and are added in the same
+// order, each a chain of the same instructions: equal bits.  (Depths that are a multiple of 128: parts of whole tiles.)
+// ------------------------------------------------------------------------------------
+template <int BM, int BN, int WAVES_M, int WAVES_N>
+__global__ void __launch_bounds__(256) linear_ring_f32(LinearArgs g, int vec) {
+  constexpr int NW = 4, STAGES = 3, BK = 32, ROWB = BK * 4, CPR = 8, RPI = 8;        // bytes and chunks per LDS row, rows per load instruction
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 16, TN = WN / 16;
+  constexpr int A_I = BM / RPI / NW, W_I = BN / RPI / NW, PER = A_I + W_I;
+  constexpr int READS = 2 * (TM + TN), MMAS = 8 * TM * TN, STAGE = (BM + BN) * ROWB;
+  static_assert(WAVES_M * WAVES_N == NW && BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile / wave layout mismatch");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64), l16 = lane % 16, grp = lane / 16;
+  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
+  int64_t tm_, tn_;
+  tile_of_block((g.m + BM - 1) / BM, (g.n + BN - 1) / BN, tm_, tn_);
+  const int64_t m0 = tm_ * BM, n0 = tn_ * BN;
+  const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
+  const float* a = (const float*)g.a + product * g.sa_b + m0 * g.lda;
+  const float* w = (const float*)g.w + product * g.sw_b + n0 * g.ldw;
+  const int row_in = lane / CPR, src_chunk = (lane % CPR) ^ ring_swizzle<64>(wave * RPI + row_in);
+  uint32_t a_off[A_I], w_off[W_I];
+#pragma unroll
+  for (int i = 0; i < A_I; ++i) {   // rows past the end shadow the last one; never stored
+    const int64_t r = (wave + NW * i) * RPI + row_in, last = g.m - 1 - m0;
+    a_off[i] = (uint32_t)((r < last ? r : last) * g.lda * 4) + src_chunk * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < W_I; ++i) {
+    const int64_t r = (wave + NW * i) * RPI + row_in, last = g.n - 1 - n0;
+    w_off[i] = (uint32_t)((r < last ? r : last) * g.ldw * 4) + src_chunk * 16;
+  }
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a), 0, -1, 0x00027000);
+  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w), 0, -1, 0x00027000);
+  auto load_part = [&](int kt, int stage, int x) {
+    unsigned char* dst = smem_raw + stage * STAGE + (x < A_I ? x * NW * 1024 : BM * ROWB + (x - A_I) * NW * 1024) + wave * 1024;
+    auto buffer_to_lds = [](__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, uint32_t tile_off, unsigned char* lds) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, lane_off, tile_off, 0, 0);
+    };
+    if (x < A_I) buffer_to_lds(a_rsrc, a_off[x < A_I ? x : 0], kt * ROWB, dst);
+    else buffer_to_lds(w_rsrc, w_off[x < A_I ? 0 : x - A_I], kt * ROWB, dst);
+  };
+  // this wave's loads of all but the youngest tile (or all of them) have landed and its LDS reads are done, then every wave's
+  auto arrived = [&](bool but_one) {
+    constexpr int kNoExp = 7 << 4;
+    asm volatile("" ::: "memory");
+    if (but_one) __builtin_amdgcn_s_waitcnt(PER | kNoExp);
+    else __builtin_amdgcn_s_waitcnt(kNoExp);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  f32x4 acc[TM][TN], total[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = total[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 fa[2][2][TM], fw[2][2][TN];
+  int frag_off[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) frag_off[s] = l16 * ROWB + ((s * 4 + grp) ^ ring_swizzle<64>(l16)) * 16;
+  const unsigned char* const sA = smem_raw + wave_m * WM * ROWB;
+  const unsigned char* const sW = smem_raw + BM * ROWB + wave_n * WN * ROWB;
+  auto read_frag = [&](f32x4 (&fa_)[2][TM], f32x4 (&fw_)[2][TN], int base, int r) {
+    const int s = r / (TM + TN), x = r % (TM + TN);
+    if (x < TN) fw_[s][x] = *reinterpret_cast<const f32x4*>(sW + base + frag_off[s] + x * 16 * ROWB);
+    else fa_[s][x - TN] = *reinterpret_cast<const f32x4*>(sA + base + frag_off[s] + (x - TN) * 16 * ROWB);
+  };
+  const int kt_count = (int)(g.k / BK), part = kt_count / kF32Runs;
+  int kt = 0, stage = 0, fold = part;
+  auto step = [&](const f32x4 (&ca)[2][TM], const f32x4 (&cw)[2][TN], f32x4 (&na)[2][TM], f32x4 (&nw)[2][TN]) {
+    const bool more = kt + STAGES < kt_count;
+    const int free_stage = stage;
+    stage = stage + 1 == STAGES ? 0 : stage + 1;
+    const int base = stage * STAGE;
+    __builtin_amdgcn_sched_barrier(0);
+    int done = 0;
+#pragma unroll
+    for (int x = 0; x < MMAS; ++x) {
+      const int s = x / (4 * TM * TN), e = x / (TM * TN) % 4, i = x / TN % TM, j = x % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(cw[s][j][e], ca[s][i][e], acc[i][j], 0, 0, 0);
+      if (done < READS && done * (3 * MMAS) < (x + 1) * 4 * READS) read_frag(na, nw, base, done++);
+#pragma unroll
+      for (int c = x * PER / MMAS; c < (x + 1) * PER / MMAS; ++c) {
+        if (more) load_part(kt + STAGES, free_stage, c);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // (tile kt + 2 must have landed; of those asked for, kt + 3 is the youngest)
+    arrived(more);
+    if (++kt == fold) {
+      fold += part;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) total[i][j][e] += acc[i][j][e];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < STAGES; ++t)      // (at least four tiles)
+#pragma unroll
+    for (int x = 0; x < PER; ++x) load_part(t, t, x);
+  {
+    constexpr int kNoExp = 7 << 4;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(PER | kNoExp);           // tiles 0 and 1
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
+#pragma unroll
+  for (int r = 0; r < READS; ++r) read_frag(fa[0], fw[0], 0, r);
+  // (tile 0 lies in registers before its buffer is loaded again)
+  arrived(true);
+  for (int t = 0; t < kt_count; t += 2) {   // (kt_count is a multiple of four)
+    step(fa[0], fw[0], fa[1], fw[1]);
+    step(fa[1], fw[1], fa[0], fw[0]);
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      epilogue_store_f32x4(g, vec, product, m0 + wave_m * WM + i * 16 + l16, n0 + wave_n * WN + j * 16 + 4 * grp, total[i][j]);
+}
+
+// ------------------------------------------------------------------------------------
 // LayerNorm + several projections of the same short rows in one kernel.
 // The pair-stack modules project every LayerNorm output four or five times with K = c_z
 // (gated a and b of the triangle update; q, k, v, gate and pair bias of the triangle attention;
@@ -1623,11 +1757,21 @@ static hipError_t mfma_f32_launch(const LinearArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N>
+static hipError_t ring_f32_launch(const LinearArgs& g, hipStream_t s) {
+  auto kern = linear_ring_f32<BM, BN, WAVES_M, WAVES_N>;
+  constexpr int lds = 3 * (BM + BN) * 128;
+  static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr_status != hipSuccess) return attr_status;
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles_of(g, BM, BN), (unsigned)g.batch), dim3(256), lds, s, g, f32_rows_vectorisable(g) ? 1 : 0);
+  return hipGetLastError();
+}
+
 // The kernel a product runs on: a function of sizes, types, strides and alignment, decided on the host.
-enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kRouteQuad, kRing256x128, kRing128x128, kRing128x192, kStaged128x128, kRing128x64, kRing64x64,
+enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kF32Ring32x64, kF32Ring32x32, kRouteQuad, kRing256x128, kRing128x128, kRing128x192, kStaged128x128, kRing128x64, kRing64x64,
              kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x192, kConv128x64, kConv64x64, kConvWide64x64, kRoutes };
 static const char* const kRouteName[kRoutes] = {
-    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
+    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "f32 32x64", "f32 32x32", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
     "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x192", "conv 128x64", "conv 64x64", "conv-wide 64x64"};
 
 static bool wide_rows(const LinearArgs& g) { return g.lda >= (1 << 22) || g.ldw >= (1 << 22); }
@@ -1664,9 +1808,32 @@ static Route f32_route(const LinearArgs& g) {
   // rows for it (16000 x 1024 x 64 61 against 77 us, 16000 x 8192 x 32 278 against 360) and behind before (256 x 1024 x 64 12.5 against 4.9).
   // By k and n alone, as the two kernels sum in different orders and a row's bits must not depend on the launch's rows.
   if (g.k <= 64 && g.n >= 1024) return kFma;
-  // The tile of least estimated time: rounds of 256 tiles x (k / 64 steps + prologue and epilogue), plus what is paid once, in us; fitted to 172 products
+  // Depths of whole tiles in each of a sum's four parts: the ring where a launch has the rows and columns for it, the kernel whose waves share out k where it
+  // is short of blocks and a quarter of the chain counts.  Estimated time: steps x the larger of what one block needs by itself (ring) and what its rounds
+  // need together, plus per tile, plus once, in us; fitted to 80 products of 68 to 16000 rows x 72 to 2848 columns x 128 to 3968 deep, on which the choice is
+  // 1 % off the best of the five on average and 6 % at worst and 1.23 times ahead of the best without the ring.  us, 32x64 / 32x32 ring, 32x64 / 32x32 / 32x16 /
+  // 16x16 shared: 1024 x 1536 x 512 19.2 / 21.7, 33.1 / 34.9 / 49.8 / 65.1; 1024 x 512 x 2048 29.9 / 31.8, 30.1 / 34.9 / 49.8 / 65.0; 256 x 512 x 2048 28.6 / 25.1,
+  // 29.0 / 18.6 / 15.0 / 18.8; 16000 x 512 x 512 79 / 92, 149 / 172 / 250 / 330; 96 x 512 x 2048 29 / 25, 29 / 19 / 15 / 11.  (Rings of 64x64 and 128x64 are never
+  // more than 1 % ahead.)
+  if (g.k % 128 == 0 && g.k <= (1 << 26) && !wide_rows(g)) {
+    struct Cost { Route route; int bm, bn; double once, step1, tile, step; };
+    static const Cost costs[5] = {{kF32Ring32x64, 32, 64, 5.48, 0.706, 0.38, 0.548}, {kF32Ring32x32, 32, 32, 5.42, 0.608, 0.03, 0.356},
+                                  {kF32_32x32, 32, 32, 3.77, 0, 1.17, 0.445}, {kF32_32x16, 32, 16, 3.35, 0, 0.83, 0.337}, {kF32_16x16, 16, 16, 3.34, 0, 0.53, 0.226}};
+    int best = -1;
+    double best_t = 0;
+    for (int c = 0; c < 5; ++c) {
+      const int64_t tiles = tiles_of(g, costs[c].bm, costs[c].bn);
+      if (!grid_fits(tiles, 256)) continue;
+      const double steps = (double)(g.k / 64), exact = (double)(tiles * g.batch) / 256, whole = (double)((tiles * g.batch + 255) / 256);
+      const double rounds = costs[c].step1 > 0 && whole > 1 ? 0.5 * (exact + whole) : whole;       // (the ring's blocks share a CU)
+      const double busy = rounds * steps * costs[c].step, one = steps * costs[c].step1, t = (busy > one ? busy : one) + rounds * costs[c].tile + costs[c].once;
+      if (best < 0 || t < best_t) { best = c; best_t = t; }
+    }
+    return best < 0 ? kFma : costs[best].route;
+  }
+  // Other depths: the tile of least estimated time: rounds of 256 tiles x (k / 64 steps + prologue and epilogue), plus what is paid once, in us; fitted to 172 products
   // of 1 to 20000 rows x 4 to 8192 columns x 36 to 8192 deep, most of them no multiples of a tile.  Within 4 % the larger tile, which reads less per
-  // output: 1024 x 1536 x 512 inside a model takes 35 us on 32x64 and 37 on 32x32, 16000 x 2048 x 128 157 and 224.  The choice is 1 % off the
+  // output: 4000 x 2048 x 96.  The choice is 1 % off the
   // best of the four on average and 32 % at worst (by area alone 11 % on average: a row past a multiple of the large tiles had sent
   // 777 x 512 x 512 to 16x16, 21.9 us, where 32x64 takes 12.7).
   struct Cost { int bm, bn; double step, tile, once; };
@@ -1753,6 +1920,8 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     case kF32_32x32: return mfma_f32_launch<2, 2>(g, s);
     case kF32_32x16: return mfma_f32_launch<2, 1>(g, s);
     case kF32_16x16: return mfma_f32_launch<1, 1>(g, s);
+    case kF32Ring32x64: return ring_f32_launch<32, 64, 1, 4>(g, s);
+    case kF32Ring32x32: return ring_f32_launch<32, 32, 2, 2>(g, s);
     case kRouteQuad: return quad_launch<false>(g, s);
     case kRing256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
     case kRing128x128: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);

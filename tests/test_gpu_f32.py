@@ -50,6 +50,28 @@ def test_linear_f32(B, m, n, k):
     assert torch.equal(part, out)
 
 
+@pytest.mark.parametrize("m,n,k", [(1024, 512, 512), (1100, 1540, 128), (1531, 601, 256), (5900, 65, 1152), (5000, 96, 384), (250, 2100, 640)])
+def test_linear_f32_depths_of_whole_tiles(B, m, n, k):
+    """Launches of a ring of tiles, odd rows and columns among them: the oracle's values, and the bits of launches of 33 rows (waves that share out k)."""
+    import torch
+    a, w = draw((m, k), 114, "f32"), draw((n, k), 115, "f32", 1 / math.sqrt(k))
+    bias, res = draw((n,), 116, "f32", 0.5), draw((m, n), 117, "f32")
+    da, dw, db, dr = (B.to_device(t, "f32") for t in (a, w, bias, res))
+    guard = torch.full((m + 2, n), float("nan"), device="cuda")
+    out = guard[1:-1]
+    B.ac_op_linear(da, dw, out, bias=db, residual=dr)
+    torch.cuda.synchronize()
+    check(host(out), O.linear(a, w, bias) + res, "f32")
+    assert bool(torch.isnan(guard[0]).all()) and bool(torch.isnan(guard[-1]).all())
+    assert B.ac_linear_kernel(m, n, k, "f32") in ("f32 32x64", "f32 32x32")
+    part = torch.full((m, n), float("nan"), device="cuda")
+    for r0 in range(0, m, 33):
+        r1 = min(m, r0 + 33)
+        B.ac_op_linear(da[r0:r1], dw, part[r0:r1], bias=db, residual=dr[r0:r1])
+    torch.cuda.synchronize()
+    assert torch.equal(part, out)
+
+
 @pytest.mark.parametrize("dh", [16, 32, 64, 128])
 @pytest.mark.parametrize("sq,sk,causal,off", [
     (1, 1, False, 0), (16, 32, False, 0), (17, 33, True, 16), (70, 129, False, 0), (200, 200, True, 0), (40, 300, True, 260)])
