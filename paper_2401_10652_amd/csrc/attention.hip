@@ -33,6 +33,16 @@ __device__ __forceinline__ int64_t xcd_contiguous(int64_t pid, int64_t nb) {
   return x * q + (x < r ? x : r) + idx;
 }
 
+// Causal blocks of a head: longest rows first, in a snake over runs of 32 (the CUs of an XCD, which take consecutive
+// blocks in turn): the first 32 blocks of a head are its longest in descending order, the next 32 the following ones in ascending order, and
+// so on, so that when all blocks of a launch are resident at once (one sequence of a few thousand rows) every CU holds about the same number
+// of key tiles; with more blocks than places the order is still longest-first run by run.
+__device__ __forceinline__ int snake(int qb, int nqb) {
+  const int run = qb / 32, col = qb % 32;
+  const int len = nqb - run * 32 < 32 ? nqb - run * 32 : 32;
+  return nqb - 1 - (run * 32 + ((run & 1) ? len - 1 - col : col));
+}
+
 // ------------------------------------------------------------------------------------
 // Generic kernel.
 // ------------------------------------------------------------------------------------
@@ -129,7 +139,8 @@ __global__ void __launch_bounds__(128) attention_rows(AttnArgs a) {
 // registers = 4 consecutive keys) which is the operand layout of the second product, and value rows are
 // read whole, lane l16 holding d = NV l16 .. NV l16 + NV - 1.
 // Measured (1024 x 1024 causal, 8 heads of 64 / 256 x 256, 4 heads of 16): 916 / 71 us with one thread per
-// row (the kernel above), 34 / 5.2 us here.
+// row (the kernel above), 23 / 5.2 us here (34 with the longest rows of every head first, which gave a CU two blocks of the same length, and the
+// heads spread over the XCDs).
 // ------------------------------------------------------------------------------------
 template <int DH>
 __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
@@ -141,9 +152,9 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, l16 = lane % 16, grp = lane / 16;
   const int sq = (int)a.sq, sk = (int)a.sk;
   const int nqb = (sq + 15) / 16;
-  const int64_t bh = blockIdx.x / nqb;
-  int qb = (int)(blockIdx.x % nqb);
-  if (a.causal) qb = nqb - 1 - qb;                         // longest rows first
+  const int64_t t = xcd_contiguous(blockIdx.x, gridDim.x), bh = t / nqb;   // (a head's blocks on one XCD: its keys and values stay in that L2)
+  int qb = (int)(t % nqb);
+  if (a.causal) qb = snake(qb, nqb);
   const int64_t b = bh / a.heads;
   const int h = (int)(bh % a.heads), q0 = qb * 16;
   const int row = q0 + l16, rowc = row < sq ? row : sq - 1;   // rows past the end shadow the last one; never stored
@@ -331,17 +342,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   const int64_t bq = t / ns;
   const int64_t bh = bq / nqb;
   int qb = (int)(bq % nqb);
-  if (CAUSAL) {
-    // Longest rows first, in a snake over runs of 32 (the CUs of an XCD, which take consecutive
-    // blocks in turn): the first 32 blocks of a head are its longest in descending order, the next
-    // 32 the following ones in ascending order, and so on, so that when all blocks of a launch are
-    // resident at once (one sequence of a few thousand rows) every CU holds about the same number
-    // of key tiles; with more blocks than places the order is still longest-first run by run.
-    const int run = qb / 32, col = qb % 32;
-    const int len = nqb - run * 32 < 32 ? nqb - run * 32 : 32;
-    const int rank = run * 32 + ((run & 1) ? len - 1 - col : col);
-    qb = nqb - 1 - rank;
-  }
+  if (CAUSAL) qb = snake(qb, nqb);
   // Problem-major order keeps the heads of one problem together (their q/k/v rows interleave in
   // memory).  Head-major order (set by the host when a bias shared by all problems is the
   // largest operand) gives each XCD a run of problems of ONE head, so that head's bias stays
