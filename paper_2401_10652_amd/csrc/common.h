@@ -255,7 +255,8 @@ struct ProjPart {
   void* out_t; int64_t t_period, t_s1, t_s2, t_s3;          // strided store of the whole part (see LinearArgs)
 };
 struct LnProjArgs {
-  const void* x; int64_t ldx;      // [rows, K]
+  const void* x; int64_t ldx;      // [rows, K]; with x_period > 0 row r lies at x[(r / x_period) * x_s1 + (r % x_period) * x_s2]
+  int64_t x_period, x_s1, x_s2;
   const void* gain; const void* shift; float eps;
   int64_t rows; int64_t k;
   int n_parts;

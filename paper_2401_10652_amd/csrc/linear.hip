@@ -1424,7 +1424,13 @@ __global__ void __launch_bounds__(256, K == 64 ? 5 : 4) ln_multi_proj_bf16(LnPro
     for (int ps = 0; ps < PASSES; ++ps) {
       int64_t r = m0 + ps * RPP + rg;
       if (r > p.rows - 1) r = p.rows - 1;     // rows past the end shadow the last row; never stored
-      load_vec(x + r * p.ldx + lg * 8, v[ps]);
+      int64_t at = r * p.ldx;
+      if (p.x_period > 0) {                   // (positions of a pair tensor in the order of their columns: a row is two whole cache lines wherever it lies)
+        int64_t q, c;
+        split_row(r, p.x_period, q, c);
+        at = q * p.x_s1 + c * p.x_s2;
+      }
+      load_vec(x + at + lg * 8, v[ps]);
     }
     float gn[8], sh[8];
     load_vec((const bf16_t*)p.gain + lg * 8, gn);
@@ -1559,7 +1565,10 @@ static bool ln_proj_overlaps(const LnProjArgs& p) {
     lo = (q < 0 ? q : 0) + (r < 0 ? r : 0) + (c < 0 ? c : 0);
     hi = (q > 0 ? q : 0) + (r > 0 ? r : 0) + (c > 0 ? c : 0);
   };
-  const bf16_t *x_lo = (const bf16_t*)p.x, *x_hi = x_lo + (p.rows - 1) * p.ldx + p.k;
+  int64_t x0, x1;
+  if (p.x_period > 0) span(p.x_period, p.x_s1, p.x_s2, p.k, 1, x0, x1);
+  else span(INT64_MAX, 0, p.ldx, p.k, 1, x0, x1);
+  const bf16_t *x_lo = (const bf16_t*)p.x + x0, *x_hi = (const bf16_t*)p.x + x1 + 1;
   for (int i = 0; i < p.n_parts; ++i) {
     const ProjPart& pp = p.part[i];
     const bf16_t* out = (const bf16_t*)(pp.out_t ? pp.out_t : pp.out);
@@ -1601,7 +1610,7 @@ hipError_t launch_ln_proj(const LnProjArgs& p_in, hipStream_t s) {
   if (p.n_parts < 1 || p.n_parts > kMaxProjParts) return hipErrorInvalidValue;
   for (int i = 0; i < p.n_parts; ++i) ns[i] = p.part[i].n;
   if (!ln_proj_shapes_ok(AC_BF16, p.k, ns, p.n_parts)) return hipErrorNotSupported;
-  if (p.ldx % 8 != 0 || ((uintptr_t)p.x % 16) != 0 || ((uintptr_t)p.gain % 16) != 0 || ((uintptr_t)p.shift % 16) != 0)
+  if ((p.x_period > 0 ? p.x_s1 % 8 != 0 || p.x_s2 % 8 != 0 : p.ldx % 8 != 0) || ((uintptr_t)p.x % 16) != 0 || ((uintptr_t)p.gain % 16) != 0 || ((uintptr_t)p.shift % 16) != 0)
     return hipErrorNotSupported;
   if (p.rows > 0x7fffffffLL) return hipErrorInvalidValue;
   for (int i = 0; i < p.n_parts; ++i) {

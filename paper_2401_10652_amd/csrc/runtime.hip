@@ -489,9 +489,11 @@ struct Walk {
     std::vector<int64_t> v(ns);
     return ln_proj_shapes_ok(p->m.dtype, k, v.data(), (int)v.size());
   }
+  // by_columns: the rows are all n * n positions of a pair tensor, taken column after column
   void ln_proj(const void* x, int64_t ldx, const void* g, const void* b, int64_t rows, int64_t k,
-               std::initializer_list<ProjPart> parts) {
+               std::initializer_list<ProjPart> parts, int64_t by_columns = 0) {
     LnProjArgs a{};
+    if (by_columns > 0) { a.x_period = by_columns; a.x_s1 = ldx; a.x_s2 = by_columns * ldx; }
     a.x = x; a.ldx = ldx; a.gain = g; a.shift = b; a.eps = p->m.ln_eps; a.rows = rows; a.k = k;
     double fl = 8.0 * rows * k, by = (double)rows * k * eb();
     for (const ProjPart& pp : parts) {
@@ -849,9 +851,9 @@ void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) 
   void* b_t = arena.push((uint64_t)ch * R * e);   // [c][j][k]
   const std::vector<RowSeg> segs = row_segments(N, seg_len(kind));
   // ---- whole operands: a and b of every position, channel-major.  Row r = (i, k) of z lands
-  // at [c][r]; for the incoming form r = (k, i), and the per-channel matrices are transposed
-  // in place afterwards.  (Built in runs of rows of the segment length whatever the chunk dim.)
-  // The fused kernel keeps nothing of a run of rows in memory, so it takes them all in one launch.
+  // at [c][r]; for the incoming form r = (k, i): the fused kernel takes the positions column after column, otherwise the
+  // per-channel matrices are transposed in place afterwards (N = 1024: 78 + 91 us, which reading by columns does not cost).  (Built in runs of rows of the
+  // segment length whatever the chunk dim.)  The fused kernel keeps nothing of a run of rows in memory, so it takes them all in one launch.
   const bool fuse_ab = fuses_ln_proj(cz, {ch, ch}), fuse_g = fuses_ln_proj(cz, {cz});
   const std::vector<RowSeg> all_rows{RowSeg{0, N}};
   seg_loop(fuse_ab ? all_rows : segs, [&](const RowSeg& sg) {
@@ -862,7 +864,7 @@ void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) 
       pa.n = ch; pa.out_t = atw(a_t, r0); pa.t_s2 = 1; pa.t_s3 = R;
       pb.w = W[TM_W_BP]; pb.bias = W[TM_B_BP]; pb.w_gate = W[TM_W_BG]; pb.bias_gate = W[TM_B_BG]; pb.gated = 1;
       pb.n = ch; pb.out_t = atw(b_t, r0); pb.t_s2 = 1; pb.t_s3 = R;
-      ln_proj(at(zin, r0 * cz), cz, W[TM_LN_IN_G], W[TM_LN_IN_B], rows, cz, {pa, pb});
+      ln_proj(at(zin, r0 * cz), cz, W[TM_LN_IN_G], W[TM_LN_IN_B], rows, cz, {pa, pb}, incoming ? N : 0);
       return;
     }
     void* t = arena.push((uint64_t)rows * cz * e);
@@ -880,7 +882,7 @@ void Walk::tri_mul(int kind, const void* const* W, const void* zin, void* zout) 
       linear(v);
     }
   });
-  if (incoming) {
+  if (incoming && !fuse_ab) {
     transpose_inplace(a_t, N, R, N, ch);
     transpose_inplace(b_t, N, R, N, ch);
   }
@@ -958,7 +960,7 @@ void Walk::tri_att(int kind, const void* const* W, const void* zin, void* zout) 
   enter(kind);
   const std::vector<RowSeg> segs = row_segments(N, seg_len(kind));
   // ---- whole operands, built from runs of rows of z.  The pair bias [h][q][k]: the projection at
-  // position (q, k) for the starting node, at (k, q) for the ending node (transposed in place
+  // position (q, k) for the starting node, at (k, q) for the ending node (by columns, or transposed in place
   // per head afterwards).  For the ENDING form also all keys as [(problem, key)][h*d] and all
   // values channel-major [h*d][problem][key]: for the ending node's row chunks the problem is the
   // column j and the key index the row k of z, so the projection stores the row of position
@@ -972,16 +974,15 @@ void Walk::tri_att(int kind, const void* const* W, const void* zin, void* zout) 
   const std::vector<RowSeg> all_rows{RowSeg{0, N}};   // the fused kernel holds nothing per run of rows: one launch
   seg_loop(fuse_a ? all_rows : segs, [&](const RowSeg& sg) {
     const int64_t r0 = sg.i0 * N, rows = sg.ni * N;
-    // keys of the whole tensor: regrouped by column for the ending node, as they are otherwise
+    // keys of the whole tensor: regrouped by column for the ending node (where its rows are not taken by columns), as they are otherwise
     void* k_dst = !k_all ? nullptr : (ending ? atw(k_all, sg.i0 * hd) : atw(k_all, r0 * hd));
     if (fuse_a) {
       ProjPart pb{}, pk{}, pv{};
       pb.w = W[TA_W_BIAS]; pb.n = H; pb.out_t = atw(bias, r0); pb.t_s2 = 1; pb.t_s3 = R;
       pk.w = W[TA_W_K]; pk.n = hd; pk.out = k_dst; pk.ldo = hd;
-      if (ending) { pk.o_period = N; pk.o_s1 = hd; pk.o_s2 = N * hd; }     // row (k - i0, j) -> (j, k)
       pv.w = W[TA_W_V]; pv.n = hd; pv.out_t = v_all ? atw(v_all, r0) : nullptr; pv.t_s2 = 1; pv.t_s3 = R;
-      if (ending_form) ln_proj(at(zin, r0 * cz), cz, W[TA_LN_G], W[TA_LN_B], rows, cz, {pb, pk, pv});
-      else ln_proj(at(zin, r0 * cz), cz, W[TA_LN_G], W[TA_LN_B], rows, cz, {pb});
+      if (ending_form) ln_proj(at(zin, r0 * cz), cz, W[TA_LN_G], W[TA_LN_B], rows, cz, {pb, pk, pv}, ending ? N : 0);
+      else ln_proj(at(zin, r0 * cz), cz, W[TA_LN_G], W[TA_LN_B], rows, cz, {pb}, ending ? N : 0);
       return;
     }
     void* t = arena.push((uint64_t)rows * cz * e);
@@ -1002,7 +1003,7 @@ void Walk::tri_att(int kind, const void* const* W, const void* zin, void* zout) 
       linear(vv);
     }
   });
-  if (ending) {
+  if (ending && !fuse_a) {
     transpose_inplace(bias, N, R, N, H);
     if (ending_form) transpose_inplace(v_all, N, R, N, hd);
   }
