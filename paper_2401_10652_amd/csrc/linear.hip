@@ -1547,6 +1547,161 @@ __global__ void __launch_bounds__(256, K == 64 ? 5 : 4) ln_multi_proj_bf16(LnPro
   }
 }
 
+// The same for many rows, where the parts make up 256 or 512 weight columns: weights in registers, 32 columns of each of SLOTS parts per wave (a
+// gated pair: both weights of the same 32 columns), for all the row tiles that a block of eight waves walks.  The next tile's rows are normalised into a second
+// buffer while this one's are multiplied, one barrier a tile, and a wave stores its own results through LDS of its own.  A part that is stored strided takes the
+// product with its operands exchanged, which leaves a lane runs of rows instead of runs of columns.  The matrix instructions and their order are the kernel's
+// above: equal bits.  What bounded that one is vector work and its two barriers per 64 columns: per 64 rows and 512 columns it also moves 128 KB of weights from L2
+// through registers into LDS.  Two gated pairs of 1048576 rows of 128 367 -> 242 us (3.3 TB/s; 409 -> 255 by columns), q, k, v and gate of 524288 rows 232 -> 154,
+// q and gate 147 -> 98; of 40000 rows 22.8 -> 17.8, 20000 rows 16.8 -> 15.6.
+struct LnProjSlice { int part, n0; };
+struct LnProjSliceArgs { LnProjArgs a; LnProjSlice slice[16]; };
+
+template <int K, int SLOTS, bool GATED, int BM>
+__global__ void __launch_bounds__(512) ln_proj_slices_bf16(LnProjSliceArgs ka) {
+  constexpr int NT = 512, AROW = K + 8, G = K / 8, RPP = NT / G, PASSES = BM / RPP > 0 ? BM / RPP : 1, KSTEPS = K / 16, SUB = BM / 32;
+  constexpr int W = GATED ? 2 : SLOTS, SROW = 40, TROW = BM + 8, STAGE = 32 * (TROW > SROW ? TROW : SROW);   // (a gated pair: gate, value)
+  static_assert(!GATED || SLOTS == 1, "a pair per wave");
+  __shared__ __attribute__((aligned(16))) bf16_t sA[2][BM * AROW];
+  __shared__ __attribute__((aligned(16))) bf16_t sStage[8][STAGE];
+  const LnProjArgs& p = ka.a;
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64), l32 = lane % 32, half = lane / 32;
+  bf16_t* const stage = sStage[wave];
+  bf16x8 w[W][KSTEPS];
+  bf16x4 bias[W][4];                       // of the lane's columns 8 q + 4 half + 0..3
+  float bias_t[W];                         // of its column, where the part is stored strided
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    const LnProjSlice sl = ka.slice[GATED ? wave : wave + 8 * i];
+    const ProjPart& q = p.part[sl.part];
+    const bf16_t* wp = (const bf16_t*)(GATED && i == 0 ? q.w_gate : q.w) + (int64_t)(sl.n0 + l32) * K + half * 8;
+    const bf16_t* bp = (const bf16_t*)(GATED && i == 0 ? q.bias_gate : q.bias);
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) w[i][ks] = *reinterpret_cast<const bf16x8*>(wp + ks * 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bias[i][j] = bp ? *reinterpret_cast<const bf16x4*>(bp + sl.n0 + 8 * j + 4 * half) : bf16x4{};
+    bias_t[i] = bp ? bf2f(bp[sl.n0 + l32]) : 0.f;
+  }
+  const int lg = tid % G, rg = tid / G;
+  const bf16_t* x = (const bf16_t*)p.x;
+  const bf16x8 gain = *reinterpret_cast<const bf16x8*>((const bf16_t*)p.gain + lg * 8), shift = *reinterpret_cast<const bf16x8*>((const bf16_t*)p.shift + lg * 8);
+  bf16x8 xr[PASSES];
+  auto load = [&](int64_t t) {
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) {
+      int64_t r = t * BM + ps * RPP + rg;
+      if (r > p.rows - 1) r = p.rows - 1;     // rows past the end shadow the last row; never stored
+      int64_t at = r * p.ldx;
+      if (p.x_period > 0) {
+        int64_t q, c;
+        split_row(r, p.x_period, q, c);
+        at = q * p.x_s1 + c * p.x_s2;
+      }
+      xr[ps] = *reinterpret_cast<const bf16x8*>(x + at + lg * 8);
+    }
+  };
+  auto normalise = [&](bf16_t* dst) {
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) {
+      float v[8], sum = 0.f, sq = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) { v[j] = bf2f(xr[ps][j]); sum += v[j]; }
+      const float mean = group_sum<G>(sum) * (1.0f / K);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) { const float d = v[j] - mean; sq += d * d; }
+      const float rstd = rsqrtf(group_sum<G>(sq) * (1.0f / K) + p.eps);
+      float o[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = (v[j] - mean) * rstd * bf2f(gain[j]) + bf2f(shift[j]);
+      if (RPP <= BM || rg < BM) store_vec(dst + (ps * RPP + rg) * AROW + lg * 8, o);
+    }
+  };
+  const int64_t tiles = (p.rows + BM - 1) / BM;
+  load(blockIdx.x);
+  normalise(sA[0]);
+  if (blockIdx.x + (int64_t)gridDim.x < tiles) load(blockIdx.x + (int64_t)gridDim.x);
+  __syncthreads();
+  int buf = 0;
+  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x, buf ^= 1) {
+    if (t + gridDim.x < tiles) {
+      normalise(sA[buf ^ 1]);
+      if (t + 2 * (int64_t)gridDim.x < tiles) load(t + 2 * (int64_t)gridDim.x);
+    }
+    const int64_t m0 = t * BM;
+    bf16x8 fa[SUB][KSTEPS];
+#pragma unroll
+    for (int s = 0; s < SUB; ++s)
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) fa[s][ks] = *reinterpret_cast<const bf16x8*>(sA[buf] + (s * 32 + l32) * AROW + half * 8 + ks * 16);
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+      const LnProjSlice sl = ka.slice[wave + 8 * i];
+      const ProjPart& q = p.part[sl.part];
+      const int act = q.act;
+      if (GATED || q.out_t) {
+#pragma unroll
+        for (int s = 0; s < SUB; ++s) {
+          f32x16 g = {}, v = {};
+#pragma unroll
+          for (int ks = 0; ks < KSTEPS; ++ks) {
+            if (GATED) g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][ks], w[0][ks], g, 0, 0, 0);
+            v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][ks], w[GATED ? 1 : i][ks], v, 0, 0, 0);
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) v[r] += bias_t[GATED ? 1 : i];
+          if (GATED) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] *= sigmoid_newton(g[r] + bias_t[0]);
+          } else if (act == AC_ACT_SIGMOID) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = sigmoid_newton(v[r]);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<bf16x4*>(stage + l32 * TROW + s * 32 + 8 * j + 4 * half) = bf16x4{f2bf(v[4 * j]), f2bf(v[4 * j + 1]), f2bf(v[4 * j + 2]), f2bf(v[4 * j + 3])};
+        }
+        __builtin_amdgcn_wave_barrier();     // (a wave's LDS operations are in order)
+#pragma unroll
+        for (int c = 0; c < BM / 16; ++c) {  // 32 columns of BM / 8 runs of eight rows
+          const int e = lane + 64 * c, n = e / (BM / 8), mm = e % (BM / 8) * 8;
+          int64_t qq, rr;
+          split_row(m0 + mm, q.t_period, qq, rr);
+          if (m0 + mm < p.rows)
+            *reinterpret_cast<bf16x8*>((bf16_t*)q.out_t + qq * q.t_s1 + rr + (sl.n0 + n) * q.t_s3) = *reinterpret_cast<const bf16x8*>(stage + n * TROW + mm);
+        }
+        __builtin_amdgcn_wave_barrier();
+      } else {
+#pragma unroll
+        for (int s = 0; s < SUB; ++s) {
+          f32x16 v = {};
+#pragma unroll
+          for (int ks = 0; ks < KSTEPS; ++ks) v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[i][ks], fa[s][ks], v, 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * j + e] += bf2f(bias[i][j][e]);
+          if (act == AC_ACT_SIGMOID) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = sigmoid_newton(v[r]);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<bf16x4*>(stage + l32 * SROW + 8 * j + 4 * half) = bf16x4{f2bf(v[4 * j]), f2bf(v[4 * j + 1]), f2bf(v[4 * j + 2]), f2bf(v[4 * j + 3])};
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {      // 32 rows of four runs of eight columns
+            const int e = lane + 64 * c, r = e / 4, cc = e % 4 * 8;
+            if (m0 + s * 32 + r < p.rows)
+              *reinterpret_cast<bf16x8*>((bf16_t*)q.out + (m0 + s * 32 + r) * q.ldo + sl.n0 + cc) = *reinterpret_cast<const bf16x8*>(stage + r * SROW + cc);
+          }
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
 bool ln_proj_shapes_ok(int dtype, int64_t k, const int64_t* n, int n_parts) {
   if (dtype != AC_BF16 || (k != 64 && k != 128)) return false;
   if (n_parts < 1 || n_parts > kMaxProjParts) return false;
@@ -1601,6 +1756,33 @@ static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The slices of the parts for the kernel of whole slices, if it covers them: 8 or 16 of 32 columns (8 gated pairs), whole 16-byte chunks of rows or
+// columns in every store, no result on the rows.  Returns their number, or 0.
+static int ln_proj_slices(const LnProjArgs& p, LnProjSliceArgs& sa) {
+  int n = 0;
+  for (int i = 0; i < p.n_parts; ++i) {
+    const ProjPart& q = p.part[i];
+    if (q.n % 32 != 0 || q.gated != p.part[0].gated || (q.gated ? q.act != AC_ACT_NONE : q.act != AC_ACT_NONE && q.act != AC_ACT_SIGMOID)) return 0;
+    if (q.out_t) {
+      if (q.t_s2 != 1 || q.t_s1 % 8 != 0 || q.t_s3 % 8 != 0 || p.rows % 8 != 0 || (q.t_period != INT64_MAX && q.t_period % 8 != 0) || (uintptr_t)q.out_t % 16 != 0) return 0;
+    } else if (q.gated || q.o_period != INT64_MAX || q.ldo % 8 != 0 || (uintptr_t)q.out % 16 != 0) {
+      return 0;
+    }
+    for (int n0 = 0; n0 < q.n; n0 += 32, ++n) {
+      if (n == 16) return 0;
+      sa.slice[n] = LnProjSlice{i, n0};
+    }
+  }
+  return (n == 8 || (n == 16 && !p.part[0].gated)) && !ln_proj_overlaps(p) ? n : 0;
+}
+template <int K, int SLOTS, bool GATED> static hipError_t ln_proj_slices_launch(const LnProjSliceArgs& sa, hipStream_t s) {
+  const int64_t rows = sa.a.rows;
+  // one block per CU; tiles of 32 rows while a block has less than eight of 64 (20000 rows: 625 of 32 are three a block, 313 of 64 two, with twice the work)
+  if (rows < 64 * 256 * 8) hipLaunchKernelGGL((ln_proj_slices_bf16<K, SLOTS, GATED, 32>), dim3((unsigned)((rows + 31) / 32 < 256 ? (rows + 31) / 32 : 256)), dim3(512), 0, s, sa);
+  else hipLaunchKernelGGL((ln_proj_slices_bf16<K, SLOTS, GATED, 64>), dim3(256), dim3(512), 0, s, sa);
+  return hipGetLastError();
+}
+
 hipError_t launch_ln_proj(const LnProjArgs& p_in, hipStream_t s) {
   if (p_in.rows <= 0) return hipSuccess;
   LnProjKernelArgs ka{};
@@ -1623,6 +1805,13 @@ hipError_t launch_ln_proj(const LnProjArgs& p_in, hipStream_t s) {
     if (pp.o_period <= 0) pp.o_period = INT64_MAX;
     if (pp.o_period != INT64_MAX && (pp.o_s1 % 4 != 0 || pp.o_s2 % 4 != 0)) return hipErrorNotSupported;
     if (pp.act == AC_ACT_GELU_ERF && !pp.gated) ka.any_gelu = 1;
+  }
+  LnProjSliceArgs sa{};
+  if (const int slices = ln_proj_slices(p, sa)) {
+    sa.a = p;
+    const bool gated = p.part[0].gated != 0;
+    if (p.k == 128) return gated ? ln_proj_slices_launch<128, 1, true>(sa, s) : slices == 16 ? ln_proj_slices_launch<128, 2, false>(sa, s) : ln_proj_slices_launch<128, 1, false>(sa, s);
+    return gated ? ln_proj_slices_launch<64, 1, true>(sa, s) : slices == 16 ? ln_proj_slices_launch<64, 2, false>(sa, s) : ln_proj_slices_launch<64, 1, false>(sa, s);
   }
   for (int i = 0; i < p.n_parts; ++i)
     for (int64_t n0 = 0; n0 < p.part[i].n; n0 += kLnProjCols) {   // a gated pair is one entry: two weight tiles, one output tile

@@ -57,3 +57,35 @@ def test_transition(B, n, c_z, factor, activation):
     cfg = I.PairConfig("tpt", 47, n, c_z, 64, 2, 32, factor, "bf16", activation=activation)
     y, ref = module(B, cfg, B.AC_REGION_PAIR_TRANSITION, settings(B, n))
     check(y, ref, "bf16")
+
+
+@pytest.mark.parametrize("k", [64, 128])
+@pytest.mark.parametrize("rows", [8, 64, 1000, 8200, 131072 + 72])      # (131072: tiles of 64 rows)
+@pytest.mark.parametrize("parts", ["four", "two", "pairs"])
+def test_projections_of_whole_slices(B, rows, k, parts):
+    """256 or 512 weight columns: the bits of the same projections with four columns more, which the kernel of 64-column tiles takes."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(49)
+    def t(*shape, std=1.0):
+        return torch.randn(shape, generator=g, device="cuda").mul_(std).bfloat16()
+    x, gain, shift, period = t(rows, k), t(k, std=0.1) + 1, t(k, std=0.1), 8 if rows % 1000 else 1000
+    w = [t(132, k, std=k ** -0.5) for _ in range(4)]
+    b = [t(132, std=0.2) for _ in range(4)]
+    def run(n):
+        def nan(*shape):
+            return torch.full(shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+        if parts == "pairs":
+            out = [nan(n, rows), nan(n, rows)]
+            specs = [dict(w=w[2 * i][:n], bias=b[2 * i], w_gate=w[2 * i + 1][:n], bias_gate=b[2 * i + 1], out_t=out[i], t_s2=1, t_s3=rows) for i in range(2)]
+        else:
+            out = [nan(rows, n), nan(rows, n), nan(rows, n), nan(rows // period, n, period)]
+            specs = [dict(w=w[0][:n], out=out[0]), dict(w=w[1][:n], bias=b[1], activation=B.AC_ACT_SIGMOID, out=out[1]), dict(w=w[2][:n], bias=b[2], out=out[2]),
+                     dict(w=w[3][:n], bias=b[3], out_t=out[3], t_period=period, t_s1=n * period, t_s2=1, t_s3=period)]
+            if parts == "two":
+                specs, out = specs[1::2], out[1::2]
+        B.ac_op_ln_linear(x, gain, shift, specs)
+        torch.cuda.synchronize()
+        return out
+    for i, (ours, other) in enumerate(zip(run(128), run(132))):
+        other = other[:128] if parts == "pairs" else other[:, :128]
+        assert torch.equal(ours, other), i
