@@ -140,8 +140,16 @@ __global__ void __launch_bounds__(256) layer_tail_f32(LayerTailF32Args p) {
   normalise_rows<D>([&](int r) { return s_h + r * HROW; }, gain, shift, p.eps, s_u, tid);
   __syncthreads();
   up.run(s_u + l16 * HROW + 4 * grp, [&](int, int c, f32x4 v) {
+    if (p.act == AC_ACT_GELU_ERF) {      // (one branch per four values)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = apply_act_rt(v[j], p.act);
+      for (int j = 0; j < 4; ++j) v[j] = gelu_erf(v[j]);
+    } else if (p.act == AC_ACT_GELU_TANH) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = gelu_tanh(v[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.0f);
+    }
     *reinterpret_cast<f32x4*>(s_f + l16 * FROW + c) = v;
   });
   __syncthreads();
@@ -176,6 +184,7 @@ hipError_t launch_ln_linear_f32(const LnLinearF32Args& p, hipStream_t s) {
 hipError_t launch_layer_tail_f32(const LayerTailF32Args& p, hipStream_t s) {
   if (p.rows <= 0) return hipSuccess;
   if (!layer_tail_f32_shapes_ok(AC_F32, p.d, 4 * p.d) || p.rows > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (p.act != AC_ACT_GELU_ERF && p.act != AC_ACT_GELU_TANH && p.act != AC_ACT_RELU) return hipErrorInvalidValue;
   for (const void* q : {p.ctx, p.resid, p.w_o, p.b_o, p.ln_g, p.ln_b, p.w_1, p.b_1, p.w_2, p.b_2, (const void*)p.out})
     if (!at16(q)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((p.rows + kRows - 1) / kRows));
