@@ -1191,7 +1191,7 @@ static hipError_t quad_launch(const LinearArgs& g, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------
-// fp32 MFMA kernel, tiles by direct global-to-LDS loads through a ring of three buffers of 32 k.
+// fp32 MFMA kernel, tiles by direct global-to-LDS loads through a ring of three buffers of 32 k (or 64).
 //
 // What bounds linear_mfma_f32 on larger products is its stream of operands: a step of 16 k asks for half a cache line of every row, a CU holds about a
 // hundred such requests in flight whatever they carry, and each wave fetches the whole tile's operands for itself.  Here a row's step is a whole line,
@@ -1200,13 +1200,15 @@ static hipError_t quad_launch(const LinearArgs& g, hipStream_t s) {
 // same permutation serves).  The four parts of a sum over k that linear_mfma_f32 gives to four waves follow one another here and are added in the same
 // order, each a chain of the same instructions: equal bits.  (Depths that are a multiple of 128: parts of whole tiles.)
 // ------------------------------------------------------------------------------------
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK>
 __global__ void __launch_bounds__(256) linear_ring_f32(LinearArgs g, int vec) {
-  constexpr int NW = 4, STAGES = 3, BK = 32, ROWB = BK * 4, CPR = 8, RPI = 8;        // bytes and chunks per LDS row, rows per load instruction
+  constexpr int NW = 4, STAGES = 3, ROWB = BK * 4, CPR = BK / 4, RPI = 256 / BK, KS = BK / 16;   // bytes and chunks per LDS row, rows per load instruction
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 16, TN = WN / 16;
   constexpr int A_I = BM / RPI / NW, W_I = BN / RPI / NW, PER = A_I + W_I;
-  constexpr int READS = 2 * (TM + TN), MMAS = 8 * TM * TN, STAGE = (BM + BN) * ROWB;
+  constexpr int READS = KS * (TM + TN), MMAS = 4 * KS * TM * TN, STAGE = (BM + BN) * ROWB;
   static_assert(WAVES_M * WAVES_N == NW && BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile / wave layout mismatch");
+  static_assert(BK == 32 || BK == 64, "rows of eight or sixteen chunks");
+  auto swizzle = [](int r) { return BK == 32 ? (r >> 1) & 7 : r & 15; };
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64), l16 = lane % 16, grp = lane / 16;
   const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
@@ -1216,7 +1218,7 @@ __global__ void __launch_bounds__(256) linear_ring_f32(LinearArgs g, int vec) {
   const int64_t product = g.batch_descending ? (int64_t)gridDim.y - 1 - blockIdx.y : (int64_t)blockIdx.y;
   const float* a = (const float*)g.a + product * g.sa_b + m0 * g.lda;
   const float* w = (const float*)g.w + product * g.sw_b + n0 * g.ldw;
-  const int row_in = lane / CPR, src_chunk = (lane % CPR) ^ ring_swizzle<64>(wave * RPI + row_in);
+  const int row_in = lane / CPR, src_chunk = (lane % CPR) ^ swizzle(wave * RPI + row_in);
   uint32_t a_off[A_I], w_off[W_I];
 #pragma unroll
   for (int i = 0; i < A_I; ++i) {   // rows past the end shadow the last one; never stored
@@ -1253,20 +1255,20 @@ __global__ void __launch_bounds__(256) linear_ring_f32(LinearArgs g, int vec) {
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = total[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 fa[2][2][TM], fw[2][2][TN];
-  int frag_off[2];
+  f32x4 fa[2][KS][TM], fw[2][KS][TN];
+  int frag_off[KS];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) frag_off[s] = l16 * ROWB + ((s * 4 + grp) ^ ring_swizzle<64>(l16)) * 16;
+  for (int s = 0; s < KS; ++s) frag_off[s] = l16 * ROWB + ((s * 4 + grp) ^ swizzle(l16)) * 16;
   const unsigned char* const sA = smem_raw + wave_m * WM * ROWB;
   const unsigned char* const sW = smem_raw + BM * ROWB + wave_n * WN * ROWB;
-  auto read_frag = [&](f32x4 (&fa_)[2][TM], f32x4 (&fw_)[2][TN], int base, int r) {
+  auto read_frag = [&](f32x4 (&fa_)[KS][TM], f32x4 (&fw_)[KS][TN], int base, int r) {
     const int s = r / (TM + TN), x = r % (TM + TN);
     if (x < TN) fw_[s][x] = *reinterpret_cast<const f32x4*>(sW + base + frag_off[s] + x * 16 * ROWB);
     else fa_[s][x - TN] = *reinterpret_cast<const f32x4*>(sA + base + frag_off[s] + (x - TN) * 16 * ROWB);
   };
   const int kt_count = (int)(g.k / BK), part = kt_count / kF32Runs;
   int kt = 0, stage = 0, fold = part;
-  auto step = [&](const f32x4 (&ca)[2][TM], const f32x4 (&cw)[2][TN], f32x4 (&na)[2][TM], f32x4 (&nw)[2][TN]) {
+  auto step = [&](const f32x4 (&ca)[KS][TM], const f32x4 (&cw)[KS][TN], f32x4 (&na)[KS][TM], f32x4 (&nw)[KS][TN]) {
     const bool more = kt + STAGES < kt_count;
     const int free_stage = stage;
     stage = stage + 1 == STAGES ? 0 : stage + 1;
@@ -1955,10 +1957,10 @@ static hipError_t mfma_f32_launch(const LinearArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK>
 static hipError_t ring_f32_launch(const LinearArgs& g, hipStream_t s) {
-  auto kern = linear_ring_f32<BM, BN, WAVES_M, WAVES_N>;
-  constexpr int lds = 3 * (BM + BN) * 128;
+  auto kern = linear_ring_f32<BM, BN, WAVES_M, WAVES_N, BK>;
+  constexpr int lds = 3 * (BM + BN) * BK * 4;
   static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr_status != hipSuccess) return attr_status;
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles_of(g, BM, BN), (unsigned)g.batch), dim3(256), lds, s, g, f32_rows_vectorisable(g) ? 1 : 0);
@@ -1966,10 +1968,10 @@ static hipError_t ring_f32_launch(const LinearArgs& g, hipStream_t s) {
 }
 
 // The kernel a product runs on: a function of sizes, types, strides and alignment, decided on the host.
-enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kF32Ring32x64, kF32Ring32x32, kRouteQuad, kRing256x128, kRing128x128, kRing128x192, kStaged128x128, kRing128x64, kRing64x64,
+enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kF32Ring32x64, kF32Ring32x32, kF32Ring32x32Deep, kRouteQuad, kRing256x128, kRing128x128, kRing128x192, kStaged128x128, kRing128x64, kRing64x64,
              kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x192, kConv128x64, kConv64x64, kConvWide64x64, kRoutes };
 static const char* const kRouteName[kRoutes] = {
-    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "f32 32x64", "f32 32x32", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
+    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "f32 32x64", "f32 32x32", "f32 32x32", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
     "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x192", "conv 128x64", "conv 64x64", "conv-wide 64x64"};
 
 static bool wide_rows(const LinearArgs& g) { return g.lda >= (1 << 22) || g.ldw >= (1 << 22); }
@@ -2014,12 +2016,16 @@ static Route f32_route(const LinearArgs& g) {
   // 29.0 / 18.6 / 15.0 / 18.8; 16000 x 512 x 512 79 / 92, 149 / 172 / 250 / 330; 96 x 512 x 2048 29 / 25, 29 / 19 / 15 / 11.  (Rings of 64x64 and 128x64 are never
   // more than 1 % ahead.)
   if (g.k % 128 == 0 && g.k <= (1 << 26) && !wide_rows(g)) {
+    // Where the parts are whole tiles of 64 terms too, the 32x32 ring takes those: half the barriers, which a launch of one or two blocks per CU waits at
+    // (1024 x 512 x 2048 31.0 -> 28.1, 256 x 512 x 2048 24.5 -> 20.1, 1024 x 512 x 512 10.8 -> 10.2); 32x64 gains up to 7 % by it there and loses 18 % in
+    // larger launches, two of whose blocks fit a CU instead of four (16000 x 512 x 512 82 -> 97).
     struct Cost { Route route; int bm, bn; double once, step1, tile, step; };
-    static const Cost costs[5] = {{kF32Ring32x64, 32, 64, 5.48, 0.706, 0.38, 0.548}, {kF32Ring32x32, 32, 32, 5.42, 0.608, 0.03, 0.356},
+    static const Cost costs[6] = {{kF32Ring32x64, 32, 64, 5.48, 0.706, 0.38, 0.548}, {kF32Ring32x32, 32, 32, 5.42, 0.608, 0.03, 0.356}, {kF32Ring32x32Deep, 32, 32, 5.27, 0.447, 0.27, 0.343},
                                   {kF32_32x32, 32, 32, 3.77, 0, 1.17, 0.445}, {kF32_32x16, 32, 16, 3.35, 0, 0.83, 0.337}, {kF32_16x16, 16, 16, 3.34, 0, 0.53, 0.226}};
     int best = -1;
     double best_t = 0;
-    for (int c = 0; c < 5; ++c) {
+    for (int c = 0; c < 6; ++c) {
+      if (costs[c].route == (g.k % 256 == 0 ? kF32Ring32x32 : kF32Ring32x32Deep)) continue;
       const int64_t tiles = tiles_of(g, costs[c].bm, costs[c].bn);
       if (!grid_fits(tiles, 256)) continue;
       const double steps = (double)(g.k / 64), exact = (double)(tiles * g.batch) / 256, whole = (double)((tiles * g.batch + 255) / 256);
@@ -2118,8 +2124,9 @@ hipError_t launch_linear(const LinearArgs& g_in, hipStream_t s) {
     case kF32_32x32: return mfma_f32_launch<2, 2>(g, s);
     case kF32_32x16: return mfma_f32_launch<2, 1>(g, s);
     case kF32_16x16: return mfma_f32_launch<1, 1>(g, s);
-    case kF32Ring32x64: return ring_f32_launch<32, 64, 1, 4>(g, s);
-    case kF32Ring32x32: return ring_f32_launch<32, 32, 2, 2>(g, s);
+    case kF32Ring32x64: return ring_f32_launch<32, 64, 1, 4, 32>(g, s);
+    case kF32Ring32x32: return ring_f32_launch<32, 32, 2, 2, 32>(g, s);
+    case kF32Ring32x32Deep: return ring_f32_launch<32, 32, 2, 2, 64>(g, s);
     case kRouteQuad: return quad_launch<false>(g, s);
     case kRing256x128: return ring_launch<256, 128, 4, 2, 64, 3>(g, s);
     case kRing128x128: return ring_launch<128, 128, 2, 4, 64, 3>(g, s);

@@ -50,7 +50,8 @@ def test_linear_f32(B, m, n, k):
     assert torch.equal(part, out)
 
 
-@pytest.mark.parametrize("m,n,k", [(1024, 512, 512), (1100, 1540, 128), (1531, 601, 256), (5900, 65, 1152), (5000, 96, 384), (250, 2100, 640)])
+@pytest.mark.parametrize("m,n,k", [(1024, 512, 512), (1100, 1540, 128), (1531, 601, 256), (5900, 65, 1152), (5000, 96, 384), (250, 2100, 640),
+                                   (260, 516, 1024), (2066, 200, 1024), (700, 516, 256)])
 def test_linear_f32_depths_of_whole_tiles(B, m, n, k):
     """Launches of a ring of tiles, odd rows and columns among them: the oracle's values, and the bits of launches of 33 rows (waves that share out k)."""
     import torch
