@@ -42,8 +42,11 @@ __device__ __forceinline__ float rounded_product(float a, float b) {   // (never
 // Causal blocks of a head: longest rows first, in a snake over runs of 32 (the CUs of an XCD, which take consecutive
 // blocks in turn): the first 32 blocks of a head are its longest in descending order, the next 32 the following ones in ascending order, and
 // so on, so that when all blocks of a launch are resident at once (one sequence of a few thousand rows) every CU holds about the same number
-// of key tiles; with more blocks than places the order is still longest-first run by run.
-__device__ __forceinline__ int snake(int qb, int nqb) {
+// of key tiles; with more blocks than places the order is still longest-first run by run.  Heads of fewer than 32 blocks take the directions of the
+// runs that they begin in, so that a CU's second block is as short as its first is long (four problems of 1000 queries, 16 heads of 64: 28.2 -> 25.2 us).
+// `first`: the head's first block in the launch.
+__device__ __forceinline__ int snake(int qb, int nqb, int64_t first) {
+  if (nqb < 32) return first / 32 % 2 == 0 ? nqb - 1 - qb : qb;
   const int run = qb / 32, col = qb % 32;
   const int len = nqb - run * 32 < 32 ? nqb - run * 32 : 32;
   return nqb - 1 - (run * 32 + ((run & 1) ? len - 1 - col : col));
@@ -160,7 +163,7 @@ __global__ void __launch_bounds__(256) attention_mfma_f32(AttnArgs a) {
   const int nqb = (sq + 15) / 16;
   const int64_t t = xcd_contiguous(blockIdx.x, gridDim.x), bh = t / nqb;   // (a head's blocks on one XCD: its keys and values stay in that L2)
   int qb = (int)(t % nqb);
-  if (a.causal) qb = snake(qb, nqb);
+  if (a.causal) qb = snake(qb, nqb, bh * nqb);
   const int64_t b = bh / a.heads;
   const int h = (int)(bh % a.heads), q0 = qb * 16;
   const int row = q0 + l16, rowc = row < sq ? row : sq - 1;   // rows past the end shadow the last one; never stored
@@ -352,7 +355,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   const int64_t bq = t / ns;
   const int64_t bh = bq / nqb;
   int qb = (int)(bq % nqb);
-  if (CAUSAL) qb = snake(qb, nqb);
+  if (CAUSAL) qb = snake(qb, nqb, bh * nqb * ns);
   // Problem-major order keeps the heads of one problem together (their q/k/v rows interleave in
   // memory).  Head-major order (set by the host when a bias shared by all problems is the
   // largest operand) gives each XCD a run of problems of ONE head, so that head's bias stays
