@@ -172,7 +172,7 @@ def class_entry(s, steps, dtype):
     return entry
 
 
-KERNEL_SOURCES = {"gemm": ["linear.hip", "common.h"], "trimul": ["linear.hip", "common.h"],
+KERNEL_SOURCES = {"gemm": ["linear.hip", "pair.hip", "layer_f32.hip", "common.h"], "trimul": ["linear.hip", "common.h"],
                   "attention": ["attention.hip", "common.h"], "layernorm": ["rowwise.hip", "common.h"],
                   "elementwise": ["rowwise.hip", "common.h"]}
 

@@ -1555,17 +1555,19 @@ __global__ void __launch_bounds__(256, K == 64 ? 5 : 4) ln_multi_proj_bf16(LnPro
 // product with its operands exchanged, which leaves a lane runs of rows instead of runs of columns.  The matrix instructions and their order are the kernel's
 // above: equal bits.  What bounded that one is vector work and its two barriers per 64 columns: per 64 rows and 512 columns it also moves 128 KB of weights from L2
 // through registers into LDS.  Two gated pairs of 1048576 rows of 128 367 -> 242 us (3.3 TB/s; 409 -> 255 by columns), q, k, v and gate of 524288 rows 232 -> 154,
-// q and gate 147 -> 98; of 40000 rows 22.8 -> 17.8, 20000 rows 16.8 -> 15.6.
+// q and gate 147 -> 98; of 40000 rows 22.8 -> 17.8, 20000 rows 16.8 -> 15.6.  Beside 256 columns a few of one more part (the pair bias) are the work of one wave, in
+// turn, with their weights in LDS: bias, k and v of 1048576 rows 312 -> 192.
 struct LnProjSlice { int part, n0; };
-struct LnProjSliceArgs { LnProjArgs a; LnProjSlice slice[16]; };
+struct LnProjSliceArgs { LnProjArgs a; LnProjSlice slice[16]; int narrow; };   // narrow: part of fewer than 32 columns, or -1
 
-template <int K, int SLOTS, bool GATED, int BM>
+template <int K, int SLOTS, bool GATED, int BM, bool NARROW>
 __global__ void __launch_bounds__(512) ln_proj_slices_bf16(LnProjSliceArgs ka) {
   constexpr int NT = 512, AROW = K + 8, G = K / 8, RPP = NT / G, PASSES = BM / RPP > 0 ? BM / RPP : 1, KSTEPS = K / 16, SUB = BM / 32;
   constexpr int W = GATED ? 2 : SLOTS, SROW = 40, TROW = BM + 8, STAGE = 32 * (TROW > SROW ? TROW : SROW);   // (a gated pair: gate, value)
   static_assert(!GATED || SLOTS == 1, "a pair per wave");
   __shared__ __attribute__((aligned(16))) bf16_t sA[2][BM * AROW];
   __shared__ __attribute__((aligned(16))) bf16_t sStage[8][STAGE];
+  __shared__ __attribute__((aligned(16))) bf16_t sN[NARROW ? 32 * AROW : 8];     // the narrow part's weights (rows past its last shadow it)
   const LnProjArgs& p = ka.a;
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64), l32 = lane % 32, half = lane / 32;
   bf16_t* const stage = sStage[wave];
@@ -1618,13 +1620,36 @@ __global__ void __launch_bounds__(512) ln_proj_slices_bf16(LnProjSliceArgs ka) {
       if (RPP <= BM || rg < BM) store_vec(dst + (ps * RPP + rg) * AROW + lg * 8, o);
     }
   };
+  if (NARROW) {
+    const ProjPart& q = p.part[ka.narrow];
+    for (int c = tid; c < 32 * G; c += NT)
+      *reinterpret_cast<bf16x8*>(sN + c / G * AROW + c % G * 8) =
+          *reinterpret_cast<const bf16x8*>((const bf16_t*)q.w + (c / G < (int)q.n ? c / G : (int)q.n - 1) * K + c % G * 8);
+  }
   const int64_t tiles = (p.rows + BM - 1) / BM;
   load(blockIdx.x);
   normalise(sA[0]);
   if (blockIdx.x + (int64_t)gridDim.x < tiles) load(blockIdx.x + (int64_t)gridDim.x);
   __syncthreads();
-  int buf = 0;
-  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x, buf ^= 1) {
+  auto stage_strided = [&](const f32x16& v, int s) {      // this lane's column, its rows of 32-row tile s
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<bf16x4*>(stage + l32 * TROW + s * 32 + 8 * j + 4 * half) = bf16x4{f2bf(v[4 * j]), f2bf(v[4 * j + 1]), f2bf(v[4 * j + 2]), f2bf(v[4 * j + 3])};
+  };
+  auto store_strided = [&](const ProjPart& q, int n0, int columns, int64_t m0) {
+    __builtin_amdgcn_wave_barrier();         // (a wave's LDS operations are in order)
+#pragma unroll
+    for (int c = 0; c < BM / 16; ++c) {      // 32 columns of BM / 8 runs of eight rows
+      const int e = lane + 64 * c, n = e / (BM / 8), mm = e % (BM / 8) * 8;
+      int64_t qq, rr;
+      split_row(m0 + mm, q.t_period, qq, rr);
+      if (n < columns && m0 + mm < p.rows)
+        *reinterpret_cast<bf16x8*>((bf16_t*)q.out_t + qq * q.t_s1 + rr + (n0 + n) * q.t_s3) = *reinterpret_cast<const bf16x8*>(stage + n * TROW + mm);
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  int buf = 0, turn = 0;
+  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x, buf ^= 1, turn = (turn + 1) % 8) {
     if (t + gridDim.x < tiles) {
       normalise(sA[buf ^ 1]);
       if (t + 2 * (int64_t)gridDim.x < tiles) load(t + 2 * (int64_t)gridDim.x);
@@ -1658,20 +1683,9 @@ __global__ void __launch_bounds__(512) ln_proj_slices_bf16(LnProjSliceArgs ka) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[r] = sigmoid_newton(v[r]);
           }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            *reinterpret_cast<bf16x4*>(stage + l32 * TROW + s * 32 + 8 * j + 4 * half) = bf16x4{f2bf(v[4 * j]), f2bf(v[4 * j + 1]), f2bf(v[4 * j + 2]), f2bf(v[4 * j + 3])};
+          stage_strided(v, s);
         }
-        __builtin_amdgcn_wave_barrier();     // (a wave's LDS operations are in order)
-#pragma unroll
-        for (int c = 0; c < BM / 16; ++c) {  // 32 columns of BM / 8 runs of eight rows
-          const int e = lane + 64 * c, n = e / (BM / 8), mm = e % (BM / 8) * 8;
-          int64_t qq, rr;
-          split_row(m0 + mm, q.t_period, qq, rr);
-          if (m0 + mm < p.rows)
-            *reinterpret_cast<bf16x8*>((bf16_t*)q.out_t + qq * q.t_s1 + rr + (sl.n0 + n) * q.t_s3) = *reinterpret_cast<const bf16x8*>(stage + n * TROW + mm);
-        }
-        __builtin_amdgcn_wave_barrier();
+        store_strided(q, sl.n0, 32, m0);
       } else {
 #pragma unroll
         for (int s = 0; s < SUB; ++s) {
@@ -1699,6 +1713,21 @@ __global__ void __launch_bounds__(512) ln_proj_slices_bf16(LnProjSliceArgs ka) {
           __builtin_amdgcn_wave_barrier();
         }
       }
+    }
+    if (NARROW && wave == turn) {            // (a tile's narrow columns are one wave's, each in its turn)
+      const ProjPart& q = p.part[ka.narrow];
+      const float b = q.bias ? bf2f(((const bf16_t*)q.bias)[l32 < (int)q.n ? l32 : (int)q.n - 1]) : 0.f;
+#pragma unroll
+      for (int s = 0; s < SUB; ++s) {
+        f32x16 v = {};
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+          v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][ks], *reinterpret_cast<const bf16x8*>(sN + l32 * AROW + half * 8 + ks * 16), v, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] += b;
+        stage_strided(v, s);
+      }
+      store_strided(q, 0, (int)q.n, m0);
     }
     __syncthreads();
   }
@@ -1759,29 +1788,32 @@ static hipError_t ln_proj_launch(const LnProjKernelArgs& ka, hipStream_t s) {
 }
 
 // The slices of the parts for the kernel of whole slices, if it covers them: 8 or 16 of 32 columns (8 gated pairs), whole 16-byte chunks of rows or
-// columns in every store, no result on the rows.  Returns their number, or 0.
+// columns in every store, no result on the rows; beside eight a plain part of fewer columns that is stored strided (the pair bias).  Returns their number, or 0.
 static int ln_proj_slices(const LnProjArgs& p, LnProjSliceArgs& sa) {
   int n = 0;
+  sa.narrow = -1;
   for (int i = 0; i < p.n_parts; ++i) {
     const ProjPart& q = p.part[i];
-    if (q.n % 32 != 0 || q.gated != p.part[0].gated || (q.gated ? q.act != AC_ACT_NONE : q.act != AC_ACT_NONE && q.act != AC_ACT_SIGMOID)) return 0;
+    const bool narrow = q.n < 32 && q.out_t && !q.gated && q.act == AC_ACT_NONE && sa.narrow < 0;
+    if ((q.n % 32 != 0 && !narrow) || q.gated != p.part[0].gated || (q.gated ? q.act != AC_ACT_NONE : q.act != AC_ACT_NONE && q.act != AC_ACT_SIGMOID)) return 0;
     if (q.out_t) {
       if (q.t_s2 != 1 || q.t_s1 % 8 != 0 || q.t_s3 % 8 != 0 || p.rows % 8 != 0 || (q.t_period != INT64_MAX && q.t_period % 8 != 0) || (uintptr_t)q.out_t % 16 != 0) return 0;
     } else if (q.gated || q.o_period != INT64_MAX || q.ldo % 8 != 0 || (uintptr_t)q.out % 16 != 0) {
       return 0;
     }
+    if (narrow) { sa.narrow = i; continue; }
     for (int n0 = 0; n0 < q.n; n0 += 32, ++n) {
       if (n == 16) return 0;
       sa.slice[n] = LnProjSlice{i, n0};
     }
   }
-  return (n == 8 || (n == 16 && !p.part[0].gated)) && !ln_proj_overlaps(p) ? n : 0;
+  return (n == 8 || (n == 16 && !p.part[0].gated && sa.narrow < 0)) && !ln_proj_overlaps(p) ? n : 0;
 }
-template <int K, int SLOTS, bool GATED> static hipError_t ln_proj_slices_launch(const LnProjSliceArgs& sa, hipStream_t s) {
+template <int K, int SLOTS, bool GATED, bool NARROW = false> static hipError_t ln_proj_slices_launch(const LnProjSliceArgs& sa, hipStream_t s) {
   const int64_t rows = sa.a.rows;
   // one block per CU; tiles of 32 rows while a block has less than eight of 64 (20000 rows: 625 of 32 are three a block, 313 of 64 two, with twice the work)
-  if (rows < 64 * 256 * 8) hipLaunchKernelGGL((ln_proj_slices_bf16<K, SLOTS, GATED, 32>), dim3((unsigned)((rows + 31) / 32 < 256 ? (rows + 31) / 32 : 256)), dim3(512), 0, s, sa);
-  else hipLaunchKernelGGL((ln_proj_slices_bf16<K, SLOTS, GATED, 64>), dim3(256), dim3(512), 0, s, sa);
+  if (rows < 64 * 256 * 8) hipLaunchKernelGGL((ln_proj_slices_bf16<K, SLOTS, GATED, 32, NARROW>), dim3((unsigned)((rows + 31) / 32 < 256 ? (rows + 31) / 32 : 256)), dim3(512), 0, s, sa);
+  else hipLaunchKernelGGL((ln_proj_slices_bf16<K, SLOTS, GATED, 64, NARROW>), dim3(256), dim3(512), 0, s, sa);
   return hipGetLastError();
 }
 
@@ -1812,6 +1844,7 @@ hipError_t launch_ln_proj(const LnProjArgs& p_in, hipStream_t s) {
   if (const int slices = ln_proj_slices(p, sa)) {
     sa.a = p;
     const bool gated = p.part[0].gated != 0;
+    if (sa.narrow >= 0) return p.k == 128 ? ln_proj_slices_launch<128, 1, false, true>(sa, s) : ln_proj_slices_launch<64, 1, false, true>(sa, s);
     if (p.k == 128) return gated ? ln_proj_slices_launch<128, 1, true>(sa, s) : slices == 16 ? ln_proj_slices_launch<128, 2, false>(sa, s) : ln_proj_slices_launch<128, 1, false>(sa, s);
     return gated ? ln_proj_slices_launch<64, 1, true>(sa, s) : slices == 16 ? ln_proj_slices_launch<64, 2, false>(sa, s) : ln_proj_slices_launch<64, 1, false>(sa, s);
   }

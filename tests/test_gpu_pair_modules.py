@@ -61,9 +61,9 @@ def test_transition(B, n, c_z, factor, activation):
 
 @pytest.mark.parametrize("k", [64, 128])
 @pytest.mark.parametrize("rows", [8, 64, 1000, 8200, 131072 + 72])      # (131072: tiles of 64 rows)
-@pytest.mark.parametrize("parts", ["four", "two", "pairs"])
+@pytest.mark.parametrize("parts", ["four", "two", "pairs", "narrow"])
 def test_projections_of_whole_slices(B, rows, k, parts):
-    """256 or 512 weight columns: the bits of the same projections with four columns more, which the kernel of 64-column tiles takes."""
+    """256 or 512 weight columns (and a few more of a part stored strided): the bits of the same projections with four columns more, which the kernel of 64-column tiles takes."""
     import torch
     g = torch.Generator(device="cuda").manual_seed(49)
     def t(*shape, std=1.0):
@@ -81,11 +81,14 @@ def test_projections_of_whole_slices(B, rows, k, parts):
             out = [nan(rows, n), nan(rows, n), nan(rows, n), nan(rows // period, n, period)]
             specs = [dict(w=w[0][:n], out=out[0]), dict(w=w[1][:n], bias=b[1], activation=B.AC_ACT_SIGMOID, out=out[1]), dict(w=w[2][:n], bias=b[2], out=out[2]),
                      dict(w=w[3][:n], bias=b[3], out_t=out[3], t_period=period, t_s1=n * period, t_s2=1, t_s3=period)]
-            if parts == "two":
+            if parts in ("two", "narrow"):
                 specs, out = specs[1::2], out[1::2]
+            if parts == "narrow":             # beside them a part of 12 columns, as the pair bias is
+                out.append(nan(12, rows))
+                specs.insert(0, dict(w=w[0][:12], bias=b[0], out_t=out[2], t_s2=1, t_s3=rows))
         B.ac_op_ln_linear(x, gain, shift, specs)
         torch.cuda.synchronize()
         return out
     for i, (ours, other) in enumerate(zip(run(128), run(132))):
-        other = other[:128] if parts == "pairs" else other[:, :128]
+        other = other[:128] if parts == "pairs" or i == 2 and parts == "narrow" else other[:, :128]
         assert torch.equal(ours, other), i
