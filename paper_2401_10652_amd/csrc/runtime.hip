@@ -963,7 +963,7 @@ void Walk::tri_att(int kind, const void* const* W, const void* zin, void* zout) 
   // position (q, k) for the starting node, at (k, q) for the ending node (by columns, or transposed in place
   // per head afterwards).  For the ENDING form also all keys as [(problem, key)][h*d] and all
   // values channel-major [h*d][problem][key]: for the ending node's row chunks the problem is the
-  // column j and the key index the row k of z, so the projection stores the row of position
+  // column j and the key index the row k of z: the fused kernel takes the positions column after column; otherwise the projection stores the row of position
   // (k, j) at (j, k), 256 contiguous bytes at a time, and the values are transposed in place per
   // channel; for the starting node's column chunks problem and key are (i, k) as z has them.
   void* bias = arena.push((uint64_t)H * R * e);
