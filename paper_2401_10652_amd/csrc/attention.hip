@@ -598,13 +598,13 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
         float psum = 0.f;
         bf16x8 pf[2][2];
         // (far from zero, where biases that mask stand, the reference is rounded by more than a probability's exponent can bear: there scores are
-        // rounded as it is, so that equal ones of any size differ by exactly zero)
-        const bool far = BIAS && __builtin_amdgcn_ballot_w64(fabsf(m_exp) > 0x1p20f) != 0;
-        if (far) {
+        // rounded as it is, so that equal ones of any size differ by exactly zero.  By the row's own reference: its bits do not depend on its neighbours)
+        const bool far = BIAS && fabsf(m_exp) > 0x1p20f;
+        if (BIAS && __builtin_amdgcn_ballot_w64(far) != 0) {
   #pragma unroll
           for (int tt = 0; tt < 2; ++tt)
   #pragma unroll
-            for (int r = 0; r < 16; ++r) acc_s[tt][r] = rounded_product(acc_s[tt][r], scale2) - m_exp;
+            for (int r = 0; r < 16; ++r) acc_s[tt][r] = far ? rounded_product(acc_s[tt][r], scale2) - m_exp : fmaf(acc_s[tt][r], scale2, -m_exp);
         } else {
   #pragma unroll
           for (int tt = 0; tt < 2; ++tt)

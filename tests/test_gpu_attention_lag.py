@@ -138,3 +138,22 @@ def test_rows_in_descending_order(B, dh, sk, causal, which):
     torch.cuda.synchronize()
     assert status == 0
     check(host(ctx), O.attention(q, k, v, 1, causal, q_offset=sk - sq if causal else 0), "bf16")
+
+
+@pytest.mark.parametrize("dh", [32, 64])
+def test_masked_rows_leave_their_neighbours_alone(B, dh):
+    """Rows whose biases lie far from zero among others: the others' bits are those of a launch without them."""
+    import torch
+    heads, sq, sk = 2, 160, 192
+    g = torch.Generator(device="cuda").manual_seed(77)
+    q, k = (torch.randn((s, heads * dh), generator=g, device="cuda").bfloat16() for s in (sq, sk))
+    vt = torch.randn((heads * dh, sk), generator=g, device="cuda").bfloat16()
+    bias = torch.randn((heads, sq, sk), generator=g, device="cuda").mul_(3).bfloat16()
+    plain, mixed = torch.empty_like(q), torch.empty_like(q)
+    B.ac_op_attention(q, k, vt, plain, heads, dh, bias=bias, v_transposed=True)
+    far = bias.clone()
+    far[:, ::3] -= 1e9
+    B.ac_op_attention(q, k, vt, mixed, heads, dh, bias=far, v_transposed=True)
+    torch.cuda.synchronize()
+    others = [r for r in range(sq) if r % 3]
+    assert torch.equal(plain[others], mixed[others]) and bool(torch.isfinite(mixed.float()).all())
