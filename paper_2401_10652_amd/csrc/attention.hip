@@ -33,12 +33,6 @@ __device__ __forceinline__ int64_t xcd_contiguous(int64_t pid, int64_t nb) {
   return x * q + (x < r ? x : r) + idx;
 }
 
-__device__ __forceinline__ float rounded_product(float a, float b) {   // (never the product of a fused multiply-add)
-  float p = a * b;
-  asm volatile("" : "+v"(p));
-  return p;
-}
-
 // Causal blocks of a head: longest rows first, in a snake over runs of 32 (the CUs of an XCD, which take consecutive
 // blocks in turn): the first 32 blocks of a head are its longest in descending order, the next 32 the following ones in ascending order, and
 // so on, so that when all blocks of a launch are resident at once (one sequence of a few thousand rows) every CU holds about the same number
@@ -329,10 +323,6 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   constexpr int V_CHUNKS = DH * (kKB / 8) / NT;   // and V^T tile
   static_assert(K_CHUNKS >= 1 && V_CHUNKS >= 1, "tile too small for the block");
   constexpr bool PIPE = attention_pipelined(DH, BIAS, KEYS);
-  // With a bias the queries are taken down by a power of two (exactly), which leaves a factor below one for the bias in the scores' units: no bias
-  // overflows there that does not in the exponent's.
-  constexpr float kQueryUnit = 16.f, kBiasUnit = (DH == 32 ? 5.65685425f : DH == 64 ? 8.f : 11.3137085f) / kQueryUnit;
-  static_assert(DH == 32 || DH == 64 || DH == 128, "square roots of these");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);     // [2][kKB][KROW]
   bf16_t* sV = sK + 2 * kKB * KROW;                      // [2][DH][VROW]
@@ -376,13 +366,7 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   {
     const bf16_t* qp = (const bf16_t*)a.q + b * a.sq_b + (int64_t)rowc * a.ldq + h * DH + half * 8;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-      if (BIAS) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) qf[ks][j] = f2bf(bf2f(qf[ks][j]) * (1.f / kQueryUnit));
-      }
-    }
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
   }
   // bias chunk i of this thread: row b_row[i] of the block's query rows, keys b_col[i] .. +8 of the tile
   const bf16_t* b_src[B_CHUNKS];
@@ -531,7 +515,8 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
   float m_run = -INFINITY, l_run = 0.f;
   float m_exp = 0.f;   // m_run, or 0 while the row has seen no key: exp2(-inf - m_exp) is then 0, not NaN
   constexpr float kLead = 24.f;
-  const float scale2 = rsqrtf((float)DH) * kLog2e * (BIAS ? kQueryUnit : 1.f), unit = scale2;      // log2 units of a score
+  const float scale2 = rsqrtf((float)DH) * kLog2e;
+  const float unit = BIAS ? 1.f : scale2;                // of the scores a tile is left with: a bias is added in the log2 domain
   // the reference against a tile's largest score per lane
   auto new_max = [&](float mx) {
     if (__builtin_amdgcn_ballot_w64(mx * unit > m_run) == 0) return;
@@ -558,27 +543,34 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
       if (more) load_tile(k0 + kKB);
 
       if (wave_active && (!CAUSAL || k0 <= wave_last)) {
-        // ---- S^T = K Q^T for two 32-key tiles; lane holds keys k0 + tt*32 + 8*(r/4) + 4*half + r%4.  A bias is what the sums start
-        // from, so that a score costs one multiply-add on its way to the exponent (added to the finished score in log2 units: two, and the sums'
-        // zeros; what bounds this loop at 32-wide heads is vector work, 257 instructions a tile then and 206 now: 512 problems of 1024 queries and keys, four
-        // heads, 655 -> 610 us).
+        // ---- S^T = K Q^T for two 32-key tiles
         f32x16 acc_s[2];
         const bf16_t* ck = sK + buf * kKB * KROW + l32 * KROW + half * 8;
-        const bf16_t* cb = sB + (wave * 32 + l32) * BROW + 4 * half;
   #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
   #pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            bf16x4 bb = {};
-            if (BIAS) bb = *reinterpret_cast<const bf16x4*>(cb + tt * 32 + 8 * g4);
-  #pragma unroll
-            for (int j = 0; j < 4; ++j) acc_s[tt][4 * g4 + j] = BIAS ? bf2f(bb[j]) * kBiasUnit : 0.f;
-          }
+          for (int r = 0; r < 16; ++r) acc_s[tt][r] = 0.f;
   #pragma unroll
           for (int ks = 0; ks < KS; ++ks) {
             const bf16x8 kf = *reinterpret_cast<const bf16x8*>(ck + tt * 32 * KROW + ks * 16);
             acc_s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], acc_s[tt], 0, 0, 0);
           }
+        }
+        // ---- lane holds keys k0 + tt*32 + 8*(r/4) + 4*half + r%4.  Scores go to the log2 domain
+        // only where needed: with a bias right away (so that equal biases of any size, as masks are, differ by exactly zero),
+        // otherwise folded into the exponent below.  The bias meets the finished dot product, whose sum is rounded at its own magnitude: as what the
+        // sums start from it is rounded by each matrix instruction (rows whose keys share a bias of -6e5, heads of 64: 1.3e-2 -> 5.0e-2 from fp64) and gives
+        // no time (512 problems of 1024 queries and keys, four heads of 32: 668 against 666 us; 680 against 1025 with a masked row per wave).
+        if (BIAS) {
+          const bf16_t* cb = sB + (wave * 32 + l32) * BROW + 4 * half;
+  #pragma unroll
+          for (int tt = 0; tt < 2; ++tt)
+  #pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+              const bf16x4 bb = *reinterpret_cast<const bf16x4*>(cb + tt * 32 + 8 * g4);
+  #pragma unroll
+              for (int j = 0; j < 4; ++j) acc_s[tt][4 * g4 + j] = fmaf(acc_s[tt][4 * g4 + j], scale2, bf2f(bb[j]) * kLog2e);
+            }
         }
         const bool need_mask = (RAGGED && k0 + kKB > sk) || (CAUSAL && k0 + kKB - 1 > wave_first);
         if (need_mask) {
@@ -597,25 +589,11 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
         new_max(mx);
         float psum = 0.f;
         bf16x8 pf[2][2];
-        // (far from zero, where biases that mask stand, the reference is rounded by more than a probability's exponent can bear: there scores are
-        // rounded as it is, so that equal ones of any size differ by exactly zero.  By the row's own reference: its bits do not depend on its neighbours)
-        const bool far = BIAS && fabsf(m_exp) > 0x1p20f;
-        if (BIAS && __builtin_amdgcn_ballot_w64(far) != 0) {
-  #pragma unroll
-          for (int tt = 0; tt < 2; ++tt)
-  #pragma unroll
-            for (int r = 0; r < 16; ++r) acc_s[tt][r] = far ? rounded_product(acc_s[tt][r], scale2) - m_exp : fmaf(acc_s[tt][r], scale2, -m_exp);
-        } else {
-  #pragma unroll
-          for (int tt = 0; tt < 2; ++tt)
-  #pragma unroll
-            for (int r = 0; r < 16; ++r) acc_s[tt][r] = fmaf(acc_s[tt][r], scale2, -m_exp);
-        }
   #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
   #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float p = __builtin_amdgcn_exp2f(acc_s[tt][r]);
+            const float p = __builtin_amdgcn_exp2f(BIAS ? acc_s[tt][r] - m_exp : fmaf(acc_s[tt][r], scale2, -m_exp));
             psum += p;
             pf[tt][r / 8][r % 8] = f2bf(p);
           }

@@ -157,3 +157,26 @@ def test_masked_rows_leave_their_neighbours_alone(B, dh):
     torch.cuda.synchronize()
     others = [r for r in range(sq) if r % 3]
     assert torch.equal(plain[others], mixed[others]) and bool(torch.isfinite(mixed.float()).all())
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("sk", [192, 200])
+@pytest.mark.parametrize("common", [-1e3, -1e4, -1e5, -6e5, -1e6, 1e5])
+def test_rows_whose_keys_share_a_large_bias(B, dh, sk, common):
+    """A score is rounded once at the bias's magnitude, in log2 units, whatever the head's width (the bias's own rounding there is the same for all keys):
+    the relative error of a probability, uniform within that half unit, is that of the context in 2-norm, beside the bf16 roundings of probabilities and
+    result.  Every third row is such a row; the others are as exact as ever."""
+    from paper_2401_10652_amd.inputs import round_to_storage
+    heads, sq = 4, 160
+    q, k, v = (draw((n, heads * dh), 350 + i, "bf16") for i, n in enumerate((sq, sk, sk)))
+    bias = draw((heads, sq, sk), 353, "bf16")
+    bias[:, ::3] = common
+    bias = round_to_storage(bias.astype(np.float32), "bf16")
+    got, ref = run(B, q, k, v, heads, False, bias=bias), O.attention(q, k, v, heads, False, bias=bias)
+    shared = np.arange(sq) % 3 == 0
+    half_unit = float(np.spacing(np.float32(abs(bias[0, 0, 0]) * 1.4426950408889634))) / 2 * np.log(2)
+    for rows, h in ((shared, half_unit), (~shared, 0.0)):
+        err = np.linalg.norm(got[rows] - ref[rows]) / np.linalg.norm(ref[rows])
+        # (uniform errors: a third of the half units' squares; bf16's are 2^-8 of a value at the foot of a binade, 0.54 of its square in the mean over it)
+        bound = 1.25 * np.sqrt((2 * 0.54 * 2.0 ** -16 + h * h) / 3)
+        assert err <= bound, (err, bound)
