@@ -300,6 +300,7 @@ struct TransitionArgs {
   float eps;
 };
 bool transition_shapes_ok(int dtype, int64_t c_z, int64_t hidden, int act);
+int64_t transition_least_rows(int64_t c_z, int64_t hidden, int act);
 hipError_t launch_transition(const TransitionArgs& p, hipStream_t s);
 // fp32 layers of 32, 64 or 128 channels; rows contiguous.  out[rows, n] = LN(x) w^T + bias, and
 // h = resid + ctx w_o^T + b_o; out = h + act(LN(h) w_1^T + b_1) w_2^T + b_2 with a feed-forward of 4 d columns.

@@ -315,6 +315,18 @@ bool transition_shapes_ok(int dtype, int64_t c_z, int64_t hidden, int act) {
          (act == AC_ACT_RELU || act == AC_ACT_GELU_ERF || act == AC_ACT_GELU_TANH);
 }
 
+// Rows from which the one kernel is ahead of the two launches (LayerNorm and first layer, second layer), whose bits are the same.  A block walks the
+// hidden columns by itself, 0.6 us per 64 of them with ReLU and 1.3 with GELU at 64 channels, 1.0 and 1.7 at 128, however few its rows are, where the
+// two launches share them out.  us, one / two, GELU (erf), 128 channels: 512 hidden 19.2 / 11.0 at 576 rows, 19.3 / 16.1 at 6400, 19.4 / 23.1 at 10816;
+// 1024 hidden 32.6 / 12.4 at 256, 33.0 / 26.5 at 9216, 33.3 / 35.6 at 14400; 128 hidden 8.5 / 9.9 at 64.  ReLU: 512 hidden 13.1 / 11.6 at 4096, 13.1 / 15.0 at
+// 5184; 64 channels, 768 hidden 11.2 / 10.3 at 256, 11.4 / 14.9 at 5184.  (477 sizes, widths and activations: 7 are more than 4 % off the better one, 12 % at
+// worst.)
+int64_t transition_least_rows(int64_t c_z, int64_t hidden, int act) {
+  const int64_t steps = hidden / kHiddenStep;
+  if (act == AC_ACT_RELU) return steps <= (c_z == 64 ? 10 : 4) ? 0 : 4608;
+  return steps <= (c_z == 64 ? 4 : 2) ? 0 : 4800 + 450 * steps;
+}
+
 template <int K, int ACT> static hipError_t transition_launch(const TransitionArgs& p, hipStream_t s) {
   auto kern = pair_transition_bf16<K, ACT>;
   static const hipError_t attr_status =

@@ -1081,11 +1081,13 @@ void Walk::transition(const void* const* W, const void* zin, void* zout) {
   const int e = eb();
   const bool col = p->set[AC_REGION_PAIR_TRANSITION].chunk_dim == AC_DIM_COL;
   enter(AC_REGION_PAIR_TRANSITION);
-  const bool one_pass = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE) && transition_shapes_ok(m.dtype, cz, F, m.activation);
+  // (where segments share launches by all rows, so that every run of them takes the same room: a run in two launches holds its hidden rows)
+  const bool one_kernel = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE) && transition_shapes_ok(m.dtype, cz, F, m.activation);
+  const int64_t least = one_kernel ? transition_least_rows(cz, F, m.activation) : 0;
   pair_loop(AC_REGION_PAIR_TRANSITION, row_segments(N, seg_len(AC_REGION_PAIR_TRANSITION)), zout, col, [&](const RowSeg& sg) {
     const int64_t rows = sg.ni * N;
     const void* zs = pair_segment(zin, sg, col);
-    if (one_pass) {   // (the plan counts the hidden rows all the same)
+    if (one_kernel && (shares() ? N * N : rows) >= least) {   // (the plan counts the hidden rows all the same)
       if (!shares()) arena.push((uint64_t)rows * F * e);
       LinearArgs dst{};
       pair_store(dst, zout, sg, col);

@@ -52,7 +52,8 @@ def test_triangle_update(B, n, c_z, c_hidden):
 
 @pytest.mark.parametrize("n,c_z,factor,activation", [
     (8, 64, 1, "relu"), (8, 128, 1, "gelu_erf"), (16, 64, 4, "gelu_tanh"), (24, 128, 4, "relu"), (40, 128, 8, "gelu_tanh"), (48, 64, 3, "gelu_erf"),
-    (72, 128, 2, "gelu_tanh"), (104, 128, 4, "gelu_erf"), (16, 128, 9, "relu")])     # (nine times as wide: two launches)
+    (72, 128, 2, "gelu_tanh"), (104, 128, 4, "gelu_erf"), (16, 128, 9, "relu"),     # (nine times as wide: two launches)
+    (24, 128, 2, "relu"), (72, 128, 4, "relu"), (96, 64, 8, "gelu_erf"), (112, 128, 8, "gelu_tanh")])   # (the last three: one kernel whole, two launches in parts)
 def test_transition(B, n, c_z, factor, activation):
     cfg = I.PairConfig("tpt", 47, n, c_z, 64, 2, 32, factor, "bf16", activation=activation)
     y, ref = module(B, cfg, B.AC_REGION_PAIR_TRANSITION, settings(B, n))

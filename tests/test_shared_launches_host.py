@@ -56,3 +56,27 @@ for i in range(12000):
         unet(batch, 8 * rng.randint(1, 12), 8 * rng.randint(1, 12), c, c // dh, 64 * rng.randint(1, max(1, c // 16)), rng.randint(1, batch),
              rng.randint(1, batch), rng.random() < 0.3, rng.choice([0, 0, 13]), rng.choice([1, 1, 2, 3]))
 """)
+
+
+def test_a_transition_of_few_rows_takes_two_launches(walk):
+    """One block walks the hidden columns of its rows by itself; where rows are few, the two launches share the columns out."""
+    walk("""
+def kernels_of(n, c_z, factor, activation, chunk=None, flags=0):
+    kernels()
+    cfg = I.PairConfig("plan", 1, n, c_z, 64, 2, 32, factor, "bf16", activation=activation)
+    walk((n, c_z, factor, activation, chunk), B.pair_desc(cfg, flags=B.AC_FLAG_LISTED_REGIONS_ONLY), [(B.AC_REGION_PAIR_TRANSITION, B.AC_DIM_ROW, chunk or n)])
+    return kernels()
+
+def one_kernel(*args):
+    names = kernels_of(*args)
+    ours = ["pair_transition" in k for k in names]
+    assert all(ours) or (not any(ours) and len(names) % 2 == 0), names
+    return ours[0]
+
+for n, c_z, factor, activation, one in (
+        (8, 128, 8, "gelu_erf", False), (96, 128, 8, "gelu_tanh", False), (112, 128, 8, "gelu_erf", True), (8, 128, 4, "relu", False), (64, 128, 4, "relu", False),
+        (72, 128, 4, "relu", True), (200, 128, 4, "relu", True), (8, 128, 2, "relu", True), (8, 128, 1, "gelu_erf", True), (8, 64, 4, "gelu_erf", True),
+        (8, 64, 8, "gelu_erf", False), (96, 64, 8, "gelu_erf", True), (8, 64, 8, "relu", True), (64, 64, 12, "relu", False)):
+    for chunk in (n, (n + 2) // 3, 1):
+        assert one_kernel(n, c_z, factor, activation, chunk) == one, (n, c_z, factor, activation, chunk)
+""")
