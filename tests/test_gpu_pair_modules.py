@@ -61,7 +61,7 @@ def test_transition(B, n, c_z, factor, activation):
 
 
 @pytest.mark.parametrize("k", [64, 128])
-@pytest.mark.parametrize("rows", [8, 64, 1000, 8200, 131072 + 72])      # (131072: tiles of 64 rows)
+@pytest.mark.parametrize("rows", [8, 64, 1000, 8200, 33008, 131072 + 72])      # (two gated pairs: from 16384 or 32768 rows on; 131072: tiles of 64 rows)
 @pytest.mark.parametrize("parts", ["four", "two", "pairs", "narrow"])
 def test_projections_of_whole_slices(B, rows, k, parts):
     """256 or 512 weight columns (and a few more of a part stored strided): the bits of the same projections with four columns more, which the kernel of 64-column tiles takes."""

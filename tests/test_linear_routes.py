@@ -97,3 +97,31 @@ assert gated_kernel(32, 32, 1280, 5120) == "256x256"
 assert gated_kernel(32, 32, 320, 1280) == "64x128"
 assert gated_kernel(64, 64, 320, 1280) == "256x256"
 """)
+
+
+def test_projections_of_few_rows_share_out_their_columns(tmp_path):
+    """Beside the kernel that keeps weights in registers, a block per CU, the one of 64-column tiles: where rows are few its launch has more blocks."""
+    import launch_stub
+    launch_stub.run(launch_stub.build(str(tmp_path)), """
+def part(i, n, rows, strided=False, gated=False):
+    p = B.ac_proj_part()
+    p.w, p.n = (1 << 43) + (i << 20), n
+    if gated: p.w_gate, p.gated = (1 << 43) + (i << 20) + 65536, 1
+    if strided: p.out_t, p.t_s2, p.t_s3 = Y + (i << 36), 1, rows
+    else: p.out, p.ldo = Y + (i << 36), n
+    return p
+
+def slices(rows, k, kind):
+    parts = {"four": lambda: [part(i, 128, rows, i == 3) for i in range(4)], "two": lambda: [part(i, 128, rows) for i in range(2)],
+             "pairs": lambda: [part(i, 128, rows, True, True) for i in range(2)],
+             "narrow": lambda: [part(2, 4, rows, True), part(0, 128, rows), part(1, 128, rows, True)]}[kind]()
+    kernels()
+    assert L.ac_op_ln_linear(X, k, W, W + 4096, 1e-5, rows, k, (B.ac_proj_part * len(parts))(*parts), len(parts), B.AC_BF16, None) == 0
+    (name,) = kernels()
+    assert "ln_proj_slices" in name or "ln_multi_proj" in name
+    return "ln_proj_slices" in name
+
+for k, kind, line in ((64, "four", 8192), (128, "four", 8192), (64, "two", 0), (128, "two", 0), (64, "pairs", 32768), (128, "pairs", 16384), (64, "narrow", 13312),
+                      (128, "narrow", 4096)):
+    assert [slices(rows, k, kind) for rows in (8, 1024, line, line + 8, 40000, 1 << 20) if rows > 0] == [rows > line for rows in (8, 1024, line, line + 8, 40000, 1 << 20) if rows > 0], (k, kind)
+""")
