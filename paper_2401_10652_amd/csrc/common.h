@@ -309,6 +309,7 @@ struct LayerTailF32Args { const void *ctx, *resid, *w_o, *b_o, *ln_g, *ln_b, *w_
 bool ln_linear_f32_shapes_ok(int dtype, int64_t d, int64_t n);
 hipError_t launch_ln_linear_f32(const LnLinearF32Args& p, hipStream_t s);
 bool layer_tail_f32_shapes_ok(int dtype, int64_t d, int64_t hidden);
+bool layer_tail_f32_ahead(int64_t d, int64_t launch_rows, int64_t rows);
 hipError_t launch_layer_tail_f32(const LayerTailF32Args& p, hipStream_t s);
 // GroupNorm (+ SiLU) of channels-last images [images, positions, channels]; partials: group_norm_workspace_bytes()
 uint64_t group_norm_workspace_bytes(int64_t images, int groups);

@@ -165,6 +165,12 @@ static bool few_channels(int64_t d) { return d == 32 || d == 64 || d == 128; }
 bool ln_linear_f32_shapes_ok(int dtype, int64_t d, int64_t n) { return dtype == AC_F32 && few_channels(d) && n >= 64 && n % 64 == 0 && n <= 65536; }
 bool layer_tail_f32_shapes_ok(int dtype, int64_t d, int64_t hidden) { return dtype == AC_F32 && few_channels(d) && hidden == 4 * d; }
 
+// Whether the tail is ahead of its four launches, whose bits are the same, for launches of `launch_rows` rows in a layer of `rows`.  At 32 and 64
+// channels it always is (one layer of 16 to 65536 rows, 64 channels: 14.6 to 171 us against 19.2 to 248; 32: 13.1 to 105 against 20.3 to 140).  At 128 every
+// 16 rows read 576 KB of weights, one chain of loads that nothing hides while a CU has a block or two, and more than L2 gives once it has many: one layer of
+// 256 rows 51.0 us against 32.1, 1024 rows 52.5 / 37.0, 2048 55.8 / 46.3, 4096 62.3 / 62.1, 6144 69.6 / 78.4, 16384 135 / 141, 32768 251 / 236, 65536 482 / 435.
+bool layer_tail_f32_ahead(int64_t d, int64_t launch_rows, int64_t rows) { return d <= 64 || (launch_rows > 4096 && rows <= 20480); }
+
 static bool at16(const void* p) { return p && (uintptr_t)p % 16 == 0; }
 
 hipError_t launch_ln_linear_f32(const LnLinearF32Args& p, hipStream_t s) {

@@ -618,7 +618,10 @@ void Walk::transformer(const void* x, void* y) {
   // fp32 layers of few channels: LayerNorm 1 and the projection in one launch, and all that follows the attention core in the feed-forward's launches (the
   // plan counts the tensors between all the same)
   const bool fused = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE);
-  const bool few_in = fused && ln_linear_f32_shapes_ok(m.dtype, d, 3 * d), few_out = fused && layer_tail_f32_shapes_ok(m.dtype, d, F);
+  const std::vector<Seg> ffn_segs = token_segments(m, p->set[AC_REGION_FFN].chunk_dim, seg_len(AC_REGION_FFN));
+  const bool few_in = fused && ln_linear_f32_shapes_ok(m.dtype, d, 3 * d);
+  const bool in_idle_memory = may_share() && ffn_segs.size() > 2;   // (the feed-forward's segments: see there)
+  const bool few_out = fused && layer_tail_f32_shapes_ok(m.dtype, d, F) && layer_tail_f32_ahead(d, in_idle_memory ? T : ffn_segs[0].nb * ffn_segs[0].ns, T);
 
   for (int l = 0; l < m.layers && ok(); ++l) {
     const void* in = l == 0 ? x : (const void*)tbuf;
@@ -731,7 +734,6 @@ void Walk::transformer(const void* x, void* y) {
     // LayerNorm 2 writes into the context buffer as well (the output projection has consumed it), for all
     // rows at once; what a segment of this region holds is its hidden tensor.
     enter(AC_REGION_FFN);
-    const std::vector<Seg> ffn_segs = token_segments(m, p->set[AC_REGION_FFN].chunk_dim, seg_len(AC_REGION_FFN));
     for (const Seg& sg : merged_segments(m, ffn_segs)) {
       if (few_out) break;
       const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
@@ -754,7 +756,7 @@ void Walk::transformer(const void* x, void* y) {
     // q, k and v are dead from here to the next layer's projection, and the hidden rows of a run lie in their memory and what
     // a segment may hold behind it.  (A region cut in two stays two launches: so ac_region_info has always reported it.)  With two
     // segments in flight the runs still go one after another, where there are no more of them than rounds of two segments.
-    bool in_runs = may_share() && ffn_segs.size() > 2;
+    bool in_runs = in_idle_memory;
     if (in_runs) {
       const uint64_t mk = arena.mark();
       auto none = [](int64_t, int64_t) { return std::vector<Span>(); };

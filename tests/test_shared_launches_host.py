@@ -80,3 +80,29 @@ for n, c_z, factor, activation, one in (
     for chunk in (n, (n + 2) // 3, 1):
         assert one_kernel(n, c_z, factor, activation, chunk) == one, (n, c_z, factor, activation, chunk)
 """)
+
+
+def test_layers_of_128_channels_take_their_tail_apart_where_rows_are_few_or_many(walk):
+    """fp32 layers: the kernel of all that follows the attention core where it is ahead of its four launches."""
+    walk("""
+def tail(batch, seq, d, chunk, dim=B.AC_DIM_SEQ):
+    kernels()
+    cfg = I.TransformerConfig("plan", 1, 1, seq, d, 2, 4 * d, False, "f32", None, batch=batch)
+    kinds = (B.AC_REGION_QKV, B.AC_REGION_ATTENTION, B.AC_REGION_OUT_PROJ, B.AC_REGION_FFN)
+    plan = B.Plan(B.transformer_desc(cfg), [(k, dim, chunk) for k in kinds])
+    info = plan.ac_plan_query()
+    assert L.ac_plan_bind_weights(plan._h, (B.VP * info.n_weights)(*[(1 << 44) + 256 * i for i in range(info.n_weights)]), info.n_weights) == 0
+    assert L.ac_execute(plan._h, X, Y, W, info.workspace_bytes, None, None) == 0, L.ac_last_error()
+    names = kernels()
+    fused = any("layer_tail" in k for k in names)
+    assert fused != any("layernorm" in k for k in names[1:]), names
+    return fused
+
+for d in (32, 64):
+    for batch, seq in ((1, 16), (1, 2048), (128, 128), (512, 128)):
+        assert tail(batch, seq, d, seq)
+for batch, seq, chunk, one in ((1, 16, 16, False), (1, 256, 64, False), (8, 128, 128, False), (1, 4096, 4096, False), (1, 5000, 5000, True), (48, 128, 128, True),
+                               (2, 5000, 5000, True), (2, 5000, 2000, True), (1, 20480, 20480, True), (160, 128, 128, True), (256, 128, 128, False), (1, 20496, 20496, False)):
+    assert tail(batch, seq, 128, chunk) == one, (batch, seq, chunk)
+assert tail(2, 3000, 128, 1, B.AC_DIM_BATCH) == False and tail(2, 3000, 128, 2, B.AC_DIM_BATCH) == True
+""")
