@@ -174,7 +174,8 @@ typedef struct ac_region_info {
   int64_t n_segments;        /* the paper's n */
   int64_t launches;          /* segment-loop iterations that launch kernels: n_segments, or fewer where consecutive
                                 segments run in one launch because that needs no more workspace than the plan's
-                                (of the last layer) */
+                                (of the last layer); 0 for the output projection of an fp32 layer of few channels
+                                whose feed-forward's launches hold it */
   uint64_t model_bytes;      /* paper-style sum X + Y + A/n of this region, ops unfused */
   uint64_t model_bytes_unchunked; /* the same with n = 1 (first activation equation) */
 } ac_region_info;

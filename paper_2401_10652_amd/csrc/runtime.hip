@@ -14,6 +14,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <mutex>
 #include <new>
 #include <string>
@@ -94,6 +95,10 @@ struct ProfRec { int cls; hipEvent_t start, stop; double flops, bytes; };
 // A run [i0, i0 + ni) of rows (or columns) of a pair tensor, of images, of token rows.
 struct RowSeg { int64_t i0, ni; };
 
+// Launches per layer of each region whose segments share launches or launch nothing of their own; -1: one per segment.
+typedef std::array<int64_t, AC_REGION_KINDS> RegionLaunches;
+static RegionLaunches one_per_segment() { RegionLaunches v; v.fill(-1); return v; }
+
 }  // namespace ac
 
 using namespace ac;
@@ -116,7 +121,7 @@ struct ac_plan {
   std::vector<hipEvent_t> sync_pool;
   size_t sync_used = 0;
   int sync_needed = 0;
-  int64_t region_launches[AC_REGION_KINDS] = {};   // launches per layer of a region whose segments share launches (0: one per segment)
+  RegionLaunches region_launches = one_per_segment();
   std::vector<std::vector<RowSeg>> shared;         // the runs of every shared_loop of a walk, in order
 };
 
@@ -148,7 +153,7 @@ struct Walk {
   void enter(int kind) { arena.watch = &region_high[kind]; }
 
   int sync_events = 0;     // planning: events one execute needs for its forks and joins
-  int64_t region_launches[AC_REGION_KINDS] = {};   // launches per layer of a region whose segments share launches
+  RegionLaunches region_launches = one_per_segment();
   void fork() {
     if (dry && lanes == 2) ++sync_events;
     if (dry || lanes != 2 || !ok()) return;
@@ -721,11 +726,11 @@ void Walk::transformer(const void* x, void* y) {
       const int64_t step = by_cols && !out_fused ? seg_len(AC_REGION_OUT_PROJ) : d;
       for (int64_t n0 = 0; n0 < d; n0 += step) col_segs.push_back(ColSeg{sg, n0, std::min<int64_t>(step, d - n0)});
     }
+    if (few_out) col_segs.clear();   // (in the feed-forward's launches)
     region_launches[AC_REGION_OUT_PROJ] = (int64_t)col_segs.size();
     seg_loop(col_segs, [&](const ColSeg& cs) {
       const Seg& sg = cs.t;
       const int64_t r0 = sg.b0 * S + sg.s0, rows = sg.nb * sg.ns;
-      if (few_out) return;
       proj(at(ctx_all, r0 * d), d, at(W(W_O), cs.n0 * d), d, at(W(W_BO), cs.n0), AC_ACT_NONE, at(in, r0 * d + cs.n0), d,
            atw(hbuf, r0 * d + cs.n0), d, rows, cs.nc);
     });
@@ -1443,8 +1448,8 @@ static bool dry_run(ac_plan* p, bool unchunked, uint64_t& arena_bytes, double& f
   arena_bytes = wk.arena.high;
   flops = wk.flops;
   if (region_high) memcpy(region_high, wk.region_high, sizeof(wk.region_high));
-  if (wk.deciding) memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches));
-  else if (!unchunked) { p->sync_needed = wk.sync_events; memcpy(p->region_launches, wk.region_launches, sizeof(wk.region_launches)); }
+  if (wk.deciding) p->region_launches = wk.region_launches;
+  else if (!unchunked) { p->sync_needed = wk.sync_events; p->region_launches = wk.region_launches; }
   return wk.ok();
 }
 
@@ -1768,7 +1773,7 @@ int ac_plan_create(const ac_model_desc* model, const ac_region_desc* regions, in
     ri.extent = s.extent;
     ri.chunk_len = s.chunk_len;
     ri.n_segments = ceil_div(s.extent, s.chunk_len);
-    ri.launches = p->region_launches[k] > 0 ? p->region_launches[k] : ri.n_segments;
+    ri.launches = p->region_launches[k] >= 0 ? p->region_launches[k] : ri.n_segments;
     ri.model_bytes = model_bytes(m, k, rows_of(s, s.chunk_len));
     ri.model_bytes_unchunked = model_bytes(m, k, rows_of(s, s.extent));
     inf.peak_bytes_model = std::max(inf.peak_bytes_model, ri.model_bytes);

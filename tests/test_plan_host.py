@@ -468,3 +468,14 @@ def test_feed_forward_segments_share_launches(cfg, c_attn, chunk, lanes):
     room = info.workspace_bytes - (3 if cfg.layers > 1 else 2) * cfg.seq * row       # all but the context, the stream, the layer's input
     n, runs = -(-cfg.seq // chunk), -(-cfg.seq // (room // (row * cfg.d_ffn // cfg.d_model)))
     assert info.regions[3].n_segments == n and info.regions[3].launches == (n if n == 2 else runs) <= n
+
+
+@pytest.mark.parametrize("flags", [0, B.AC_FLAG_TWO_SEGMENTS_IN_FLIGHT])
+@pytest.mark.parametrize("d,seq,chunk,in_ffn", [(64, 256, 64, True), (64, 256, 256, True), (32, 1000, 100, True), (128, 6000, 2000, True), (128, 256, 64, False), (256, 256, 64, False)])
+def test_an_output_projection_in_the_feed_forwards_launches_reports_none(flags, d, seq, chunk, in_ffn):
+    for dtype, extra, launches in (("f32", 0, 0 if in_ffn else 1), ("bf16", 0, 1), ("f32", B.AC_FLAG_UNFUSED_ELEMENTWISE, -(-seq // chunk))):
+        cfg = I.TransformerConfig("few", 1, 2, seq, d, 4, 4 * d, False, dtype, None)
+        plan = B.Plan(B.transformer_desc(cfg, flags=flags | extra), regions(chunk, chunk, chunk))
+        info = plan.ac_plan_query()
+        assert info.regions[2].launches == launches and min(info.regions[k].launches for k in (0, 1, 3)) >= 1
+        plan.close()
