@@ -2078,11 +2078,10 @@ static Route f32_route(const LinearArgs& g) {
     }
     return best < 0 ? kFma : costs[best].route;
   }
-  // Other depths: the tile of least estimated time: rounds of 256 tiles x (k / 64 steps + prologue and epilogue), plus what is paid once, in us; fitted to 172 products
-  // of 1 to 20000 rows x 4 to 8192 columns x 36 to 8192 deep, most of them no multiples of a tile.  Within 4 % the larger tile, which reads less per
-  // output: 4000 x 2048 x 96.  The choice is 1 % off the
-  // best of the four on average and 32 % at worst (by area alone 11 % on average: a row past a multiple of the large tiles had sent
-  // 777 x 512 x 512 to 16x16, 21.9 us, where 32x64 takes 12.7).
+  // Other depths: the tile of least estimated time: rounds of 256 tiles x (k / 64 steps + prologue and epilogue), plus what is paid once, in us.  Within 4 % the
+  // larger tile, which reads less per output (4000 x 2048 x 96: 40.5 us on 32x64, 50.0 on 32x32).  On 170 products of 1 to 20000 rows x 4 to 8192 columns x 36 to
+  // 8192 deep, no depth a multiple of 128, the choice is 0.9 % off the best of the four on average and 27 % at worst (644 x 3808 x 5032, 403 us on
+  // 32x64 and 318 on 32x32); by area alone a row past a multiple of the large tiles would send 777 x 512 x 500 to 16x16, 12.9 us, where 32x64 takes 10.3.
   struct Cost { int bm, bn; double step, tile, once; };
   static const Cost costs[4] = {{32, 64, 0.77, 1.9, 2.5}, {32, 32, 0.38, 0.9, 3.0}, {32, 16, 0.27, 0.5, 3.1}, {16, 16, 0.18, 0.25, 3.2}};
   int best = -1;
