@@ -2014,7 +2014,7 @@ static hipError_t ring_f32_launch(const LinearArgs& g, hipStream_t s) {
 enum Route { kFma, kF32_32x64, kF32_32x32, kF32_32x16, kF32_16x16, kF32Ring32x64, kF32Ring32x32, kF32Ring32x32Deep, kRouteQuad, kRing256x128, kRing128x128, kRing128x192, kStaged128x128, kRing128x64, kRing64x64,
              kStaged64x64, kStaged32x64, kRagged256x128, kRagged64x64, kConv128x128, kConv128x192, kConv128x64, kConv64x64, kConvWide64x64, kRoutes };
 static const char* const kRouteName[kRoutes] = {
-    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "f32 32x64", "f32 32x32", "f32 32x32", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
+    "fma 64x64", "f32 32x64", "f32 32x32", "f32 32x16", "f32 16x16", "f32-ring 32x64", "f32-ring 32x32", "f32-ring-deep 32x32", "quad 256x256", "ring 256x128", "ring 128x128", "ring 128x192", "staged 128x128", "ring 128x64", "ring 64x64",
     "staged 64x64", "staged 32x64", "ragged 256x128", "ragged 64x64", "conv 128x128", "conv 128x192", "conv 128x64", "conv 64x64", "conv-wide 64x64"};
 
 static bool wide_rows(const LinearArgs& g) { return g.lda >= (1 << 22) || g.ldw >= (1 << 22); }

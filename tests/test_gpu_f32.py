@@ -50,9 +50,11 @@ def test_linear_f32(B, m, n, k):
     assert torch.equal(part, out)
 
 
-@pytest.mark.parametrize("m,n,k", [(1024, 512, 512), (1100, 1540, 128), (1531, 601, 256), (5900, 65, 1152), (5000, 96, 384), (250, 2100, 640),
-                                   (260, 516, 1024), (2066, 200, 1024), (700, 516, 256)])
-def test_linear_f32_depths_of_whole_tiles(B, m, n, k):
+@pytest.mark.parametrize("m,n,k,kernel", [
+    (1024, 512, 512, "f32-ring-deep 32x32"), (1100, 1540, 128, "f32-ring 32x32"), (1531, 601, 256, "f32-ring 32x64"), (5900, 65, 1152, "f32-ring 32x32"),
+    (5000, 96, 384, "f32-ring 32x32"), (250, 2100, 640, "f32-ring 32x64"), (260, 516, 1024, "f32 32x32"), (520, 516, 1024, "f32-ring-deep 32x32"),
+    (2066, 200, 1024, "f32-ring-deep 32x32"), (700, 516, 256, "f32-ring-deep 32x32")])
+def test_linear_f32_depths_of_whole_tiles(B, m, n, k, kernel):
     """Launches of a ring of tiles, odd rows and columns among them: the oracle's values, and the bits of launches of 33 rows (waves that share out k)."""
     import torch
     a, w = draw((m, k), 114, "f32"), draw((n, k), 115, "f32", 1 / math.sqrt(k))
@@ -64,7 +66,7 @@ def test_linear_f32_depths_of_whole_tiles(B, m, n, k):
     torch.cuda.synchronize()
     check(host(out), O.linear(a, w, bias) + res, "f32")
     assert bool(torch.isnan(guard[0]).all()) and bool(torch.isnan(guard[-1]).all())
-    assert B.ac_linear_kernel(m, n, k, "f32") in ("f32 32x64", "f32 32x32")
+    assert B.ac_linear_kernel(m, n, k, "f32") == kernel and B.ac_linear_kernel(33, n, k, "f32").startswith("f32 ")
     part = torch.full((m, n), float("nan"), device="cuda")
     for r0 in range(0, m, 33):
         r1 = min(m, r0 + 33)

@@ -4,7 +4,7 @@ import pytest
 from paper_2401_10652_amd import binding as B
 from paper_2401_10652_amd.build import ensure_built
 
-THREADS = {"fma": 256, "f32": 256, "staged 32x64": 128, "staged": 256, "quad": 512, "ring 256x128": 512, "ring 128x128": 512, "ring": 256,
+THREADS = {"fma": 256, "f32": 256, "f32-ring": 256, "f32-ring-deep": 256, "staged 32x64": 128, "staged": 256, "quad": 512, "ring 256x128": 512, "ring 128x128": 512, "ring": 256,
            "ragged 256x128": 512, "ragged": 256, "conv 128x128": 512, "conv": 256,
            "conv-wide": 256}
 
@@ -49,12 +49,15 @@ def test_long_row_strides_keep_the_matrix_cores(m, n, k, side):
 @pytest.mark.parametrize("m,n,k", [(1024, 2048, 512), (1024, 1536, 512), (768, 512, 512), (1500, 2048, 512), (200, 1536, 512)])
 def test_a_row_more_does_not_send_an_fp32_product_to_the_smallest_tile(m, n, k):
     for rows in (m, m + 1, m + 9):
-        assert B.ac_linear_kernel(rows, n, k, "f32") in ("f32 32x64", "f32 32x32")
+        assert B.ac_linear_kernel(rows, n, k, "f32").split()[1] in ("32x64", "32x32")
 
 
 def test_near_ties_of_fp32_tiles_go_to_the_larger():
-    for m, n, k in ((1024, 1536, 512), (4000, 2048, 128), (4000, 2048, 96)):
+    """(Depths of whole tiles in each part of a sum have prices of their own, fitted closely enough for no preference.)"""
+    for m, n, k in ((1024, 1536, 500), (4000, 2048, 124), (4000, 2048, 96)):
         assert B.ac_linear_kernel(m, n, k, "f32") == "f32 32x64"
+    for m, n, k in ((1024, 1536, 512), (4000, 2048, 128)):
+        assert B.ac_linear_kernel(m, n, k, "f32") == "f32-ring 32x64"
 
 
 def test_short_fp32_sums_of_many_columns_take_one_kernel_whatever_the_rows():
@@ -124,4 +127,31 @@ def slices(rows, k, kind):
 for k, kind, line in ((64, "four", 8192), (128, "four", 8192), (64, "two", 0), (128, "two", 0), (64, "pairs", 32768), (128, "pairs", 16384), (64, "narrow", 13312),
                       (128, "narrow", 4096)):
     assert [slices(rows, k, kind) for rows in (8, 1024, line, line + 8, 40000, 1 << 20) if rows > 0] == [rows > line for rows in (8, 1024, line, line + 8, 40000, 1 << 20) if rows > 0], (k, kind)
+""")
+
+
+def test_an_fp32_products_name_is_the_kernel_that_is_launched(tmp_path):
+    """Every fp32 kernel, by the launch that the call makes."""
+    import launch_stub
+    launch_stub.run(launch_stub.build(str(tmp_path)), """
+import re
+SHARED = {"2, 4": "f32 32x64", "2, 2": "f32 32x32", "2, 1": "f32 32x16", "1, 1": "f32 16x16"}
+RING = {"32, 64, 1, 4, 32": "f32-ring 32x64", "32, 32, 2, 2, 32": "f32-ring 32x32", "32, 32, 2, 2, 64": "f32-ring-deep 32x32"}
+def launched(m, n, k, batch):
+    kernels()
+    if batch == 1: status = L.ac_op_linear(X, k, W, k, None, None, 0, None, 0, Y, n, None, n, 0, 0, 0, 0, m, n, k, 0, B.AC_F32, None)
+    else: status = L.ac_op_triangle_contract(X, k, m * k, W, k, n * k, Y, n, m * n, m, n, k, batch, B.AC_F32, None)
+    assert status == 0, L.ac_last_error()
+    (name,) = kernels()
+    numbers = ", ".join(re.findall(r"ELi(\\d+)|ILi(\\d+)", name) and [a or b for a, b in re.findall(r"ELi(\\d+)|ILi(\\d+)", name)])
+    return "fma 64x64" if "linear_fma" in name else SHARED[numbers] if "linear_mfma_f32" in name else RING[numbers] if "linear_ring_f32" in name else name
+
+seen = set()
+rng = random.Random(3)
+sizes = [(rng.choice([1, 33, 200, 260, 700, 1024, 2066, 5000]), 4 * rng.randint(1, 500), rng.choice([64, 100, 128, 256, 384, 500, 640, 1024, 2048]), rng.choice([1, 1, 1, 16, 128])) for _ in range(600)]
+for m, n, k, batch in sizes + [(1000, 1024, 64, 1)]:
+    name = B.ac_linear_kernel(m, n, k, "f32", batch=batch)
+    assert name == launched(m, n, k, batch), (m, n, k, batch, name)
+    seen.add(name)
+assert len(seen) == 8, seen
 """)
