@@ -302,7 +302,7 @@ struct TransitionArgs {
 bool transition_shapes_ok(int dtype, int64_t c_z, int64_t hidden, int act);
 int64_t transition_least_rows(int64_t c_z, int64_t hidden, int act);
 hipError_t launch_transition(const TransitionArgs& p, hipStream_t s);
-// fp32 layers of 32, 64 or 128 channels; rows contiguous.  out[rows, n] = LN(x) w^T + bias, and
+// fp32 layers of few channels; rows contiguous.  out[rows, n] = LN(x) w^T + bias (64 or 128 channels, n in multiples of 64), and (32, 64 or 128)
 // h = resid + ctx w_o^T + b_o; out = h + act(LN(h) w_1^T + b_1) w_2^T + b_2 with a feed-forward of 4 d columns.
 struct LnLinearF32Args { const void *x, *gain, *shift, *w, *bias; void* out; int64_t rows, d, n; float eps; };
 struct LayerTailF32Args { const void *ctx, *resid, *w_o, *b_o, *ln_g, *ln_b, *w_1, *b_1, *w_2, *b_2; void* out; int64_t rows, d; int act; float eps; };

@@ -1,5 +1,6 @@
-// fp32 transformer layers of few channels (32, 64 or 128, the feed-forward four times as wide): LayerNorm + packed projection in one kernel, and
-// all that follows the attention core (output projection, residual, LayerNorm, feed-forward, residual) in another.
+// fp32 transformer layers of few channels: LayerNorm + packed projection in one kernel (64 or 128), and all that follows the attention core (output
+// projection, residual, LayerNorm, feed-forward, residual) in another (32, 64 or, for some row counts, 128, the feed-forward four times as wide).  With the
+// attention core 64 channels take three launches, 32, whose 96 packed columns are no multiple of 64, four.
 //
 // What bounds such a layer is the number of its launches, 3 to 5 us each whatever they do, and inside a launch the latency of loads and of the chain
 // over k.  Both kernels therefore keep 16 rows of a block on chip from one step to the next, read weights (L2) straight into registers several matrix
@@ -161,9 +162,8 @@ __global__ void __launch_bounds__(256) layer_tail_f32(LayerTailF32Args p) {
   });
 }
 
-static bool few_channels(int64_t d) { return d == 32 || d == 64 || d == 128; }
-bool ln_linear_f32_shapes_ok(int dtype, int64_t d, int64_t n) { return dtype == AC_F32 && few_channels(d) && n >= 64 && n % 64 == 0 && n <= 65536; }
-bool layer_tail_f32_shapes_ok(int dtype, int64_t d, int64_t hidden) { return dtype == AC_F32 && few_channels(d) && hidden == 4 * d; }
+bool ln_linear_f32_shapes_ok(int dtype, int64_t d, int64_t n) { return dtype == AC_F32 && (d == 64 || d == 128) && n >= 64 && n % 64 == 0 && n <= 65536; }
+bool layer_tail_f32_shapes_ok(int dtype, int64_t d, int64_t hidden) { return dtype == AC_F32 && (d == 32 || d == 64 || d == 128) && hidden == 4 * d; }
 
 // Whether the tail is ahead of its four launches, whose bits are the same, for launches of `launch_rows` rows in a layer of `rows`.  At 32 and 64
 // channels it always is (one layer of 16 to 65536 rows, 64 channels: 14.6 to 171 us against 19.2 to 248; 32: 13.1 to 105 against 20.3 to 140).  At 128 every
@@ -181,8 +181,7 @@ hipError_t launch_ln_linear_f32(const LnLinearF32Args& p, hipStream_t s) {
   // as many shares of the columns as a launch of few rows leaves places for
   const int64_t blocks = (p.rows + kRows - 1) / kRows, runs = p.n / 64, room = 1024 / blocks;
   const dim3 grid((unsigned)blocks, (unsigned)(room < 1 ? 1 : room < runs ? room : runs));
-  if (p.d == 32) hipLaunchKernelGGL((ln_linear_f32<32>), grid, dim3(256), 0, s, p);
-  else if (p.d == 64) hipLaunchKernelGGL((ln_linear_f32<64>), grid, dim3(256), 0, s, p);
+  if (p.d == 64) hipLaunchKernelGGL((ln_linear_f32<64>), grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL((ln_linear_f32<128>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }

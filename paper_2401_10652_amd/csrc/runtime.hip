@@ -620,8 +620,8 @@ void Walk::transformer(const void* x, void* y) {
   // attention of an fp32 model, by a transpose after the projection region
   void* vt = (bf || stored_scores) ? arena.push((uint64_t)T * d * e) : nullptr;
   const int64_t ldqk = (bf ? 2 : 3) * d;
-  // fp32 layers of few channels: LayerNorm 1 and the projection in one launch, and all that follows the attention core in the feed-forward's launches (the
-  // plan counts the tensors between all the same)
+  // fp32 layers of few channels: LayerNorm 1 and the projection in one launch (64 or 128 channels), and all that follows the attention core in the
+  // feed-forward's launches, each by itself (the plan counts the tensors between all the same)
   const bool fused = !(m.flags & AC_FLAG_UNFUSED_ELEMENTWISE);
   const std::vector<Seg> ffn_segs = token_segments(m, p->set[AC_REGION_FFN].chunk_dim, seg_len(AC_REGION_FFN));
   const bool few_in = fused && ln_linear_f32_shapes_ok(m.dtype, d, 3 * d);

@@ -1,5 +1,5 @@
-"""fp32 layers of 32, 64 and 128 channels in three launches: the bits of the separate kernels (each op called by itself), row counts around the blocks'
-16 rows, every activation, chunked plans, several layers."""
+"""fp32 layers of 32, 64 and 128 channels, whose LayerNorm 1 and projection (64 and 128) and whose tail (32, 64, and 128 where rows are neither few nor
+many) are one kernel each: the bits of the separate kernels (each op called by itself), row counts around the blocks' 16 rows, every activation, chunked plans, several layers."""
 import pytest
 
 from paper_2401_10652_amd import inputs as I
