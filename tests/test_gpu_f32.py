@@ -155,3 +155,51 @@ def test_attention_f32_many_blocks(B):
     torch.cuda.synchronize()
     check(host(ctx[0]), O.attention(q, k, v, heads, False), "f32")
     assert all(torch.equal(ctx[i:i + 1], ctx[:1]) for i in range(1, batch, 1093)) and torch.equal(ctx[-1], ctx[0])
+
+
+@pytest.mark.parametrize("batch,m,n,k,kernel", [(64, 128, 128, 128, "f32-ring 32x32"), (48, 100, 130, 128, "f32-ring 32x32"), (16, 256, 250, 256, "f32-ring 32x64"),
+                                                (16, 150, 140, 512, "f32-ring-deep 32x32")])
+def test_many_products_f32_of_whole_tile_depths(B, batch, m, n, k, kernel):
+    """Batched launches of the rings, odd rows and columns among them, operands and results apart from their neighbours: the oracle's values, and the bits of
+    each product by itself in launches of 33 rows."""
+    import torch
+    assert B.ac_linear_kernel(m, n, k, "f32", batch=batch) == kernel
+    a, w = draw((batch, m, k), 118, "f32"), draw((batch, n, k), 119, "f32", 1 / math.sqrt(k))
+    da, dw = (torch.full((batch, r + 3, k + 4), float("nan"), device="cuda") for r in (m, n))
+    da[:, :m, :k], dw[:, :n, :k] = B.to_device(a, "f32"), B.to_device(w, "f32")
+    out = torch.full((batch, m + 1, n + 6), float("nan"), device="cuda")
+    B.ac_op_triangle_contract(da[:, :m, :k], dw[:, :n, :k], out[:, :m, :n])
+    torch.cuda.synchronize()
+    check(host(out[:, :m, :n]), np.matmul(a.astype(np.float64), w.astype(np.float64).transpose(0, 2, 1)), "f32")
+    assert bool(torch.isnan(out[:, m]).all()) and bool(torch.isnan(out[:, :, n:]).all())
+    part = torch.full((batch, m, n), float("nan"), device="cuda")
+    for b in range(0, batch, 5):
+        for r0 in range(0, m, 33):
+            B.ac_op_linear(da[b, r0:min(m, r0 + 33), :k], dw[b, :n, :k], part[b, r0:r0 + 33])
+    torch.cuda.synchronize()
+    assert torch.equal(part[::5], out[::5, :m, :n])
+
+
+def test_pair_stack_f32_of_whole_tile_depths(B):
+    """The contraction over 128 residues on a ring, batches in either order, rows and columns in chunks: the oracle's values, the same bits."""
+    import torch
+    from oracle import pairstack as P
+    from paper_2401_10652_amd import inputs as I
+    n, kinds = 128, (B.AC_REGION_TRIMUL_OUT, B.AC_REGION_TRIMUL_IN)
+    assert B.ac_linear_kernel(n, n, n, "f32", batch=64) == "f32-ring 32x32"
+    cfg = I.PairConfig("tpr", 45, n, 16, 64, 2, 16, 2, "f32")
+    z, w = I.pair_inputs(cfg, bias_std=0.1, ln_jitter=0.1)
+    dz = B.to_device(z, "f32")
+    dw = [B.to_device(w[name], "f32") for name, _ in I.pair_tensor_shapes(cfg)]
+    for kind, name in zip(kinds, P.PAIR_MODULES):
+        first = None
+        for dim, chunk in ((B.AC_DIM_ROW, n), (B.AC_DIM_ROW, 40), (B.AC_DIM_COL, 64)):
+            plan = B.Plan(B.pair_desc(cfg, flags=B.AC_FLAG_LISTED_REGIONS_ONLY), [(kind, dim, chunk)])
+            plan.ac_plan_bind_weights(dw)
+            y = torch.full_like(dz, float("nan"))
+            plan.ac_execute(dz, y, B.empty_workspace(plan.ac_plan_query().workspace_bytes))
+            torch.cuda.synchronize()
+            plan.close()
+            first = y if first is None else first
+            assert torch.equal(y, first), (name, dim, chunk)
+        check(host(first), P.pair_module(name, z, w, cfg.heads, cfg.activation, cfg.ln_eps), "f32", what=name)
