@@ -36,11 +36,13 @@ __device__ __forceinline__ int64_t xcd_contiguous(int64_t pid, int64_t nb) {
 // Causal blocks of a head: longest rows first, in a snake over runs of 32 (the CUs of an XCD, which take consecutive
 // blocks in turn): the first 32 blocks of a head are its longest in descending order, the next 32 the following ones in ascending order, and
 // so on, so that when all blocks of a launch are resident at once (one sequence of a few thousand rows) every CU holds about the same number
-// of key tiles; with more blocks than places the order is still longest-first run by run.  Heads of fewer than 32 blocks take the directions of the
-// runs that they begin in, so that a CU's second block is as short as its first is long (four problems of 1000 queries, 16 heads of 64: 28.2 -> 25.2 us).
-// `first`: the head's first block in the launch.
+// of key tiles; with more blocks than places the order is still longest-first run by run.  Heads of 2, 4 or 8 blocks, of which a CU would get
+// the same ones again and again, take the directions of the runs that they begin in, so that its second block is as short as its first is long (four problems of 1000
+// queries, 16 heads of 64: 24.0 -> 20.9 us; 22 of 912, 12 heads: 98 -> 82); other short heads stay longest first, as heads that run the other way leave their
+// longest blocks to the end (two problems of 3216, 12 heads of 64: 51 us, 67 with directions in turn), and so do heads of two blocks in launches that do not fill the
+// chip's places (ten of 216, 16 heads of 128: 13.7 against 15.2).  `first`: the head's first block in the launch.
 __device__ __forceinline__ int snake(int qb, int nqb, int64_t first) {
-  if (nqb < 32) return first / 32 % 2 == 0 ? nqb - 1 - qb : qb;
+  if (nqb < 32) return ((nqb == 2 && gridDim.x >= 512) || nqb == 4 || nqb == 8) && first / 32 % 2 == 1 ? qb : nqb - 1 - qb;
   const int run = qb / 32, col = qb % 32;
   const int len = nqb - run * 32 < 32 ? nqb - run * 32 : 32;
   return nqb - 1 - (run * 32 + ((run & 1) ? len - 1 - col : col));

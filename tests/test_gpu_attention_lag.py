@@ -180,3 +180,25 @@ def test_rows_whose_keys_share_a_large_bias(B, dh, sk, common):
         # (uniform errors: a third of the half units' squares; bf16's are 2^-8 of a value at the foot of a binade, 0.54 of its square in the mean over it)
         bound = 1.25 * np.sqrt((2 * 0.54 * 2.0 ** -16 + h * h) / 3)
         assert err <= bound, (err, bound)
+
+
+@pytest.mark.parametrize("dtype,batch,sq,heads,dh", [
+    ("bf16", 256, 200, 1, 64), ("bf16", 3, 256, 2, 128), ("bf16", 12, 500, 4, 64), ("bf16", 7, 1000, 6, 64), ("bf16", 5, 700, 3, 128), ("bf16", 2, 4200, 2, 64),
+    ("f32", 1, 520, 8, 32), ("f32", 2, 1100, 4, 64), ("f32", 3, 520, 2, 32), ("f32", 5, 300, 8, 16), ("f32", 1, 2431, 4, 64)])
+def test_causal_blocks_in_whatever_order(B, dtype, batch, sq, heads, dh):
+    """Heads of one, two, four, eight and other numbers of blocks, whole numbers of heads per XCD and others: each problem's rows are those of a launch
+    with this problem alone, one head after another."""
+    import torch
+    d = heads * dh
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v = (torch.randn((batch, sq, d), generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(3))
+    vt = v.transpose(1, 2).contiguous() if dtype == "bf16" else v
+    ctx, alone = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    B.ac_op_attention(q[0], k[0], vt[0], ctx[0], heads, dh, causal=True, v_transposed=dtype == "bf16", batch=batch, strides=(sq * d, sq * d, sq * d, 0, sq * d))
+    for b in range(batch) if batch <= 12 else (0, 1, batch // 2, batch - 1):
+        for h in range(heads):
+            c = slice(h * dh, (h + 1) * dh)
+            B.ac_op_attention(q[b, :, c], k[b, :, c], vt[b, c] if dtype == "bf16" else vt[b, :, c], alone[b, :, c], 1, dh, causal=True, v_transposed=dtype == "bf16")
+        torch.cuda.synchronize()
+        assert torch.equal(ctx[b], alone[b]), b
+    assert bool(torch.isfinite(ctx.float()).all())
