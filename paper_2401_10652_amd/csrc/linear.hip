@@ -1809,15 +1809,15 @@ static int ln_proj_slices(const LnProjArgs& p, LnProjSliceArgs& sa) {
   }
   return (n == 8 || (n == 16 && !p.part[0].gated && sa.narrow < 0)) && !ln_proj_overlaps(p) ? n : 0;
 }
-// Rows beyond which the kernel of whole slices is ahead.  It has a block per CU, which first loads all its weights and, up to 8192 rows, uses them for one tile; the
+// Where the kernel of whole slices is ahead.  It has a block per CU, which first loads all its weights and, up to 8192 rows, uses them for one tile; the
 // kernel of 64-column tiles shares a short launch's columns out over more blocks.  The bits are the same.  us, slices / tiles, 128 wide: q, k, v and gate 7.7 /
 // 5.2 at 256 rows, 8.9 / 8.2 at 8192, 10.1 / 10.3 at 9000, 12.8 / 14.4 at 18000; two gated pairs 7.3 / 6.2 at 256, 9.6 / 8.4 at 10400, 12.5 / 13.2 at 18000;
 // bias, k and v 5.7 / 5.2 at 1024, 5.9 / 5.9 at 4096, 6.2 / 6.9 at 8192; k and v alone 4.9 / 5.1 at 256.  64 wide: the pairs 8.3 / 7.6 at 16384, 12.9 / 12.5 at 32768,
-// 14.7 / 17.6 at 36000; bias, k and v 6.9 / 6.3 at 13000, 6.9 / 8.1 at 14400.
-static int64_t ln_proj_slices_beyond(const LnProjArgs& p, const LnProjSliceArgs& sa, int slices) {
-  if (p.part[0].gated) return p.k == 128 ? 16384 : 32768;
-  if (sa.narrow >= 0) return p.k == 128 ? 4096 : 13312;
-  return slices == 16 ? 8192 : 0;
+// 14.7 / 17.6 at 36000; bias, k and v 6.9 / 6.3 at 13000, 6.9 / 8.1 at 14400; k and v alone (one strided) 4.6 / 4.7 at 968, 7.2 / 6.1 at 10440, 6.3 / 6.4 at 13992.
+static bool ln_proj_slices_ahead(const LnProjArgs& p, const LnProjSliceArgs& sa, int slices) {
+  if (p.part[0].gated) return p.rows > (p.k == 128 ? 16384 : 32768);
+  if (sa.narrow >= 0) return p.rows > (p.k == 128 ? 4096 : 13312);
+  return slices == 16 ? p.rows > 8192 : p.k == 128 || p.rows <= 8192 || p.rows > 13312;
 }
 template <int K, int SLOTS, bool GATED, bool NARROW = false> static hipError_t ln_proj_slices_launch(const LnProjSliceArgs& sa, hipStream_t s) {
   const int64_t rows = sa.a.rows;
@@ -1851,7 +1851,7 @@ hipError_t launch_ln_proj(const LnProjArgs& p_in, hipStream_t s) {
     if (pp.act == AC_ACT_GELU_ERF && !pp.gated) ka.any_gelu = 1;
   }
   LnProjSliceArgs sa{};
-  if (const int slices = ln_proj_slices(p, sa); slices > 0 && p.rows > ln_proj_slices_beyond(p, sa, slices)) {
+  if (const int slices = ln_proj_slices(p, sa); slices > 0 && ln_proj_slices_ahead(p, sa, slices)) {
     sa.a = p;
     const bool gated = p.part[0].gated != 0;
     if (sa.narrow >= 0) return p.k == 128 ? ln_proj_slices_launch<128, 1, false, true>(sa, s) : ln_proj_slices_launch<64, 1, false, true>(sa, s);

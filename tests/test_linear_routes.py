@@ -124,7 +124,8 @@ def slices(rows, k, kind):
     assert "ln_proj_slices" in name or "ln_multi_proj" in name
     return "ln_proj_slices" in name
 
-for k, kind, line in ((64, "four", 8192), (128, "four", 8192), (64, "two", 0), (128, "two", 0), (64, "pairs", 32768), (128, "pairs", 16384), (64, "narrow", 13312),
+assert [slices(rows, 64, "two") for rows in (8, 8192, 8200, 13312, 13320, 1 << 20)] == [True, True, False, False, True, True]
+for k, kind, line in ((64, "four", 8192), (128, "four", 8192), (128, "two", 0), (64, "pairs", 32768), (128, "pairs", 16384), (64, "narrow", 13312),
                       (128, "narrow", 4096)):
     assert [slices(rows, k, kind) for rows in (8, 1024, line, line + 8, 40000, 1 << 20) if rows > 0] == [rows > line for rows in (8, 1024, line, line + 8, 40000, 1 << 20) if rows > 0], (k, kind)
 """)
