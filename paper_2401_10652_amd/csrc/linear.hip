@@ -2057,7 +2057,9 @@ static Route f32_route(const LinearArgs& g) {
   // 1 % off the best of the five on average and 6 % at worst and 1.23 times ahead of the best without the ring.  us, 32x64 / 32x32 ring, 32x64 / 32x32 / 32x16 /
   // 16x16 shared: 1024 x 1536 x 512 19.2 / 21.7, 33.1 / 34.9 / 49.8 / 65.1; 1024 x 512 x 2048 29.9 / 31.8, 30.1 / 34.9 / 49.8 / 65.0; 256 x 512 x 2048 28.6 / 25.1,
   // 29.0 / 18.6 / 15.0 / 18.8; 16000 x 512 x 512 79 / 92, 149 / 172 / 250 / 330; 96 x 512 x 2048 29 / 25, 29 / 19 / 15 / 11.  (Rings of 64x64 and 128x64 are never
-  // more than 1 % ahead.)
+  // more than 1 % ahead.)  Over 404 more products, half of them of 40 rows or columns at most and many in batches, the choice is 1.11 times ahead of the four shared tiles
+  // by their prices below; 9 are more than 4 % behind, all but one of 22 rows or columns at most (64 products of 1 x 704 x 2048 69 -> 81 us, 8 of 1 x 2244 x 4352 65 -> 82; a
+  // line at 16 rows and columns would cost more than it gives: 64 of 2460 x 12 x 768 103 us, 140 on shared tiles).
   if (g.k % 128 == 0 && g.k <= (1 << 26) && !wide_rows(g)) {
     // Where the parts are whole tiles of 64 terms too, the 32x32 ring takes those: half the barriers, which a launch of one or two blocks per CU waits at
     // (1024 x 512 x 2048 31.0 -> 28.1, 256 x 512 x 2048 24.5 -> 20.1, 1024 x 512 x 512 10.8 -> 10.2); 32x64 gains up to 7 % by it there and loses 18 % in
