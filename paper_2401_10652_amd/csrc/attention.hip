@@ -566,8 +566,9 @@ __global__ void __launch_bounds__(64 * NW, attention_pipelined(DH, BIAS, KEYS) ?
         // ---- lane holds keys k0 + tt*32 + 8*(r/4) + 4*half + r%4.  Scores go to the log2 domain
         // only where needed: with a bias right away (so that equal biases of any size, as masks are, differ by exactly zero),
         // otherwise folded into the exponent below.  The bias meets the finished dot product, whose sum is rounded at its own magnitude: as what the
-        // sums start from it is rounded by each matrix instruction (rows whose keys share a bias of -6e5, heads of 64: 1.3e-2 -> 5.0e-2 from fp64) and gives
-        // no time (512 problems of 1024 queries and keys, four heads of 32: 668 against 666 us; 680 against 1025 with a masked row per wave).
+        // sums start from it is rounded by each matrix instruction: rows whose keys share a bias of -6e5, heads of 64, were 5.0e-2 from fp64 instead of
+        // 1.3e-2.  (That form takes 217 vector instructions a tile, this one 245: 512 problems of 1024 queries and keys, four heads of 32, 665 against 655 us by
+        // themselves, 1025 against 680 with a masked row per wave; a pair block of 1024 residues 6.28 against 6.43 ms.)
         if (BIAS) {
           const bf16_t* cb = sB + (wave * 32 + l32) * BROW + 4 * half;
   #pragma unroll
